@@ -175,6 +175,7 @@ enum WsSlot {
   WS_APPLYQ,
   WS_MISC,
   WS_CHOLQR,
+  WS_SPMM_RUNS,
   WS_NUM_SLOTS
 };
 
@@ -336,6 +337,11 @@ rfmls_status tri_apply(rfmls_handle* h, const rfmls_precond_t* P, int trans, con
                        double* out, double hcoef, const double* dcoef, const double* prev,
                        double* sq, const int* done);
 rfmls_status unpack_precond(rfmls_handle* h, const rfmls_precond_t* P, double* Xdense);
+// column runs of M's rows (lsqr.hip): nrun[i] runs of row i (-1: more than
+// kMaxRuns), run k starting at column rcol[i kMaxRuns + k] and ending before
+// entry rend[i kMaxRuns + k] of the row
+constexpr int kMaxRuns = 8;
+void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol, int32_t* rend);
 rfmls_status run_solve(rfmls_handle* h, const rfmls_csr* A, const rfmls_csr* AT,
                        const rfmls_precond_t* P, const double* B, int64_t ldb, int64_t nrhs,
                        double* X, int64_t ldx, double* Rout, int64_t ldr, const rfmls_opts* o,

@@ -197,7 +197,6 @@ __global__ void __launch_bounds__(kThreads)
 // contiguous stretches.  nrun[i] = -1 marks a row with more runs, which takes
 // the column-index path.
 // ---------------------------------------------------------------------------
-constexpr int kMaxRuns = 8;
 // lanes per row of the run SpMV for matrices whose rows average fewer than
 // 512 entries (more rows in flight per wavefront: spmv_A 0.054 -> 0.048 ms on
 // the 8x8-box system's 216-entry rows, 0.060 -> 0.055 ms on the Helmholtz
@@ -737,6 +736,11 @@ rfmls_status tri_apply(rfmls_handle* h, const rfmls_precond_t* P, int trans, con
 }
 
 
+void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol, int32_t* rend) {
+  hipLaunchKernelGGL(k_find_runs, dim3(spmv_blocks(M->m)), dim3(kThreads), 0, st, M->row_ptr, M->col, M->m, nrun, rcol,
+                     rend);
+}
+
 static rfmls_status spmv(Ctx& c, const rfmls_csr* M, const double* x, double sA, double hcoef,
                          const double* dcoef, const double* prev, double* out, double* sq,
                          const int* done, int* nblk) {
@@ -1002,8 +1006,7 @@ static rfmls_status make_ctx(rfmls_handle* h, const rfmls_csr* A, const rfmls_cs
       int32_t* c0 = n0 + rows;
       int32_t* e0 = c0 + rows * kMaxRuns;
       q = e0 + rows * kMaxRuns;
-      hipLaunchKernelGGL(k_find_runs, dim3(spmv_blocks(rows)), dim3(kThreads), 0, c.st, M->row_ptr, M->col, rows, n0,
-                         c0, e0);
+      find_runs(c.st, M, n0, c0, e0);
       *nr = n0;
       *rc = c0;
       *re = e0;

@@ -28,10 +28,77 @@ def test_explicit_operator_slices(m, n):
     A = _csr(Ad)
     opts = R.default_opts(atol=1e-13, btol=1e-13)
     AT = R.rfmls_transpose(h, A)
-    P = R.rfmls_precond_import_R(h, torch.tensor(np.abs(np.diag(np.diag(np.linalg.qr(Ad)[1]))) +
-                                                 np.eye(n), device="cuda"))
+    U = np.linalg.qr(Ad)[1]
+    P = R.rfmls_precond_import_R(h, torch.tensor(np.sign(np.diag(U))[:, None] * U, device="cuda"))
     x, res, _, rc = R.rfmls_solve_explicit(h, A, AT, P, R.rfmls_form_B(h, A, P), torch.tensor(b, device="cuda"), opts)
     want = np.linalg.lstsq(Ad, b, rcond=None)[0]
     assert rc == 0
     assert np.linalg.norm(x.cpu().numpy() - want) <= 1e-10 * np.linalg.norm(want)
     assert np.linalg.norm(res.cpu().numpy() - (b - Ad @ want)) <= 1e-10 * np.linalg.norm(b)
+
+
+def _blocks(pieces, n, seed):
+    """CSR rows by (rows, [(first column, length), ...]) pieces, values N(0, 1)."""
+    rng = np.random.default_rng(seed)
+    ptr, col, val = [0], [], []
+    for rows, runs in pieces:
+        cols = np.concatenate([np.arange(c, c + k) for c, k in runs]) if runs else np.zeros(0, int)
+        for _ in range(rows):
+            col.append(cols)
+            val.append(rng.standard_normal(cols.size))
+            ptr.append(ptr[-1] + cols.size)
+    return np.array(ptr, np.int64), np.concatenate(col).astype(np.int32), np.concatenate(val)
+
+
+# 32-column products over pieces of dense runs: row counts at the edges of the
+# 16-row tiles and of a 64-row group, run lengths at the edges of a 16-entry
+# step, rows without entries, one to eight runs a row, and (the last two) rows
+# of nine runs and pieces too short, which take the windowed kernel.  B = A X
+# with X = I: every output is one product a_ij * 1 plus zeros, so B equals A bit
+# for bit on either kernel.
+RUN_CASES = [
+    (40, [(64, [(0, 40)]), (64, [(0, 16)])]),
+    (131, [(15, [(0, 15)]), (17, [(3, 17)]), (33, [(0, 1)]), (1, [(130, 1)]), (63, [(5, 33), (60, 70)])]),
+    (300, [(100, [(0, 300)]), (49, []), (16, [(1, 31), (40, 47), (90, 16), (200, 100)]), (70, [(299, 1)])]),
+    (90, [(48, [(10 * k, 5) for k in range(8)]), (32, [(0, 64)])]),
+    (90, [(48, [(10 * k, 5) for k in range(9)]), (60, [(0, 64)])]),
+    (64, [(1, [(k, 1 + k % 3)]) for k in range(62)]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(RUN_CASES)))
+def test_run_products_reproduce_the_matrix(case):
+    n, pieces = RUN_CASES[case]
+    ptr, col, val = _blocks(pieces, n, case)
+    m = len(ptr) - 1
+    h = R.Handle(device="cuda:0")
+    A = R.CSR.from_numpy(ptr, col, val, m, n)
+    P = R.rfmls_precond_import_R(h, torch.eye(n, dtype=torch.float64, device="cuda"))
+    want = np.zeros((m, n))
+    want[np.repeat(np.arange(m), np.diff(ptr)), col] = val
+    assert np.array_equal(R.rfmls_form_B(h, A, P).cpu().numpy(), want)
+
+
+# The transposed product with long rows, split into K chunks that are then
+# merged, and more right-hand sides than one block of 32: per column the
+# lockstep solution is the single-column one (another summation order), both
+# within 10 * 1e-13 of the least-squares solution at kappa = O(10).
+@pytest.mark.parametrize("nrhs", [2, 33])
+def test_run_products_in_chunks(nrhs):
+    n = 96
+    pieces = [(900, [(0, 48)]), (700, [(48, 48)]), (333, [(0, 96)]), (5, [])]
+    ptr, col, val = _blocks(pieces, n, 7)
+    m = len(ptr) - 1
+    Ad = np.zeros((m, n))
+    Ad[np.repeat(np.arange(m), np.diff(ptr)), col] = val
+    B = np.random.default_rng(1).standard_normal((nrhs, m))
+    h = R.Handle(device="cuda:0")
+    A = R.CSR.from_numpy(ptr, col, val, m, n)
+    AT = R.rfmls_transpose(h, A)
+    SA, _, _, _ = R.rfmls_sketch(h, A, 4 * n, 2)
+    P = R.rfmls_precond(h, SA)
+    X, Res, _, rc = R.rfmls_solve(h, A, AT, P, torch.tensor(B, device="cuda"), R.default_opts(atol=1e-13, btol=1e-13))
+    want = np.linalg.lstsq(Ad, B.T, rcond=None)[0].T
+    assert rc == 0
+    assert np.linalg.norm(X.cpu().numpy() - want) <= 1e-10 * np.linalg.norm(want)
+    assert np.linalg.norm(Res.cpu().numpy() - (B - want @ Ad.T)) <= 1e-10 * np.linalg.norm(B)

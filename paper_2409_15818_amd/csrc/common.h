@@ -176,6 +176,7 @@ enum WsSlot {
   WS_MISC,
   WS_CHOLQR,
   WS_SPMM_RUNS,
+  WS_QR_ORDER,
   WS_NUM_SLOTS
 };
 

@@ -1,5 +1,7 @@
 // Blocked Householder QR of the sketch SA (s x n, row-major, in place):
-// Alg. 1 step 3.  Only R is needed; Q is never formed.
+// Alg. 1 step 3.  Only R is needed; Q is never formed, and the rows of a sparse
+// sketch are first sorted by where they start (sort_rows), so that s below is the
+// number of rows that have started.
 //
 // Two levels of blocking.  Outer blocks of kOuter = 256 or 512 columns
 // are factored panel by panel (kMaxNb = 64 columns each); the trailing matrix
@@ -583,6 +585,93 @@ __global__ void k_qr_keep_gram(const T* __restrict__ W, int64_t ldw, int bw, T* 
   if (r / kMaxNb < c / kMaxNb) To[(int64_t)r * ldt + c] = W[(int64_t)r * ldw + c];
 }
 
+// ---------------------------------------------------------------------------
+// Row order of a sparse sketch.  R does not depend on the order of SA's rows, and
+// a row takes part in the elimination only from the column of its first nonzero
+// on.  A sketch row is the sum of a few rows of A, each over one or two boxes'
+// columns, so its first nonzero lies anywhere in [0, n).  Sorted by the 64-column
+// panel of their first nonzero, the rows of panel k and before fill rows
+// [0, act[k]) and those below are still zero in panel k's columns: every product
+// and panel of the QR runs over act[k] - p rows instead of s - p.  On the
+// 8x8-box sketch (51,200 x 12,800, 2.2 rows of A per sketch row) that is 0.41 of
+// the flops, on the 4^3-box one 0.48, on the Helmholtz one 0.72.  Measured, whole
+// solves: 8x8-box 368 -> 248 ms (the trailing products 115 -> 57, V^T C 117 -> 60
+// ms, the rows' move 3 ms), 4^3-box float32 703 -> 505 ms, Helmholtz 30.2 -> 29.8,
+// 4x4-box 11.2 -> 11.0 ms.
+// ---------------------------------------------------------------------------
+// key[i] = panel of row i's first nonzero (npan for a zero row); one wavefront per row
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_row_keys(const T* __restrict__ SA, int64_t ld, int64_t s, int64_t n, int npan, int32_t* __restrict__ key) {
+  const int lane = threadIdx.x & 63;
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= s) return;
+  const T* p = SA + row * ld;
+  int k = npan;
+  constexpr int kAhead = 4;  // panels read together: the search is a chain of loads
+  for (int64_t c0 = 0; c0 < n; c0 += kAhead * kMaxNb) {
+    T v[kAhead];
+#pragma unroll
+    for (int q = 0; q < kAhead; ++q) {
+      const int64_t c = c0 + q * kMaxNb + lane;
+      v[q] = c < n ? p[c] : T(0);
+    }
+    int f = npan;
+#pragma unroll
+    for (int q = kAhead - 1; q >= 0; --q)
+      if (__ballot(v[q] != T(0))) f = (int)(c0 / kMaxNb) + q;
+    if (f < npan) {  // uniform
+      k = f;
+      break;
+    }
+  }
+  if (lane == 0) key[row] = k;
+}
+
+// Stable sort of the rows by key: workgroup k counts the rows of smaller keys,
+// then lists its own in ascending order; cnt[k] = rows of keys <= k.
+__global__ void __launch_bounds__(256)
+    k_row_order(const int32_t* __restrict__ key, int64_t s, int32_t* __restrict__ perm, int32_t* __restrict__ cnt) {
+  __shared__ int wsum[4];
+  const int k = blockIdx.x;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int below = 0;
+  for (int64_t i = threadIdx.x; i < s; i += 256) below += key[i] < k ? 1 : 0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) below += __shfl_xor(below, off, 64);
+  if (lane == 0) wsum[w] = below;
+  __syncthreads();
+  int base = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
+  for (int64_t i0 = 0; i0 < s; i0 += 256) {
+    const int64_t i = i0 + threadIdx.x;
+    const bool mine = i < s && key[i] == k;
+    const unsigned long long b = __ballot(mine);
+    __syncthreads();  // the previous round's sums have been read
+    if (lane == 0) wsum[w] = __popcll(b);
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      before += q < w ? wsum[q] : 0;
+      all += wsum[q];
+    }
+    if (mine) perm[base + before + __popcll(b & ((1ull << lane) - 1ull))] = (int32_t)i;
+    base += all;
+  }
+  if (threadIdx.x == 0) cnt[k] = base;
+}
+
+// out[i][c] = in[row(i)][c], c < width; row(i) = perm[i], or i without perm
+template <typename T>
+__global__ void __launch_bounds__(256)
+    k_move_rows(const T* __restrict__ in, int64_t ldi, const int32_t* __restrict__ perm, int64_t width,
+                T* __restrict__ out, int64_t ldo) {
+  const int64_t i = blockIdx.x;
+  const T* p = in + (perm ? (int64_t)perm[i] : i) * ldi;
+  T* o = out + i * ldo;
+  for (int64_t c = threadIdx.x; c < width; c += 256) o[c] = p[c];
+}
+
 // Panel launch shapes (rows per thread Q, rows per block 16 Q), increasing.
 // The largest are the largest that compile without spills at 1024 threads.
 struct PanelShape {
@@ -669,6 +758,14 @@ GemmArgs<T> v_update(T* P, int64_t ld, int64_t M, int64_t vcols, int64_t ncols, 
   return g;
 }
 
+// Rows that a panel or an outer block works on: all s, or with sorted rows the
+// act[k] rows whose first nonzero lies in panel k or before it.
+struct RowCounts {
+  int64_t s = 0;
+  std::vector<int64_t> act;  // per 64-column panel; empty: s
+  int64_t at(int64_t col) const { return act.empty() ? s : act[(size_t)(col / kMaxNb)]; }
+};
+
 // Buffers of one outer block's panels: tau and the diagonal 64-blocks of T_o
 // (written by the panels), and the inner products' slices, Gram and T^T W.
 template <typename T>
@@ -684,12 +781,12 @@ struct PanelBufs {
 // applied to the rest of the block, on h->stream; tau_out (if given) receives
 // the block's tau.
 template <typename T>
-rfmls_status qr_block_panels(rfmls_handle* h, int64_t s, int64_t k0, int64_t bw, int64_t kOuter, T* SA, int64_t ld,
-                             const PanelBufs<T>& pb, uint64_t* ll, double* cq_ws, int* cq_status, T* tau_out) {
+rfmls_status qr_block_panels(rfmls_handle* h, const RowCounts& rows, int64_t k0, int64_t bw, int64_t kOuter, T* SA,
+                             int64_t ld, const PanelBufs<T>& pb, uint64_t* ll, double* cq_ws, int* cq_status, T* tau_out) {
   hipStream_t st = h->stream;
   for (int64_t p0 = k0; p0 < k0 + bw; p0 += kMaxNb) {
     const int jb = (int)(k0 + bw - p0 < kMaxNb ? k0 + bw - p0 : kMaxNb);
-    const int64_t M = s - p0;
+    const int64_t M = rows.at(p0) - p0;
     const int64_t split_in = inner_split(M);
     PanelShape sh;
     int64_t G = 0;
@@ -779,11 +876,11 @@ struct TrailBufs {
 // and T_o is built from that Gram (its diagonal 64-blocks from the panels,
 // except the last panel's); without, T_o must already hold the block's T.
 template <typename T>
-rfmls_status qr_block_trailing(rfmls_handle* h, int64_t s, int64_t k0, int64_t bw, int64_t kOuter, T* SA, int64_t ld,
-                               int64_t off, int64_t nc, int64_t nc_m, bool gram, const T* tau, T* To,
+rfmls_status qr_block_trailing(rfmls_handle* h, const RowCounts& rows, int64_t k0, int64_t bw, int64_t kOuter, T* SA,
+                               int64_t ld, int64_t off, int64_t nc, int64_t nc_m, bool gram, const T* tau, T* To,
                                const TrailBufs<T>& tb, bool keep_gram = false) {
   hipStream_t st = h->stream;
-  const int64_t M0 = s - k0;
+  const int64_t M0 = rows.at(k0 + bw - 1) - k0;
   const int64_t split_out = outer_split(M0);
   T* P0 = SA + k0 * ld + k0;
   const int64_t vc = gram ? bw : 0;  // V's own columns in the product
@@ -799,8 +896,8 @@ rfmls_status qr_block_trailing(rfmls_handle* h, int64_t s, int64_t k0, int64_t b
   const int64_t nsc = (Kc + split_out - 1) / split_out;
   const int64_t nsp = 1 + nsc + (Kt > 0 ? 1 : 0);
   const int64_t zs = bw * ldw;
-  auto product = [&](int64_t r0, int64_t rows, T* out, int64_t ksplit) {
-    GemmArgs<T> g = vt_gemm<T>(P0 + r0 * ld, ld, rows, bw, ncols, out, ldw, ksplit);
+  auto product = [&](int64_t r0, int64_t nr, T* out, int64_t ksplit) {
+    GemmArgs<T> g = vt_gemm<T>(P0 + r0 * ld, ld, nr, bw, ncols, out, ldw, ksplit);
     if (!gram) {
       g.B = Bc + r0 * ld;
       g.b_vcols = 0;
@@ -903,6 +1000,77 @@ rfmls_status lookahead_stream(rfmls_handle* h) {
   return RFMLS_OK;
 }
 
+// Sorts SA's rows by the panel of their first nonzero where that saves at least
+// a tenth of the QR's work, and gives the rows each panel works on.  tmp (tmp_len
+// elements) holds a slab of columns during the move: a slab's rows are gathered
+// into tmp in the new order and copied back, the rows still zero there left where
+// they are (nothing reads them until a later slab moves them).
+//   act[k]  at least the panel's rows (so that R's rows exist), and at least
+//           kCholqrMinRows of them, so that the first panels of a sparse sketch
+//           stay on CholeskyQR2; whole multiples of 64 keep the clean kernels.
+// Costs a host wait for the counts (about 30 us with the search and the sort), so
+// small sketches, where the panels' latency is most of the time, keep their order.
+constexpr int64_t kSortMinElems = (int64_t)1 << 21;
+template <typename T>
+rfmls_status sort_rows(rfmls_handle* h, int64_t s, int64_t n, int64_t kOuter, T* SA, int64_t ld, T* tmp,
+                       int64_t tmp_len, RowCounts* rows) {
+  rows->s = s;
+  rows->act.clear();
+  if (s * n < kSortMinElems || s >= INT32_MAX) return RFMLS_OK;
+  hipStream_t st = h->stream;
+  const int64_t npan = (n + kMaxNb - 1) / kMaxNb;
+  void* p;
+  RFMLS_CHECK(workspace(h, WS_QR_ORDER, sizeof(int32_t) * (size_t)(2 * s + npan + 1), &p));
+  int32_t* key = (int32_t*)p;
+  int32_t* perm = key + s;
+  int32_t* cnt = perm + s;
+  std::vector<int32_t> c((size_t)npan + 1);
+  {
+    Trace tr(h, "qr_row_order", 4.0 * 3.0 * (double)s, 0.0);
+    hipLaunchKernelGGL(k_row_keys<T>, dim3(ceil_div(s, 4)), dim3(256), 0, st, (const T*)SA, ld, s, n, (int)npan, key);
+    hipLaunchKernelGGL(k_row_order, dim3((unsigned)npan + 1), dim3(256), 0, st, (const int32_t*)key, s, perm, cnt);
+    RFMLS_HIP(h, hipGetLastError());
+  }
+  RFMLS_HIP(h, hipMemcpyAsync(c.data(), cnt, sizeof(int32_t) * c.size(), hipMemcpyDeviceToHost, st));
+  RFMLS_HIP(h, hipStreamSynchronize(st));
+  std::vector<int64_t> act((size_t)npan);
+  double plain = 0.0, sorted = 0.0;
+  for (int64_t k = 0; k < npan; ++k) {
+    const int64_t p0 = k * kMaxNb;
+    int64_t a = c[(size_t)k];
+    a = a > p0 + kMaxNb + kCholqrMinRows ? a : p0 + kMaxNb + kCholqrMinRows;
+    a = (a + kMaxNb - 1) / kMaxNb * kMaxNb;
+    if (k > 0 && act[(size_t)k - 1] > a) a = act[(size_t)k - 1];
+    act[(size_t)k] = a < s ? a : s;
+    plain += (double)(s - p0) * (double)(n - p0);
+    sorted += (double)(act[(size_t)k] - p0) * (double)(n - p0);
+  }
+  if (sorted > 0.9 * plain) return RFMLS_OK;
+  // slabs of whole panels, as many columns as tmp holds for the rows that the
+  // outer block of the slab's last panel works on (its V spans the whole block,
+  // so a panel's zeros are needed down to there)
+  const int64_t po = kOuter / kMaxNb;
+  auto moved = [&](int64_t k) {
+    const int64_t e = (k / po + 1) * po - 1;
+    return act[(size_t)(e < npan ? e : npan - 1)];
+  };
+  if (moved(npan - 1) * kMaxNb > tmp_len) return RFMLS_OK;
+  for (int64_t k0 = 0; k0 < npan;) {
+    int64_t k1 = k0 + 1;
+    while (k1 < npan && moved(k1) * (k1 + 1 - k0) * kMaxNb <= tmp_len) ++k1;
+    const int64_t c0 = k0 * kMaxNb, w = (k1 * kMaxNb < n ? k1 * kMaxNb : n) - c0, na = moved(k1 - 1);
+    Trace tr(h, "qr_row_move", 2.0 * sizeof(T) * (double)na * (double)w, 0.0);
+    hipLaunchKernelGGL(k_move_rows<T>, dim3((unsigned)na), dim3(256), 0, st, (const T*)(SA + c0), ld,
+                       (const int32_t*)perm, w, tmp, w);
+    hipLaunchKernelGGL(k_move_rows<T>, dim3((unsigned)na), dim3(256), 0, st, (const T*)tmp, w, (const int32_t*)nullptr,
+                       w, SA + c0, ld);
+    k0 = k1;
+  }
+  RFMLS_HIP(h, hipGetLastError());
+  rows->act.swap(act);
+  return RFMLS_OK;
+}
+
 // n_room >= n columns of SA may be written: the big trailing products round
 // their column count up to the tile width inside that room (full tiles, no
 // ragged edge); the extra columns only ever hold values nothing reads.
@@ -967,9 +1135,17 @@ rfmls_status qr_impl(rfmls_handle* h, int64_t s, int64_t n, int64_t n_room, T* S
     PanelBufs<T> pb = {tau2[blk & 1], To2[blk & 1], in, in + in_wz, in + in_wz + in_w};
     return pb;
   };
+  // the rows' order is free when no reflector is applied afterwards
+  RowCounts rows;
+  rows.s = s;
+  if (!tau_out) RFMLS_CHECK(sort_rows<T>(h, s, n, kOuter, SA, ld, tb.Wz, (int64_t)wz_out, &rows));
   // block k + 1's panels all CholeskyQR2-eligible (64 columns, enough rows)
-  auto cq_block = [&](int64_t k1, int64_t bw1) { return bw1 % kMaxNb == 0 && s - (k1 + bw1 - kMaxNb) >= kCholqrMinRows; };
-  RFMLS_CHECK(qr_block_panels<T>(h, s, 0, n < kOuter ? n : kOuter, kOuter, SA, ld, bufs(0), ll, cq_ws, cq_status,
+  auto cq_block = [&](int64_t k1, int64_t bw1) {
+    for (int64_t p = k1; p < k1 + bw1; p += kMaxNb)
+      if (rows.at(p) - p < kCholqrMinRows) return false;
+    return bw1 % kMaxNb == 0;
+  };
+  RFMLS_CHECK(qr_block_panels<T>(h, rows, 0, n < kOuter ? n : kOuter, kOuter, SA, ld, bufs(0), ll, cq_ws, cq_status,
                                  tau_out));
   int64_t blk = 0;
   for (int64_t k0 = 0; k0 < n; k0 += kOuter, ++blk) {
@@ -983,24 +1159,24 @@ rfmls_status qr_impl(rfmls_handle* h, int64_t s, int64_t n, int64_t n_room, T* S
     const PanelBufs<T> pb = bufs(blk), pb1 = bufs(blk + 1);
     if (lookahead && ntr_m > kOuter && cq_block(k1, bw1)) {
       // block k + 1's columns first, its panels on the second stream, the rest here
-      RFMLS_CHECK(qr_block_trailing<T>(h, s, k0, bw, kOuter, SA, ld, 0, kOuter, kOuter, true, pb.tau, pb.To, tb,
+      RFMLS_CHECK(qr_block_trailing<T>(h, rows, k0, bw, kOuter, SA, ld, 0, kOuter, kOuter, true, pb.tau, pb.To, tb,
                                        true));
       RFMLS_HIP(h, hipEventRecord(h->la_event[0], st));
       RFMLS_HIP(h, hipStreamWaitEvent(h->la_stream, h->la_event[0], 0));
       h->stream = h->la_stream;
       const rfmls_status ps =
-          qr_block_panels<T>(h, s, k1, bw1, kOuter, SA, ld, pb1, ll, cq_ws, cq_status, tau_out);
+          qr_block_panels<T>(h, rows, k1, bw1, kOuter, SA, ld, pb1, ll, cq_ws, cq_status, tau_out);
       const hipError_t er = hipEventRecord(h->la_event[1], h->la_stream);
       h->stream = st;
       RFMLS_CHECK(ps);
       RFMLS_HIP(h, er);
-      const rfmls_status ts = qr_block_trailing<T>(h, s, k0, bw, kOuter, SA, ld, kOuter, ntr - kOuter,
+      const rfmls_status ts = qr_block_trailing<T>(h, rows, k0, bw, kOuter, SA, ld, kOuter, ntr - kOuter,
                                                    ntr_m - kOuter, false, pb.tau, pb.To, tb);
       RFMLS_HIP(h, hipStreamWaitEvent(st, h->la_event[1], 0));
       RFMLS_CHECK(ts);
     } else {
-      RFMLS_CHECK(qr_block_trailing<T>(h, s, k0, bw, kOuter, SA, ld, 0, ntr, ntr_m, true, pb.tau, pb.To, tb));
-      RFMLS_CHECK(qr_block_panels<T>(h, s, k1, bw1, kOuter, SA, ld, pb1, ll, cq_ws, cq_status, tau_out));
+      RFMLS_CHECK(qr_block_trailing<T>(h, rows, k0, bw, kOuter, SA, ld, 0, ntr, ntr_m, true, pb.tau, pb.To, tb));
+      RFMLS_CHECK(qr_block_panels<T>(h, rows, k1, bw1, kOuter, SA, ld, pb1, ll, cq_ws, cq_status, tau_out));
     }
   }
   return RFMLS_OK;

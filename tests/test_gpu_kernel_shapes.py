@@ -102,3 +102,52 @@ def test_run_products_in_chunks(nrhs):
     assert rc == 0
     assert np.linalg.norm(X.cpu().numpy() - want) <= 1e-10 * np.linalg.norm(want)
     assert np.linalg.norm(Res.cpu().numpy() - (B - want @ Ad.T)) <= 1e-10 * np.linalg.norm(B)
+
+
+def _staircase(s, n, width, per_row, seed, zero_rows=0):
+    """Rows with entries in `per_row` random blocks of `width` columns, as a count
+    sketch of box-structured rows has them; the last zero_rows rows empty."""
+    rng = np.random.default_rng(seed)
+    M = np.zeros((s, n))
+    nb = -(-n // width)
+    for i in range(s - zero_rows):
+        for q in rng.choice(nb, size=min(nb, per_row), replace=False):
+            M[i, q * width:(q + 1) * width] = rng.standard_normal(min(n, (q + 1) * width) - q * width)
+    return M
+
+
+# QR of sketches whose rows start late, factored in sorted row order: the last
+# panel ragged, one to three outer blocks, entries that start inside a panel, the
+# moving slabs smaller than the matrix, empty rows, and the right-hand sides' extra
+# columns.  R^T R = (SA)^T SA to the gate of the dense factorisations, 20 n u.
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("s,n,width,per_row,zero_rows", [
+    (9000, 250, 25, 1, 0), (6000, 400, 40, 2, 500), (5200, 577, 30, 2, 0), (3300, 640, 64, 1, 3),
+    (33500, 320, 20, 1, 100)])
+def test_qr_of_rows_that_start_late(s, n, width, per_row, zero_rows, dtype):
+    SA = _staircase(s, n, width, per_row, s + n, zero_rows)
+    u = 2.0 ** -53 if dtype == "f64" else 2.0 ** -24
+    td = torch.float64 if dtype == "f64" else torch.float32
+    h = R.Handle(device="cuda:0")
+    gram = SA.T @ SA
+    Rs = []
+    for extra in (0, 2):
+        buf = R.sketch_buffer(s, n + extra, dtype)
+        buf.zero_()
+        buf[:, :n] = torch.tensor(SA, device="cuda", dtype=td)
+        if extra:
+            Sb = torch.randn((extra, s), dtype=torch.float64, device="cuda", generator=torch.Generator("cuda").manual_seed(3))
+            P, X0 = R.rfmls_precond_x0(h, buf, n, Sb, dtype, dtype)
+            if dtype == "f64":  # kappa(SA) is a few tens: the least-squares solution to 1e-11
+                want = np.linalg.lstsq(SA, Sb.cpu().numpy().T, rcond=None)[0].T
+                assert np.linalg.norm(X0.cpu().numpy() - want) <= 1e-11 * np.linalg.norm(want)
+        else:
+            P = R.rfmls_precond(h, buf[:, :n], dtype, dtype)
+        Rm = R.rfmls_precond_export_R(h, P).cpu().numpy()
+        assert np.all(np.diag(Rm) > 0) and np.array_equal(Rm, np.triu(Rm))
+        ref = gram if dtype == "f64" else None
+        if ref is None:
+            S32 = SA.astype(np.float32).astype(np.float64)
+            ref = S32.T @ S32
+        assert np.linalg.norm(Rm.T @ Rm - ref) <= 20 * n * u * np.linalg.norm(SA) ** 2
+        Rs.append(Rm)

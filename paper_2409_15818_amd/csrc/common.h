@@ -331,12 +331,38 @@ rfmls_status put_sketched_rhs(rfmls_handle* h, int64_t s, int64_t n, int64_t nrh
 rfmls_status sketched_solution(rfmls_handle* h, const rfmls_precond_t* P, int64_t nrhs,
                                rfmls_dtype dt, const void* SA, int64_t ld, double* X0,
                                int64_t ldx0);
-// out = X in (trans 0) or X^T in (trans 1), X the stored preconditioner (R^{-1} or P),
-// minus hcoef (*dcoef) prev when prev is given; per-block sums of squares of
-// out into sq when given; nothing when *done is set
+// Scalars of out = s acc - c prev, formed on the device.  The LSQR vectors are kept
+// unnormalised (beta u, alpha v) and a product is divided by the norm of the vector
+// it was taken with, so no pass over a vector only scales it.
+//   plain      s, c as given
+//   sdiv       s / *sdiv, and with cnum c *cnum / *cden  (a norm of 0 divides to 0)
+//   sq         the norm nu = sqrt(sum sq[0 .. nsq)) of the vector just multiplied:
+//              s / nu and c nu / *cden; nu is stored in *norm (by one block)
+struct LazyScale {
+  double s = 1.0, c = 0.0;
+  const double* sdiv = nullptr;
+  const double *cnum = nullptr, *cden = nullptr;
+  const double* sq = nullptr;
+  int nsq = 0;
+  double* norm = nullptr;
+};
+struct LsqrDev;
+// Commit of an iteration's state by one extra workgroup of a later kernel (or by a
+// kernel of its own): see commit_state in lsqr.hip.  st null: nothing to commit.
+struct LsqrCommit {
+  LsqrDev* st = nullptr;
+  LsqrDev* next = nullptr;
+  const double *ysq = nullptr, *wsq = nullptr;
+  int n = 0;
+  int consistent = 0;
+};
+// out = s (X in) (trans 0) or s (X^T in) (trans 1) - c prev, X the stored
+// preconditioner (R^{-1} or P); per-block sums of squares of out into sq (their
+// count in *nsq) when given; nothing when *done is set
 rfmls_status tri_apply(rfmls_handle* h, const rfmls_precond_t* P, int trans, const double* in,
-                       double* out, double hcoef, const double* dcoef, const double* prev,
-                       double* sq, const int* done);
+                       double* out, const LazyScale& sc = LazyScale(), const double* prev = nullptr,
+                       double* sq = nullptr, int* nsq = nullptr, const int* done = nullptr,
+                       const LsqrCommit& commit = LsqrCommit());
 rfmls_status unpack_precond(rfmls_handle* h, const rfmls_precond_t* P, double* Xdense);
 // column runs of M's rows (lsqr.hip): nrun[i] runs of row i (-1: more than
 // kMaxRuns), run k starting at column rcol[i kMaxRuns + k] and ending before

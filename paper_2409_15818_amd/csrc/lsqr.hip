@@ -7,7 +7,12 @@
 //   u^ = A z - a u     SpMV over each row's column runs                (k_spmv_runs)
 //   q = A^T u          the same with the explicit transpose            (k_spmv_runs)
 //   v^ = X^T q - b v   transposed triangular product                   (k_trmvT_*)
-// followed by the plane rotation and the updates of y and w.  Norms are
+// followed by the plane rotation and the updates of y and w.  u and v are kept
+// unnormalised (beta u, alpha v): the pass that would only scale a vector by its
+// new norm is folded into the next product (LazyScale), and the scalars of an
+// iteration are formed by every workgroup of the update kernel from the partial
+// sums.  An iteration is seven launches (five for small preconditioners, whose
+// triangular products need no second pass) instead of eleven.  Norms are
 // reduced in a fixed order (per-block partials, then a fixed tree), so runs
 // are bitwise reproducible.  The host only polls a device "done" flag every
 // few iterations; kernels launched after the stop return immediately.
@@ -21,6 +26,85 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kSpmvMaxBlocks = 2048;
+
+__device__ __forceinline__ double inv_or_0(double x) { return x > 0.0 ? 1.0 / x : 0.0; }
+
+// sum sq[0..nsq) in a fixed order, on every thread of the block
+__device__ double reduce_partials(const double* __restrict__ sq, int nsq, double* scratch) {
+  double t = 0.0;
+  for (int i = threadIdx.x; i < nsq; i += blockDim.x) t += sq[i];
+  return block_sum(t, scratch);
+}
+
+// The scalars of out = s acc - c prev (every thread of the block calls it).
+__device__ __forceinline__ void lazy_scale(const LazyScale& L, double* scratch, double* s, double* c) {
+  *s = L.s;
+  *c = L.c;
+  if (L.sq) {
+    const double nu = sqrt(reduce_partials(L.sq, L.nsq, scratch));
+    if (blockIdx.x == 0 && threadIdx.x == 0) *L.norm = nu;
+    *s *= inv_or_0(nu);
+    if (L.cden) *c *= nu * inv_or_0(*L.cden);
+  } else {
+    if (L.sdiv) *s *= inv_or_0(*L.sdiv);
+    if (L.cnum) *c *= *L.cnum * inv_or_0(*L.cden);
+  }
+}
+
+// Takes the state an iteration left in `next` (k_lsqr_step) into `st`, with the
+// sums of its y and w and the stopping tests (S1 needs ||y_k||, known only once
+// every workgroup of the update is done).  One workgroup; nothing when there is
+// no uncommitted state, so it may run both at the end of a poll interval and in
+// the next iteration's first kernel.  That kernel's other workgroups use nothing
+// of the state but the stop flag, whose being set early or late by one kernel
+// changes no result.
+__device__ void commit_state(const LsqrCommit& cm, double* scratch) {
+  if (!cm.next->fresh) return;  // uniform
+  const double y2 = reduce_partials(cm.ysq, cm.n, scratch);
+  const double w2 = reduce_partials(cm.wsq, cm.n, scratch);
+  if (threadIdx.x != 0) return;
+  LsqrDev s = *cm.next;
+  cm.next->fresh = 0;
+  s.fresh = 0;
+  if (!s.done) {
+    s.ynorm = sqrt(y2);
+    s.w2 = w2;
+    const double anorm = sqrt(s.anorm2);
+    const double rtol = cm.consistent ? s.btol * s.bnorm : s.btol * s.bnorm + s.atol * anorm * s.ynorm;
+    int istop = 0;
+    if (s.normr <= rtol) istop = 1;
+    else if (s.pending) istop = s.pending;
+    else if (s.itn >= s.itmax) istop = 7;
+    if (istop) {
+      s.istop = istop;
+      s.done = 1;
+    }
+  }
+  *cm.st = s;
+}
+__global__ void __launch_bounds__(kThreads) k_commit(LsqrCommit cm) {
+  __shared__ double scratch[kThreads / 64];
+  commit_state(cm, scratch);
+}
+
+// Sums of 16 rows over the wavefront's lanes (a[q]: this lane's part of row q):
+// halving exchanges, 17 in all instead of six per row; every lane receives row
+// lane / 4.
+__device__ __forceinline__ double rows16_sum(double (&a)[16], int lane) {
+#pragma unroll
+  for (int o = 8; o > 0; o >>= 1) {
+    const bool hi = lane & (4 * o);
+#pragma unroll
+    for (int q = 0; q < o; ++q) {
+      const double keep = hi ? a[q + o] : a[q], give = hi ? a[q] : a[q + o];
+      a[q] = keep + __shfl_xor(give, 4 * o, 64);
+    }
+  }
+  double s = a[0];
+  s += __shfl_xor(s, 2, 64);
+  s += __shfl_xor(s, 1, 64);
+  return s;
+}
 
 // ---------------------------------------------------------------------------
 // Triangular products with the packed tiles of X (64 x 64, upper triangle)
@@ -53,11 +137,8 @@ __global__ void __launch_bounds__(kThreads)
 #pragma unroll
     for (int q = 0; q < 16; ++q) acc[q] += (double)t[(w + 4 * q) * kTile + lane] * vc;
   }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const double s = wave_sum(acc[q]);
-    if (lane == 0) part[((int64_t)I * maxk + k) * kTile + w + 4 * q] = s;
-  }
+  const double s = rows16_sum(acc, lane);
+  if ((lane & 3) == 0) part[((int64_t)I * maxk + k) * kTile + w + 4 * (lane >> 2)] = s;
 }
 
 // p = X^T q: block e handles tile column J = tab[e].x, tiles I in [k C, min((k+1) C, col_end(J))).
@@ -100,36 +181,48 @@ __global__ void __launch_bounds__(kThreads)
         (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
 }
 
-// out[i] = sum_k part[row(i)][k] - coef * prev[i];  partial sum of squares per block.
+// out[i] = s sum_k part[row(i)][k] - c prev[i];  partial sum of squares per block.
 // nk(I) = number of chunks of tile row/column I (trans: ceil(col_end(I)/C), else
 // ceil((nt - row_first(I))/C)).
 // A block handles tile rows I (64 outputs each, grid-stride); its four
 // wavefronts sum every fourth partial of each output (independent loads in
-// flight), and the four quarter sums are added in a fixed order.
+// flight), and the four quarter sums are added in a fixed order.  With a commit,
+// the last block only commits.
 constexpr int kRedMaxBlocks = 2048;
 
 __global__ void __launch_bounds__(kThreads)
     k_tri_reduce(const double* __restrict__ part, int64_t nt, int64_t n, int full, int C, int maxk, int trans,
-                 double hcoef, const double* __restrict__ dcoef, const double* prev,
-                 double* out, double* __restrict__ sq, const int* __restrict__ done) {
-  if (done && *done) return;
+                 LazyScale sc, const double* prev, double* out, double* __restrict__ sq,
+                 const int* __restrict__ done, LsqrCommit cm) {
   __shared__ double scratch[kThreads / 64];
   __shared__ double quarter[kThreads / 64][kTile];
+  unsigned nblk = gridDim.x;
+  if (cm.st) {
+    if (blockIdx.x == --nblk) {
+      commit_state(cm, scratch);
+      return;
+    }
+  }
+  if (done && *done) return;
   const int r = threadIdx.x & (kTile - 1);
   const int q = threadIdx.x / kTile;
-  double cf = hcoef;
-  if (dcoef) cf *= *dcoef;
+  double s1 = 0.0, cf = 0.0;
+  bool scaled = false;
   double ss = 0.0;
-  for (int64_t I = blockIdx.x; I < nt; I += gridDim.x) {
+  for (int64_t I = blockIdx.x; I < nt; I += nblk) {
     const int64_t i = I * kTile + r;
     const int64_t nk = trans ? (col_end(I, nt, full) + C - 1) / C : (nt - row_first(I, full) + C - 1) / C;
     double s = 0.0;
     if (i < n)
       for (int64_t k = q; k < nk; k += kThreads / kTile) s += part[(I * maxk + k) * kTile + r];
     quarter[q][r] = s;
+    if (!scaled) {  // after the first sums' loads have been issued
+      lazy_scale(sc, scratch, &s1, &cf);
+      scaled = true;
+    }
     __syncthreads();
     if (q == 0 && i < n) {
-      double t = (quarter[0][r] + quarter[1][r]) + (quarter[2][r] + quarter[3][r]);
+      double t = s1 * ((quarter[0][r] + quarter[1][r]) + (quarter[2][r] + quarter[3][r]));
       if (prev && cf != 0.0) t -= cf * prev[i];
       out[i] = t;
       ss += t * t;
@@ -142,8 +235,124 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
+// The triangular products of a preconditioner of at most kSmallTiles tile rows in
+// one launch: a workgroup of eight wavefronts per 16 outputs, the tiles of its
+// row (column) dealt to the wavefronts in turn and their sums added in order, so
+// no partial sums go through memory.  There, the second launch of the two-pass
+// form costs more than the coarser split: n = 1,600, X v 7.4 + 3.8 us in two
+// launches (a workgroup here reads at most 256 KB of X); wider ones need the
+// split over tiles to keep every compute unit reading.
+constexpr int64_t kSmallTiles = 32;
+constexpr int kSmallWaves = 8;
+
+__device__ __forceinline__ void small_store(double v, int64_t i, bool live, double s1, double cf, const double* prev,
+                                            double* out, double* sq) {
+  double t = 0.0;
+  if (live) {
+    t = s1 * v;
+    if (prev && cf != 0.0) t -= cf * prev[i];
+    out[i] = t;
+  }
+  if (sq) {  // lanes 0 .. 15 of wavefront 0
+    t *= t;
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    if (threadIdx.x == 0) sq[blockIdx.x] = t;
+  }
+}
+
+template <typename TS>
+__global__ void __launch_bounds__(64 * kSmallWaves)
+    k_trmv_small(const TS* __restrict__ Xpk, int64_t nt, int64_t n, int full, const double* __restrict__ v,
+                 LazyScale sc, const double* prev, double* out, double* __restrict__ sq,
+                 const int* __restrict__ done, LsqrCommit cm) {
+  __shared__ double scratch[kSmallWaves];
+  __shared__ double red[kSmallWaves][16];
+  if (cm.st && blockIdx.x == gridDim.x - 1) {
+    commit_state(cm, scratch);
+    return;
+  }
+  if (done && *done) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t I = blockIdx.x >> 2;
+  const int r0 = 16 * (blockIdx.x & 3);
+  double acc[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) acc[q] = 0.0;
+#pragma unroll 2
+  for (int64_t J = row_first(I, full) + w; J < nt; J += kSmallWaves) {
+    const TS* t = Xpk + ptile(I, J, nt, full) * (int64_t)(kTile * kTile) + r0 * kTile;
+    const int64_t gc = J * kTile + lane;
+    const double vc = gc < n ? v[gc] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) acc[q] += (double)t[q * kTile + lane] * vc;
+  }
+  const double s = rows16_sum(acc, lane);
+  if ((lane & 3) == 0) red[w][lane >> 2] = s;
+  double s1, cf;
+  lazy_scale(sc, scratch, &s1, &cf);
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < kSmallWaves; ++q) t += red[q][threadIdx.x];
+    const int64_t i = I * kTile + r0 + threadIdx.x;
+    small_store(t, i, i < n, s1, cf, prev, out, sq);
+  }
+}
+
+template <typename TS>
+__global__ void __launch_bounds__(64 * kSmallWaves)
+    k_trmvT_small(const TS* __restrict__ Xpk, int64_t nt, int64_t n, int full, const double* __restrict__ qv,
+                  LazyScale sc, const double* prev, double* out, double* __restrict__ sq,
+                  const int* __restrict__ done, LsqrCommit cm) {
+  __shared__ double scratch[kSmallWaves];
+  __shared__ double red[kSmallWaves][16];
+  if (cm.st && blockIdx.x == gridDim.x - 1) {
+    commit_state(cm, scratch);
+    return;
+  }
+  if (done && *done) return;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int lr = lane & 15, lk = lane >> 4;
+  const int64_t J = blockIdx.x >> 2;
+  const int c0 = 16 * (blockIdx.x & 3);
+  const int64_t Iend = col_end(J, nt, full);
+  double acc0 = 0.0, acc1 = 0.0;
+  for (int64_t I = w; I < Iend; I += kSmallWaves) {
+    const TS* t = Xpk + ptile(I, J, nt, full) * (int64_t)(kTile * kTile) + c0 + lr;
+    double x[16], y[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int r = 4 * q + lk;
+      const int64_t gr = I * kTile + r;
+      x[q] = (double)t[r * kTile];
+      y[q] = gr < n ? qv[gr] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; q += 2) {
+      acc0 += x[q] * y[q];
+      acc1 += x[q + 1] * y[q + 1];
+    }
+  }
+  double s = acc0 + acc1;
+  s += __shfl_xor(s, 16, 64);
+  s += __shfl_xor(s, 32, 64);
+  if (lane < 16) red[w][lane] = s;
+  double s1, cf;
+  lazy_scale(sc, scratch, &s1, &cf);
+  __syncthreads();
+  if (threadIdx.x < 16) {
+    double t = 0.0;
+#pragma unroll
+    for (int q = 0; q < kSmallWaves; ++q) t += red[q][threadIdx.x];
+    const int64_t i = J * kTile + c0 + threadIdx.x;
+    small_store(t, i, i < n, s1, cf, prev, out, sq);
+  }
+}
+
 // ---------------------------------------------------------------------------
-// CSR SpMV: out[row] = sA * (A x)[row] - coef * prev[row]; half a wavefront (32
+// CSR SpMV: out[row] = s (A x)[row] - c prev[row]; half a wavefront (32
 // lanes) per row, two entries per lane in flight (measured on the RFM matrix
 // and its transpose: 5.2-5.9 TB/s against 3.8-4.3 for a wavefront per row).
 // ---------------------------------------------------------------------------
@@ -151,16 +360,22 @@ constexpr int kSpvLanes = 32;
 
 __global__ void __launch_bounds__(kThreads)
     k_spmv(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
-           const double* __restrict__ val, int64_t rows, const double* __restrict__ x, double sA,
-           double hcoef, const double* __restrict__ dcoef, const double* prev, double* out,
-           double* __restrict__ sq, const int* __restrict__ done) {
-  if (done && *done) return;
+           const double* __restrict__ val, int64_t rows, const double* __restrict__ x, LazyScale sc,
+           const double* prev, double* out, double* __restrict__ sq, const int* __restrict__ done, LsqrCommit cm) {
   __shared__ double scratch[kThreads / 64];
+  unsigned nblk = gridDim.x;
+  if (cm.st) {
+    if (blockIdx.x == --nblk) {
+      commit_state(cm, scratch);
+      return;
+    }
+  }
+  if (done && *done) return;
   const int lane = threadIdx.x & (kSpvLanes - 1);
   const int64_t sub = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / kSpvLanes;
-  const int64_t nsub = (int64_t)gridDim.x * (kThreads / kSpvLanes);
-  double cf = hcoef;
-  if (dcoef) cf *= *dcoef;
+  const int64_t nsub = (int64_t)nblk * (kThreads / kSpvLanes);
+  double sA, cf;
+  lazy_scale(sc, scratch, &sA, &cf);
   double ss = 0.0;
   for (int64_t row = sub; row < rows; row += nsub) {
     const int64_t lo = rp[row], hi = rp[row + 1];
@@ -243,15 +458,22 @@ __global__ void __launch_bounds__(kThreads)
     k_spmv_runs(const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
                 const double* __restrict__ val, int64_t rows, const int32_t* __restrict__ nrun,
                 const int32_t* __restrict__ rcol, const int32_t* __restrict__ rend,
-                const double* __restrict__ x, double sA, double hcoef, const double* __restrict__ dcoef,
-                const double* prev, double* out, double* __restrict__ sq, const int* __restrict__ done) {
-  if (done && *done) return;
+                const double* __restrict__ x, LazyScale sc, const double* prev, double* out,
+                double* __restrict__ sq, const int* __restrict__ done, LsqrCommit cm) {
   __shared__ double scratch[kThreads / 64];
+  unsigned nblk = gridDim.x;
+  if (cm.st) {
+    if (blockIdx.x == --nblk) {
+      commit_state(cm, scratch);
+      return;
+    }
+  }
+  if (done && *done) return;
   const int lane = threadIdx.x & (L - 1);
   const int64_t sub = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / L;
-  const int64_t nsub = (int64_t)gridDim.x * (kThreads / L);
-  double cf = hcoef;
-  if (dcoef) cf *= *dcoef;
+  const int64_t nsub = (int64_t)nblk * (kThreads / L);
+  double sA, cf;
+  lazy_scale(sc, scratch, &sA, &cf);
   double ss = 0.0;
   int64_t lo = 0, hi = 0;
   int nr = 0;
@@ -326,63 +548,14 @@ __global__ void __launch_bounds__(kThreads)
 // ---------------------------------------------------------------------------
 // Vector helpers
 // ---------------------------------------------------------------------------
-// nrm = sqrt(sum sq[0..nsq)), fixed order; every block computes it, block 0 stores it.
-__device__ double reduce_partials(const double* __restrict__ sq, int nsq, double* scratch) {
-  double t = 0.0;
-  for (int i = threadIdx.x; i < nsq; i += blockDim.x) t += sq[i];
-  return block_sum(t, scratch);
-}
-
-__global__ void __launch_bounds__(kThreads)
-    k_normalize(double* vec, int64_t len, const double* __restrict__ sq, int nsq,
-                double* __restrict__ nrm_out, const int* __restrict__ done) {
-  if (done && *done) return;
-  __shared__ double scratch[kThreads / 64];
-  const double nrm = sqrt(reduce_partials(sq, nsq, scratch));
-  const double inv = nrm > 0.0 ? 1.0 / nrm : 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < len;
-       i += (int64_t)gridDim.x * kThreads)
-    vec[i] *= inv;
-  if (blockIdx.x == 0 && threadIdx.x == 0) *nrm_out = nrm;
-}
-
-// out = (a * x + b * y) with a = ha * (*da), b = hb * (*db) (null pointers read as 1)
-__global__ void k_axpby(int64_t len, double ha, const double* __restrict__ da, const double* x,
-                        double hb, const double* __restrict__ db, const double* y, double* out,
-                        const int* __restrict__ done) {
-  if (done && *done) return;
-  double a = ha, b = hb;
-  if (da) a *= *da;
-  if (db) b *= *db;
+// out = a x + b y
+__global__ void k_axpby(int64_t len, double a, const double* x, double b, const double* y, double* out) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < len;
        i += (int64_t)gridDim.x * blockDim.x) {
     double o = a * x[i];
     if (y) o += b * y[i];
     out[i] = o;
   }
-}
-
-// out = (x - hb * (*db) * y) / (*dal)   (0 where *dal is not positive)
-__global__ void k_recip_scale(const double* x, double hb, const double* __restrict__ db,
-                              const double* y, const double* __restrict__ dal, double* out,
-                              int64_t len, const int* __restrict__ done) {
-  if (done && *done) return;
-  const double al = *dal;
-  const double inv = al > 0.0 ? 1.0 / al : 0.0;
-  double b = hb;
-  if (db) b *= *db;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < len;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    double o = x[i];
-    if (y && b != 0.0) o -= b * y[i];
-    out[i] = o * inv;
-  }
-}
-
-__global__ void k_fill(double* p, int64_t len, double v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < len;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
 }
 
 // out[0] = sqrt(sum sq[0..nsq)) in the fixed order of reduce_partials (one block)
@@ -393,13 +566,17 @@ __global__ void __launch_bounds__(kThreads) k_sqrt_sum(const double* __restrict_
   if (threadIdx.x == 0) out[0] = sqrt(t);
 }
 
-__global__ void __launch_bounds__(kThreads) k_sumsq(const double* __restrict__ x, int64_t len,
-                                                    double* __restrict__ sq) {
+// per-block sums of squares of x, which is also copied to out when given
+__global__ void __launch_bounds__(kThreads) k_copy_sumsq(const double* x, int64_t len, double* out,
+                                                         double* __restrict__ sq) {
   __shared__ double scratch[kThreads / 64];
   double t = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < len;
-       i += (int64_t)gridDim.x * kThreads)
-    t += x[i] * x[i];
+       i += (int64_t)gridDim.x * kThreads) {
+    const double v = x[i];
+    if (out) out[i] = v;
+    t += v * v;
+  }
   t = block_sum(t, scratch);
   if (threadIdx.x == 0) sq[blockIdx.x] = t;
 }
@@ -407,91 +584,139 @@ __global__ void __launch_bounds__(kThreads) k_sumsq(const double* __restrict__ x
 // ---------------------------------------------------------------------------
 // LSQR scalars
 // ---------------------------------------------------------------------------
-// After beta_1 = ||b||: set up the state.
-__global__ void k_lsqr_start(LsqrDev* st) {
-  st->bnorm = st->beta;
-  st->phibar = st->beta;
-  st->anorm2 = 0.0;
-  st->ddnorm = 0.0;
-  st->itn = 0;
-  st->istop = 7;
-  st->pending = 0;
-  st->done = 0;
-  if (!isfinite(st->beta)) {  // a non-finite right-hand side: breakdown, not "x = 0 is exact"
-    st->istop = -3;
-    st->done = 1;
-  } else if (!(st->beta > 0.0)) {
-    st->istop = 0;
-    st->done = 1;
-  }
-}
-
-// After alpha_1 = ||B^T u_1||.
-__global__ void k_lsqr_start2(LsqrDev* st) {
-  if (st->done) return;
-  st->rhobar = st->alpha;
-  st->normr = st->beta;
-  st->normar = st->alpha * st->beta;
-  if (!isfinite(st->alpha)) {
-    st->istop = -3;
-    st->done = 1;
-  } else if (!(st->alpha > 0.0)) {
-    st->istop = 0;
-    st->done = 1;
-  }
-}
-
-// Plane rotation of iteration k (alpha = alpha_{k+1}, beta = beta_{k+1} are
-// already in the state); wsq holds the partial sums of ||w_k||^2.
-__global__ void __launch_bounds__(kThreads) k_lsqr_rotate(LsqrDev* st, const double* __restrict__ wsq,
-                                                          int nsq) {
-  if (st->done) return;
-  __shared__ double scratch[kThreads / 64];
-  const double w2 = reduce_partials(wsq, nsq, scratch);
-  if (threadIdx.x != 0) return;
-  const double alpha = st->alpha, beta = st->beta;
-  st->itn += 1;
-  st->anorm2 += st->alpha_prev * st->alpha_prev + beta * beta;
-  const double rho = hypot(st->rhobar, beta);
-  if (!(rho > 0.0) || !isfinite(rho)) {
-    st->istop = isfinite(rho) ? 1 : -3;
-    st->done = 1;
-    st->phi_rho = 0.0;
-    st->theta_rho = 0.0;
-    return;
-  }
-  const double c = st->rhobar / rho;
-  const double s = beta / rho;
-  const double theta = s * alpha;
-  st->rhobar = -c * alpha;
-  const double phi = c * st->phibar;
-  st->phibar = s * st->phibar;
-  st->phi_rho = phi / rho;
-  st->theta_rho = theta / rho;
-  st->ddnorm += w2 / (rho * rho);
-  const double anorm = sqrt(st->anorm2);
-  st->acond = anorm * sqrt(st->ddnorm);
-  st->normr = st->phibar;
-  st->normar = st->phibar * alpha * fabs(c);
-  st->pending = 0;
-  if (st->normr == 0.0 || st->normar <= st->atol * anorm * st->normr) st->pending = 2;
-  else if (st->conlim > 0.0 && st->acond >= st->conlim) st->pending = 3;
-  st->alpha_prev = alpha;
-}
-
-// y += phi/rho w;  w = v - theta/rho w;  partial sums of ||y||^2 and ||w||^2.
+// beta_1 = ||b|| from the partial sums: set up the state.
 __global__ void __launch_bounds__(kThreads)
-    k_lsqr_update(const LsqrDev* __restrict__ st, const double* __restrict__ v, double* w,
-                  double* y, int64_t n, double* __restrict__ ysq, double* __restrict__ wsq) {
+    k_lsqr_begin(LsqrDev* st, LsqrDev* next, const double* __restrict__ sq, int nsq, double atol, double btol,
+                 double conlim, int64_t itmax) {
+  __shared__ double scratch[kThreads / 64];
+  const double beta = sqrt(reduce_partials(sq, nsq, scratch));
+  if (threadIdx.x != 0) return;
+  LsqrDev s{};
+  s.atol = atol;
+  s.btol = btol;
+  s.conlim = conlim;
+  s.itmax = itmax;
+  s.beta = s.bnorm = s.phibar = beta;
+  s.istop = 7;
+  if (!isfinite(beta)) {  // a non-finite right-hand side: breakdown, not "x = 0 is exact"
+    s.istop = -3;
+    s.done = 1;
+  } else if (!(beta > 0.0)) {
+    s.istop = 0;
+    s.done = 1;
+  }
+  *st = s;
+  next->fresh = 0;
+}
+
+// After alpha_1 (sq: the partial sums of its vector).
+__global__ void __launch_bounds__(kThreads) k_lsqr_begin2(LsqrDev* st, const double* __restrict__ sq, int nsq) {
   if (st->done) return;
   __shared__ double scratch[kThreads / 64];
-  const double a = st->phi_rho, b = st->theta_rho;
+  const double alpha = sqrt(reduce_partials(sq, nsq, scratch));
+  if (threadIdx.x != 0) return;
+  st->alpha = st->alpha_prev = st->rhobar = alpha;
+  st->normr = st->beta;
+  st->normar = alpha * st->beta;
+  st->w2 = 1.0;  // w_1 = v_1
+  if (!isfinite(alpha)) {
+    st->istop = -3;
+    st->done = 1;
+  } else if (!(alpha > 0.0)) {
+    st->istop = 0;
+    st->done = 1;
+  }
+}
+
+// y_1 = 0 and w_1 = v^/alpha (v^ = alpha v), or of the backward's shadow vector
+// vt_1 = u^/(beta alpha), which is also kept in vt; wsq (optional): the partial sums
+// of ||w_1||^2
+__global__ void __launch_bounds__(kThreads)
+    k_lsqr_first_w(const LsqrDev* __restrict__ st, const double* __restrict__ v, int over_beta, double* vt, double* w,
+                   double* y, int64_t n, double* __restrict__ wsq) {
+  __shared__ double scratch[kThreads / 64];
+  double f = inv_or_0(st->alpha);
+  if (over_beta) f *= inv_or_0(st->beta);
+  double sw = 0.0;
+  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+    const double wi = v[i] * f;
+    if (vt) vt[i] = wi;
+    w[i] = wi;
+    y[i] = 0.0;
+    sw += wi * wi;
+  }
+  if (!wsq) return;
+  sw = block_sum(sw, scratch);
+  if (threadIdx.x == 0) wsq[blockIdx.x] = sw;
+}
+__global__ void __launch_bounds__(kThreads) k_lsqr_w2(LsqrDev* st, const double* __restrict__ wsq, int nsq) {
+  __shared__ double scratch[kThreads / 64];
+  const double t = reduce_partials(wsq, nsq, scratch);
+  if (threadIdx.x == 0) st->w2 = t;
+}
+
+// The rest of iteration k after alpha v^ (asq: the partial sums of its squares)
+// and beta (in the state): plane rotation, y += phi/rho w, w = v - theta/rho w,
+// partial sums of ||y||^2 and ||w||^2.  Every workgroup forms the same scalars from
+// the committed state; the first leaves the new one in `next` (commit_state).
+//   backward (vt given): v is the beta u of the iteration; the shadow vector vt =
+//   (u - beta vt) / alpha takes v's part.
+__global__ void __launch_bounds__(kThreads)
+    k_lsqr_step(const LsqrDev* __restrict__ st, LsqrDev* next, const double* __restrict__ asq, int nasq,
+                const double* __restrict__ v, double* vt, double* w, double* y, int64_t n, double* __restrict__ ysq,
+                double* __restrict__ wsq) {
+  if (st->done) return;
+  __shared__ double scratch[kThreads / 64];
+  LsqrDev s = *st;
+  const double alpha = sqrt(reduce_partials(asq, nasq, scratch));
+  const double beta = s.beta;
+  s.alpha = alpha;
+  s.itn += 1;
+  s.anorm2 += s.alpha_prev * s.alpha_prev + beta * beta;
+  const double rho = hypot(s.rhobar, beta);
+  s.pending = 0;
+  const bool good = rho > 0.0 && isfinite(rho);
+  if (good) {
+    const double c = s.rhobar / rho;
+    const double sn = beta / rho;
+    const double theta = sn * alpha;
+    s.rhobar = -c * alpha;
+    const double phi = c * s.phibar;
+    s.phibar = sn * s.phibar;
+    s.phi_rho = phi / rho;
+    s.theta_rho = theta / rho;
+    s.ddnorm += s.w2 / (rho * rho);
+    const double anorm = sqrt(s.anorm2);
+    s.acond = anorm * sqrt(s.ddnorm);
+    s.normr = s.phibar;
+    s.normar = s.phibar * alpha * fabs(c);
+    if (s.normr == 0.0 || s.normar <= s.atol * anorm * s.normr) s.pending = 2;
+    else if (s.conlim > 0.0 && s.acond >= s.conlim) s.pending = 3;
+    s.alpha_prev = alpha;
+  } else {
+    s.istop = isfinite(rho) ? 1 : -3;
+    s.done = 1;
+    s.phi_rho = 0.0;
+    s.theta_rho = 0.0;
+  }
+  s.fresh = 1;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next = s;
+  if (!good) return;
+  const double a = s.phi_rho, b = s.theta_rho;
+  const double ia = inv_or_0(alpha), ib = inv_or_0(beta);
   double sy = 0.0, sw = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * kThreads) {
     const double wi = w[i];
     const double yi = y[i] + a * wi;
-    const double wn = v[i] - b * wi;
+    double vi;
+    if (vt) {
+      vi = (v[i] * ib - beta * vt[i]) * ia;
+      vt[i] = vi;
+    } else {
+      vi = v[i] * ia;
+    }
+    const double wn = vi - b * wi;
     y[i] = yi;
     w[i] = wn;
     sy += yi * yi;
@@ -502,27 +727,6 @@ __global__ void __launch_bounds__(kThreads)
   if (threadIdx.x == 0) {
     ysq[blockIdx.x] = sy;
     wsq[blockIdx.x] = sw;
-  }
-}
-
-// Stopping tests of iteration k (S1 needs ||y_k||, available only now).
-__global__ void __launch_bounds__(kThreads) k_lsqr_check(LsqrDev* st, const double* __restrict__ ysq,
-                                                         int nsq, int consistent) {
-  if (st->done) return;
-  __shared__ double scratch[kThreads / 64];
-  const double y2 = reduce_partials(ysq, nsq, scratch);
-  if (threadIdx.x != 0) return;
-  st->ynorm = sqrt(y2);
-  const double anorm = sqrt(st->anorm2);
-  int istop = 0;
-  const double rtol = consistent ? st->btol * st->bnorm
-                                 : st->btol * st->bnorm + st->atol * anorm * st->ynorm;
-  if (st->normr <= rtol) istop = 1;
-  else if (st->pending) istop = st->pending;
-  else if (st->itn >= st->itmax) istop = 7;
-  if (istop) {
-    st->istop = istop;
-    st->done = 1;
   }
 }
 
@@ -547,18 +751,18 @@ __global__ void k_pattern_grad(const int64_t* __restrict__ rp, const int32_t* __
 // ---------------------------------------------------------------------------
 // Dense products with the explicit B = A R^{-1} (row-major m x n, Alg. 1 step 4).
 // ---------------------------------------------------------------------------
-// out[i] = sA (B v)[i] - cf prev[i], cf = hcoef (*dcoef); one wavefront per
+// out[i] = s (B v)[i] - c prev[i]; one wavefront per
 // row, four independent partial sums per lane, a fixed-order tree across the
 // wavefront; per-block sums of squares of out into sq.
 __global__ void __launch_bounds__(kThreads)
     k_gemv(const double* __restrict__ B, int64_t ldb, int64_t m, int64_t n,
-           const double* __restrict__ v, double sA, double hcoef, const double* __restrict__ dcoef,
-           const double* prev, double* out, double* __restrict__ sq, const int* __restrict__ done) {
+           const double* __restrict__ v, LazyScale sc, const double* prev, double* out, double* __restrict__ sq,
+           const int* __restrict__ done) {
   if (done && *done) return;
   __shared__ double scratch[kThreads / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  double cf = hcoef;
-  if (dcoef) cf *= *dcoef;
+  double sA, cf;
+  lazy_scale(sc, scratch, &sA, &cf);
   double ss = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * (kThreads / 64) + w; i < m; i += (int64_t)gridDim.x * (kThreads / 64)) {
     const double* row = B + i * ldb;
@@ -619,19 +823,18 @@ __global__ void __launch_bounds__(kThreads)
   part[(int64_t)blockIdx.y * n + j] = a0 + a1;
 }
 
-// out[j] = sum_z part[z][j] - cf prev[j]; per-block sums of squares.  A block
+// out[j] = s sum_z part[z][j] - c prev[j]; per-block sums of squares.  A block
 // takes 64 columns at a time (grid-stride); its four wavefronts sum every
 // fourth slice, and the four sums are added in a fixed order.
 __global__ void __launch_bounds__(kThreads)
-    k_gemvT_reduce(const double* __restrict__ part, int nz, int64_t n, double hcoef,
-                   const double* __restrict__ dcoef, const double* prev, double* out,
+    k_gemvT_reduce(const double* __restrict__ part, int nz, int64_t n, LazyScale sc, const double* prev, double* out,
                    double* __restrict__ sq, const int* __restrict__ done) {
   if (done && *done) return;
   __shared__ double scratch[kThreads / 64];
   __shared__ double quarter[kThreads / 64][64];
   const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-  double cf = hcoef;
-  if (dcoef) cf *= *dcoef;
+  double s1, cf;
+  lazy_scale(sc, scratch, &s1, &cf);
   double ss = 0.0;
   for (int64_t j0 = (int64_t)blockIdx.x * 64; j0 < n; j0 += (int64_t)gridDim.x * 64) {
     const int64_t j = j0 + c;
@@ -643,7 +846,7 @@ __global__ void __launch_bounds__(kThreads)
     quarter[q][c] = t;
     __syncthreads();
     if (q == 0 && j < n) {
-      t = (quarter[0][c] + quarter[1][c]) + (quarter[2][c] + quarter[3][c]);
+      t = s1 * ((quarter[0][c] + quarter[1][c]) + (quarter[2][c] + quarter[3][c]));
       if (prev && cf != 0.0) t -= cf * prev[j];
       out[j] = t;
       ss += t * t;
@@ -673,10 +876,9 @@ struct Ctx {
   // work vectors
   double *u, *v, *w, *y, *z, *q, *t, *r, *xs;
   double *sqA, *sqB, *sqY, *sqW;
-  double* hn;  // one device double for norms read by the host
-  LsqrDev* dst;
+  double* hn;  // device doubles for norms read by the host
+  LsqrDev* dst;   // the state, and after it the iteration's uncommitted one
   IterGraph* graph = nullptr;  // captured poll interval of the loop, or null: eager launches
-  int nspmvA, nspmvAT, nvec_n, nvec_m;
   // column runs of A and A^T (null: the column-index SpMV)
   const int32_t *nrunA = nullptr, *rcolA = nullptr, *rendA = nullptr;
   const int32_t *nrunAT = nullptr, *rcolAT = nullptr, *rendAT = nullptr;
@@ -697,8 +899,8 @@ int tri_reduce_blocks(int64_t n) {
 }
 
 rfmls_status tri_apply(rfmls_handle* h, const rfmls_precond_t* P, int trans, const double* in,
-                       double* out, double hcoef, const double* dcoef, const double* prev,
-                       double* sq, const int* done) {
+                       double* out, const LazyScale& sc, const double* prev, double* sq, int* nsq,
+                       const int* done, const LsqrCommit& commit) {
   const int64_t n = P->n, nt = P->nt;
   const int C = P->chunk;
   const int maxk = (int)((nt + C - 1) / C);
@@ -707,11 +909,26 @@ rfmls_status tri_apply(rfmls_handle* h, const rfmls_precond_t* P, int trans, con
   const double esz = P->store == RFMLS_F64 ? 8.0 : 4.0;
   const int full = P->full;
   const double tri_elems = full ? (double)n * (double)n : (double)n * (double)(n + 1) / 2.0;
-  {
+  const unsigned extra = commit.st ? 1u : 0u;
   // algorithmic: the stored entries of X once (n(n+1)/2, or n^2 for the full
   // SVD preconditioner), the input vector, the output
-  Trace tr(h, full ? (trans ? "gemv_Pt" : "gemv_P") : (trans ? "trmv_Xt" : "trmv_X"),
-           esz * tri_elems + 16.0 * (double)n, 2.0 * tri_elems);
+  const char* name = full ? (trans ? "gemv_Pt" : "gemv_P") : (trans ? "trmv_Xt" : "trmv_X");
+  if (nt <= kSmallTiles) {
+    Trace tr(h, name, esz * tri_elems + 16.0 * (double)n, 2.0 * tri_elems);
+    const unsigned nb = ceil_div(n, 16);
+    if (P->store == RFMLS_F64)
+      hipLaunchKernelGGL(trans ? k_trmvT_small<double> : k_trmv_small<double>, dim3(nb + extra),
+                         dim3(64 * kSmallWaves), 0, st, (const double*)P->Xpk, nt, n, full, in, sc, prev, out, sq, done,
+                         commit);
+    else
+      hipLaunchKernelGGL(trans ? k_trmvT_small<float> : k_trmv_small<float>, dim3(nb + extra), dim3(64 * kSmallWaves),
+                         0, st, (const float*)P->Xpk, nt, n, full, in, sc, prev, out, sq, done, commit);
+    if (nsq) *nsq = (int)nb;
+    RFMLS_HIP(h, hipGetLastError());
+    return RFMLS_OK;
+  }
+  {
+  Trace tr(h, name, esz * tri_elems + 16.0 * (double)n, 2.0 * tri_elems);
   if (!trans) {
     if (P->store == RFMLS_F64)
       hipLaunchKernelGGL(k_trmv_part<double>, dim3((unsigned)P->ntab), dim3(kThreads), 0, st,
@@ -729,8 +946,10 @@ rfmls_status tri_apply(rfmls_handle* h, const rfmls_precond_t* P, int trans, con
   }
   }
   Trace tr2(h, "tri_reduce", 8.0 * (double)nt * maxk * kTile + 16.0 * (double)n, 0.0);
-  hipLaunchKernelGGL(k_tri_reduce, dim3((unsigned)tri_reduce_blocks(n)), dim3(kThreads), 0, st, part, nt, n,
-                     full, C, maxk, trans, hcoef, dcoef, prev, out, sq, done);
+  const int nb = tri_reduce_blocks(n);
+  hipLaunchKernelGGL(k_tri_reduce, dim3((unsigned)nb + extra), dim3(kThreads), 0, st, part, nt, n,
+                     full, C, maxk, trans, sc, prev, out, sq, done, commit);
+  if (nsq) *nsq = nb;
   RFMLS_HIP(h, hipGetLastError());
   return RFMLS_OK;
 }
@@ -741,10 +960,11 @@ void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol,
                      rend);
 }
 
-static rfmls_status spmv(Ctx& c, const rfmls_csr* M, const double* x, double sA, double hcoef,
-                         const double* dcoef, const double* prev, double* out, double* sq,
-                         const int* done, int* nblk) {
+static rfmls_status spmv(Ctx& c, const rfmls_csr* M, const double* x, double* out,
+                         const LazyScale& sc = LazyScale(), const double* prev = nullptr, double* sq = nullptr,
+                         int* nblk = nullptr, const int* done = nullptr, const LsqrCommit& commit = LsqrCommit()) {
   const unsigned nb = spmv_blocks(M->m);
+  const unsigned extra = commit.st ? 1u : 0u;
   const int32_t* nrun = M == c.A ? c.nrunA : c.nrunAT;
   const int32_t* rcol = M == c.A ? c.rcolA : c.rcolAT;
   const int32_t* rend = M == c.A ? c.rendA : c.rendAT;
@@ -759,25 +979,25 @@ static rfmls_status spmv(Ctx& c, const rfmls_csr* M, const double* x, double sA,
   if (nrun && M->nnz < 512 * M->m) {
     const int64_t b = (M->m + kThreads / kSpvLanesShort - 1) / (kThreads / kSpvLanesShort);
     const unsigned nbs = (unsigned)(b < kSpmvMaxBlocks ? (b > 0 ? b : 1) : kSpmvMaxBlocks);
-    hipLaunchKernelGGL(k_spmv_runs<kSpvLanesShort>, dim3(nbs), dim3(kThreads), 0, c.st, M->row_ptr, M->col, M->val,
-                       M->m, nrun, rcol, rend, x, sA, hcoef, dcoef, prev, out, sq, done);
+    hipLaunchKernelGGL(k_spmv_runs<kSpvLanesShort>, dim3(nbs + extra), dim3(kThreads), 0, c.st, M->row_ptr, M->col,
+                       M->val, M->m, nrun, rcol, rend, x, sc, prev, out, sq, done, commit);
     if (nblk) *nblk = (int)nbs;
     RFMLS_HIP(c.h, hipGetLastError());
     return RFMLS_OK;
   }
   if (nrun)
-    hipLaunchKernelGGL(k_spmv_runs<kSpvLanes>, dim3(nb), dim3(kThreads), 0, c.st, M->row_ptr, M->col, M->val, M->m,
-                       nrun, rcol, rend, x, sA, hcoef, dcoef, prev, out, sq, done);
+    hipLaunchKernelGGL(k_spmv_runs<kSpvLanes>, dim3(nb + extra), dim3(kThreads), 0, c.st, M->row_ptr, M->col, M->val,
+                       M->m, nrun, rcol, rend, x, sc, prev, out, sq, done, commit);
   else
-    hipLaunchKernelGGL(k_spmv, dim3(nb), dim3(kThreads), 0, c.st, M->row_ptr, M->col, M->val, M->m,
-                       x, sA, hcoef, dcoef, prev, out, sq, done);
+    hipLaunchKernelGGL(k_spmv, dim3(nb + extra), dim3(kThreads), 0, c.st, M->row_ptr, M->col, M->val, M->m,
+                       x, sc, prev, out, sq, done, commit);
   if (nblk) *nblk = (int)nb;
   RFMLS_HIP(c.h, hipGetLastError());
   return RFMLS_OK;
 }
 
-// Products with the explicit B (Ctx::Bm): out = B v - cf prev over the m rows,
-// and out = B^T u - cf prev over the n columns (slice partials, then a
+// Products with the explicit B (Ctx::Bm): out = s B v - c prev over the m rows,
+// and out = s B^T u - c prev over the n columns (slice partials, then a
 // fixed-order sum); each writes per-block sums of squares to sq and returns
 // their count in *nblk.
 // Row slices of B^T u: about eight workgroups per compute unit over the column
@@ -788,21 +1008,20 @@ static int64_t gemvT_slices(const rfmls_handle* h, int64_t m, int64_t n) {
   const int64_t z = want < most ? want : most;
   return z > 0 ? z : 1;
 }
-static rfmls_status bmul(Ctx& c, const double* v, double hcoef, const double* dcoef,
-                         const double* prev, double* out, double* sq, const int* done, int* nblk) {
+static rfmls_status bmul(Ctx& c, const double* v, const LazyScale& sc, const double* prev, double* out, double* sq,
+                         const int* done, int* nblk) {
   const int64_t m = c.A->m, n = c.A->n;
   const int64_t b = (m + kThreads / 64 - 1) / (kThreads / 64);
   const unsigned nb = (unsigned)(b < kSpmvMaxBlocks ? (b > 0 ? b : 1) : kSpmvMaxBlocks);
   Trace tr(c.h, "gemv_B", 8.0 * (double)m * (double)n + 8.0 * (double)n + 8.0 * (double)m * (prev ? 2.0 : 1.0),
            2.0 * (double)m * (double)n);
-  hipLaunchKernelGGL(k_gemv, dim3(nb), dim3(kThreads), 0, c.st, c.Bm, c.ldbm, m, n, v, 1.0, hcoef, dcoef,
-                     prev, out, sq, done);
+  hipLaunchKernelGGL(k_gemv, dim3(nb), dim3(kThreads), 0, c.st, c.Bm, c.ldbm, m, n, v, sc, prev, out, sq, done);
   *nblk = (int)nb;
   RFMLS_HIP(c.h, hipGetLastError());
   return RFMLS_OK;
 }
-static rfmls_status btmul(Ctx& c, const double* u, double hcoef, const double* dcoef,
-                          const double* prev, double* out, double* sq, const int* done, int* nblk) {
+static rfmls_status btmul(Ctx& c, const double* u, const LazyScale& sc, const double* prev, double* out, double* sq,
+                          const int* done, int* nblk) {
   const int64_t m = c.A->m, n = c.A->n;
   const int64_t ns = gemvT_slices(c.h, m, n);
   const int64_t rps = m > ns ? (m + ns - 1) / ns : 1;
@@ -814,130 +1033,141 @@ static rfmls_status btmul(Ctx& c, const double* u, double hcoef, const double* d
     hipLaunchKernelGGL(k_gemvT_part, dim3(ceil_div(n, kThreads), (unsigned)nz), dim3(kThreads), 0, c.st,
                        c.Bm, c.ldbm, m, n, u, rps, c.gpart, done);
     hipLaunchKernelGGL(k_gemvT_reduce, dim3(nr), dim3(kThreads), 0, c.st, (const double*)c.gpart, nz, n,
-                       hcoef, dcoef, prev, out, sq, done);
+                       sc, prev, out, sq, done);
   }
   *nblk = (int)nr;
   RFMLS_HIP(c.h, hipGetLastError());
   return RFMLS_OK;
 }
 
-// The pinned staging buffer: [0, 1024) uploads, [1024, 4096) downloads.  Every
-// upload is followed by a stream synchronisation before the buffer is reused.
-static rfmls_status upload_state(Ctx& c, const rfmls_opts* o, int64_t itmax) {
-  LsqrDev* pin = (LsqrDev*)c.h->pinned;
+// The state as of the last commit, through the pinned staging buffer.
+static rfmls_status read_state(Ctx& c, LsqrDev* out) {
+  LsqrDev* pin = (LsqrDev*)((char*)c.h->pinned + 2048);
+  RFMLS_HIP(c.h, hipMemcpyAsync(pin, c.dst, sizeof(LsqrDev), hipMemcpyDeviceToHost, c.st));
   RFMLS_HIP(c.h, hipStreamSynchronize(c.st));
-  *pin = LsqrDev{};
-  pin->atol = o->atol;
-  pin->btol = o->btol;
-  pin->conlim = o->conlim;
-  pin->itmax = itmax;
-  RFMLS_HIP(c.h, hipMemcpyAsync(c.dst, pin, sizeof(LsqrDev), hipMemcpyHostToDevice, c.st));
+  *out = *pin;
   return RFMLS_OK;
 }
 
-static rfmls_status poll_done(Ctx& c, int* host_done) {
-  int* pin = (int*)((char*)c.h->pinned + 1024);
-  RFMLS_HIP(c.h, hipMemcpyAsync(pin, &c.dst->done, sizeof(int), hipMemcpyDeviceToHost, c.st));
-  RFMLS_HIP(c.h, hipStreamSynchronize(c.st));
-  *host_done = *pin;
-  return RFMLS_OK;
+static LsqrCommit commit_of(const Ctx& c, int consistent) {
+  LsqrCommit cm;
+  cm.st = c.dst;
+  cm.next = c.dst + 1;
+  cm.ysq = c.sqY;
+  cm.wsq = c.sqW;
+  cm.n = (int)vec_blocks(c.A->n);
+  cm.consistent = consistent;
+  return cm;
 }
 
-// One LSQR iteration (Golub-Kahan step, plane rotation, updates of y and w,
-// stopping tests), enqueued on c.st; nred = number of partial sums of ||v||^2.
-static rfmls_status lsqr_iteration(Ctx& c, int nred) {
+// Runs `iteration` (which enqueues one iteration on c.st) up to itmax times, the
+// host reading the committed state after every `every` iterations; with
+// c.graph the poll interval is captured once and replayed.  *s: the final state.
+template <class F>
+static rfmls_status run_iterations(Ctx& c, int64_t itmax, int every, int consistent, LsqrDev* s, F&& iteration) {
   rfmls_handle* h = c.h;
-  const int64_t m = c.A->m, n = c.A->n;
-  const int* done = &c.dst->done;
-  const unsigned vbn = vec_blocks(n), vbm = vec_blocks(m);
-  // beta u = A (X v) - alpha u  (or B v - alpha u)
-  int nb = 0;
-  if (c.Bm) {
-    RFMLS_CHECK(bmul(c, c.v, 1.0, &c.dst->alpha, c.u, c.u, c.sqA, done, &nb));
-  } else {
-    RFMLS_CHECK(tri_apply(h, c.P, 0, c.v, c.z, 0.0, nullptr, nullptr, nullptr, done));
-    RFMLS_CHECK(spmv(c, c.A, c.z, 1.0, 1.0, &c.dst->alpha, c.u, c.u, c.sqA, done, &nb));
-  }
-  hipLaunchKernelGGL(k_normalize, dim3(vbm), dim3(kThreads), 0, c.st, c.u, m, c.sqA, nb,
-                     &c.dst->beta, done);
-  // alpha v = X^T (A^T u) - beta v  (or B^T u - beta v)
-  if (c.Bm) {
-    RFMLS_CHECK(btmul(c, c.u, 1.0, &c.dst->beta, c.v, c.v, c.sqB, done, &nred));
-  } else {
-    RFMLS_CHECK(spmv(c, c.AT, c.u, 1.0, 0.0, nullptr, nullptr, c.q, nullptr, done, nullptr));
-    RFMLS_CHECK(tri_apply(h, c.P, 1, c.q, c.v, 1.0, &c.dst->beta, c.v, c.sqB, done));
-  }
-  hipLaunchKernelGGL(k_normalize, dim3(vbn), dim3(kThreads), 0, c.st, c.v, n, c.sqB, nred,
-                     &c.dst->alpha, done);
-  hipLaunchKernelGGL(k_lsqr_rotate, dim3(1), dim3(kThreads), 0, c.st, c.dst, c.sqW, (int)vbn);
-  hipLaunchKernelGGL(k_lsqr_update, dim3(vbn), dim3(kThreads), 0, c.st, c.dst, c.v, c.w, c.y, n,
-                     c.sqY, c.sqW);
-  hipLaunchKernelGGL(k_lsqr_check, dim3(1), dim3(kThreads), 0, c.st, c.dst, c.sqY, (int)vbn, 0);
-  RFMLS_HIP(h, hipGetLastError());
-  return RFMLS_OK;
-}
-
-// One LSQR sweep for min ||A X y - rhs||; on return c.y holds y and the state
-// is in c.dst.  rhs is an m-vector (device).
-static rfmls_status lsqr_sweep(Ctx& c, const double* rhs, const rfmls_opts* o, int64_t itmax) {
-  rfmls_handle* h = c.h;
-  const int64_t m = c.A->m, n = c.A->n;
-  const int* done = &c.dst->done;
-  RFMLS_CHECK(upload_state(c, o, itmax));
-  const unsigned vbn = vec_blocks(n), vbm = vec_blocks(m);
-  // beta_1 u_1 = rhs
-  hipLaunchKernelGGL(k_axpby, dim3(vbm), dim3(kThreads), 0, c.st, m, 1.0, (const double*)nullptr,
-                     rhs, 0.0, (const double*)nullptr, (const double*)nullptr, c.u,
-                     (const int*)nullptr);
-  hipLaunchKernelGGL(k_sumsq, dim3(vbm), dim3(kThreads), 0, c.st, c.u, m, c.sqA);
-  hipLaunchKernelGGL(k_normalize, dim3(vbm), dim3(kThreads), 0, c.st, c.u, m, c.sqA, (int)vbm,
-                     &c.dst->beta, (const int*)nullptr);
-  hipLaunchKernelGGL(k_lsqr_start, dim3(1), dim3(1), 0, c.st, c.dst);
-  hipLaunchKernelGGL(k_fill, dim3(vbn), dim3(kThreads), 0, c.st, c.y, n, 0.0);
-  // alpha_1 v_1 = B^T u_1 = X^T (A^T u_1) (or the explicit B^T u_1)
-  int nred = tri_reduce_blocks(n);
-  if (c.Bm) {
-    RFMLS_CHECK(btmul(c, c.u, 0.0, nullptr, nullptr, c.v, c.sqB, done, &nred));
-  } else {
-    RFMLS_CHECK(spmv(c, c.AT, c.u, 1.0, 0.0, nullptr, nullptr, c.q, nullptr, done, nullptr));
-    RFMLS_CHECK(tri_apply(h, c.P, 1, c.q, c.v, 0.0, nullptr, nullptr, c.sqB, done));
-  }
-  hipLaunchKernelGGL(k_normalize, dim3(vbn), dim3(kThreads), 0, c.st, c.v, n, c.sqB, nred,
-                     &c.dst->alpha, done);
-  hipLaunchKernelGGL(k_lsqr_start2, dim3(1), dim3(1), 0, c.st, c.dst);
-  // w_1 = v_1 and ||w_1||^2
-  hipLaunchKernelGGL(k_axpby, dim3(vbn), dim3(kThreads), 0, c.st, n, 1.0, (const double*)nullptr,
-                     c.v, 0.0, (const double*)nullptr, (const double*)nullptr, c.w, done);
-  hipLaunchKernelGGL(k_sumsq, dim3(vbn), dim3(kThreads), 0, c.st, c.w, n, c.sqW);
-  // alpha_prev for the ||B||_F estimate: alpha_1
-  hipLaunchKernelGGL(k_axpby, dim3(1), dim3(1), 0, c.st, (int64_t)1, 1.0, (const double*)nullptr,
-                     &c.dst->alpha, 0.0, (const double*)nullptr, (const double*)nullptr,
-                     &c.dst->alpha_prev, (const int*)nullptr);
-  const int every = o->check_every > 0 ? o->check_every : 8;
-  int hd = 0;
-  RFMLS_CHECK(poll_done(c, &hd));
+  const LsqrCommit cm = commit_of(c, consistent);
+  auto interval = [&](int64_t count) -> rfmls_status {
+    for (int64_t k = 0; k < count; ++k) RFMLS_CHECK(iteration());
+    hipLaunchKernelGGL(k_commit, dim3(1), dim3(kThreads), 0, c.st, cm);
+    RFMLS_HIP(h, hipGetLastError());
+    return RFMLS_OK;
+  };
   if (c.graph && !h->trace) {
     // the poll interval's launches recorded once per call, then replayed
     if (!c.graph->exec)
       RFMLS_CHECK(capture_graph(h, c.graph, [&]() -> rfmls_status {
         const hipStream_t s0 = c.st;
         c.st = h->stream;
-        rfmls_status r = RFMLS_OK;
-        for (int k = 0; k < every && r >= 0; ++k) r = lsqr_iteration(c, nred);
+        const rfmls_status r = interval(every);
         c.st = s0;
         return r;
       }));
-    for (int64_t it = 0; it < itmax && !hd; it += every) {
+    *s = LsqrDev{};
+    for (int64_t it = 0; it < itmax && !s->done; it += every) {
       RFMLS_HIP(h, hipGraphLaunch(c.graph->exec, c.st));
-      RFMLS_CHECK(poll_done(c, &hd));
+      RFMLS_CHECK(read_state(c, s));
     }
     return RFMLS_OK;
   }
-  for (int64_t it = 0; it < itmax && !hd; ++it) {
-    RFMLS_CHECK(lsqr_iteration(c, nred));
-    if ((it + 1) % every == 0) RFMLS_CHECK(poll_done(c, &hd));
+  *s = LsqrDev{};
+  for (int64_t it = 0; it < itmax && !s->done; it += every) {
+    RFMLS_CHECK(interval(itmax - it < every ? itmax - it : every));
+    RFMLS_CHECK(read_state(c, s));
   }
   return RFMLS_OK;
+}
+
+// One LSQR iteration (Golub-Kahan step, plane rotation, updates of y and w),
+// enqueued on c.st.  c.u and c.v hold beta u and alpha v.
+static rfmls_status lsqr_iteration(Ctx& c) {
+  rfmls_handle* h = c.h;
+  LsqrDev* st = c.dst;
+  const int* done = &st->done;
+  const LsqrCommit cm = commit_of(c, 0);
+  int nb = 0, nred = 0;
+  // beta' u' = A (X v) - alpha u, with v = v^/alpha and u = u^/beta
+  LazyScale su;
+  su.sdiv = &st->alpha;
+  su.c = 1.0;
+  su.cnum = &st->alpha;
+  su.cden = &st->beta;
+  if (c.Bm) {
+    // B v uses the state at once, so the commit goes before it
+    hipLaunchKernelGGL(k_commit, dim3(1), dim3(kThreads), 0, c.st, cm);
+    RFMLS_CHECK(bmul(c, c.v, su, c.u, c.u, c.sqA, done, &nb));
+  } else {
+    RFMLS_CHECK(tri_apply(h, c.P, 0, c.v, c.z, LazyScale(), nullptr, nullptr, nullptr, done, cm));
+    RFMLS_CHECK(spmv(c, c.A, c.z, c.u, su, c.u, c.sqA, &nb, done));
+  }
+  // alpha' v' = X^T (A^T u') - beta' v, with u' = u^'/beta', beta' from the partial sums
+  LazyScale sv;
+  sv.c = 1.0;
+  sv.sq = c.sqA;
+  sv.nsq = nb;
+  sv.norm = &st->beta;
+  sv.cden = &st->alpha;
+  if (c.Bm) {
+    RFMLS_CHECK(btmul(c, c.u, sv, c.v, c.v, c.sqB, done, &nred));
+  } else {
+    RFMLS_CHECK(spmv(c, c.AT, c.u, c.q, LazyScale(), nullptr, nullptr, nullptr, done));
+    RFMLS_CHECK(tri_apply(h, c.P, 1, c.q, c.v, sv, c.v, c.sqB, &nred, done));
+  }
+  hipLaunchKernelGGL(k_lsqr_step, dim3(vec_blocks(c.A->n)), dim3(kThreads), 0, c.st, (const LsqrDev*)st, st + 1,
+                     (const double*)c.sqB, nred, (const double*)c.v, (double*)nullptr, c.w, c.y, c.A->n, c.sqY, c.sqW);
+  RFMLS_HIP(h, hipGetLastError());
+  return RFMLS_OK;
+}
+
+// One LSQR sweep for min ||A X y - rhs||; on return c.y holds y and *s the
+// final state.  rhs is an m-vector (device).
+static rfmls_status lsqr_sweep(Ctx& c, const double* rhs, const rfmls_opts* o, int64_t itmax, LsqrDev* s) {
+  rfmls_handle* h = c.h;
+  const int64_t m = c.A->m, n = c.A->n;
+  const unsigned vbn = vec_blocks(n), vbm = vec_blocks(m);
+  LsqrDev* st = c.dst;
+  const int* done = &st->done;
+  // beta_1 u_1 = rhs
+  hipLaunchKernelGGL(k_copy_sumsq, dim3(vbm), dim3(kThreads), 0, c.st, rhs, m, c.u, c.sqA);
+  hipLaunchKernelGGL(k_lsqr_begin, dim3(1), dim3(kThreads), 0, c.st, st, st + 1, (const double*)c.sqA, (int)vbm,
+                     o->atol, o->btol, o->conlim, itmax);
+  // alpha_1 v_1 = B^T u_1 = X^T (A^T u_1) (or the explicit B^T u_1)
+  LazyScale s1;
+  s1.sdiv = &st->beta;
+  int nred = 0;
+  if (c.Bm) {
+    RFMLS_CHECK(btmul(c, c.u, s1, nullptr, c.v, c.sqB, done, &nred));
+  } else {
+    RFMLS_CHECK(spmv(c, c.AT, c.u, c.q, LazyScale(), nullptr, nullptr, nullptr, done));
+    RFMLS_CHECK(tri_apply(h, c.P, 1, c.q, c.v, s1, nullptr, c.sqB, &nred, done));
+  }
+  hipLaunchKernelGGL(k_lsqr_begin2, dim3(1), dim3(kThreads), 0, c.st, st, (const double*)c.sqB, nred);
+  // y = 0, w_1 = v_1 (unconditional: y is used when the sweep stops at once too)
+  hipLaunchKernelGGL(k_lsqr_first_w, dim3(vbn), dim3(kThreads), 0, c.st, (const LsqrDev*)st, (const double*)c.v, 0,
+                     (double*)nullptr, c.w, c.y, n, (double*)nullptr);
+  RFMLS_HIP(h, hipGetLastError());
+  return run_iterations(c, itmax, o->check_every > 0 ? o->check_every : 8, 0, s,
+                        [&]() -> rfmls_status { return lsqr_iteration(c); });
 }
 
 // Doubles of device memory one single-right-hand-side solve works in: the
@@ -1018,24 +1248,12 @@ static rfmls_status make_ctx(rfmls_handle* h, const rfmls_csr* A, const rfmls_cs
   return RFMLS_OK;
 }
 
-static rfmls_status read_state(Ctx& c, LsqrDev* out) {
-  LsqrDev* pin = (LsqrDev*)((char*)c.h->pinned + 2048);
-  RFMLS_HIP(c.h, hipMemcpyAsync(pin, c.dst, sizeof(LsqrDev), hipMemcpyDeviceToHost, c.st));
-  RFMLS_HIP(c.h, hipStreamSynchronize(c.st));
-  *out = *pin;
-  return RFMLS_OK;
-}
-
-// ||v|| of a device vector into host (reduced on the device, 8 bytes copied
-// through the pinned staging buffer)
-static rfmls_status host_norm(Ctx& c, const double* v, int64_t len, double* out) {
+// ||v|| of a device vector into c.hn[k] (read by the host later)
+static rfmls_status norm_to(Ctx& c, const double* v, int64_t len, int k) {
   const unsigned nb = vec_blocks(len);
-  hipLaunchKernelGGL(k_sumsq, dim3(nb), dim3(kThreads), 0, c.st, v, len, c.sqY);
-  hipLaunchKernelGGL(k_sqrt_sum, dim3(1), dim3(kThreads), 0, c.st, (const double*)c.sqY, (int)nb, c.hn);
-  double* pin = (double*)((char*)c.h->pinned + 3072);
-  RFMLS_HIP(c.h, hipMemcpyAsync(pin, c.hn, sizeof(double), hipMemcpyDeviceToHost, c.st));
-  RFMLS_HIP(c.h, hipStreamSynchronize(c.st));
-  *out = *pin;
+  hipLaunchKernelGGL(k_copy_sumsq, dim3(nb), dim3(kThreads), 0, c.st, v, len, (double*)nullptr, c.sqY);
+  hipLaunchKernelGGL(k_sqrt_sum, dim3(1), dim3(kThreads), 0, c.st, (const double*)c.sqY, (int)nb, c.hn + k);
+  RFMLS_HIP(c.h, hipGetLastError());
   return RFMLS_OK;
 }
 
@@ -1061,6 +1279,10 @@ static rfmls_status solve_impl(rfmls_handle* h, const rfmls_csr* A, const rfmls_
   const int64_t m = A->m, n = A->n;
   const int64_t itmax = o->itmax > 0 ? o->itmax : n;
   const unsigned vbn = vec_blocks(n), vbm = vec_blocks(m);
+  // r = b - A x
+  LazyScale residual;
+  residual.s = -1.0;
+  residual.c = -1.0;
   rfmls_status ret = RFMLS_OK;
   for (int64_t k = 0; k < nrhs; ++k) {
     const double* b = B + k * ldb;
@@ -1071,15 +1293,14 @@ static rfmls_status solve_impl(rfmls_handle* h, const rfmls_csr* A, const rfmls_
     // solves for the correction from the true residual r = b - A x
     const bool warm = o->x_init != 0;
     if (warm) {
-      RFMLS_CHECK(host_norm(c, b, m, &inf.normb));
-      RFMLS_CHECK(spmv(c, A, x, -1.0, -1.0, nullptr, b, rres, nullptr, nullptr, nullptr));
+      RFMLS_CHECK(norm_to(c, b, m, 2));
+      RFMLS_CHECK(spmv(c, A, x, rres, residual, b));
     }
     for (int sweep = 0; sweep <= o->refine; ++sweep) {
       const bool from_zero = sweep == 0 && !warm;
       const double* rhs = from_zero ? b : rres;
-      RFMLS_CHECK(lsqr_sweep(c, rhs, o, itmax));
       LsqrDev s;
-      RFMLS_CHECK(read_state(c, &s));
+      RFMLS_CHECK(lsqr_sweep(c, rhs, o, itmax, &s));
       if (s.istop < 0) return fail(h, RFMLS_E_BREAKDOWN, "non-finite value in LSQR");
       if (sweep == 0) {
         inf.itn_first = s.itn;
@@ -1094,23 +1315,27 @@ static rfmls_status solve_impl(rfmls_handle* h, const rfmls_csr* A, const rfmls_
       inf.itn += s.itn;
       inf.istop_last = s.istop;
       // x (+)= X y
-      RFMLS_CHECK(tri_apply(h, P, 0, c.y, from_zero ? x : c.xs, 0.0, nullptr, nullptr, nullptr,
-                            nullptr));
+      RFMLS_CHECK(tri_apply(h, P, 0, c.y, from_zero ? x : c.xs));
       if (!from_zero)
-        hipLaunchKernelGGL(k_axpby, dim3(vbn), dim3(kThreads), 0, c.st, n, 1.0,
-                           (const double*)nullptr, (const double*)x, 1.0, (const double*)nullptr,
-                           (const double*)c.xs, x, (const int*)nullptr);
+        hipLaunchKernelGGL(k_axpby, dim3(vbn), dim3(kThreads), 0, c.st, n, 1.0, (const double*)x, 1.0,
+                           (const double*)c.xs, x);
       // r = b - A x
-      RFMLS_CHECK(spmv(c, A, x, -1.0, -1.0, nullptr, b, rres, nullptr, nullptr, nullptr));
+      RFMLS_CHECK(spmv(c, A, x, rres, residual, b));
       if (s.itn == 0) break;
     }
-    RFMLS_CHECK(host_norm(c, rres, m, &inf.normr));
-    RFMLS_CHECK(spmv(c, AT, rres, 1.0, 0.0, nullptr, nullptr, c.q, nullptr, nullptr, nullptr));
-    RFMLS_CHECK(host_norm(c, c.q, n, &inf.normar));
+    RFMLS_CHECK(norm_to(c, rres, m, 0));
+    RFMLS_CHECK(spmv(c, AT, rres, c.q));
+    RFMLS_CHECK(norm_to(c, c.q, n, 1));
+    double* pin = (double*)((char*)h->pinned + 3072);
+    RFMLS_HIP(h, hipMemcpyAsync(pin, c.hn, 3 * sizeof(double), hipMemcpyDeviceToHost, c.st));
     if (Rout)
-      hipLaunchKernelGGL(k_axpby, dim3(vbm), dim3(kThreads), 0, c.st, m, 1.0, (const double*)nullptr,
-                         (const double*)rres, 0.0, (const double*)nullptr, (const double*)nullptr,
-                         Rout + k * ldr, (const int*)nullptr);
+      hipLaunchKernelGGL(k_axpby, dim3(vbm), dim3(kThreads), 0, c.st, m, 1.0, (const double*)rres, 0.0,
+                         (const double*)nullptr, Rout + k * ldr);
+    RFMLS_HIP(h, hipGetLastError());
+    RFMLS_HIP(h, hipStreamSynchronize(c.st));
+    inf.normr = pin[0];
+    inf.normar = pin[1];
+    if (warm) inf.normb = pin[2];
     if (info) info[k] = inf;
   }
   RFMLS_HIP(h, hipStreamSynchronize(c.st));
@@ -1201,8 +1426,7 @@ rfmls_status run_backward(rfmls_handle* h, const rfmls_csr* A, const rfmls_csr* 
   const int64_t m = A->m, n = A->n;
   const int64_t itmax = o->itmax > 0 ? o->itmax : m;
   const unsigned vbn = vec_blocks(n), vbm = vec_blocks(m);
-  const int nred = tri_reduce_blocks(n);
-  // roles: un = u (n-vector), vm = v (m-vector), vt/wt/zz shadows (n-vectors)
+  // roles: un = beta u (n-vector), vm = alpha v (m-vector), vt/wt/zz shadows (n-vectors)
   double* un = c.z;   // n
   double* vm = c.t;   // m
   double* vt = c.w;   // n
@@ -1210,78 +1434,53 @@ rfmls_status run_backward(rfmls_handle* h, const rfmls_csr* A, const rfmls_csr* 
   double* zz = c.y;   // n
   double* tmpn = c.xs;  // n
   double* lam = c.r;  // m
-  const int* done = &c.dst->done;
+  LsqrDev* st = c.dst;
+  const int* done = &st->done;
+  const LsqrCommit cm = commit_of(c, 1);
   rfmls_status ret = RFMLS_OK;
   IterGraph graph;  // one capture serves every right-hand side (same buffers)
+  if (o->graph) c.graph = &graph;
   for (int64_t k = 0; k < nrhs; ++k) {
-    RFMLS_CHECK(upload_state(c, o, itmax));
+    int nred = 0, nb = 0;
     // beta_1 u_1 = c = X^T g
-    RFMLS_CHECK(tri_apply(h, P, 1, G + k * ldg, un, 0.0, nullptr, nullptr, c.sqB, nullptr));
-    hipLaunchKernelGGL(k_normalize, dim3(vbn), dim3(kThreads), 0, c.st, un, n, c.sqB, nred,
-                       &c.dst->beta, (const int*)nullptr);
-    hipLaunchKernelGGL(k_lsqr_start, dim3(1), dim3(1), 0, c.st, c.dst);
-    hipLaunchKernelGGL(k_fill, dim3(vbn), dim3(kThreads), 0, c.st, zz, n, 0.0);
+    RFMLS_CHECK(tri_apply(h, P, 1, G + k * ldg, un, LazyScale(), nullptr, c.sqB, &nred));
+    hipLaunchKernelGGL(k_lsqr_begin, dim3(1), dim3(kThreads), 0, c.st, st, st + 1, (const double*)c.sqB, nred, o->atol,
+                       o->btol, o->conlim, itmax);
     // alpha_1 v_1 = M^T u_1 = A (X u_1);  vt_1 = u_1 / alpha_1
-    RFMLS_CHECK(tri_apply(h, P, 0, un, tmpn, 0.0, nullptr, nullptr, nullptr, done));
-    int nb = 0;
-    RFMLS_CHECK(spmv(c, A, tmpn, 1.0, 0.0, nullptr, nullptr, vm, c.sqA, done, &nb));
-    hipLaunchKernelGGL(k_normalize, dim3(vbm), dim3(kThreads), 0, c.st, vm, m, c.sqA, nb,
-                       &c.dst->alpha, done);
-    hipLaunchKernelGGL(k_lsqr_start2, dim3(1), dim3(1), 0, c.st, c.dst);
-    hipLaunchKernelGGL(k_recip_scale, dim3(vbn), dim3(kThreads), 0, c.st, un, 0.0, (const double*)nullptr,
-                       (const double*)nullptr, &c.dst->alpha, vt, n, done);
-    hipLaunchKernelGGL(k_axpby, dim3(vbn), dim3(kThreads), 0, c.st, n, 1.0, (const double*)nullptr,
-                       (const double*)vt, 0.0, (const double*)nullptr, (const double*)nullptr, wt,
-                       done);
-    hipLaunchKernelGGL(k_sumsq, dim3(vbn), dim3(kThreads), 0, c.st, wt, n, c.sqW);
-    hipLaunchKernelGGL(k_axpby, dim3(1), dim3(1), 0, c.st, (int64_t)1, 1.0, (const double*)nullptr,
-                       &c.dst->alpha, 0.0, (const double*)nullptr, (const double*)nullptr,
-                       &c.dst->alpha_prev, (const int*)nullptr);
-    const int every = o->check_every > 0 ? o->check_every : 8;
-    int hd = 0;
-    RFMLS_CHECK(poll_done(c, &hd));
-    auto iteration = [&]() -> rfmls_status {
-      // beta u = X^T (A^T v) - alpha u
-      RFMLS_CHECK(spmv(c, AT, vm, 1.0, 0.0, nullptr, nullptr, tmpn, nullptr, done, nullptr));
-      RFMLS_CHECK(tri_apply(h, P, 1, tmpn, un, 1.0, &c.dst->alpha, un, c.sqB, done));
-      hipLaunchKernelGGL(k_normalize, dim3(vbn), dim3(kThreads), 0, c.st, un, n, c.sqB, nred,
-                         &c.dst->beta, done);
-      // alpha v = A (X u) - beta v;  vt = (u - beta vt) / alpha
-      RFMLS_CHECK(tri_apply(h, P, 0, un, tmpn, 0.0, nullptr, nullptr, nullptr, done));
-      RFMLS_CHECK(spmv(c, A, tmpn, 1.0, 1.0, &c.dst->beta, vm, vm, c.sqA, done, &nb));
-      hipLaunchKernelGGL(k_normalize, dim3(vbm), dim3(kThreads), 0, c.st, vm, m, c.sqA, nb,
-                         &c.dst->alpha, done);
-      hipLaunchKernelGGL(k_recip_scale, dim3(vbn), dim3(kThreads), 0, c.st, un, 1.0,
-                         (const double*)&c.dst->beta, (const double*)vt, &c.dst->alpha, vt, n, done);
-      hipLaunchKernelGGL(k_lsqr_rotate, dim3(1), dim3(kThreads), 0, c.st, c.dst, c.sqW, (int)vbn);
-      hipLaunchKernelGGL(k_lsqr_update, dim3(vbn), dim3(kThreads), 0, c.st, c.dst, vt, wt, zz, n,
-                         c.sqY, c.sqW);
-      hipLaunchKernelGGL(k_lsqr_check, dim3(1), dim3(kThreads), 0, c.st, c.dst, c.sqY, (int)vbn, 1);
+    LazyScale s1;
+    s1.sdiv = &st->beta;
+    RFMLS_CHECK(tri_apply(h, P, 0, un, tmpn, LazyScale(), nullptr, nullptr, nullptr, done));
+    RFMLS_CHECK(spmv(c, A, tmpn, vm, s1, nullptr, c.sqA, &nb, done));
+    hipLaunchKernelGGL(k_lsqr_begin2, dim3(1), dim3(kThreads), 0, c.st, st, (const double*)c.sqA, nb);
+    hipLaunchKernelGGL(k_lsqr_first_w, dim3(vbn), dim3(kThreads), 0, c.st, (const LsqrDev*)st, (const double*)un, 1,
+                       vt, wt, zz, n, c.sqW);
+    hipLaunchKernelGGL(k_lsqr_w2, dim3(1), dim3(kThreads), 0, c.st, st, (const double*)c.sqW, (int)vbn);
+    RFMLS_HIP(h, hipGetLastError());
+    LsqrDev s;
+    RFMLS_CHECK(run_iterations(c, itmax, o->check_every > 0 ? o->check_every : 8, 1, &s, [&]() -> rfmls_status {
+      // beta' u' = X^T (A^T v) - alpha u, with v = v^/alpha and u = u^/beta
+      LazyScale su;
+      su.sdiv = &st->alpha;
+      su.c = 1.0;
+      su.cnum = &st->alpha;
+      su.cden = &st->beta;
+      RFMLS_CHECK(spmv(c, AT, vm, tmpn, LazyScale(), nullptr, nullptr, nullptr, done, cm));
+      RFMLS_CHECK(tri_apply(h, P, 1, tmpn, un, su, un, c.sqB, &nred, done));
+      // alpha' v' = A (X u') - beta' v, with u' = u^'/beta', beta' from the partial sums;
+      // vt' = (u' - beta' vt) / alpha' in k_lsqr_step
+      LazyScale sv;
+      sv.c = 1.0;
+      sv.sq = c.sqB;
+      sv.nsq = nred;
+      sv.norm = &st->beta;
+      sv.cden = &st->alpha;
+      RFMLS_CHECK(tri_apply(h, P, 0, un, tmpn, LazyScale(), nullptr, nullptr, nullptr, done));
+      RFMLS_CHECK(spmv(c, A, tmpn, vm, sv, vm, c.sqA, &nb, done));
+      hipLaunchKernelGGL(k_lsqr_step, dim3(vbn), dim3(kThreads), 0, c.st, (const LsqrDev*)st, st + 1,
+                         (const double*)c.sqA, nb, (const double*)un, vt, wt, zz, n, c.sqY, c.sqW);
       RFMLS_HIP(h, hipGetLastError());
       return RFMLS_OK;
-    };
-    if (o->graph && !h->trace) {
-      if (!graph.exec)
-        RFMLS_CHECK(capture_graph(h, &graph, [&]() -> rfmls_status {
-          const hipStream_t s0 = c.st;
-          c.st = h->stream;
-          rfmls_status r = RFMLS_OK;
-          for (int q = 0; q < every && r >= 0; ++q) r = iteration();
-          c.st = s0;
-          return r;
-        }));
-      for (int64_t it = 0; it < itmax && !hd; it += every) {
-        RFMLS_HIP(h, hipGraphLaunch(graph.exec, c.st));
-        RFMLS_CHECK(poll_done(c, &hd));
-      }
-    } else {
-      for (int64_t it = 0; it < itmax && !hd; ++it) {
-        RFMLS_CHECK(iteration());
-        if ((it + 1) % every == 0) RFMLS_CHECK(poll_done(c, &hd));
-      }
-    }
-    LsqrDev s;
-    RFMLS_CHECK(read_state(c, &s));
+    }));
     if (s.istop < 0) return fail(h, RFMLS_E_BREAKDOWN, "non-finite value in backward LSQR");
     if (s.istop == 7) ret = RFMLS_W_NOCONV;
     if (info) {
@@ -1293,12 +1492,11 @@ rfmls_status run_backward(rfmls_handle* h, const rfmls_csr* A, const rfmls_csr* 
       info[k] = inf;
     }
     // w = X z (into tmpn), lam = A w
-    RFMLS_CHECK(tri_apply(h, P, 0, zz, tmpn, 0.0, nullptr, nullptr, nullptr, nullptr));
-    RFMLS_CHECK(spmv(c, A, tmpn, 1.0, 0.0, nullptr, nullptr, lam, nullptr, nullptr, nullptr));
+    RFMLS_CHECK(tri_apply(h, P, 0, zz, tmpn));
+    RFMLS_CHECK(spmv(c, A, tmpn, lam));
     if (dB)
-      hipLaunchKernelGGL(k_axpby, dim3(vbm), dim3(kThreads), 0, c.st, m, 1.0, (const double*)nullptr,
-                         (const double*)lam, 0.0, (const double*)nullptr, (const double*)nullptr,
-                         dB + k * lddb, (const int*)nullptr);
+      hipLaunchKernelGGL(k_axpby, dim3(vbm), dim3(kThreads), 0, c.st, m, 1.0, (const double*)lam, 0.0,
+                         (const double*)nullptr, dB + k * lddb);
     if (dAval)
       hipLaunchKernelGGL(k_pattern_grad, dim3(spmv_blocks(m)), dim3(kThreads), 0, c.st, A->row_ptr,
                          A->col, m, Rres + k * ldr, (const double*)tmpn, (const double*)lam,

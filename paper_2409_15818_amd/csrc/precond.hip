@@ -609,7 +609,7 @@ rfmls_status sketched_solution(rfmls_handle* h, const rfmls_precond_t* P, int64_
   RFMLS_HIP(h, hipGetLastError());
   // x0_k = R^{-1} y0_k with the stored X
   for (int64_t k = 0; k < nrhs; ++k)
-    RFMLS_CHECK(tri_apply(h, P, 0, Y0 + k * n, X0 + k * ldx0, 0.0, nullptr, nullptr, nullptr, nullptr));
+    RFMLS_CHECK(tri_apply(h, P, 0, Y0 + k * n, X0 + k * ldx0));
   return RFMLS_OK;
 }
 

@@ -177,16 +177,42 @@ enum WsSlot {
   WS_CHOLQR,
   WS_SPMM_RUNS,
   WS_QR_ORDER,
+  WS_TR_PIECES,
   WS_NUM_SLOTS
 };
 
 // ---------------------------------------------------------------------------
 // Device helpers
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+// v of the lane the DPP pattern CTRL names
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// Sum over the 16 lanes of a DPP row, on each of them: rotations by 1, 2, 4, 8.
+__device__ __forceinline__ double row16_sum(double v) {
+  constexpr int kRowRor = 0x120;  // DPP row_ror:n = 0x120 + n
+  v += dpp_move<kRowRor + 1>(v);
+  v += dpp_move<kRowRor + 2>(v);
+  v += dpp_move<kRowRor + 4>(v);
+  v += dpp_move<kRowRor + 8>(v);
   return v;
+}
+__device__ __forceinline__ double lane_read(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, lane);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// Sum over the wavefront, the same on every lane: DPP rows, then the four row sums
+// in a fixed order (no LDS permutes: a tenth of the latency and of the code of six
+// __shfl_xor steps, which the small kernels of an iteration feel).
+__device__ __forceinline__ double wave_sum(double v) {
+  v = row16_sum(v);
+  return (lane_read(v, 0) + lane_read(v, 16)) + (lane_read(v, 32) + lane_read(v, 48));
 }
 
 // Deterministic block sum of one double per thread (blockDim.x threads, a

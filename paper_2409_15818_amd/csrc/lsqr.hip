@@ -59,11 +59,18 @@ __device__ __forceinline__ void lazy_scale(const LazyScale& L, double* scratch, 
 // of the state but the stop flag, whose being set early or late by one kernel
 // changes no result.
 __device__ void commit_state(const LsqrCommit& cm, double* scratch) {
-  if (!cm.next->fresh) return;  // uniform
-  const double y2 = reduce_partials(cm.ysq, cm.n, scratch);
-  const double w2 = reduce_partials(cm.wsq, cm.n, scratch);
-  if (threadIdx.x != 0) return;
+  // every load issued before the first use: the state of an iteration that left
+  // none is read for nothing
   LsqrDev s = *cm.next;
+  double y2 = 0.0, w2 = 0.0;
+  for (int i = threadIdx.x; i < cm.n; i += blockDim.x) {
+    y2 += cm.ysq[i];
+    w2 += cm.wsq[i];
+  }
+  if (!s.fresh) return;  // uniform
+  y2 = block_sum(y2, scratch);
+  w2 = block_sum(w2, scratch);
+  if (threadIdx.x != 0) return;
   cm.next->fresh = 0;
   s.fresh = 0;
   if (!s.done) {
@@ -85,6 +92,22 @@ __device__ void commit_state(const LsqrCommit& cm, double* scratch) {
 __global__ void __launch_bounds__(kThreads) k_commit(LsqrCommit cm) {
   __shared__ double scratch[kThreads / 64];
   commit_state(cm, scratch);
+}
+
+// Sum over groups of L = 8 or 32 neighbouring lanes, on each of them, on the DPP path
+// (quad permutations and a mirror of 8 lanes; 32: the two 16-lane rows' sums).
+template <int L>
+__device__ __forceinline__ double group_sum(double v) {
+  if constexpr (L == 8) {
+    v += dpp_move<0xB1>(v);   // quad_perm(1, 0, 3, 2)
+    v += dpp_move<0x4E>(v);   // quad_perm(2, 3, 0, 1)
+    v += dpp_move<0x141>(v);  // row_half_mirror
+    return v;
+  } else {
+    static_assert(L == 32, "group");
+    v = row16_sum(v);
+    return v + __shfl_xor(v, 16, 64);
+  }
 }
 
 // Sums of 16 rows over the wavefront's lanes (a[q]: this lane's part of row q):
@@ -239,9 +262,10 @@ __global__ void __launch_bounds__(kThreads)
 // one launch: a workgroup of eight wavefronts per 16 outputs, the tiles of its
 // row (column) dealt to the wavefronts in turn and their sums added in order, so
 // no partial sums go through memory.  There, the second launch of the two-pass
-// form costs more than the coarser split: n = 1,600, X v 7.4 + 3.8 us in two
-// launches (a workgroup here reads at most 256 KB of X); wider ones need the
-// split over tiles to keep every compute unit reading.
+// form costs more than the coarser split (a workgroup here reads at most 256 KB
+// of X): n = 1,600, X v 7.4 + 3.8 -> 6.3 us, X^T q 5.1 + 3.8 -> 8.2; n = 200, 7.4 +
+// 2.9 -> 3.7 and 3.8 + 2.9 -> 3.9.  Wider ones need the split over tiles to keep
+// every compute unit reading.
 constexpr int64_t kSmallTiles = 32;
 constexpr int kSmallWaves = 8;
 
@@ -254,9 +278,7 @@ __device__ __forceinline__ void small_store(double v, int64_t i, bool live, doub
     out[i] = t;
   }
   if (sq) {  // lanes 0 .. 15 of wavefront 0
-    t *= t;
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    t = row16_sum(t * t);
     if (threadIdx.x == 0) sq[blockIdx.x] = t;
   }
 }
@@ -272,23 +294,42 @@ __global__ void __launch_bounds__(64 * kSmallWaves)
     commit_state(cm, scratch);
     return;
   }
-  if (done && *done) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t I = blockIdx.x >> 2;
   const int r0 = 16 * (blockIdx.x & 3);
-  double acc[16];
+  // lane (lr, lk) takes columns 16 p + lr of rows lk + 4 q; the next tile's loads in
+  // flight during this one's products, the first tile's issued with the stop flag's
+  const int lr = lane & 15, lk = lane >> 4;
+  TS x[16];
+  double vc[4];
+  auto load = [&](int64_t J) {
+    const TS* t = Xpk + ptile(I, J, nt, full) * (int64_t)(kTile * kTile) + (r0 + lk) * kTile + lr;
 #pragma unroll
-  for (int q = 0; q < 16; ++q) acc[q] = 0.0;
-#pragma unroll 2
-  for (int64_t J = row_first(I, full) + w; J < nt; J += kSmallWaves) {
-    const TS* t = Xpk + ptile(I, J, nt, full) * (int64_t)(kTile * kTile) + r0 * kTile;
-    const int64_t gc = J * kTile + lane;
-    const double vc = gc < n ? v[gc] : 0.0;
+    for (int p = 0; p < 4; ++p) {
+      const int64_t gc = J * kTile + 16 * p + lr;
+      vc[p] = gc < n ? v[gc] : 0.0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) acc[q] += (double)t[q * kTile + lane] * vc;
+      for (int q = 0; q < 4; ++q) x[4 * q + p] = t[4 * q * kTile + 16 * p];
+    }
+  };
+  int64_t J = row_first(I, full) + w;
+  if (J < nt) load(J);
+  if (done && *done) return;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  while (J < nt) {
+    double pr[16];
+#pragma unroll
+    for (int e = 0; e < 16; ++e) pr[e] = (double)x[e] * vc[e & 3];
+    J += kSmallWaves;
+    if (J < nt) load(J);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] += (pr[4 * q] + pr[4 * q + 1]) + (pr[4 * q + 2] + pr[4 * q + 3]);
   }
-  const double s = rows16_sum(acc, lane);
-  if ((lane & 3) == 0) red[w][lane >> 2] = s;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double s = row16_sum(acc[q]);
+    if (lr == 0) red[w][lk + 4 * q] = s;
+  }
   double s1, cf;
   lazy_scale(sc, scratch, &s1, &cf);
   __syncthreads();
@@ -312,27 +353,37 @@ __global__ void __launch_bounds__(64 * kSmallWaves)
     commit_state(cm, scratch);
     return;
   }
-  if (done && *done) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int lr = lane & 15, lk = lane >> 4;
   const int64_t J = blockIdx.x >> 2;
   const int c0 = 16 * (blockIdx.x & 3);
   const int64_t Iend = col_end(J, nt, full);
-  double acc0 = 0.0, acc1 = 0.0;
-  for (int64_t I = w; I < Iend; I += kSmallWaves) {
+  TS x[16];
+  double y[16];
+  auto load = [&](int64_t I) {  // as in k_trmv_small
     const TS* t = Xpk + ptile(I, J, nt, full) * (int64_t)(kTile * kTile) + c0 + lr;
-    double x[16], y[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const int r = 4 * q + lk;
       const int64_t gr = I * kTile + r;
-      x[q] = (double)t[r * kTile];
+      x[q] = t[r * kTile];
       y[q] = gr < n ? qv[gr] : 0.0;
     }
+  };
+  int64_t I = w;
+  if (I < Iend) load(I);
+  if (done && *done) return;
+  double acc0 = 0.0, acc1 = 0.0;
+  while (I < Iend) {
+    double p[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) p[q] = (double)x[q] * y[q];
+    I += kSmallWaves;
+    if (I < Iend) load(I);
 #pragma unroll
     for (int q = 0; q < 16; q += 2) {
-      acc0 += x[q] * y[q];
-      acc1 += x[q + 1] * y[q + 1];
+      acc0 += p[q];
+      acc1 += p[q + 1];
     }
   }
   double s = acc0 + acc1;
@@ -386,9 +437,7 @@ __global__ void __launch_bounds__(kThreads)
       s1 += val[e + kSpvLanes] * x[col[e + kSpvLanes]];
     }
     if (e < hi) s0 += val[e] * x[col[e]];
-    double t = s0 + s1;
-#pragma unroll
-    for (int o = kSpvLanes / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    const double t = group_sum<kSpvLanes>(s0 + s1);
     if (lane == 0) {
       double o = sA * t;
       if (prev && cf != 0.0) o -= cf * prev[row];
@@ -468,13 +517,9 @@ __global__ void __launch_bounds__(kThreads)
       return;
     }
   }
-  if (done && *done) return;
   const int lane = threadIdx.x & (L - 1);
   const int64_t sub = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / L;
   const int64_t nsub = (int64_t)nblk * (kThreads / L);
-  double sA, cf;
-  lazy_scale(sc, scratch, &sA, &cf);
-  double ss = 0.0;
   int64_t lo = 0, hi = 0;
   int nr = 0;
   int32_t e0 = 0, c0 = 0;
@@ -485,6 +530,10 @@ __global__ void __launch_bounds__(kThreads)
     e0 = rend[sub * kMaxRuns];
     c0 = rcol[sub * kMaxRuns];
   }
+  if (done && *done) return;  // its load goes out with the first row's
+  double sA, cf;
+  lazy_scale(sc, scratch, &sA, &cf);
+  double ss = 0.0;
   for (int64_t row = sub; row < rows; row += nsub) {
     const int64_t nrow = row + nsub;
     int64_t nlo = 0, nhi = 0;
@@ -524,9 +573,7 @@ __global__ void __launch_bounds__(kThreads)
         off = end;
       }
     }
-    double t = s0 + s1;
-#pragma unroll
-    for (int o = L / 2; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+    const double t = group_sum<L>(s0 + s1);
     if (lane == 0) {
       double o = sA * t;
       if (prev && cf != 0.0) o -= cf * prev[row];
@@ -665,10 +712,18 @@ __global__ void __launch_bounds__(kThreads)
     k_lsqr_step(const LsqrDev* __restrict__ st, LsqrDev* next, const double* __restrict__ asq, int nasq,
                 const double* __restrict__ v, double* vt, double* w, double* y, int64_t n, double* __restrict__ ysq,
                 double* __restrict__ wsq) {
-  if (st->done) return;
   __shared__ double scratch[kThreads / 64];
+  // the state, the partial sums and the first entries of the vectors are loaded
+  // together (one memory round trip), then the stop flag is looked at
   LsqrDev s = *st;
-  const double alpha = sqrt(reduce_partials(asq, nasq, scratch));
+  double a2 = 0.0;
+  for (int i = threadIdx.x; i < nasq; i += kThreads) a2 += asq[i];
+  const int64_t i0 = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  const bool in0 = i0 < n;
+  const double w0 = in0 ? w[i0] : 0.0, y0 = in0 ? y[i0] : 0.0, v0 = in0 ? v[i0] : 0.0;
+  const double vt0 = vt && in0 ? vt[i0] : 0.0;
+  if (s.done) return;
+  const double alpha = sqrt(block_sum(a2, scratch));
   const double beta = s.beta;
   s.alpha = alpha;
   s.itn += 1;
@@ -705,16 +760,16 @@ __global__ void __launch_bounds__(kThreads)
   const double a = s.phi_rho, b = s.theta_rho;
   const double ia = inv_or_0(alpha), ib = inv_or_0(beta);
   double sy = 0.0, sw = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * kThreads) {
-    const double wi = w[i];
-    const double yi = y[i] + a * wi;
-    double vi;
+  for (int64_t i = i0; i < n; i += (int64_t)gridDim.x * kThreads) {
+    const bool first = i == i0;
+    const double wi = first ? w0 : w[i];
+    const double yi = (first ? y0 : y[i]) + a * wi;
+    double vi = first ? v0 : v[i];
     if (vt) {
-      vi = (v[i] * ib - beta * vt[i]) * ia;
+      vi = (vi * ib - beta * (first ? vt0 : vt[i])) * ia;
       vt[i] = vi;
     } else {
-      vi = v[i] * ia;
+      vi *= ia;
     }
     const double wn = vi - b * wi;
     y[i] = yi;

@@ -200,13 +200,6 @@ __global__ void __launch_bounds__(256)
 }
 
 // v of lane (lane ^ mask) within 32 lanes, on the DPP path where it has the pattern
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
 template <int MASK>
 __device__ __forceinline__ double lane_xor(double v) {
   if constexpr (MASK == 1) return dpp_move<0xB1>(v);         // quad_perm(1, 0, 3, 2)

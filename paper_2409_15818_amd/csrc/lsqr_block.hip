@@ -19,6 +19,7 @@
 
 #include "common.h"
 #include "lsqr_dev.h"
+#include "runs.h"
 
 namespace rfmls {
 
@@ -576,7 +577,6 @@ __global__ void __launch_bounds__(kThreads)
 // (A) and 530 us (A^T) and its walk 2 ms a call; 32 right-hand sides 42.1 ->
 // 14.1 ms.  See spmm_prepare for which matrices take this kernel.
 // ---------------------------------------------------------------------------
-constexpr int kPieceRows = 64;
 constexpr int kRunStep = 16;
 typedef double d2u __attribute__((ext_vector_type(2), aligned(8)));
 
@@ -590,10 +590,9 @@ struct RunMat {
   int64_t kchunk;                     // entries per K chunk, a multiple of kRunStep
 };
 
-// Pieces of each 64-row group: a piece starts at the group's first row and at
-// every row whose runs differ from the row before.  Count pass: pcount[group];
-// fill pass: pieces from pptr[group] on.  bad is set when a row has no run
-// description or a run leaves the matrix's columns.
+// Pieces of each 64-row group (group_pieces).  Count pass: pcount[group]; fill
+// pass: pieces from pptr[group] on.  bad is set when a row has no run description
+// or a run leaves the matrix's columns.
 template <bool Fill>
 __global__ void __launch_bounds__(kThreads)
     k_run_pieces(int64_t rows, int64_t ncols, const int32_t* __restrict__ nrun, const int32_t* __restrict__ rcol,
@@ -603,34 +602,16 @@ __global__ void __launch_bounds__(kThreads)
   const int64_t ngroups = (rows + kPieceRows - 1) / kPieceRows;
   const int64_t nw = (int64_t)gridDim.x * (kThreads / 64);
   for (int64_t g = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); g < ngroups; g += nw) {
-    const int64_t row = g * kPieceRows + lane;
-    const bool live = row < rows;
-    const int k = live ? nrun[row] : 0;
-    bool start = live && lane == 0;
-    bool wrong = k < 0;
-    if (live && k >= 0) {
-      int32_t off = 0;
-      const bool cmp = lane > 0;
-      if (cmp && nrun[row - 1] != k) start = true;
-      for (int q = 0; q < k; ++q) {
-        const int32_t c = rcol[row * kMaxRuns + q], e = rend[row * kMaxRuns + q];
-        wrong |= c < 0 || (int64_t)c + (e - off) > ncols;
-        off = e;
-        if (cmp && !start && (rcol[(row - 1) * kMaxRuns + q] != c || rend[(row - 1) * kMaxRuns + q] != e)) start = true;
-      }
-    }
-    const unsigned long long starts = __ballot(start), wrongs = __ballot(wrong), lives = __ballot(live);
+    unsigned long long starts, lives, wrong;
+    group_pieces(g, rows, ncols, nrun, rcol, rend, &starts, &lives, &wrong);
     if (!Fill) {
       if (lane == 0) {
         pcount[g] = __popcll(starts);
-        if (wrongs) atomicOr(bad, 1);
+        if (wrong) atomicOr(bad, 1);
       }
-    } else if (start) {
+    } else if (starts >> lane & 1) {
       const unsigned long long below = starts & ((1ull << lane) - 1ull);
-      // the rows up to the next start, or to the group's last live row
-      const unsigned long long later = lane == 63 ? 0ull : starts >> (lane + 1);
-      const int len = later ? __builtin_ctzll(later) + 1 : __popcll(lives) - lane;
-      pieces[pptr[g] + __popcll(below)] = make_int2((int)row, len);
+      pieces[pptr[g] + __popcll(below)] = make_int2((int)(g * kPieceRows + lane), piece_len(starts, lives, lane));
     }
   }
 }

@@ -151,3 +151,33 @@ def test_qr_of_rows_that_start_late(s, n, width, per_row, zero_rows, dtype):
             ref = S32.T @ S32
         assert np.linalg.norm(Rm.T @ Rm - ref) <= 20 * n * u * np.linalg.norm(SA) ** 2
         Rs.append(Rm)
+
+
+# Transposes of at least 2^20 entries, which are sorted piece by piece where the
+# rows' runs allow it: pieces cut by the 64-row groups, runs that leave a 64-entry
+# tile, empty rows, more columns than one counting pass holds (16,384); and the two
+# kinds that are not (a row of nine runs; every row with runs of its own).  Whole
+# numbers and copies: equal to scipy's transpose bit for bit.
+TRANSPOSES = [
+    (700, [(900, [(0, 333)]), (37, []), (1501, [(10, 64), (200, 65), (699, 1)]), (1, [(5, 7)]), (3000, [(333, 200)])]),
+    (20000, [(5000, [(100 * k, 30) for k in range(7)]), (130, [(16000, 2000)]), (63, [(19999, 1)]), (65, [(0, 20000)])]),
+    (400, [(4000, [(0, 300)]), (64, [(10 * k, 5) for k in range(9)])]),
+    (2000, [(1, [(k % 1500, 200 + k % 300)]) for k in range(4000)]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(TRANSPOSES)))
+def test_transpose_piece_by_piece(case):
+    import scipy.sparse as sp
+
+    n, pieces = TRANSPOSES[case]
+    ptr, col, val = _blocks(pieces, n, case)
+    m = len(ptr) - 1
+    assert ptr[-1] >= 1 << 20
+    h = R.Handle(device="cuda:0")
+    T = R.rfmls_transpose(h, R.CSR.from_numpy(ptr, col, val, m, n))
+    ref = sp.csr_matrix((val, col, ptr), shape=(m, n)).T.tocsr()
+    ref.sort_indices()
+    assert np.array_equal(T.row_ptr.cpu().numpy(), ref.indptr)
+    assert np.array_equal(T.col.cpu().numpy(), ref.indices)
+    assert np.array_equal(T.val.cpu().numpy(), ref.data)

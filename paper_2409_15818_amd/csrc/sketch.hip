@@ -135,9 +135,10 @@ __global__ void __launch_bounds__(256) k_sort_buckets(const int64_t* __restrict_
 }
 
 // One block per sketch row j.  The bucket's rows (columns ascending within a
-// row) each cover one contiguous column span; the spans, merged in order of
-// their first column, map the row's touched columns onto a compact LDS window
-// (at most kWin doubles).  Zeros go out first for every 16-byte segment clear
+// row) each cover one contiguous column span, or two where both halves of the
+// row's entries are gapless (an RFM interface row: two boxes, which may lie far
+// apart); the spans, merged in order of their first column, map the row's touched
+// columns onto a compact LDS window (at most kWin doubles).  Zeros go out first for every 16-byte segment clear
 // of the window, the bucket's rows are then added into the window in ascending
 // row order (a barrier between rows), and the window's segments are stored:
 // the dense row is written once, with 16-byte non-temporal stores, and A's
@@ -145,9 +146,10 @@ __global__ void __launch_bounds__(256) k_sort_buckets(const int64_t* __restrict_
 // wider than kWin takes the chunked path: chunks of kWin columns, every row of
 // the bucket visited per chunk.  Either way every element is summed in float64
 // from +0 over the bucket's rows in ascending row order.
-constexpr int kSketchThreads = 256;
-constexpr int kWin = 2048;
+// threads: twice as many beside the 32 KB window, of which only four fit a compute unit
+constexpr int sketch_threads(int win) { return win > 2048 ? 512 : 256; }
 constexpr int kMaxBucketRows = 64;
+constexpr int kMaxSpans = 2 * kMaxBucketRows;
 
 template <typename TOut>
 struct SketchVec;
@@ -162,18 +164,26 @@ struct SketchVec<float> {
   typedef float vec __attribute__((ext_vector_type(4)));
 };
 
-// Vec: the row start is 16-byte aligned (SA and ld suit 16-byte stores)
-template <typename TOut, bool Vec>
-__global__ void __launch_bounds__(kSketchThreads)
+// Vec: the row start is 16-byte aligned (SA and ld suit 16-byte stores).  kWin: see
+// run_sketch.
+template <typename TOut, bool Vec, int kWin>
+__global__ void __launch_bounds__(sketch_threads(kWin))
     k_sketch_rows(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                   const double* __restrict__ val, const int8_t* __restrict__ sign,
                   const int64_t* __restrict__ bptr, const int32_t* __restrict__ perm, int64_t n,
                   TOut* __restrict__ SA, int64_t ld) {
+  constexpr int NT = sketch_threads(kWin);
   constexpr int V = Vec ? SketchVec<TOut>::V : 1;
   typedef typename SketchVec<TOut>::vec vec_t;
   __shared__ double acc[kWin];
-  __shared__ int32_t sp0[kMaxBucketRows], sp1[kMaxBucketRows];
-  __shared__ int32_t ist[kMaxBucketRows], ien[kMaxBucketRows], ioff[kMaxBucketRows];
+  __shared__ int32_t raw0[kMaxSpans], raw1[kMaxSpans];
+  int32_t* sp0 = (int32_t*)acc;  // the sorted spans, in the window's place until it is cleared
+  int32_t* sp1 = sp0 + kMaxSpans;
+  __shared__ int32_t ist[kMaxSpans], ien[kMaxSpans], ioff[kMaxSpans];
+  __shared__ int32_t wof[kMaxSpans];  // window position of a span's column c: c + wof
+  // the bucket's rows in order: first entry, entries, sign
+  __shared__ int32_t rlo[kMaxBucketRows], rlen[kMaxBucketRows];  // (fewer than 2^31 entries)
+  __shared__ int8_t rsg[kMaxBucketRows];
   __shared__ int nint_s;
   const int t = threadIdx.x;
   const int64_t j = blockIdx.x;
@@ -185,25 +195,40 @@ __global__ void __launch_bounds__(kSketchThreads)
     if (t < nb) {
       const int32_t i = perm[blo + t];
       const int64_t lo = row_ptr[i], hi = row_ptr[i + 1];
-      sp0[t] = hi > lo ? col[lo] : 1;  // an empty row: an empty span
-      sp1[t] = hi > lo ? col[hi - 1] : 0;
+      rlo[t] = (int32_t)lo;
+      rlen[t] = (int32_t)(hi - lo);
+      rsg[t] = sign[i];
+      // empty spans (1, 0) for what a row does not have
+      int32_t f0 = 1, l0 = 0, f1 = 1, l1 = 0;
+      if (hi > lo) {
+        const int64_t h = (hi - lo) / 2;  // entries of the first half
+        f0 = col[lo];
+        l0 = col[hi - 1];
+        const int32_t e0 = col[lo + (h > 0 ? h - 1 : 0)], b1 = col[lo + h];
+        if (h > 0 && b1 > e0 + 1 && (int64_t)e0 - f0 == h - 1 && (int64_t)l0 - b1 == hi - lo - h - 1) {
+          f1 = b1;
+          l1 = l0;
+          l0 = e0;
+        }
+      }
+      raw0[2 * t] = f0;
+      raw1[2 * t] = l0;
+      raw0[2 * t + 1] = f1;
+      raw1[2 * t + 1] = l1;
     }
     __syncthreads();
-    if (t == 0) {
-      // sort the spans by first column (insertion sort; a handful of rows), merge
-      for (int a = 1; a < nb; ++a) {
-        const int32_t x0 = sp0[a], x1 = sp1[a];
-        int b2 = a - 1;
-        while (b2 >= 0 && sp0[b2] > x0) {
-          sp0[b2 + 1] = sp0[b2];
-          sp1[b2 + 1] = sp1[b2];
-          --b2;
-        }
-        sp0[b2 + 1] = x0;
-        sp1[b2 + 1] = x1;
-      }
+    const int ns = 2 * (int)nb;
+    if (t < ns) {  // sorted by first column: each span to the place its rank gives
+      const int32_t x0 = raw0[t];
+      int rank = 0;
+      for (int u = 0; u < ns; ++u) rank += (raw0[u] < x0 || (raw0[u] == x0 && u < t)) ? 1 : 0;
+      sp0[rank] = x0;
+      sp1[rank] = raw1[t];
+    }
+    __syncthreads();
+    if (t == 0) {  // merge
       int k = 0, total = 0;
-      for (int a = 0; a < nb; ++a) {
+      for (int a = 0; a < ns; ++a) {
         if (sp1[a] < sp0[a]) continue;  // empty
         if (k > 0 && sp0[a] <= ien[k - 1] + 1) {
           if (sp1[a] > ien[k - 1]) {
@@ -230,41 +255,77 @@ __global__ void __launch_bounds__(kSketchThreads)
         if (c >= ist[k] && c <= ien[k]) return ioff[k] + (int)(c - ist[k]);
       return -1;
     };
-    auto touches = [&](int64_t c0) {
-      for (int k = 0; k < nint; ++k)
-        if (c0 <= ien[k] && c0 + V - 1 >= ist[k]) return true;
-      return false;
-    };
+    if (t < 2 * (int)nb && raw1[t] >= raw0[t]) {
+      int k = 0;
+      while (k + 1 < nint && ist[k + 1] <= raw0[t]) ++k;
+      wof[t] = ioff[k] - ist[k];
+    }
     const int64_t nseg = n / V;
-    // zeros for the segments clear of the window (no wait on anything below)
-    for (int64_t g = t; g < nseg; g += kSketchThreads) {
-      const int64_t c0 = g * V;
-      if (touches(c0)) continue;
-      if constexpr (Vec) {
-        __builtin_nontemporal_store(vec_t{}, (vec_t*)(out + c0));
-      } else {
-        __builtin_nontemporal_store((TOut)0, out + c0);
+    // zeros for the whole segments between the intervals (no wait on anything below)
+    for (int k = 0; k <= nint; ++k) {
+      const int64_t g0 = k > 0 ? ien[k - 1] / V + 1 : 0;
+      const int64_t g1 = k < nint && ist[k] / V < nseg ? ist[k] / V : nseg;
+      for (int64_t g = g0 + t; g < g1; g += NT) {
+        if constexpr (Vec) {
+          __builtin_nontemporal_store(vec_t{}, (vec_t*)(out + g * V));
+        } else {
+          __builtin_nontemporal_store((TOut)0, out + g);
+        }
       }
     }
     const int wlen = nint > 0 ? ioff[nint - 1] + ien[nint - 1] - ist[nint - 1] + 1 : 0;
-    for (int w = t; w < wlen; w += kSketchThreads) acc[w] = 0.0;
+    for (int w = t; w < wlen; w += NT) acc[w] = 0.0;
     __syncthreads();
-    for (int64_t q = blo; q < bhi; ++q) {
-      const int32_t i = perm[q];
-      const double sg = (double)sign[i];
-      const int64_t lo = row_ptr[i], hi = row_ptr[i + 1];
-      for (int64_t e = lo + t; e < hi; e += kSketchThreads) {
-        // a column outside the row's span (a row against the ascending-column
-        // contract) is dropped rather than written outside the window
-        const int pw = wpos(col[e]);
-        if (pw >= 0) acc[pw] += sg * val[e];
+    // the next two rows' first kPre entries per thread in flight while this row's
+    // are added; a row's place, length and sign come from LDS
+    constexpr int kPre = 768 / NT;
+    struct Ahead {
+      int32_t c[kPre + 1];
+      double v[kPre + 1];
+    };
+    auto fetch = [&](Ahead& p, int q) {
+#pragma unroll
+      for (int u = 0; u <= kPre; ++u) {
+        const int e = t + u * NT;
+        const bool in = q < (int)nb && e < rlen[q];
+        p.c[u] = in ? col[(int64_t)rlo[q] + e] : -1;
+        p.v[u] = in ? val[(int64_t)rlo[q] + e] : 0.0;
       }
+    };
+    auto row = [&](const Ahead& p, int q) {
+      const double sg = (double)rsg[q];
+      const int32_t a0 = raw0[2 * q], a1 = raw1[2 * q], b0 = raw0[2 * q + 1], b1 = raw1[2 * q + 1];
+      const int32_t aw = wof[2 * q], bw = wof[2 * q + 1];
+      // a column outside the row's spans (a row against the ascending-column
+      // contract) is dropped rather than written outside the window
+      auto add = [&](int32_t c, double x) {
+        const bool ina = c >= a0 && c <= a1;
+        if (ina || (c >= b0 && c <= b1)) acc[c + (ina ? aw : bw)] += x;
+      };
+#pragma unroll
+      for (int u = 0; u <= kPre; ++u)
+        if (t + u * NT < rlen[q]) add(p.c[u], sg * p.v[u]);
+      for (int e = t + (kPre + 1) * NT; e < rlen[q]; e += NT)
+        add(col[(int64_t)rlo[q] + e], sg * val[(int64_t)rlo[q] + e]);
       __syncthreads();
+    };
+    Ahead p0, p1, p2;
+    fetch(p0, 0);
+    fetch(p1, 1);
+    for (int q = 0; q < (int)nb; q += 3) {
+      fetch(p2, q + 2);
+      row(p0, q);
+      if (q + 1 >= (int)nb) break;
+      fetch(p0, q + 3);
+      row(p1, q + 1);
+      if (q + 2 >= (int)nb) break;
+      fetch(p1, q + 4);
+      row(p2, q + 2);
     }
     // the window's segments (a segment across two intervals is written twice, alike)
     for (int k = 0; k < nint; ++k) {
       const int64_t g0 = ist[k] / V, g1 = ien[k] / V < nseg ? ien[k] / V : nseg - 1;
-      for (int64_t g = g0 + t; g <= g1; g += kSketchThreads) {
+      for (int64_t g = g0 + t; g <= g1; g += NT) {
         const int64_t c0 = g * V;
         if constexpr (Vec) {
           vec_t v;
@@ -281,7 +342,7 @@ __global__ void __launch_bounds__(kSketchThreads)
       }
     }
     // columns past the last whole segment
-    for (int64_t c = nseg * V + t; c < n; c += kSketchThreads) {
+    for (int64_t c = nseg * V + t; c < n; c += NT) {
       const int p = wpos(c);
       out[c] = p >= 0 ? (TOut)acc[p] : (TOut)0;
     }
@@ -290,19 +351,19 @@ __global__ void __launch_bounds__(kSketchThreads)
   // chunked path
   for (int64_t c0 = 0; c0 < n; c0 += kWin) {
     const int64_t cw = (n - c0) < kWin ? (n - c0) : kWin;
-    for (int w = t; w < kWin; w += kSketchThreads) acc[w] = 0.0;
+    for (int w = t; w < kWin; w += NT) acc[w] = 0.0;
     __syncthreads();
     for (int64_t q = blo; q < bhi; ++q) {
       const int32_t i = perm[q];
       const double sg = (double)sign[i];
       const int64_t lo = row_ptr[i], hi = row_ptr[i + 1];
-      for (int64_t e = lo + t; e < hi; e += kSketchThreads) {
+      for (int64_t e = lo + t; e < hi; e += NT) {
         const int64_t c = (int64_t)col[e] - c0;
         if (c >= 0 && c < cw) acc[c] += sg * val[e];
       }
       __syncthreads();
     }
-    for (int w = t; w < cw; w += kSketchThreads) out[c0 + w] = (TOut)acc[w];
+    for (int w = t; w < cw; w += NT) out[c0 + w] = (TOut)acc[w];
     __syncthreads();
   }
 }
@@ -384,19 +445,28 @@ rfmls_status run_sketch(rfmls_handle* h, const rfmls_csr* A, int64_t s, const in
            (double)A->nnz);
   // 16-byte stores when every row starts 16-byte aligned
   const bool vec = (reinterpret_cast<uintptr_t>(SA) % 16 == 0) && ((int64_t)esz * ld) % 16 == 0;
+  // window of 2,048 columns (16 KB of LDS, eight workgroups per compute unit), or
+  // 4,096 where the buckets hold more than 1,024 entries on average and so often
+  // touch more than 2,048 columns: a bucket past the window reads its rows once per
+  // chunk.  With an interface row's two boxes as two spans and two rows' entries in
+  // flight: 105,840 x 9,450, float32, 2,352 entries a bucket, 0.70 -> 0.54 ms;
+  // Helmholtz sketch (2,900) 0.31 -> 0.24 ms; the 8x8-box sketch (475, bound by
+  // writing 5.2 GB) stays at 2,048 and pays 1.07 -> 1.18 ms of its 245 ms solve for
+  // the spans' sort.
+  const bool wide = A->nnz > 1024 * s;
   if (dt == RFMLS_F64) {
     if (vec)
-      hipLaunchKernelGGL((k_sketch_rows<double, true>), dim3((unsigned)s), dim3(kSketchThreads), 0, h->stream,
+      hipLaunchKernelGGL((wide ? k_sketch_rows<double, true, 4096> : k_sketch_rows<double, true, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
                          A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (double*)SA, ld);
     else
-      hipLaunchKernelGGL((k_sketch_rows<double, false>), dim3((unsigned)s), dim3(kSketchThreads), 0, h->stream,
+      hipLaunchKernelGGL((wide ? k_sketch_rows<double, false, 4096> : k_sketch_rows<double, false, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
                          A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (double*)SA, ld);
   } else {
     if (vec)
-      hipLaunchKernelGGL((k_sketch_rows<float, true>), dim3((unsigned)s), dim3(kSketchThreads), 0, h->stream,
+      hipLaunchKernelGGL((wide ? k_sketch_rows<float, true, 4096> : k_sketch_rows<float, true, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
                          A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (float*)SA, ld);
     else
-      hipLaunchKernelGGL((k_sketch_rows<float, false>), dim3((unsigned)s), dim3(kSketchThreads), 0, h->stream,
+      hipLaunchKernelGGL((wide ? k_sketch_rows<float, false, 4096> : k_sketch_rows<float, false, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
                          A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (float*)SA, ld);
   }
   }

@@ -181,3 +181,27 @@ def test_transpose_piece_by_piece(case):
     assert np.array_equal(T.row_ptr.cpu().numpy(), ref.indptr)
     assert np.array_equal(T.col.cpu().numpy(), ref.indices)
     assert np.array_equal(T.val.cpu().numpy(), ref.data)
+
+
+# Sketch rows whose buckets hold rows of two distant gapless halves, odd and even
+# entry counts, single entries, empty rows and rows with gaps, with windows below and
+# above both window sizes: the same adds in the same order as the oracle, so equal
+# bit for bit.
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("s,big", [(7, False), (40, False), (7, True), (300, True)])
+def test_sketch_of_two_span_rows(s, big, dtype):
+    from oracle import countsketch
+
+    n = 9001 if big else 1203
+    w = 900 if big else 40
+    runs = [[(0, w)], [(5, w), (n - w, w)], [(0, w + 1), (2 * w + 3, w)], [(n - 1, 1)], [],
+            [(w, 1), (n - 2, 1)], [(3, 2), (9, 2), (20, 2)], [(w // 2, 7), (n // 2, 8)]]
+    ptr, col, val = _blocks([(5 if k % 2 else 2, runs[k % len(runs)]) for k in range(24)], n, s)
+    m = len(ptr) - 1
+    h = R.Handle(device="cuda:0")
+    A = R.CSR.from_numpy(ptr, col, val, m, n)
+    SA, hg, sg, _ = R.rfmls_sketch(h, A, s, 11, dtype=dtype, want_maps=True)
+    ho, so = countsketch.hash_sign(m, s, 11)
+    ref, _ = countsketch.sketch_dense(ptr, col, val, ho, so, s, n)
+    assert np.array_equal(hg.cpu().numpy(), ho) and np.array_equal(sg.cpu().numpy(), so)
+    assert np.array_equal(SA.cpu().numpy(), ref if dtype == "f64" else ref.astype(np.float32))

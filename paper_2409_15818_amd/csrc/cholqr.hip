@@ -13,7 +13,7 @@
 //      D^{-1} G D^{-1} = U1^T U1, R1 = U1 D and W1 = R1^{-1};
 //   3. k_cq_apply_gram + k_cq_reduce: P <- Q1 = P W1 fused with the Gram of Q1;
 //   4. k_cq_factor (pass 2): Cholesky of Q1's Gram = U2^T U2 (Q = Q1 U2^{-1},
-//      R = U2 R1), then the Householder reconstruction (Ballard, Demmel,
+//      R = U2 R1), and the Householder reconstruction (Ballard, Demmel,
 //      Grigori, Jacquelin, Knight and Nguyen, "Reconstructing Householder
 //      vectors from tall-skinny QR", 2015) of Q's top 64 x 64 block: with
 //      S = diag(s_j), Q S - [I; 0] = Y (-T Y_1^T) is an LU factorisation
@@ -22,7 +22,7 @@
 //      -sign(c_j) chosen column by column from the current pivot c_j (so
 //      |U_jj| >= 1 and the elimination is stable); the QR's triangular factor
 //      is S R.  The panel's top block gets S R and Y_1;
-//   5. k_cq_apply: the rows below become Y_2 = Q1 (U2^{-1} S U^{-1}).
+//   5. k_cq_apply: the rows below become Y_2 = Q1 (U2^{-1} S U^{-1}) = Q1 (U S U2)^{-1}.
 // The panel is left exactly as the unblocked kernel leaves it: S R on and
 // above the diagonal, the vectors below it (unit diagonal implied), tau.
 //
@@ -224,17 +224,22 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Z[w] = inverse of diagonal block w of the upper triangular U, wavefront w
-// taking block w, lane l < 16 column l, by a column sweep with U's entries read
-// uniformly from LDS.
-__device__ void blk_diag_inverses(const Mat& U, Blk* Z) {
-  const int t = threadIdx.x;
-  const int w = t >> 6, l = t & 63;
-  const int k0 = w * kB;
+// 1 / x by the hardware estimate and two Newton steps (to about an ulp; x finite and
+// nonzero): a dependent chain a third as long as the library's division.
+__device__ __forceinline__ double rcp2(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+
+// Z = inverse of the diagonal block at k0 of the upper triangular U, by one
+// wavefront: lane l < 16 forms column l by a column sweep with U's entries read
+// uniformly from LDS (what lies below the diagonal is not read).
+__device__ void diag_inverse(const Mat& U, int k0, Blk& Z, int l) {
   double rd[kB], acc[kB];
 #pragma unroll
   for (int i = 0; i < kB; ++i) {
-    rd[i] = 1.0 / U[k0 + i][k0 + i];
+    rd[i] = rcp2(U[k0 + i][k0 + i]);
     acc[i] = (i == l) ? 1.0 : 0.0;
   }
 #pragma unroll
@@ -246,76 +251,120 @@ __device__ void blk_diag_inverses(const Mat& U, Blk* Z) {
   }
   if (l < kB)
 #pragma unroll
-    for (int i = 0; i < kB; ++i) Z[w][i][l] = acc[i];
-  __syncthreads();
+    for (int i = 0; i < kB; ++i) Z[i][l] = acc[i];
 }
 
-// Cholesky A = U^T U of the symmetric positive definite A (both triangles
-// read: A is kept whole), U written over A with its lower triangle set to
-// zero; Z[kb] receives the inverse of diagonal block kb.  Returns false
-// (every thread) on a non-positive or non-finite pivot; pmin / pmax: the
-// extreme pivots u_kk.  Block row kb (16 rows, columns k0 = 16 kb .. 63) is
-// factored by wavefront 0 alone, lane l holding column k0 + l: step s takes
+// Block row kb of the Cholesky factor A = U^T U (A symmetric, kept whole; U written
+// over A with zeros below the diagonal of the diagonal block), by one wavefront:
+// 16 rows, columns k0 = 16 kb .. 63, lane l holding column k0 + l.  Step s takes
 // the pivot from lane s (v_readlane), scales the lanes' row s entries to U's
 // row s and subtracts u_s,i u_s,l from the rows i > s below it, u_s,i read
 // from lane i; the whole block row of U comes out of the one elimination (no
 // product with the diagonal block's inverse) and no LDS round trip sits on the
-// chain.  The trailing block then takes A22 -= U12^T U12 on the matrix cores.
-__device__ bool blk_cholesky(Mat& A, Blk* Z, double* pmin, double* pmax) {
-  __shared__ int bad;
-  __shared__ double ext[2];
-  const int t = threadIdx.x;
-  if (t == 0) bad = 0;
-  __syncthreads();
-  double mn = 1e300, mx = 0.0;  // uniform on wavefront 0 (pivots by readlane)
-  for (int kb = 0; kb < kNb / kB; ++kb) {
-    const int k0 = kb * kB;
-    if (t < 64) {
-      const int l = t;
-      const bool act = l < kNb - k0;
-      double d[kB];
+// chain.  mn / mx follow the pivots u_kk; *bad is set on a non-positive or
+// non-finite pivot.
+__device__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* bad) {
+  const int k0 = kb * kB;
+  const bool act = l < kNb - k0;
+  double d[kB];
 #pragma unroll
-      for (int i = 0; i < kB; ++i) d[i] = act ? A[k0 + i][k0 + l] : 0.0;
-      bool badl = false;
+  for (int i = 0; i < kB; ++i) d[i] = act ? A[k0 + i][k0 + l] : 0.0;
 #pragma unroll
-      for (int s2 = 0; s2 < kB; ++s2) {
-        const double piv = lane_bcast(d[s2], s2);
-        if (!(piv > 0.0) || !isfinite(piv)) badl = true;
-        const double r = rsqrt(piv > 0.0 ? piv : 1.0);
-        const double ukk = piv * r;
-        mn = fmin(mn, ukk);
-        mx = fmax(mx, ukk);
-        const double us = l == s2 ? ukk : d[s2] * r;  // u_{s,l} for l >= s
-        d[s2] = l >= s2 ? us : 0.0;
+  for (int s2 = 0; s2 < kB; ++s2) {
+    const double piv = lane_bcast(d[s2], s2);
+    if (!(piv > 0.0) || !isfinite(piv)) *bad = true;
+    const double r = rsqrt(piv > 0.0 ? piv : 1.0);
+    const double ukk = piv * r;
+    *mn = fmin(*mn, ukk);
+    *mx = fmax(*mx, ukk);
+    const double us = l == s2 ? ukk : d[s2] * r;  // u_{s,l} for l >= s
+    d[s2] = l >= s2 ? us : 0.0;
 #pragma unroll
-        for (int i = s2 + 1; i < kB; ++i) d[i] = fma(-lane_bcast(us, i), us, d[i]);
-      }
-      if (act)
+    for (int i = s2 + 1; i < kB; ++i) d[i] = fma(-lane_bcast(us, i), us, d[i]);
+  }
+  if (act)
 #pragma unroll
-        for (int i = 0; i < kB; ++i) A[k0 + i][k0 + l] = d[i];
-      if (t == 0) {
-        if (badl) bad = 1;
-        ext[0] = mn;
-        ext[1] = mx;
-      }
+    for (int i = 0; i < kB; ++i) A[k0 + i][k0 + l] = d[i];
+}
+
+// Columns k0 .. k0 + 15 of the reconstruction's LU (see k_cq_factor), rows k0 .. 63,
+// by one wavefront, lane i holding row i.  Step j: the current pivot e_j by
+// readlane, s_j = -sign(e_j), row j minus s_j times U2's row j (whose diagonal is
+// positive, so the pivot's size is |e_j| + u_jj), multipliers and the panel's
+// remaining columns.  A gets the multipliers below the diagonal and U~ on and
+// above it, tau_j = |pivot| / u_jj.
+__device__ void recon_panel(Mat& A, const Mat& U2, int kb, int i, double* sg, double* tau) {
+  const int k0 = kb * kB;
+  double p[kB], u[kB];
+#pragma unroll
+  for (int m = 0; m < kB; ++m) {
+    p[m] = A[i][k0 + m];
+    u[m] = U2[i][k0 + m];  // row i of U2 (used on the panel's own rows only)
+  }
+#pragma unroll
+  for (int j = 0; j < kB; ++j) {
+    const int pr = k0 + j;
+    const double ej = lane_bcast(p[j], pr);
+    const double ujj = lane_bcast(u[j], pr);
+    const double sj = ej >= 0.0 ? -1.0 : 1.0;
+    const double piv = ej - sj * ujj;
+    const double rp = rcp2(piv);
+    if (i == pr) {
+      sg[pr] = sj;
+      tau[pr] = fabs(piv) / ujj;
+#pragma unroll
+      for (int m = j; m < kB; ++m) p[m] -= sj * u[m];
     }
-    __syncthreads();
-    if (bad) break;  // uniform: read after the barrier
-    const int nc = kNb - k0 - kB;
-    if (nc > 0)  // A22 -= U12^T U12
-      lds_mm(&A[k0 + kB][k0 + kB], kLd, &A[k0][k0 + kB], kLd, true, &A[k0][k0 + kB], kLd, nc, nc, kB, -1.0, 1.0);
+    const bool below = i > pr;
+    const double lij = p[j] * rp;
+    if (below) p[j] = lij;
+#pragma unroll
+    for (int m = j + 1; m < kB; ++m) {
+      const double un = lane_bcast(p[m], pr);
+      if (below) p[m] = fma(-lij, un, p[m]);
+    }
   }
-  // lower triangle outside the diagonal blocks
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, j = e % kNb;
-    if ((i >> 4) > (j >> 4)) A[i][j] = 0.0;
+  if (i >= k0)
+#pragma unroll
+    for (int m = 0; m < kB; ++m) A[i][k0 + m] = p[m];
+}
+// The same rows k0 .. k0 + 15 of U~ in the columns right of the panel, a column per
+// lane: unit lower forward substitution, then minus s_i U2.
+__device__ void recon_rows(Mat& A, const Mat& U2, int kb, int l, const double* sg) {
+  const int k0 = kb * kB, c = k0 + kB + l;
+  if (c >= kNb) return;
+  double x[kB];
+#pragma unroll
+  for (int i = 0; i < kB; ++i) x[i] = A[k0 + i][c];
+#pragma unroll
+  for (int i = 0; i < kB; ++i) {
+    x[i] -= sg[k0 + i] * U2[k0 + i][c];
+#pragma unroll
+    for (int m = i + 1; m < kB; ++m) x[m] = fma(-A[k0 + m][k0 + i], x[i], x[m]);
   }
-  __syncthreads();
-  const bool good = !bad;
-  if (good) blk_diag_inverses(A, Z);
-  *pmin = ext[0];
-  *pmax = ext[1];
-  return good;
+#pragma unroll
+  for (int i = 0; i < kB; ++i) A[k0 + i][c] = x[i];
+}
+
+// R1 <- U2 R1 (both upper triangular, zeros below the diagonal inside the diagonal
+// blocks) by one wavefront on the matrix cores: block column by block column, the
+// blocks from the top down, each needing only the blocks of R1 at and below it.
+__device__ void upper_product(const Mat& U2, Mat& R1, int lane) {
+  const int lr = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int tj = 0; tj < kNb / kB; ++tj)
+#pragma unroll
+    for (int ti = 0; ti <= tj; ++ti) {
+      v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int k = 4 * ti; k < 4 * (tj + 1); ++k)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(U2[16 * ti + lr][4 * k + lk], R1[4 * k + lk][16 * tj + lr], acc, 0,
+                                                   0, 0);
+      wave_sync();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) R1[16 * ti + lk + 4 * r][16 * tj + lr] = acc[r];
+      wave_sync();
+    }
 }
 
 // W = U^{-1} for the upper triangular U (zero below the diagonal; Z the
@@ -335,93 +384,28 @@ __device__ void blk_upper_inverse(const Mat& U, const Blk* Z, Mat& W, Mat& T) {
   }
 }
 
-// LU without pivoting of Q1 S - I (Q1 the top 64 x 64 block of Q, in A) with
-// s_j = -sign(c_j) taken from the current pivot c_j: the identity and the
-// column signs only touch the pivots (u_jj = -|c_j| - 1) and the multipliers
-// (l_ij = s_j a_ij / u_jj), so the elimination runs on Q1 itself, blocked by 16
-// columns: the 64 x 16 panel on wavefront 0 (lane i holding row i), the block
-// row by forward substitution, the trailing block on the matrix cores.  On
-// return A holds the multipliers below the diagonal and U = (eliminated Q1
-// entries times s_c) above it, u_jj on it; sg holds s.
-__device__ void blk_recon_lu(Mat& A, double* sg) {
-  __shared__ double prow[kB];
-  const int t = threadIdx.x;
-  for (int kb = 0; kb < kNb / kB; ++kb) {
-    const int k0 = kb * kB;
-    if (t < 64) {
-      // lane i holds row i of the 64 x 16 panel; step j: the pivot by
-      // readlane, the pivot row's next entry by readlane, the rest of it through
-      // LDS (written by the pivot row's lane, read uniformly)
-      const int i = t;
-      double p[kB];
-#pragma unroll
-      for (int m = 0; m < kB; ++m) p[m] = A[i][k0 + m];
-#pragma unroll
-      for (int j = 0; j < kB; ++j) {
-        const int pr = k0 + j;
-        const double cj = lane_bcast(p[j], pr);
-        const double sj = cj >= 0.0 ? -1.0 : 1.0;
-        const double ujj = -fabs(cj) - 1.0;
-        const double fj = sj * (1.0 / ujj);
-        if (i == pr) {
-          sg[pr] = sj;
-          p[j] = ujj;
-#pragma unroll
-          for (int m = j + 2; m < kB; ++m) prow[m] = p[m];
-        }
-        const double lij = p[j] * fj;
-        if (i > pr) p[j] = lij;
-        if (j + 1 < kB) {
-          const double un = lane_bcast(p[j + 1], pr);
-          if (i > pr) p[j + 1] = fma(-lij, un, p[j + 1]);
-          wave_sync();
-#pragma unroll
-          for (int m = j + 2; m < kB; ++m)
-            if (i > pr) p[m] = fma(-lij, prow[m], p[m]);
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < kB; ++m) A[i][k0 + m] = p[m];
-    }
-    __syncthreads();
-    const int nc = kNb - k0 - kB;
-    if (nc > 0) {
-      if (t < nc) {  // block row: unit lower forward substitution, a column per thread
-        const int c = k0 + kB + t;
-        double x[kB];
-#pragma unroll
-        for (int i = 0; i < kB; ++i) {
-          double acc = A[k0 + i][c];
-#pragma unroll
-          for (int m = 0; m < i; ++m) acc = fma(-A[k0 + i][k0 + m], x[m], acc);
-          x[i] = acc;
-        }
-#pragma unroll
-        for (int i = 0; i < kB; ++i) A[k0 + i][c] = x[i];
-      }
-      __syncthreads();
-      lds_mm(&A[k0 + kB][k0 + kB], kLd, &A[k0 + kB][k0], kLd, false, &A[k0][k0 + kB], kLd, nc, nc, kB, -1.0, 1.0);
-    }
-  }
-  // the column signs on U's off-diagonal entries (the diagonal holds u_jj)
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, c = e % kNb;
-    if (i < c) A[i][c] *= sg[c];
-  }
-  __syncthreads();
-}
-
 // One Cholesky step of CholeskyQR2 on the reduced Gram G.
 // pass 1 (column-scaled Gram D^{-1} G D^{-1} = U^T U): R1 = U D into Rc and
 //   Wk = R1^{-1} = D^{-1} U^{-1} (the operand of the fused apply + Gram).
 // pass 2 (Gram of Q1 = U2^T U2): R = U2 R1 into the panel's top block as S R,
-//   and the Householder reconstruction of Q = Q1 U2^{-1}: its top block
-//   Q1top U2^{-1} is factored by blk_recon_lu, the multipliers go below the
-//   diagonal of the panel's top block, tau_j = -u_jj, and
-//   Wk = U2^{-1} S U^{-1}, with which the rows below become the Householder
-//   vectors L2 = Q1bot U2^{-1} S U^{-1}.
+//   and the Householder reconstruction of Q = Q1 U2^{-1}: with S = diag(s_j),
+//   Q's top block gives Q S - I = L U (no pivoting, s_j = -sign of the current
+//   pivot).  Multiplied by S U2 from the right that is
+//     A - S U2 = L U~,  A = Q1's top block,  U~ = U S U2,
+//   so the elimination runs on A and U2 directly: Q's top block and U2^{-1} are
+//   not formed, the current pivot e_j is u2_jj times Q's, tau_j = -u_jj = |u~_jj| /
+//   u2_jj, and the rows below become Q1bot U2^{-1} S U^{-1} = Q1bot U~^{-1}: one
+//   triangular inverse, Wk = U~^{-1}, where U2^{-1} and U^{-1} and two products with
+//   them were formed before.  L goes below the diagonal of the panel's top block.
 // A pivot ratio u_min / u_max below min_pivot_ratio (or a non-positive pivot)
 // sets *status = pass and leaves everything else untouched.
+//
+// Bound by the eliminations' chains (a step per column), so independent ones run
+// beside each other, one wavefront each: stage kb has block row kb of the Cholesky
+// factor (wavefront 0), the reconstruction's panel kb - 1 (1), the inverse of an
+// earlier diagonal block (2) and at the end U2 R1 (3); the trailing products between
+// the stages are shared by all four.  Average of the two passes 47.3 -> 37.7 us
+// (4x4-box solve 9.8 -> 9.3 ms, Helmholtz 27.4 -> 26.4 ms).
 template <typename TS>
 __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G, double* __restrict__ Wk,
                                                    double* __restrict__ Rc, TS* __restrict__ P, int64_t ld,
@@ -431,9 +415,12 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
   __shared__ Mat M0, M1, M2, M3;
   __shared__ Blk Z[kNb / kB];
   __shared__ double dsc[kNb];
-  __shared__ double sg[kNb];
-  __shared__ int bad0;
+  __shared__ double sg[kNb], tj[kNb];
+  __shared__ int bad_s;
+  __shared__ double ext[2];
+  constexpr int kBlocks = kNb / kB;
   const int t = threadIdx.x;
+  const int lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6);
   // thread t takes element (t / 64 + 4 q, t % 64), q < 16, of every 64 x 64
   // operand; each operand's 16 loads are issued together
   const int er = t >> 6, ec = t & 63;
@@ -441,76 +428,87 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
 #pragma unroll
   for (int q = 0; q < 16; ++q) gv[q] = G[(er + 4 * q) * kNb + ec];
   if (pass == 2) {
-    // the panel's top block (Q1's) into M3, read after the Cholesky
-    double pv[16];
+    // the panel's top block (Q1's) into M3, R1 into M2
+    double pv[16], rv[16];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) pv[q] = (double)P[(int64_t)(er + 4 * q) * ld + ec];
+    for (int q = 0; q < 16; ++q) {
+      pv[q] = (double)P[(int64_t)(er + 4 * q) * ld + ec];
+      rv[q] = Rc[(er + 4 * q) * kNb + ec];
+    }
 #pragma unroll
-    for (int q = 0; q < 16; ++q) M3[er + 4 * q][ec] = pv[q];
+    for (int q = 0; q < 16; ++q) {
+      M3[er + 4 * q][ec] = pv[q];
+      M2[er + 4 * q][ec] = rv[q];
+    }
   }
   if (t < kNb) {
     const double gjj = G[t * kNb + t];
     dsc[t] = pass == 1 ? sqrt(gjj > 0.0 ? gjj : 0.0) : 1.0;
   }
-  if (t == 0) bad0 = 0;
+  if (t == 0) bad_s = 0;
   __syncthreads();
-  if (t < kNb && !(dsc[t] > 0.0)) bad0 = 1;
+  if (t < kNb && !(dsc[t] > 0.0)) bad_s = 1;
   {
     const double dj = dsc[ec];
+    const double rj = dj > 0.0 ? 1.0 / dj : 0.0;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const double di = dsc[er + 4 * q];
-      M0[er + 4 * q][ec] = (di > 0.0 && dj > 0.0) ? gv[q] * (1.0 / di) * (1.0 / dj) : 0.0;
+      M0[er + 4 * q][ec] = di > 0.0 ? gv[q] * (1.0 / di) * rj : 0.0;
     }
   }
   __syncthreads();
-  double pmin = 0.0, pmax = 0.0;
-  const bool ok = !bad0 && blk_cholesky(M0, Z, &pmin, &pmax);
-  if (!ok || !(pmin >= min_pivot_ratio * pmax)) {
+  double mn = 1e300, mx = 0.0;  // pivots, uniform on wavefront 0
+  bool ok = !bad_s;
+  for (int kb = 0; kb <= kBlocks + (pass == 2 ? 1 : 0) && ok; ++kb) {
+    const int k0 = kb * kB;
+    if (kb > 0 && kb < kBlocks)  // A22 -= U12^T U12 with the block row of the stage before
+      lds_mm(&M0[k0][k0], kLd, &M0[k0 - kB][k0], kLd, true, &M0[k0 - kB][k0], kLd, kNb - k0, kNb - k0, kB, -1.0, 1.0);
+    if (w == 0 && kb < kBlocks) {
+      bool bad = false;
+      chol_panel(M0, kb, lane, &mn, &mx, &bad);
+      if (lane == 0) {
+        if (bad) bad_s = 1;
+        ext[0] = mn;
+        ext[1] = mx;
+      }
+    }
+    if (pass == 1) {
+      if (w == 1 && kb > 0) diag_inverse(M0, k0 - kB, Z[kb - 1], lane);
+    } else {
+      if (w == 1 && kb > 0 && kb <= kBlocks) {
+        recon_panel(M3, M0, kb - 1, lane, sg, tj);
+        wave_sync();
+        recon_rows(M3, M0, kb - 1, lane, sg);
+      }
+      if (w == 2 && kb > 1) diag_inverse(M3, k0 - 2 * kB, Z[kb - 2], lane);
+      if (w == 3 && kb == kBlocks) upper_product(M0, M2, lane);
+    }
+    __syncthreads();
+    ok = !bad_s;
+    if (pass == 2 && kb > 0 && kb < kBlocks)  // trailing block of the panel just reconstructed
+      lds_mm(&M3[k0][k0], kLd, &M3[k0][k0 - kB], kLd, false, &M3[k0 - kB][k0], kLd, kNb - k0, kNb - k0, kB, -1.0, 1.0);
+  }
+  if (!ok || !(ext[0] >= min_pivot_ratio * ext[1])) {
     if (t == 0) *status = pass;
     return;
   }
-  blk_upper_inverse(M0, Z, M1, M2);  // M1 = U^{-1}
   if (pass == 1) {
+    blk_upper_inverse(M0, Z, M1, M2);  // M1 = U^{-1}
     for (int e = t; e < kNb * kNb; e += 256) {
       const int i = e / kNb, j = e % kNb;
       Wk[e] = M1[i][j] * (1.0 / dsc[i]);
-      Rc[e] = M0[i][j] * dsc[j];
+      Rc[e] = i <= j ? M0[i][j] * dsc[j] : 0.0;
     }
     return;
   }
-  // pass 2: M2 = R = U2 R1 (written over R1); M0 = Q1top U2^{-1}
-  {
-    double rv[16];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) rv[q] = Rc[(er + 4 * q) * kNb + ec];
-#pragma unroll
-    for (int q = 0; q < 16; ++q) M2[er + 4 * q][ec] = rv[q];
-  }
-  __syncthreads();
-  lds_mm(&M2[0][0], kLd, &M0[0][0], kLd, false, &M2[0][0], kLd, kNb, kNb, kNb, 1.0, 0.0);
-  lds_mm(&M0[0][0], kLd, &M3[0][0], kLd, false, &M1[0][0], kLd, kNb, kNb, kNb, 1.0, 0.0);
-  blk_recon_lu(M0, sg);
   for (int e = t; e < kNb * kNb; e += 256) {
     const int i = e / kNb, c = e % kNb;
-    P[(int64_t)i * ld + c] = (TS)(i <= c ? sg[i] * M2[i][c] : M0[i][c]);
+    P[(int64_t)i * ld + c] = (TS)(i <= c ? sg[i] * M2[i][c] : M3[i][c]);
   }
-  if (t < kNb) tau[t] = (TS)(-M0[t][t]);
-  __syncthreads();
-  for (int e = t; e < kNb * kNb; e += 256) {  // U alone (zero below the diagonal)
-    const int i = e / kNb, c = e % kNb;
-    if (i > c) M0[i][c] = 0.0;
-  }
-  __syncthreads();
-  blk_diag_inverses(M0, Z);
-  blk_upper_inverse(M0, Z, M2, M3);  // M2 = U^{-1}
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, c = e % kNb;
-    M2[i][c] *= sg[i];
-  }
-  __syncthreads();
-  lds_mm(&M3[0][0], kLd, &M1[0][0], kLd, false, &M2[0][0], kLd, kNb, kNb, kNb, 1.0, 0.0);
-  for (int e = t; e < kNb * kNb; e += 256) Wk[e] = M3[e / kNb][e % kNb];
+  if (t < kNb) tau[t] = (TS)tj[t];
+  blk_upper_inverse(M3, Z, M1, M0);  // M1 = U~^{-1} (above the diagonal blocks M3 holds U~)
+  for (int e = t; e < kNb * kNb; e += 256) Wk[e] = M1[e / kNb][e % kNb];
 }
 
 // A operands of P W for one row: lane (lr, lk) of a wavefront takes row lr of

@@ -33,8 +33,7 @@
 // non-positive pivot or a pivot ratio below the caller's threshold is flagged
 // (status 1) and factored by the unblocked kernel instead, on the untouched
 // panel; a second Cholesky failure (status 2) leaves Q1 in the panel, which the
-// unblocked kernel then factors, its R multiplied by R1 afterwards
-// (k_cq_fix).  Every sum runs in a fixed order.
+// unblocked kernel then factors, multiplying its R by R1 at the end.  Every sum runs in a fixed order.
 #include "common.h"
 
 namespace rfmls {
@@ -513,16 +512,16 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
 
 // A operands of P W for one row: lane (lr, lk) of a wavefront takes row lr of
 // a 16-row group, and step t of the product's K range one of its columns,
-// kcol(t, lk).  With 16-byte loads (V16: the row start and ld allow them)
-// the lane reads E = 16 / sizeof(TS) adjacent columns at a time, so step t
-// takes column 4E (t / E) + E lk + t % E; otherwise column 4 t + lk.  Either
-// way the four lanes of a step hold four distinct columns inside the 4E-column
-// (or 4-column) chunk of the step, all 64 columns are covered once, and the
-// steps t < 4 (q + 1) hold every column <= 16 q + 15.
-template <typename TS, bool V16>
+// kcol(t, lk): with E = 16 / sizeof(TS), step t takes column 4E (t / E) + E lk +
+// t % E, so that the lane reads E adjacent columns at a time, by one 16-byte load
+// where the row start and ld allow it (V16) and one by one otherwise; the K order,
+// and so every bit of the product, is the same.  The four lanes of a step hold four
+// distinct columns inside the 4E-column chunk of the step, all 64 columns are covered
+// once, and the steps t < 4 (q + 1) hold every column <= 16 q + 15.
+template <typename TS>
 __device__ __forceinline__ int kcol(int t, int lk) {
   constexpr int E = 16 / (int)sizeof(TS);
-  return V16 ? 4 * E * (t / E) + E * lk + t % E : 4 * t + lk;
+  return 4 * E * (t / E) + E * lk + t % E;
 }
 template <typename TS, bool V16>
 __device__ __forceinline__ void load_arow(double (&a)[16], const TS* __restrict__ row, int lk, bool in) {
@@ -545,7 +544,7 @@ __device__ __forceinline__ void load_arow(double (&a)[16], const TS* __restrict_
   } else {
 #pragma unroll
     for (int t = 0; t < 16; ++t) {
-      const double v = (double)row[4 * t + lk];
+      const double v = (double)row[kcol<TS>(t, lk)];
       a[t] = in ? v : 0.0;
     }
   }
@@ -553,14 +552,14 @@ __device__ __forceinline__ void load_arow(double (&a)[16], const TS* __restrict_
 // D = A W for a 16-row group, W upper triangular (zeros below its diagonal
 // are skipped: tile q's K range stops at column 16 q + 15).  Accumulator
 // register r of tile q holds D[lk + 4 r][16 q + lr].
-template <typename TS, bool V16>
+template <typename TS>
 __device__ __forceinline__ void group_times_upper(const double (&a)[16], const double (*Ws)[kNb + 1], int lr, int lk,
                                                   v4d (&acc)[4]) {
 #pragma unroll
   for (int q = 0; q < 4; ++q) acc[q] = v4d{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
   for (int t = 0; t < 16; ++t) {
-    const int kk = kcol<TS, V16>(t, lk);
+    const int kk = kcol<TS>(t, lk);
 #pragma unroll
     for (int q = 0; q < 4; ++q)
       if (t < 4 * (q + 1)) acc[q] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t], Ws[kk][16 * q + lr], acc[q], 0, 0, 0);
@@ -587,7 +586,7 @@ __global__ void __launch_bounds__(256) k_cq_apply(TS* __restrict__ P, int64_t ld
   for (int e = t; e < kNb * kNb; e += 256) Ws[e / kNb][e % kNb] = W[e];
   __syncthreads();
   v4d acc[4];
-  group_times_upper<TS, V16>(a, Ws, lr, lk, acc);
+  group_times_upper<TS>(a, Ws, lr, lk, acc);
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int64_t row = rbase + lk + 4 * r;
@@ -632,7 +631,7 @@ __global__ void __launch_bounds__(256) k_cq_apply_gram(TS* __restrict__ P, int64
   for (int grp = 0; grp < NG; ++grp) {
     const int64_t rbase = (int64_t)blockIdx.x * (64 * NG) + 16 * NG * w + 16 * grp;
     v4d acc[4];
-    group_times_upper<TS, V16>(ag[grp], Ws, lr, lk, acc);
+    group_times_upper<TS>(ag[grp], Ws, lr, lk, acc);
     if constexpr (sizeof(TS) < sizeof(double)) {
       // the Gram below is of the rows as stored
 #pragma unroll
@@ -680,30 +679,6 @@ __global__ void __launch_bounds__(256) k_cq_apply_gram(TS* __restrict__ P, int64
   }
 }
 
-// After the unblocked kernel factored Q1 (status 2): its R' times R1 (upper
-// triangular products, terms in order), written back into the panel's top rows.
-template <typename TS>
-__global__ void __launch_bounds__(256) k_cq_fix(TS* __restrict__ P, int64_t ld, const double* __restrict__ Rc,
-                                                const int* __restrict__ status) {
-  if (*status != 2) return;
-  __shared__ double A[kNb][kNb + 1];
-  __shared__ double B[kNb][kNb + 1];
-  const int t = threadIdx.x;
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int r = e / kNb, c = e % kNb;
-    A[r][c] = c >= r ? (double)P[(int64_t)r * ld + c] : 0.0;
-    B[r][c] = Rc[e];
-  }
-  __syncthreads();
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int r = e / kNb, c = e % kNb;
-    if (c < r) continue;
-    double sacc = 0.0;
-    for (int k = r; k <= c; ++k) sacc = fma(A[r][k], B[k][c], sacc);
-    P[(int64_t)r * ld + c] = (TS)sacc;
-  }
-}
-
 }  // namespace
 
 // Partial Grams of an M-row panel.
@@ -720,8 +695,8 @@ int64_t cholqr_workspace_doubles(int64_t M) {
 // (M >= 64 rows, stored as TS, all arithmetic in float64); ws holds
 // cholqr_workspace_doubles(M) doubles.  A pass whose Cholesky pivot ratio falls
 // below min_ratio1 (first pass) or min_ratio2 (second) sets the status.  The
-// caller then launches the unblocked kernel gated on *status != 0, and
-// cholqr_fix.
+// caller then launches the unblocked kernel gated on *status != 0, with R1
+// (cholqr_r1).
 template <typename TS>
 static rfmls_status cholqr_panel(rfmls_handle* h, TS* P, int64_t ld, int64_t M, TS* tau, double* ws, int* status,
                                  double min_ratio1, double min_ratio2) {
@@ -783,19 +758,8 @@ rfmls_status run_cholqr_panel(rfmls_handle* h, float* P, int64_t ld, int64_t M, 
   return cholqr_panel<float>(h, P, ld, M, tau, ws, status, min_ratio1, min_ratio2);
 }
 
-// Status 2 only: the panel's R (from the unblocked kernel, on Q1) times R1.
-template <typename TS>
-static rfmls_status cholqr_fix_t(rfmls_handle* h, TS* P, int64_t ld, int64_t M, const double* ws, const int* status) {
-  const double* Rc = ws + (cholqr_workspace_doubles(M) - 3 * kNb * kNb - 64) + 2 * kNb * kNb;
-  hipLaunchKernelGGL(k_cq_fix<TS>, dim3(1), dim3(256), 0, h->stream, P, ld, Rc, status);
-  RFMLS_HIP(h, hipGetLastError());
-  return RFMLS_OK;
-}
-rfmls_status cholqr_fix(rfmls_handle* h, double* P, int64_t ld, int64_t M, const double* ws, const int* status) {
-  return cholqr_fix_t<double>(h, P, ld, M, ws, status);
-}
-rfmls_status cholqr_fix(rfmls_handle* h, float* P, int64_t ld, int64_t M, const double* ws, const int* status) {
-  return cholqr_fix_t<float>(h, P, ld, M, ws, status);
+const double* cholqr_r1(const double* ws, int64_t M) {
+  return ws + (cholqr_workspace_doubles(M) - 3 * kNb * kNb - 64) + 2 * kNb * kNb;
 }
 
 }  // namespace rfmls

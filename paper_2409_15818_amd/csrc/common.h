@@ -315,8 +315,8 @@ rfmls_status run_cholqr_panel(rfmls_handle* h, double* P, int64_t ld, int64_t M,
                               int* status, double min_ratio1, double min_ratio2);
 rfmls_status run_cholqr_panel(rfmls_handle* h, float* P, int64_t ld, int64_t M, float* tau, double* ws, int* status,
                               double min_ratio1, double min_ratio2);
-rfmls_status cholqr_fix(rfmls_handle* h, double* P, int64_t ld, int64_t M, const double* ws, const int* status);
-rfmls_status cholqr_fix(rfmls_handle* h, float* P, int64_t ld, int64_t M, const double* ws, const int* status);
+// R1 (64 x 64 row-major, zeros below the diagonal) of run_cholqr_panel's workspace
+const double* cholqr_r1(const double* ws, int64_t M);
 rfmls_status launch_hash_sign(rfmls_handle* h, int64_t m, int64_t s, uint64_t seed, int32_t* hash,
                               int8_t* sign);
 rfmls_status run_sketch(rfmls_handle* h, const rfmls_csr* A, int64_t s, const int32_t* hash,

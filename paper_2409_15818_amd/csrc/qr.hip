@@ -32,10 +32,12 @@ namespace rfmls {
 namespace {
 
 constexpr int kMaxNb = 64;
-// CholeskyQR2 panels: at least this many rows (shorter panels are cheap for
-// the unblocked kernel), and the first Cholesky's pivot ratio below which a
-// panel falls back to it (scaled panel condition near u^{-1/2})
-constexpr int64_t kCholqrMinRows = 1024;
+// CholeskyQR2 panels: at least this many rows, and the first Cholesky's pivot ratio
+// below which a panel falls back to the unblocked kernel (scaled panel condition
+// near u^{-1/2}).  The unblocked kernel exchanges sums between workgroups for every
+// column, 190 to 230 us a panel at 128 to 1,024 rows, CholeskyQR2's passes and
+// factorisations 120 us (2x2-box solve 3.0 -> 2.4 ms against a limit of 1,024 rows).
+constexpr int64_t kCholqrMinRows = 128;
 constexpr double kCholqrMinPivot = 1e-7;
 
 // Cross-block exchange of the panel kernel.  Every value crosses blocks in a
@@ -143,7 +145,8 @@ __host__ __device__ constexpr int64_t ll_words(int64_t G) { return 2 * (2 * kMax
 template <typename T, int Q>
 __global__ void __launch_bounds__(kPanelThreads)
     k_qr_panel(T* __restrict__ P, int64_t ld, int64_t M, int nb, int rpw, T* __restrict__ tau,
-               uint64_t* __restrict__ ll, int* __restrict__ err, unsigned tag0, const int* __restrict__ run_if) {
+               uint64_t* __restrict__ ll, int* __restrict__ err, unsigned tag0, const int* __restrict__ run_if,
+               const double* __restrict__ R1) {
   static_assert(kPanelGroups * Q >= kMaxNb, "block 0 must hold the panel's top rows");
   // gated launch (after a CholeskyQR2 attempt): every block reads the same
   // flag and leaves before any exchange when the panel is already factored
@@ -305,6 +308,25 @@ __global__ void __launch_bounds__(kPanelThreads)
   for (int q = 0; q < Q; ++q, pw_row += rstep) {
     const int li = rg + kPanelGroups * q;
     if (li < nr && c < nb) *pw_row = a[q];
+  }
+  // after a failed second Cholesky the panel was Q1: its R times R1 (64 x 64 upper
+  // triangular, terms in order), by the workgroup that holds the top rows
+  if (run_if && *run_if == 2 && top) {
+    __syncthreads();
+    double o[kMaxNb / kPanelGroups];
+#pragma unroll
+    for (int q = 0; q < kMaxNb / kPanelGroups; ++q) {
+      const int r = rg + kPanelGroups * q;
+      double s = 0.0;
+      for (int k = r; k <= c; ++k) s = fma((double)P[(int64_t)r * ld + k], R1[k * kMaxNb + c], s);
+      o[q] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kMaxNb / kPanelGroups; ++q) {
+      const int r = rg + kPanelGroups * q;
+      if (c >= r) P[(int64_t)r * ld + c] = (T)o[q];
+    }
   }
 }
 
@@ -797,6 +819,7 @@ rfmls_status qr_block_panels(rfmls_handle* h, const RowCounts& rows, int64_t k0,
     int rpw_i = (int)rpw;
     unsigned tag0 = (unsigned)p0;
     const int* run_if = nullptr;
+    const double* r1 = nullptr;
     // Householder on an M x jb panel: sum_j 4 (M - j)(jb - j) flops; panel
     // read and written once (the method's work, whichever way it is factored)
     const double pf = 4.0 * (double)M * jb * (jb + 1) / 2.0;
@@ -808,9 +831,11 @@ rfmls_status qr_block_panels(rfmls_handle* h, const RowCounts& rows, int64_t k0,
       const double thr2 = h->qr_panel == 3 ? 2.0 : kCholqrMinPivot;
       RFMLS_CHECK(run_cholqr_panel(h, P, ld, M, tau_p, cq_ws, cq_status, thr1, thr2));
       run_if = cq_status;
+      r1 = cholqr_r1(cq_ws, M);
     }
     void* args[] = {(void*)&P,     (void*)&ld, (void*)&M,            (void*)&jb,   (void*)&rpw_i,
-                    (void*)&tau_p, (void*)&ll, (void*)&h->dev_flags, (void*)&tag0, (void*)&run_if};
+                    (void*)&tau_p, (void*)&ll, (void*)&h->dev_flags, (void*)&tag0, (void*)&run_if,
+                    (void*)&r1};
     const void* fn = sh.fn;
     {
       Trace tr(h, run_if ? "qr_panel_fallback" : "qr_panel", run_if ? 0.0 : 2.0 * sizeof(T) * (double)M * jb,
@@ -825,7 +850,6 @@ rfmls_status qr_block_panels(rfmls_handle* h, const RowCounts& rows, int64_t k0,
       else
         RFMLS_HIP(h, hipLaunchCooperativeKernel(fn, dim3((unsigned)G), dim3(kPanelThreads), args, 0, st));
     }
-    if (run_if) RFMLS_CHECK(cholqr_fix(h, P, ld, M, cq_ws, cq_status));
     const int64_t rem = k0 + bw - (p0 + jb);
     if (rem <= 0) continue;
     const int64_t ncols = jb + rem;

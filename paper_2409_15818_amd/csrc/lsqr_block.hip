@@ -11,7 +11,11 @@
 //                  on the matrix cores
 //   Q = A^T U      the same with the transpose
 //   V = X^T Q - V b
-// Vectors are interleaved row-major blocks (element (i, c) at i * 32 + c).
+// Vectors are interleaved row-major blocks (element (i, c) at i * 32 + c).  As in
+// the single-column loop, u and v are kept unnormalised (beta u, alpha v): the next
+// product divides by the norm (BlkScale), and the update kernel's workgroups form the
+// rotation themselves, so that no pass only scales a block and no launch only
+// computes scalars.
 // A column that has stopped keeps its y and x; the host polls one
 // "all columns done" flag every few iterations.
 #include <algorithm>
@@ -30,21 +34,127 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kSpmmMaxBlocks = 2048;  // capacity of the per-column partial-sum buffers
 // Producers of per-column partial sums use at most these many blocks (grid-
-// stride loops), and the single-block kernels that fold the partials into the
-// column scalars use 1024 threads (32 columns x 32 slices).
+// stride loops).
 constexpr int kSpmmBlocks = 512;
 constexpr int kRowBlocks = 1024;  // 8-row blocks: enough loads in flight for the row-wise passes
-constexpr int kRedThreads = 1024;
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 struct BlockState {
   LsqrDev col[kBlk];
-  int all_done;
+  int all_done;  // (in the uncommitted state: whether it holds an iteration)
   int pad[15];
 };
 
 __device__ __forceinline__ bool all_done(const BlockState* st) { return st->all_done != 0; }
+__device__ __forceinline__ double inv_or_0(double x) { return x > 0.0 ? 1.0 / x : 0.0; }
+
+constexpr int kStride = (int)(sizeof(LsqrDev) / sizeof(double));  // between columns' states, in doubles
+static_assert(sizeof(LsqrDev) % sizeof(double) == 0, "LsqrDev must be a whole number of doubles");
+
+// Per-column sums of squares: producers leave partials sq[block][32], k_blk_presum
+// folds them into kPre rows, and every consumer adds those itself.
+constexpr int kPre = 32;
+__device__ __forceinline__ double blk_total(const double* __restrict__ pre, int c) {
+  double v[kPre];
+#pragma unroll
+  for (int z = 0; z < kPre; ++z) v[z] = pre[z * kBlk + c];
+#pragma unroll
+  for (int o = kPre / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int z = 0; z < o; ++z) v[z] += v[z + o];
+  return v[0];
+}
+
+// Scalars of column c in out = s acc - c prev; the fields as LazyScale's (common.h),
+// each pointer at column 0's value, columns kStride apart; pre: the folded sums of
+// the block just multiplied, whose norm one thread per column (writer) stores in
+// norm while the column is active.
+struct BlkScale {
+  double s = 1.0, c = 0.0;
+  const double* sdiv = nullptr;
+  const double *cnum = nullptr, *cden = nullptr;
+  const double* pre = nullptr;
+  double* norm = nullptr;
+};
+__device__ __forceinline__ void blk_scale(const BlkScale& B, int c, bool writer, double* s, double* cf) {
+  *s = B.s;
+  *cf = B.c;
+  if (B.pre) {
+    const double nu = sqrt(blk_total(B.pre, c));
+    if (writer && B.norm) B.norm[c * kStride] = nu;
+    *s *= inv_or_0(nu);
+    if (B.cden) *cf *= nu * inv_or_0(B.cden[c * kStride]);
+  } else {
+    if (B.sdiv) *s *= inv_or_0(B.sdiv[c * kStride]);
+    if (B.cnum) *cf *= B.cnum[c * kStride] * inv_or_0(B.cden[c * kStride]);
+  }
+}
+
+// Takes the state an iteration left in next into st, with the sums of its y and w
+// and the stopping tests, by one workgroup of kThreads (commit_state of the
+// single-column loop, per column).
+struct BlkCommit {
+  BlockState* st = nullptr;
+  BlockState* next = nullptr;
+  const double *ysq = nullptr, *wsq = nullptr;
+  int n = 0;
+  int consistent = 0;
+};
+__device__ void all_done_update(BlockState* st) {
+  int all = 1;
+  for (int c = 0; c < kBlk; ++c) all &= st->col[c].done != 0;
+  st->all_done = all;
+}
+__device__ void commit_block(const BlkCommit& cm, double (*red)[kBlk]) {
+  if (!cm.next->all_done) return;  // uniform
+  const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
+  constexpr int kR = kThreads / kBlk;
+  double y2 = 0.0, w2 = 0.0;
+#pragma unroll 4
+  for (int b = rsub; b < cm.n; b += kR) {
+    y2 += cm.ysq[b * kBlk + c];
+    w2 += cm.wsq[b * kBlk + c];
+  }
+  red[rsub][c] = y2;
+  red[kR + rsub][c] = w2;
+  __syncthreads();
+  if (rsub == 0) {
+    y2 = w2 = 0.0;
+    for (int q = 0; q < kR; ++q) {
+      y2 += red[q][c];
+      w2 += red[kR + q][c];
+    }
+    LsqrDev s = cm.next->col[c];
+    if (s.fresh) {
+      s.fresh = 0;
+      if (!s.done) {
+        s.ynorm = sqrt(y2);
+        s.w2 = w2;
+        const double anorm = sqrt(s.anorm2);
+        const double rtol = cm.consistent ? s.btol * s.bnorm : s.btol * s.bnorm + s.atol * anorm * s.ynorm;
+        int istop = 0;
+        if (s.normr <= rtol) istop = 1;
+        else if (s.pending) istop = s.pending;
+        else if (s.itn >= s.itmax) istop = 7;
+        if (istop) {
+          s.istop = istop;
+          s.done = 1;
+        }
+      }
+      cm.st->col[c] = s;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    cm.next->all_done = 0;
+    all_done_update(cm.st);
+  }
+}
+__global__ void __launch_bounds__(kThreads) k_blk_commit(BlkCommit cm) {
+  __shared__ double red[2 * kThreads / kBlk][kBlk];
+  commit_block(cm, red);
+}
 
 // ---------------------------------------------------------------------------
 // Triangular products with 64 x 32 blocks on the matrix cores.
@@ -62,11 +172,18 @@ template <typename TS>
 __global__ void __launch_bounds__(kThreads)
     k_trmm_part(const TS* __restrict__ Xpk, int64_t nt, int64_t n, int full, const int2* __restrict__ tab,
                 int C, int maxk, const double* __restrict__ V, double* __restrict__ part,
-                const BlockState* __restrict__ st) {
-  if (st && all_done(st)) return;
+                const BlockState* __restrict__ st, BlkCommit cm) {
+  // the last workgroup commits the iteration before; the others use nothing of the
+  // state but the stop word, whose early or late setting changes no result
+  const bool committing = cm.st && blockIdx.x == gridDim.x - 1;
+  if (!committing && st && all_done(st)) return;
   constexpr int kPer = kTile * kTile / kThreads;  // 16 X elements per thread per tile
   __shared__ TS Xs[kTile][kTile + 1];
   __shared__ double Vs[kTile][kBlk + 1];
+  if (committing) {
+    commit_block(cm, (double (*)[kBlk])&Vs[0][0]);
+    return;
+  }
   const int2 e = tab[blockIdx.x];
   const int64_t I = e.x;
   const int k = e.y;
@@ -127,11 +244,18 @@ template <typename TS>
 __global__ void __launch_bounds__(kThreads)
     k_trmmT_part(const TS* __restrict__ Xpk, int64_t nt, int64_t n, int full, const int2* __restrict__ tab,
                  int C, int maxk, const double* __restrict__ Qv, double* __restrict__ part,
-                 const BlockState* __restrict__ st) {
-  if (st && all_done(st)) return;
+                 const BlockState* __restrict__ st, BlkCommit cm) {
+  // the last workgroup commits the iteration before; the others use nothing of the
+  // state but the stop word, whose early or late setting changes no result
+  const bool committing = cm.st && blockIdx.x == gridDim.x - 1;
+  if (!committing && st && all_done(st)) return;
   constexpr int kPer = kTile * kTile / kThreads;
   __shared__ TS Xs[kTile][kTile + 1];
   __shared__ double Qs[kTile][kBlk + 1];
+  if (committing) {
+    commit_block(cm, (double (*)[kBlk])&Qs[0][0]);
+    return;
+  }
   const int2 e = tab[blockIdx.x];
   const int64_t J = e.x;
   const int k = e.y;
@@ -187,20 +311,19 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// out[i][c] = sum_k part[...][i][c] - coef_c prev[i][c]; per-column partial sums of squares.
-// coef_c = hcoef * coef[c * cstride] (coef may be null).  Thread (i, c) with c = tid % 32.
+// out[i][c] = s_c sum_k part[...][i][c] - coef_c prev[i][c]; per-column partial sums of
+// squares.  Thread (i, c) with c = tid % 32.
 __global__ void __launch_bounds__(kThreads)
     k_blk_tri_reduce(const double* __restrict__ part, int64_t nt, int64_t n, int full, int C, int maxk,
-                     int trans, double hcoef, const double* __restrict__ coef, int cstride,
-                     const double* prev, double* out, double* __restrict__ sq,
+                     int trans, BlkScale sc, const double* prev, double* out, double* __restrict__ sq,
                      const BlockState* __restrict__ st) {
   if (st && all_done(st)) return;
   __shared__ double red[kThreads / kBlk][kBlk];
   const int c = threadIdx.x % kBlk;
   const int rsub = threadIdx.x / kBlk;
-  double cf = hcoef;
-  if (coef) cf *= coef[c * cstride];
   const bool act = !st || !st->col[c].done;
+  double s1, cf;
+  blk_scale(sc, c, blockIdx.x == 0 && rsub == 0 && act, &s1, &cf);
   double ss = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * (kThreads / kBlk) + rsub; i < n;
        i += (int64_t)gridDim.x * (kThreads / kBlk)) {
@@ -219,6 +342,7 @@ __global__ void __launch_bounds__(kThreads)
       for (int q = 0; q < 8; ++q) s += v[q];
     }
     for (; kq < nk; ++kq) s += pp[kq * kTile * kBlk];
+    s *= s1;
     if (prev && cf != 0.0) s -= cf * prev[i * kBlk + c];
     if (act) out[i * kBlk + c] = s;
     ss += s * s;
@@ -265,7 +389,7 @@ __device__ __forceinline__ void spmm_split_range(const int64_t* __restrict__ rp,
 }
 
 // CSR SpMM on the matrix cores:
-//   out[row][c] = sA (M Xin)[row][c] - coef_c prev[row][c],  c < 32,
+//   out[row][c] = s_c (M Xin)[row][c] - coef_c prev[row][c],  c < 32,
 // plus per-column partial sums of squares of out.  Rows go in groups of
 // kSpmmGroup (64), wavefront w of a workgroup rows 16 w .. 16 w + 15; a group's
 // (ascending) column indices are walked in windows of W input rows, each
@@ -391,8 +515,8 @@ __global__ void __launch_bounds__(kThreads)
 template <int W>
 __global__ void __launch_bounds__(kThreads)
     k_spmm(const int32_t* __restrict__ col, const double* __restrict__ val, int64_t rows, int64_t ncols,
-           const double* __restrict__ Xin, double sA, double hcoef, const double* __restrict__ coef, int cstride,
-           const double* prev, double* out, double* __restrict__ sq, const BlockState* __restrict__ st, int nsplit,
+           const double* __restrict__ Xin, BlkScale sc, const double* prev, double* out, double* __restrict__ sq,
+           const BlockState* __restrict__ st, int nsplit,
            double* __restrict__ part, const int64_t* __restrict__ wptr, const int32_t* __restrict__ wstart,
            const int64_t* __restrict__ wdesc) {
   static_assert(W % 32 == 0 && W <= 128, "window");
@@ -404,13 +528,13 @@ __global__ void __launch_bounds__(kThreads)
   const int lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  double cf[2];
+  double sA[2], cf[2];
   bool act[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int c = 16 * q + lr;
-    cf[q] = coef ? hcoef * coef[c * cstride] : hcoef;
     act[q] = !st || !st->col[c].done;
+    if (nsplit == 1) blk_scale(sc, c, blockIdx.x == 0 && w == 0 && lk == 0 && act[q], &sA[q], &cf[q]);
   }
   double ss[2] = {0.0, 0.0};
   // Window data in registers: the input rows [w0, w0 + W) (coalesced, 32
@@ -500,7 +624,7 @@ __global__ void __launch_bounds__(kThreads)
         const int64_t row = r0 + 16 * w + lk + 4 * r;
         const int c = 16 * q + lr;
         if (row < rows) {
-          double o = sA * acc[q][r];
+          double o = sA[q] * acc[q][r];
           if (prev && cf[q] != 0.0) o -= cf[q] * prev[row * kBlk + c];
           if (act[q]) out[row * kBlk + c] = o;
           ss[q] += o * o;
@@ -520,22 +644,22 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// out[row][c] = sA sum_z part[z][row][c] (z in order) - cf prev[row][c] for the
+// out[row][c] = s_c sum_z part[z][row][c] (z in order) - cf_c prev[row][c] for the
 // rows of a split SpMM; per-column sums of squares per block as k_spmm's.
 __global__ void __launch_bounds__(kThreads)
-    k_spmm_merge(const double* __restrict__ part, int nsplit, int64_t rows, double sA, double hcoef,
-                 const double* __restrict__ coef, int cstride, const double* prev, double* out,
-                 double* __restrict__ sq, const BlockState* __restrict__ st) {
+    k_spmm_merge(const double* __restrict__ part, int nsplit, int64_t rows, BlkScale sc, const double* prev,
+                 double* out, double* __restrict__ sq, const BlockState* __restrict__ st) {
   if (st && all_done(st)) return;
   __shared__ double red[kThreads / kBlk][kBlk];
   const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
-  double cf = hcoef;
-  if (coef) cf *= coef[c * cstride];
   const bool act = !st || !st->col[c].done;
+  double sA, cf;
+  blk_scale(sc, c, blockIdx.x == 0 && rsub == 0 && act, &sA, &cf);
   double ss = 0.0;
   for (int64_t row = (int64_t)blockIdx.x * (kThreads / kBlk) + rsub; row < rows;
        row += (int64_t)gridDim.x * (kThreads / kBlk)) {
     double a = 0.0;
+#pragma unroll 8
     for (int z = 0; z < nsplit; ++z) a += part[((int64_t)z * rows + row) * kBlk + c];
     double o = sA * a;
     if (prev && cf != 0.0) o -= cf * prev[row * kBlk + c];
@@ -715,8 +839,7 @@ __device__ __forceinline__ void run_piece_product(const RunMat& M, int64_t row0,
 // only which workgroup is which slot; a slot's pieces, their order and its
 // partial sums are the same.
 __global__ void __launch_bounds__(kThreads, 2)
-    k_spmm_runs(RunMat M, int last_first, const double* __restrict__ Xin, double sA, double hcoef,
-                const double* __restrict__ coef, int cstride, const double* prev, double* out,
+    k_spmm_runs(RunMat M, int last_first, const double* __restrict__ Xin, BlkScale sc, const double* prev, double* out,
                 double* __restrict__ sq, const BlockState* __restrict__ st, double* __restrict__ part) {
   if (st && all_done(st)) return;
   __shared__ double buf[4][4][4][64];  // wavefront, row group, register, lane
@@ -724,13 +847,13 @@ __global__ void __launch_bounds__(kThreads, 2)
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lr = lane & 15, lk = lane >> 4;
-  double cf[2];
+  double sA[2], cf[2];
   bool act[2];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int c = 2 * lr + q;
-    cf[q] = coef ? hcoef * coef[c * cstride] : hcoef;
     act[q] = !st || !st->col[c].done;
+    if (M.nsplit == 1) blk_scale(sc, c, blockIdx.x == 0 && w == 0 && lk == 0 && act[q], &sA[q], &cf[q]);
   }
   double ss[2] = {0.0, 0.0};
   const int64_t items = M.npieces * M.nsplit;
@@ -778,7 +901,7 @@ __global__ void __launch_bounds__(kThreads, 2)
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         const int c = 2 * lr + q;
-        double o = sA * tot[q][r];
+        double o = sA[q] * tot[q][r];
         if (prev && cf[q] != 0.0) o -= cf[q] * prev[row * kBlk + c];
         if (act[q]) out[row * kBlk + c] = o;
         ss[q] += o * o;
@@ -797,46 +920,27 @@ __global__ void __launch_bounds__(kThreads, 2)
   }
 }
 
-// Per-column norms from partial sums: nrm_c = sqrt(sum_b sq[b][c]) -> state field
-// (field = 0: beta, 1: alpha).  Columns already stopped keep their state.
-__global__ void __launch_bounds__(kRedThreads) k_blk_norms(const double* __restrict__ sq, int nsq,
-                                                        BlockState* st, int field, int force) {
-  if (!force && all_done(st)) return;
-  __shared__ double red[kRedThreads / kBlk][kBlk];
+// pre[z][c] = sum of sq[b][c] over b = z, z + kPre, ... < nsq (workgroup z; fixed order)
+__global__ void __launch_bounds__(kThreads) k_blk_presum(const double* __restrict__ sq, int nsq,
+                                                         double* __restrict__ pre,
+                                                         const BlockState* __restrict__ st) {
+  if (st && all_done(st)) return;
+  __shared__ double red[kThreads / kBlk][kBlk];
   const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
   double t = 0.0;
-  for (int b = rsub; b < nsq; b += kRedThreads / kBlk) t += sq[b * kBlk + c];
+#pragma unroll 4
+  for (int b = blockIdx.x + kPre * rsub; b < nsq; b += kPre * (kThreads / kBlk)) t += sq[b * kBlk + c];
   red[rsub][c] = t;
   __syncthreads();
   if (rsub == 0) {
     double s = 0.0;
-    for (int q = 0; q < kRedThreads / kBlk; ++q) s += red[q][c];
-    LsqrDev& d = st->col[c];
-    if (force || !d.done) {
-      if (field == 0) d.beta = sqrt(s);
-      else d.alpha = sqrt(s);
-    }
+    for (int q = 0; q < kThreads / kBlk; ++q) s += red[q][c];
+    pre[blockIdx.x * kBlk + c] = s;
   }
 }
-
-// vec[i][c] *= 1 / state_c (beta or alpha) for active columns
-__global__ void k_blk_scale(double* vec, int64_t len, const BlockState* __restrict__ st, int field,
-                            int force) {
-  if (!force && all_done(st)) return;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < len * kBlk;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const LsqrDev& d = st->col[e % kBlk];
-    if (!force && d.done) continue;
-    const double nv = field == 0 ? d.beta : d.alpha;
-    vec[e] = nv > 0.0 ? vec[e] / nv : 0.0;
-  }
-}
-
-// out = x (copy) for active columns
-__global__ void k_blk_copy(const double* x, double* out, int64_t len) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < len * kBlk;
-       e += (int64_t)gridDim.x * blockDim.x)
-    out[e] = x[e];
+// out[c] = sqrt of the folded sums
+__global__ void k_blk_norm_out(const double* __restrict__ pre, double* __restrict__ out) {
+  if (threadIdx.x < kBlk) out[threadIdx.x] = sqrt(blk_total(pre, threadIdx.x));
 }
 
 __global__ void k_blk_fill(double* p, int64_t len, double v) {
@@ -845,15 +949,18 @@ __global__ void k_blk_fill(double* p, int64_t len, double v) {
     p[e] = v;
 }
 
-// per-column sums of squares of a len x 32 block
+// per-column sums of squares of a len x 32 block, which is also copied to out when given
 __global__ void __launch_bounds__(kThreads) k_blk_sumsq(const double* __restrict__ x, int64_t len,
-                                                        double* __restrict__ sq) {
+                                                        double* __restrict__ out, double* __restrict__ sq) {
   __shared__ double red[kThreads / kBlk][kBlk];
   const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
   double t = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * (kThreads / kBlk) + rsub; i < len;
-       i += (int64_t)gridDim.x * (kThreads / kBlk))
-    t += x[i * kBlk + c] * x[i * kBlk + c];
+       i += (int64_t)gridDim.x * (kThreads / kBlk)) {
+    const double v = x[i * kBlk + c];
+    if (out) out[i * kBlk + c] = v;
+    t += v * v;
+  }
   red[rsub][c] = t;
   __syncthreads();
   if (rsub == 0) {
@@ -863,25 +970,18 @@ __global__ void __launch_bounds__(kThreads) k_blk_sumsq(const double* __restrict
   }
 }
 
-__device__ void all_done_update(BlockState* st) {
-  int all = 1;
-  for (int c = 0; c < kBlk; ++c) all &= st->col[c].done != 0;
-  st->all_done = all;
-}
-
-__global__ void k_blk_start(BlockState* st, double atol, double btol, double conlim, int64_t itmax) {
+// beta_1 from the folded sums: set up the states.
+__global__ void k_blk_begin(BlockState* st, BlockState* next, const double* __restrict__ pre, double atol, double btol,
+                            double conlim, int64_t itmax) {
   const int c = threadIdx.x;
   if (c < kBlk) {
-    LsqrDev& d = st->col[c];
-    const double beta = d.beta;
-    d = LsqrDev{};
-    d.beta = beta;
+    const double beta = sqrt(blk_total(pre, c));
+    LsqrDev d{};
     d.atol = atol;
     d.btol = btol;
     d.conlim = conlim;
     d.itmax = itmax;
-    d.bnorm = beta;
-    d.phibar = beta;
+    d.beta = d.bnorm = d.phibar = beta;
     d.istop = 7;
     if (!isfinite(beta)) {  // a non-finite right-hand side: breakdown, not "x = 0 is exact"
       d.istop = -3;
@@ -890,24 +990,29 @@ __global__ void k_blk_start(BlockState* st, double atol, double btol, double con
       d.istop = 0;
       d.done = 1;
     }
+    st->col[c] = d;
+    next->col[c].fresh = 0;
   }
+  if (c == 0) next->all_done = 0;
   __syncthreads();
   if (c == 0) all_done_update(st);
 }
 
-__global__ void k_blk_start2(BlockState* st) {
+// alpha_1 from the folded sums.
+__global__ void k_blk_begin2(BlockState* st, const double* __restrict__ pre) {
   const int c = threadIdx.x;
   if (c < kBlk) {
     LsqrDev& d = st->col[c];
     if (!d.done) {
-      d.rhobar = d.alpha;
-      d.alpha_prev = d.alpha;
+      const double alpha = sqrt(blk_total(pre, c));
+      d.alpha = d.alpha_prev = d.rhobar = alpha;
       d.normr = d.beta;
-      d.normar = d.alpha * d.beta;
-      if (!isfinite(d.alpha)) {
+      d.normar = alpha * d.beta;
+      d.w2 = 1.0;  // w_1 = v_1
+      if (!isfinite(alpha)) {
         d.istop = -3;
         d.done = 1;
-      } else if (!(d.alpha > 0.0)) {
+      } else if (!(alpha > 0.0)) {
         d.istop = 0;
         d.done = 1;
       }
@@ -916,80 +1021,113 @@ __global__ void k_blk_start2(BlockState* st) {
   __syncthreads();
   if (c == 0) all_done_update(st);
 }
-
-// plane rotation per active column (same arithmetic as the single-column kernel)
-__global__ void __launch_bounds__(kRedThreads) k_blk_rotate(BlockState* st, const double* __restrict__ wsq,
-                                                         int nsq) {
-  if (all_done(st)) return;
-  __shared__ double red[kRedThreads / kBlk][kBlk];
-  const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
-  double t = 0.0;
-  for (int b = rsub; b < nsq; b += kRedThreads / kBlk) t += wsq[b * kBlk + c];
-  red[rsub][c] = t;
-  __syncthreads();
-  if (rsub != 0) return;
-  double w2 = 0.0;
-  for (int q = 0; q < kRedThreads / kBlk; ++q) w2 += red[q][c];
-  LsqrDev& d = st->col[c];
-  if (d.done) {
-    d.phi_rho = 0.0;
-    d.theta_rho = 0.0;
-    return;
-  }
-  const double alpha = d.alpha, beta = d.beta;
-  d.itn += 1;
-  d.anorm2 += d.alpha_prev * d.alpha_prev + beta * beta;
-  const double rho = hypot(d.rhobar, beta);
-  if (!(rho > 0.0) || !isfinite(rho)) {
-    d.istop = isfinite(rho) ? 1 : -3;
-    d.done = 1;
-    d.phi_rho = 0.0;
-    d.theta_rho = 0.0;
-    return;
-  }
-  const double cs = d.rhobar / rho;
-  const double sn = beta / rho;
-  const double theta = sn * alpha;
-  d.rhobar = -cs * alpha;
-  const double phi = cs * d.phibar;
-  d.phibar = sn * d.phibar;
-  d.phi_rho = phi / rho;
-  d.theta_rho = theta / rho;
-  d.ddnorm += w2 / (rho * rho);
-  const double anorm = sqrt(d.anorm2);
-  d.acond = anorm * sqrt(d.ddnorm);
-  d.normr = d.phibar;
-  d.normar = d.phibar * alpha * fabs(cs);
-  d.pending = 0;
-  if (d.normr == 0.0 || d.normar <= d.atol * anorm * d.normr) d.pending = 2;
-  else if (d.conlim > 0.0 && d.acond >= d.conlim) d.pending = 3;
-  d.alpha_prev = alpha;
+__global__ void k_blk_w2(BlockState* st, const double* __restrict__ pre) {
+  if (threadIdx.x < kBlk) st->col[threadIdx.x].w2 = blk_total(pre, threadIdx.x);
 }
 
+// y_1 = 0 and w_1 = v^/alpha, or of the backward's shadow vector vt_1 = u^/(beta alpha),
+// also kept in vt; wsq (optional): partial sums of ||w_1||^2
 __global__ void __launch_bounds__(kThreads)
-    k_blk_update(const BlockState* __restrict__ st, const double* __restrict__ v, double* w, double* y,
-                 int64_t n, double* __restrict__ ysq, double* __restrict__ wsq) {
-  if (all_done(st)) return;
-  __shared__ double ry[kThreads / kBlk][kBlk], rw[kThreads / kBlk][kBlk];
+    k_blk_first_w(const BlockState* __restrict__ st, const double* __restrict__ v, int over_beta, double* vt, double* w,
+                  double* y, int64_t n, double* __restrict__ wsq) {
+  __shared__ double red[kThreads / kBlk][kBlk];
   const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
-  const LsqrDev& d = st->col[c];
-  const bool act = !d.done;
-  const double a = d.phi_rho, b = d.theta_rho;
-  double sy = 0.0, sw = 0.0;
+  double f = inv_or_0(st->col[c].alpha);
+  if (over_beta) f *= inv_or_0(st->col[c].beta);
+  double sw = 0.0;
   for (int64_t i = (int64_t)blockIdx.x * (kThreads / kBlk) + rsub; i < n;
        i += (int64_t)gridDim.x * (kThreads / kBlk)) {
     const int64_t e = i * kBlk + c;
-    double yi = y[e], wn = w[e];
-    if (act) {
+    const double wi = f > 0.0 ? v[e] * f : 0.0;
+    if (vt) vt[e] = wi;
+    w[e] = wi;
+    y[e] = 0.0;
+    sw += wi * wi;
+  }
+  if (!wsq) return;
+  red[rsub][c] = sw;
+  __syncthreads();
+  if (rsub == 0) {
+    double tw = 0.0;
+    for (int q = 0; q < kThreads / kBlk; ++q) tw += red[q][c];
+    wsq[blockIdx.x * kBlk + c] = tw;
+  }
+}
+
+// The rest of iteration k after alpha v^ (apre: its folded sums) and beta (in the
+// state): plane rotation, y += phi/rho w, w = v - theta/rho w and the partial sums of
+// ||y||^2 and ||w||^2, per active column (k_lsqr_step of the single-column loop;
+// vt given: the backward's shadow vector takes v's part).  Every thread forms its
+// column's scalars; the first workgroup leaves the new states in next.
+__global__ void __launch_bounds__(kThreads)
+    k_blk_step(const BlockState* __restrict__ st, BlockState* next, const double* __restrict__ apre,
+               const double* __restrict__ v, double* vt, double* w, double* y, int64_t n, double* __restrict__ ysq,
+               double* __restrict__ wsq) {
+  if (all_done(st)) return;
+  __shared__ double ry[kThreads / kBlk][kBlk], rw[kThreads / kBlk][kBlk];
+  const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
+  LsqrDev s = st->col[c];
+  const double alpha = sqrt(blk_total(apre, c));
+  const double beta = s.beta;
+  bool act = !s.done;
+  if (act) {
+    s.alpha = alpha;
+    s.itn += 1;
+    s.anorm2 += s.alpha_prev * s.alpha_prev + beta * beta;
+    const double rho = hypot(s.rhobar, beta);
+    s.pending = 0;
+    if (rho > 0.0 && isfinite(rho)) {
+      const double cs = s.rhobar / rho;
+      const double sn = beta / rho;
+      const double theta = sn * alpha;
+      s.rhobar = -cs * alpha;
+      const double phi = cs * s.phibar;
+      s.phibar = sn * s.phibar;
+      s.phi_rho = phi / rho;
+      s.theta_rho = theta / rho;
+      s.ddnorm += s.w2 / (rho * rho);
+      const double anorm = sqrt(s.anorm2);
+      s.acond = anorm * sqrt(s.ddnorm);
+      s.normr = s.phibar;
+      s.normar = s.phibar * alpha * fabs(cs);
+      if (s.normr == 0.0 || s.normar <= s.atol * anorm * s.normr) s.pending = 2;
+      else if (s.conlim > 0.0 && s.acond >= s.conlim) s.pending = 3;
+      s.alpha_prev = alpha;
+    } else {
+      s.istop = isfinite(rho) ? 1 : -3;
+      s.done = 1;
+      s.phi_rho = 0.0;
+      s.theta_rho = 0.0;
+      act = false;
+    }
+    s.fresh = 1;
+    if (blockIdx.x == 0 && rsub == 0) next->col[c] = s;
+  } else if (blockIdx.x == 0 && rsub == 0) {
+    next->col[c].fresh = 0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) next->all_done = 1;
+  const double a = s.phi_rho, b = s.theta_rho;
+  const double ia = inv_or_0(alpha), ib = inv_or_0(beta);
+  double sy = 0.0, sw = 0.0;
+  if (act)
+    for (int64_t i = (int64_t)blockIdx.x * (kThreads / kBlk) + rsub; i < n;
+         i += (int64_t)gridDim.x * (kThreads / kBlk)) {
+      const int64_t e = i * kBlk + c;
       const double wi = w[e];
-      yi = yi + a * wi;
-      wn = v[e] - b * wi;
+      const double yi = y[e] + a * wi;
+      double vi = v[e];
+      if (vt) {
+        vi = (vi * ib - beta * vt[e]) * ia;
+        vt[e] = vi;
+      } else {
+        vi *= ia;
+      }
+      const double wn = vi - b * wi;
       y[e] = yi;
       w[e] = wn;
+      sy += yi * yi;
+      sw += wn * wn;
     }
-    sy += yi * yi;
-    sw += wn * wn;
-  }
   ry[rsub][c] = sy;
   rw[rsub][c] = sw;
   __syncthreads();
@@ -1002,38 +1140,6 @@ __global__ void __launch_bounds__(kThreads)
     ysq[blockIdx.x * kBlk + c] = ty;
     wsq[blockIdx.x * kBlk + c] = tw;
   }
-}
-
-// consistent != 0: the system has an exact solution (backward pass), S1 is ||r|| <= btol ||b||
-__global__ void __launch_bounds__(kRedThreads) k_blk_check(BlockState* st, const double* __restrict__ ysq,
-                                                        int nsq, int consistent) {
-  if (all_done(st)) return;
-  __shared__ double red[kRedThreads / kBlk][kBlk];
-  const int c = threadIdx.x % kBlk, rsub = threadIdx.x / kBlk;
-  double t = 0.0;
-  for (int b = rsub; b < nsq; b += kRedThreads / kBlk) t += ysq[b * kBlk + c];
-  red[rsub][c] = t;
-  __syncthreads();
-  if (rsub == 0) {
-    double y2 = 0.0;
-    for (int q = 0; q < kRedThreads / kBlk; ++q) y2 += red[q][c];
-    LsqrDev& d = st->col[c];
-    if (!d.done) {
-      d.ynorm = sqrt(y2);
-      const double anorm = sqrt(d.anorm2);
-      int istop = 0;
-      const double rtol = consistent ? d.btol * d.bnorm : d.btol * d.bnorm + d.atol * anorm * d.ynorm;
-      if (d.normr <= rtol) istop = 1;
-      else if (d.pending) istop = d.pending;
-      else if (d.itn >= d.itmax) istop = 7;
-      if (istop) {
-        d.istop = istop;
-        d.done = 1;
-      }
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) all_done_update(st);
 }
 
 // column-major (ld) <-> interleaved block conversions
@@ -1057,21 +1163,6 @@ __global__ void k_blk_axpy(double* x, const double* __restrict__ dx, int64_t len
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < len * kBlk;
        e += (int64_t)gridDim.x * blockDim.x)
     x[e] += dx[e];
-}
-
-// out[i][c] = (x[i][c] - hb beta_c prev[i][c]) / alpha_c for active columns (0 where alpha_c <= 0);
-// force: every column (set-up, before the stop flags mean anything)
-__global__ void k_blk_recip_scale(const double* x, double hb, const double* prev, double* out,
-                                  int64_t len, const BlockState* __restrict__ st, int force) {
-  if (!force && all_done(st)) return;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < len * kBlk;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const LsqrDev& d = st->col[e % kBlk];
-    if (!force && d.done) continue;
-    double o = x[e];
-    if (prev && hb != 0.0) o -= hb * d.beta * prev[e];
-    out[e] = d.alpha > 0.0 ? o / d.alpha : 0.0;
-  }
 }
 
 // dA[e] (+)= sum_c (r[i][c] w[j][c] - lam[i][c] x[j][c]) on the pattern of A; one wavefront
@@ -1172,12 +1263,13 @@ struct BCtx {
   const rfmls_csr* AT;
   const rfmls_precond_t* P;
   hipStream_t st;
-  double *U, *V, *W, *Y, *Z, *Q, *T, *Rr, *Xb, *Bb, *DX, *Sm, *Sn;
+  double *U, *V, *W, *Y, *Z, *Q, *Rr, *Xb, *Bb, *DX;
   double *sqA, *sqB, *sqY, *sqW, *part;
+  double *preA, *preB, *hn;  // folded sums (kPre x 32), and norms read by the host
   double* spart;  // partial sums of split SpMM groups (nsplit x rows x 32)
   SpmmDesc dA, dAT;  // SpMM window descriptors of A and A^T (k_spmm_walk)
   RunMat rA{}, rAT{};  // A and A^T as pieces of dense runs (npieces 0: the windowed kernel)
-  BlockState* dst;
+  BlockState* dst;  // the states, and after them the iteration's uncommitted ones
   IterGraph* graph = nullptr;  // captured poll interval of the loop, or null: eager launches
 };
 
@@ -1185,18 +1277,33 @@ struct BCtx {
 // to itmax times, the host polling the "all columns done" word after every
 // `every` iterations; with c.graph the poll interval is captured once and replayed.
 template <class F>
-static rfmls_status run_loop(BCtx& c, int64_t itmax, int every, F&& iteration);
+static rfmls_status run_loop(BCtx& c, int64_t itmax, int every, int consistent, F&& iteration);
 
 double* state_field(BlockState* s, int which) {
   // pointer to col[0].<field>; stride between columns in doubles
   LsqrDev* d = &s->col[0];
   return which == 0 ? &d->beta : &d->alpha;
 }
-constexpr int kStride = (int)(sizeof(LsqrDev) / sizeof(double));
-static_assert(sizeof(LsqrDev) % sizeof(double) == 0, "LsqrDev must be a whole number of doubles");
+BlkCommit commit_of(const BCtx& c, int consistent) {
+  BlkCommit cm;
+  cm.st = c.dst;
+  cm.next = c.dst + 1;
+  cm.ysq = c.sqY;
+  cm.wsq = c.sqW;
+  cm.n = (int)rows_grid(c.A->n);
+  cm.consistent = consistent;
+  return cm;
+}
+// Folds a producer's nsq rows of partial sums into pre.
+rfmls_status presum(BCtx& c, const double* sq, int nsq, double* pre, const BlockState* stp) {
+  hipLaunchKernelGGL(k_blk_presum, dim3(kPre), dim3(kThreads), 0, c.st, sq, nsq, pre, stp);
+  RFMLS_HIP(c.h, hipGetLastError());
+  return RFMLS_OK;
+}
 
-rfmls_status tri_block(BCtx& c, int trans, const double* in, double* out, double hcoef,
-                       const double* coef, const double* prev, double* sq, const BlockState* stp) {
+rfmls_status tri_block(BCtx& c, int trans, const double* in, double* out, const BlkScale& sc = BlkScale(),
+                       const double* prev = nullptr, double* sq = nullptr, const BlockState* stp = nullptr,
+                       const BlkCommit& cm = BlkCommit()) {
   const rfmls_precond_t* P = c.P;
   const int64_t n = P->n, nt = P->nt;
   const int C = P->chunk;
@@ -1209,22 +1316,22 @@ rfmls_status tri_block(BCtx& c, int trans, const double* in, double* out, double
              esz * tri + 2.0 * 8.0 * kBlk * (double)n, 2.0 * tri * kBlk);
     if (!trans) {
       if (P->store == RFMLS_F64)
-        hipLaunchKernelGGL(k_trmm_part<double>, dim3((unsigned)P->ntab), dim3(kThreads), 0, c.st,
-                           (const double*)P->Xpk, nt, n, full, P->tab_row, C, maxk, in, c.part, stp);
+        hipLaunchKernelGGL(k_trmm_part<double>, dim3((unsigned)P->ntab + (cm.st ? 1u : 0u)), dim3(kThreads), 0, c.st,
+                           (const double*)P->Xpk, nt, n, full, P->tab_row, C, maxk, in, c.part, stp, cm);
       else
-        hipLaunchKernelGGL(k_trmm_part<float>, dim3((unsigned)P->ntab), dim3(kThreads), 0, c.st,
-                           (const float*)P->Xpk, nt, n, full, P->tab_row, C, maxk, in, c.part, stp);
+        hipLaunchKernelGGL(k_trmm_part<float>, dim3((unsigned)P->ntab + (cm.st ? 1u : 0u)), dim3(kThreads), 0, c.st,
+                           (const float*)P->Xpk, nt, n, full, P->tab_row, C, maxk, in, c.part, stp, cm);
     } else {
       if (P->store == RFMLS_F64)
-        hipLaunchKernelGGL(k_trmmT_part<double>, dim3((unsigned)P->ntab), dim3(kThreads), 0, c.st,
-                           (const double*)P->Xpk, nt, n, full, P->tab_col, C, maxk, in, c.part, stp);
+        hipLaunchKernelGGL(k_trmmT_part<double>, dim3((unsigned)P->ntab + (cm.st ? 1u : 0u)), dim3(kThreads), 0, c.st,
+                           (const double*)P->Xpk, nt, n, full, P->tab_col, C, maxk, in, c.part, stp, cm);
       else
-        hipLaunchKernelGGL(k_trmmT_part<float>, dim3((unsigned)P->ntab), dim3(kThreads), 0, c.st,
-                           (const float*)P->Xpk, nt, n, full, P->tab_col, C, maxk, in, c.part, stp);
+        hipLaunchKernelGGL(k_trmmT_part<float>, dim3((unsigned)P->ntab + (cm.st ? 1u : 0u)), dim3(kThreads), 0, c.st,
+                           (const float*)P->Xpk, nt, n, full, P->tab_col, C, maxk, in, c.part, stp, cm);
     }
   }
   hipLaunchKernelGGL(k_blk_tri_reduce, dim3(rows_grid(n)), dim3(kThreads), 0, c.st, (const double*)c.part,
-                     nt, n, full, C, maxk, trans, hcoef, coef, kStride, prev, out, sq, stp);
+                     nt, n, full, C, maxk, trans, sc, prev, out, sq, stp);
   RFMLS_HIP(c.h, hipGetLastError());
   return RFMLS_OK;
 }
@@ -1303,9 +1410,8 @@ static rfmls_status spmm_build_desc(BCtx& c, const rfmls_csr* M, int W, SpmmDesc
   return RFMLS_OK;
 }
 
-static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh, const double* x, double sA,
-                                double hcoef, const double* coef, const double* prev, double* out, double* sq,
-                                const BlockState* stp, int* nblk);
+static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh, const double* x, const BlkScale& sc,
+                                const double* prev, double* out, double* sq, const BlockState* stp, int* nblk);
 static const RunMat& run_mat(const BCtx& c, const rfmls_csr* M) { return M == c.A ? c.rA : c.rAT; }
 
 // Autotuner of the SpMM launch shape (window width) for M: the first time a
@@ -1330,10 +1436,10 @@ static rfmls_status spmm_tune(BCtx& c, const rfmls_csr* M, double* xin, double* 
   h->trace = false;  // the trial launches are not part of any traced step
   for (size_t k = 0; k < cands.size() && st >= 0; ++k) {
     float t[3];
-    st = spmm_launch(c, M, cands[k], xin, 1.0, 0.0, nullptr, nullptr, out, sq, nullptr, nullptr);
+    st = spmm_launch(c, M, cands[k], xin, BlkScale(), nullptr, out, sq, nullptr, nullptr);
     for (int r = 0; r < 3 && st >= 0; ++r) {
       hipEventRecord(ev[0], c.st);
-      st = spmm_launch(c, M, cands[k], xin, 1.0, 0.0, nullptr, nullptr, out, sq, nullptr, nullptr);
+      st = spmm_launch(c, M, cands[k], xin, BlkScale(), nullptr, out, sq, nullptr, nullptr);
       hipEventRecord(ev[1], c.st);
       if (hipEventSynchronize(ev[1]) != hipSuccess || hipEventElapsedTime(&t[r], ev[0], ev[1]) != hipSuccess)
         st = fail(h, RFMLS_E_HIP, "SpMM autotuner: event timing failed");
@@ -1469,8 +1575,8 @@ static rfmls_status spmm_prepare(BCtx& c) {
 // shapes the loop will use (before any capture of the loop).
 static rfmls_status spmm_tune_both(BCtx& c) {
   RFMLS_CHECK(spmm_prepare(c));
-  RFMLS_CHECK(spmm_tune(c, c.A, c.Z, c.T, c.sqA));
-  if (c.AT != c.A) RFMLS_CHECK(spmm_tune(c, c.AT, c.T, c.Sn, c.sqA));
+  RFMLS_CHECK(spmm_tune(c, c.A, c.Z, c.U, c.sqA));
+  if (c.AT != c.A) RFMLS_CHECK(spmm_tune(c, c.AT, c.U, c.Q, c.sqA));
   for (const rfmls_csr* M : {c.A, c.AT}) {
     const bool runs = run_mat(c, M).npieces > 0;
     if (runs) continue;
@@ -1482,18 +1588,17 @@ static rfmls_status spmm_tune_both(BCtx& c) {
   return RFMLS_OK;
 }
 
-rfmls_status spmm(BCtx& c, const rfmls_csr* M, const double* x, double sA, double hcoef,
-                  const double* coef, const double* prev, double* out, double* sq,
-                  const BlockState* stp, int* nblk) {
+rfmls_status spmm(BCtx& c, const rfmls_csr* M, const double* x, double* out, const BlkScale& sc = BlkScale(),
+                  const double* prev = nullptr, double* sq = nullptr, const BlockState* stp = nullptr,
+                  int* nblk = nullptr) {
   const bool runs = run_mat(c, M).npieces > 0;
   SpmmShape sh;
   if (!spmm_lookup(c.h, M, runs, &sh)) sh = spmm_shape(runs);
-  return spmm_launch(c, M, sh, x, sA, hcoef, coef, prev, out, sq, stp, nblk);
+  return spmm_launch(c, M, sh, x, sc, prev, out, sq, stp, nblk);
 }
 
-static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh, const double* x, double sA,
-                                double hcoef, const double* coef, const double* prev, double* out, double* sq,
-                                const BlockState* stp, int* nblk) {
+static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh, const double* x, const BlkScale& sc,
+                                const double* prev, double* out, double* sq, const BlockState* stp, int* nblk) {
   const RunMat& rm = run_mat(c, M);
   const bool runs = rm.npieces > 0;
   const int64_t ng = runs ? rm.npieces : (M->m + sh.group - 1) / sh.group;
@@ -1504,11 +1609,11 @@ static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh
            (runs ? 8.0 : 12.0) * (double)M->nnz + 8.0 * (double)(M->m + 1) +
                8.0 * kBlk * ((double)M->n + (double)M->m * (prev ? 2.0 : 1.0)),
            2.0 * kBlk * (double)M->nnz);
-  int kStride_v = kStride;
+  BlkScale sc_v = sc;
   double* spart = c.spart;
   if (runs) {
-    hipLaunchKernelGGL(k_spmm_runs, dim3(nb), dim3(kThreads), 0, c.st, rm, sh.last_first, x, sA, hcoef, coef, kStride,
-                       prev, out, sq, stp, spart);
+    hipLaunchKernelGGL(k_spmm_runs, dim3(nb), dim3(kThreads), 0, c.st, rm, sh.last_first, x, sc, prev, out, sq, stp,
+                       spart);
   } else {
   SpmmDesc* dsc = M == c.A ? &c.dA : &c.dAT;
   if (dsc->W != sh.win) RFMLS_CHECK(spmm_build_desc(c, M, sh.win, dsc));
@@ -1516,7 +1621,7 @@ static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh
   const int32_t* wstart = dsc->wstart;
   const int64_t* wdesc = dsc->wdesc;
   void* args[] = {(void*)&M->col, (void*)&M->val, (void*)&M->m, (void*)&M->n,
-                  (void*)&x, (void*)&sA, (void*)&hcoef, (void*)&coef, (void*)&kStride_v, (void*)&prev,
+                  (void*)&x, (void*)&sc_v, (void*)&prev,
                   (void*)&out, (void*)&sq, (void*)&stp, (void*)&nsplit, (void*)&spart, (void*)&wptr,
                   (void*)&wstart, (void*)&wdesc};
   RFMLS_HIP(c.h, hipLaunchKernel(sh.fn, dim3(nb), dim3(kThreads), args, 0, c.st));
@@ -1524,7 +1629,7 @@ static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh
   if (nsplit > 1) {
     const unsigned gm = rows_grid(M->m);
     hipLaunchKernelGGL(k_spmm_merge, dim3(gm), dim3(kThreads), 0, c.st, (const double*)spart, nsplit, M->m,
-                       sA, hcoef, coef, kStride, prev, out, sq, stp);
+                       sc, prev, out, sq, stp);
     if (nblk) *nblk = (int)gm;
   } else if (nblk) {
     *nblk = (int)nb;
@@ -1544,63 +1649,71 @@ rfmls_status poll_all(BCtx& c, int* done) {
 // One lockstep sweep for min ||A X y - rhs|| over the 32 columns of rhs (m x 32).
 rfmls_status block_sweep(BCtx& c, const double* rhs, const rfmls_opts* o, int64_t itmax) {
   const int64_t m = c.A->m, n = c.A->n;
-  const unsigned gm = grid_for(m * kBlk), gn = grid_for(n * kBlk);
+  BlockState* st = c.dst;
+  const BlockState* cst = st;
+  double *alpha = &st->col[0].alpha, *beta = &st->col[0].beta;
+  const unsigned rn = rows_grid(n);
   // beta_1 u_1 = rhs
-  hipLaunchKernelGGL(k_blk_copy, dim3(gm), dim3(kThreads), 0, c.st, rhs, c.U, m);
-  hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(m)), dim3(kThreads), 0, c.st, (const double*)c.U, m,
-                     c.sqA);
-  hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqA,
-                     (int)rows_grid(m), c.dst, 0, 1);
-  hipLaunchKernelGGL(k_blk_start, dim3(1), dim3(64), 0, c.st, c.dst, o->atol, o->btol, o->conlim, itmax);
-  hipLaunchKernelGGL(k_blk_scale, dim3(gm), dim3(kThreads), 0, c.st, c.U, m, (const BlockState*)c.dst, 0, 1);
-  hipLaunchKernelGGL(k_blk_fill, dim3(gn), dim3(kThreads), 0, c.st, c.Y, n * kBlk, 0.0);
+  hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(m)), dim3(kThreads), 0, c.st, rhs, m, c.U, c.sqA);
+  RFMLS_CHECK(presum(c, c.sqA, (int)rows_grid(m), c.preA, nullptr));
+  hipLaunchKernelGGL(k_blk_begin, dim3(1), dim3(64), 0, c.st, st, st + 1, (const double*)c.preA, o->atol, o->btol,
+                     o->conlim, itmax);
   // alpha_1 v_1 = X^T (A^T u_1)
-  RFMLS_CHECK(spmm(c, c.AT, c.U, 1.0, 0.0, nullptr, nullptr, c.Q, nullptr, nullptr, nullptr));
-  RFMLS_CHECK(tri_block(c, 1, c.Q, c.V, 0.0, nullptr, nullptr, c.sqB, nullptr));
-  hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqB,
-                     (int)rows_grid(n), c.dst, 1, 0);
-  hipLaunchKernelGGL(k_blk_scale, dim3(gn), dim3(kThreads), 0, c.st, c.V, n, (const BlockState*)c.dst, 1, 0);
-  hipLaunchKernelGGL(k_blk_start2, dim3(1), dim3(64), 0, c.st, c.dst);
-  hipLaunchKernelGGL(k_blk_copy, dim3(gn), dim3(kThreads), 0, c.st, (const double*)c.V, c.W, n);
-  hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(n)), dim3(kThreads), 0, c.st, (const double*)c.W, n,
-                     c.sqW);
+  BlkScale s1;
+  s1.sdiv = beta;
+  RFMLS_CHECK(spmm(c, c.AT, c.U, c.Q));
+  RFMLS_CHECK(tri_block(c, 1, c.Q, c.V, s1, nullptr, c.sqB));
+  RFMLS_CHECK(presum(c, c.sqB, (int)rn, c.preB, nullptr));
+  hipLaunchKernelGGL(k_blk_begin2, dim3(1), dim3(64), 0, c.st, st, (const double*)c.preB);
+  hipLaunchKernelGGL(k_blk_first_w, dim3(rn), dim3(kThreads), 0, c.st, cst, (const double*)c.V, 0, (double*)nullptr, c.W,
+                     c.Y, n, (double*)nullptr);
   RFMLS_HIP(c.h, hipGetLastError());
   const int every = o->check_every > 0 ? o->check_every : 8;
-  const BlockState* cst = c.dst;
-  return run_loop(c, itmax, every, [&]() -> rfmls_status {
-    RFMLS_CHECK(tri_block(c, 0, c.V, c.Z, 0.0, nullptr, nullptr, nullptr, cst));
+  const BlkCommit cm = commit_of(c, 0);
+  return run_loop(c, itmax, every, 0, [&]() -> rfmls_status {
+    // beta' u' = A (X v) - alpha u, with v = v^/alpha and u = u^/beta
+    BlkScale su;
+    su.sdiv = alpha;
+    su.c = 1.0;
+    su.cnum = alpha;
+    su.cden = beta;
     int nb = 0;
-    RFMLS_CHECK(spmm(c, c.A, c.Z, 1.0, 1.0, state_field(c.dst, 1), c.U, c.U, c.sqA, cst, &nb));
-    hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqA, nb, c.dst, 0, 0);
-    hipLaunchKernelGGL(k_blk_scale, dim3(gm), dim3(kThreads), 0, c.st, c.U, m, cst, 0, 0);
-    RFMLS_CHECK(spmm(c, c.AT, c.U, 1.0, 0.0, nullptr, nullptr, c.Q, nullptr, cst, nullptr));
-    RFMLS_CHECK(tri_block(c, 1, c.Q, c.V, 1.0, state_field(c.dst, 0), c.V, c.sqB, cst));
-    hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqB,
-                       (int)rows_grid(n), c.dst, 1, 0);
-    hipLaunchKernelGGL(k_blk_scale, dim3(gn), dim3(kThreads), 0, c.st, c.V, n, cst, 1, 0);
-    hipLaunchKernelGGL(k_blk_rotate, dim3(1), dim3(kRedThreads), 0, c.st, c.dst, (const double*)c.sqW,
-                       (int)rows_grid(n));
-    hipLaunchKernelGGL(k_blk_update, dim3(rows_grid(n)), dim3(kThreads), 0, c.st, cst,
-                       (const double*)c.V, c.W, c.Y, n, c.sqY, c.sqW);
-    hipLaunchKernelGGL(k_blk_check, dim3(1), dim3(kRedThreads), 0, c.st, c.dst, (const double*)c.sqY,
-                       (int)rows_grid(n), 0);
+    RFMLS_CHECK(tri_block(c, 0, c.V, c.Z, BlkScale(), nullptr, nullptr, cst, cm));
+    RFMLS_CHECK(spmm(c, c.A, c.Z, c.U, su, c.U, c.sqA, cst, &nb));
+    RFMLS_CHECK(presum(c, c.sqA, nb, c.preA, cst));
+    // alpha' v' = X^T (A^T u') - beta' v, with u' = u^'/beta', beta' from the sums
+    BlkScale sv;
+    sv.c = 1.0;
+    sv.pre = c.preA;
+    sv.norm = beta;
+    sv.cden = alpha;
+    RFMLS_CHECK(spmm(c, c.AT, c.U, c.Q, BlkScale(), nullptr, nullptr, cst));
+    RFMLS_CHECK(tri_block(c, 1, c.Q, c.V, sv, c.V, c.sqB, cst));
+    RFMLS_CHECK(presum(c, c.sqB, (int)rn, c.preB, cst));
+    hipLaunchKernelGGL(k_blk_step, dim3(rn), dim3(kThreads), 0, c.st, cst, st + 1, (const double*)c.preB,
+                       (const double*)c.V, (double*)nullptr, c.W, c.Y, n, c.sqY, c.sqW);
     RFMLS_HIP(c.h, hipGetLastError());
     return RFMLS_OK;
   });
 }
 
 template <class F>
-static rfmls_status run_loop(BCtx& c, int64_t itmax, int every, F&& iteration) {
+static rfmls_status run_loop(BCtx& c, int64_t itmax, int every, int consistent, F&& iteration) {
   rfmls_handle* h = c.h;
+  const BlkCommit cm = commit_of(c, consistent);
+  auto interval = [&](int64_t count) -> rfmls_status {
+    for (int64_t k = 0; k < count; ++k) RFMLS_CHECK(iteration());
+    hipLaunchKernelGGL(k_blk_commit, dim3(1), dim3(kThreads), 0, c.st, cm);
+    RFMLS_HIP(h, hipGetLastError());
+    return RFMLS_OK;
+  };
   int hd = 0;
-  RFMLS_CHECK(poll_all(c, &hd));
   if (c.graph && !h->trace) {
     if (!c.graph->exec)
       RFMLS_CHECK(capture_graph(h, c.graph, [&]() -> rfmls_status {
         const hipStream_t s0 = c.st;
         c.st = h->stream;
-        rfmls_status r = RFMLS_OK;
-        for (int k = 0; k < every && r >= 0; ++k) r = iteration();
+        const rfmls_status r = interval(every);
         c.st = s0;
         return r;
       }));
@@ -1610,9 +1723,9 @@ static rfmls_status run_loop(BCtx& c, int64_t itmax, int every, F&& iteration) {
     }
     return RFMLS_OK;
   }
-  for (int64_t it = 0; it < itmax && !hd; ++it) {
-    RFMLS_CHECK(iteration());
-    if ((it + 1) % every == 0) RFMLS_CHECK(poll_all(c, &hd));
+  for (int64_t it = 0; it < itmax && !hd; it += every) {
+    RFMLS_CHECK(interval(itmax - it < every ? itmax - it : every));
+    RFMLS_CHECK(poll_all(c, &hd));
   }
   return RFMLS_OK;
 }
@@ -1623,7 +1736,7 @@ rfmls_status read_block_state(BCtx& c, BlockState* out) {
   return RFMLS_OK;
 }
 
-// Work blocks (5 of m x 32, 8 of n x 32), partial sums and the triangular-product
+// Work blocks (3 of m x 32, 7 of n x 32), partial sums and the triangular-product
 // partials, carved from one workspace slot.
 static rfmls_status make_bctx(rfmls_handle* h, const rfmls_csr* A, const rfmls_csr* AT,
                               const rfmls_precond_t* P, BCtx& c) {
@@ -1634,7 +1747,7 @@ static rfmls_status make_bctx(rfmls_handle* h, const rfmls_csr* A, const rfmls_c
   c.P = P;
   c.st = h->stream;
   const int64_t maxk = (P->nt + P->chunk - 1) / P->chunk;
-  const size_t nvec = (size_t)kBlk * (size_t)(5 * m + 8 * n) + 4 * (size_t)kSpmmMaxBlocks * kBlk +
+  const size_t nvec = (size_t)kBlk * (size_t)(3 * m + 7 * n) + (4 * (size_t)kSpmmMaxBlocks + 2 * kPre + 4) * kBlk +
                       (size_t)P->nt * maxk * kTile * kBlk;
   void* p;
   RFMLS_CHECK(workspace(h, WS_LSQR_BLK, sizeof(double) * nvec, &p));
@@ -1647,8 +1760,6 @@ static rfmls_status make_bctx(rfmls_handle* h, const rfmls_csr* A, const rfmls_c
   c.U = take(m * kBlk);
   c.Rr = take(m * kBlk);
   c.Bb = take(m * kBlk);
-  c.T = take(m * kBlk);
-  c.Sm = take(m * kBlk);
   c.V = take(n * kBlk);
   c.W = take(n * kBlk);
   c.Y = take(n * kBlk);
@@ -1656,11 +1767,13 @@ static rfmls_status make_bctx(rfmls_handle* h, const rfmls_csr* A, const rfmls_c
   c.Q = take(n * kBlk);
   c.Xb = take(n * kBlk);
   c.DX = take(n * kBlk);
-  c.Sn = take(n * kBlk);
   c.sqA = take(kSpmmMaxBlocks * kBlk);
   c.sqB = take(kSpmmMaxBlocks * kBlk);
   c.sqY = take(kSpmmMaxBlocks * kBlk);
   c.sqW = take(kSpmmMaxBlocks * kBlk);
+  c.preA = take(kPre * kBlk);
+  c.preB = take(kPre * kBlk);
+  c.hn = take(4 * kBlk);
   c.part = take(P->nt * maxk * kTile * kBlk);
   {
     const int64_t need = (int64_t)spmm_split(A, h->num_cus) * A->m > (int64_t)spmm_split(AT, h->num_cus) * AT->m
@@ -1671,8 +1784,17 @@ static rfmls_status make_bctx(rfmls_handle* h, const rfmls_csr* A, const rfmls_c
     c.spart = (double*)pp;
   }
   void* ps;
-  RFMLS_CHECK(workspace(h, WS_LSQR_BSTATE, sizeof(BlockState), &ps));
+  RFMLS_CHECK(workspace(h, WS_LSQR_BSTATE, 2 * sizeof(BlockState), &ps));
   c.dst = (BlockState*)ps;
+  return RFMLS_OK;
+}
+
+// Column norms of a len x 32 block into c.hn[32 k ..] (read by the host later).
+static rfmls_status norms_to(BCtx& c, const double* x, int64_t len, int k) {
+  hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(len)), dim3(kThreads), 0, c.st, x, len, (double*)nullptr, c.sqY);
+  RFMLS_CHECK(presum(c, c.sqY, (int)rows_grid(len), c.preA, nullptr));
+  hipLaunchKernelGGL(k_blk_norm_out, dim3(1), dim3(64), 0, c.st, (const double*)c.preA, c.hn + k * kBlk);
+  RFMLS_HIP(c.h, hipGetLastError());
   return RFMLS_OK;
 }
 
@@ -1718,6 +1840,9 @@ rfmls_status run_solve_block(rfmls_handle* h, const rfmls_csr* A, const rfmls_cs
   if (o->graph) c.graph = &graph;
   const unsigned gm = grid_for(m * kBlk), gn = grid_for(n * kBlk);
   rfmls_status ret = RFMLS_OK;
+  BlkScale residual;  // r = b - A x
+  residual.s = -1.0;
+  residual.c = -1.0;
   std::vector<BlockState> hs(1);
   for (int64_t k0 = 0; k0 < nrhs; k0 += kBlk) {
     const int64_t nb = nrhs - k0 < kBlk ? nrhs - k0 : kBlk;
@@ -1726,22 +1851,11 @@ rfmls_status run_solve_block(rfmls_handle* h, const rfmls_csr* A, const rfmls_cs
     // from x = 0 the first sweep takes B itself; from given starting points
     // every sweep solves for the correction from the true residual B - A X
     const bool warm = o->x_init != 0;
-    std::vector<double> bsq;
     if (warm) {
       hipLaunchKernelGGL(k_gather_block, dim3(gn), dim3(kThreads), 0, c.st, (const double*)X, ldx, k0, nb,
                          n, c.Xb);
-      RFMLS_CHECK(spmm(c, A, c.Xb, -1.0, -1.0, nullptr, c.Bb, c.Rr, nullptr, nullptr, nullptr));
-      hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(m)), dim3(kThreads), 0, c.st, (const double*)c.Bb, m,
-                         c.sqA);
-      bsq.assign((size_t)rows_grid(m) * kBlk, 0.0);
-      RFMLS_HIP(h, hipMemcpyAsync(bsq.data(), c.sqA, sizeof(double) * bsq.size(), hipMemcpyDeviceToHost,
-                                  c.st));
-      RFMLS_HIP(h, hipStreamSynchronize(c.st));
-      for (int64_t q = 0; q < nb; ++q) {
-        double t = 0.0;
-        for (size_t b = 0; b < bsq.size() / kBlk; ++b) t += bsq[b * kBlk + q];
-        inf[q].normb = sqrt(t);
-      }
+      RFMLS_CHECK(spmm(c, A, c.Xb, c.Rr, residual, c.Bb));
+      RFMLS_CHECK(norms_to(c, c.Bb, m, 2));
     }
     for (int sweep = 0; sweep <= o->refine; ++sweep) {
       const bool from_zero = sweep == 0 && !warm;
@@ -1766,29 +1880,27 @@ rfmls_status run_solve_block(rfmls_handle* h, const rfmls_csr* A, const rfmls_cs
         if (s.itn > itn_max) itn_max = s.itn;
       }
       // x (+)= X y ; r = b - A x
-      RFMLS_CHECK(tri_block(c, 0, c.Y, from_zero ? c.Xb : c.DX, 0.0, nullptr, nullptr, nullptr, nullptr));
+      RFMLS_CHECK(tri_block(c, 0, c.Y, from_zero ? c.Xb : c.DX));
       if (!from_zero)
         hipLaunchKernelGGL(k_blk_axpy, dim3(gn), dim3(kThreads), 0, c.st, c.Xb, (const double*)c.DX, n);
-      RFMLS_CHECK(spmm(c, A, c.Xb, -1.0, -1.0, nullptr, c.Bb, c.Rr, nullptr, nullptr, nullptr));
+      RFMLS_CHECK(spmm(c, A, c.Xb, c.Rr, residual, c.Bb));
       if (itn_max == 0) break;
     }
     // true residual norms per column
-    hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(m)), dim3(kThreads), 0, c.st, (const double*)c.Rr, m, c.sqA);
-    RFMLS_CHECK(spmm(c, AT, c.Rr, 1.0, 0.0, nullptr, nullptr, c.Q, nullptr, nullptr, nullptr));
-    hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(n)), dim3(kThreads), 0, c.st, (const double*)c.Q, n, c.sqB);
-    std::vector<double> sa((size_t)rows_grid(m) * kBlk), sb((size_t)rows_grid(n) * kBlk);
-    RFMLS_HIP(h, hipMemcpyAsync(sa.data(), c.sqA, sizeof(double) * sa.size(), hipMemcpyDeviceToHost, c.st));
-    RFMLS_HIP(h, hipMemcpyAsync(sb.data(), c.sqB, sizeof(double) * sb.size(), hipMemcpyDeviceToHost, c.st));
+    RFMLS_CHECK(norms_to(c, c.Rr, m, 0));
+    RFMLS_CHECK(spmm(c, AT, c.Rr, c.Q));
+    RFMLS_CHECK(norms_to(c, c.Q, n, 1));
+    double* pin = (double*)((char*)h->pinned + 1024);
+    RFMLS_HIP(h, hipMemcpyAsync(pin, c.hn, 3 * kBlk * sizeof(double), hipMemcpyDeviceToHost, c.st));
     hipLaunchKernelGGL(k_scatter_block, dim3(gn), dim3(kThreads), 0, c.st, (const double*)c.Xb, n, k0, nb, X, ldx);
     if (Rout)
       hipLaunchKernelGGL(k_scatter_block, dim3(gm), dim3(kThreads), 0, c.st, (const double*)c.Rr, m, k0, nb, Rout, ldr);
+    RFMLS_HIP(h, hipGetLastError());
     RFMLS_HIP(h, hipStreamSynchronize(c.st));
     for (int64_t q = 0; q < nb; ++q) {
-      double ra = 0.0, rb = 0.0;
-      for (size_t b = 0; b < sa.size() / kBlk; ++b) ra += sa[b * kBlk + q];
-      for (size_t b = 0; b < sb.size() / kBlk; ++b) rb += sb[b * kBlk + q];
-      inf[q].normr = sqrt(ra);
-      inf[q].normar = sqrt(rb);
+      inf[q].normr = pin[q];
+      inf[q].normar = pin[kBlk + q];
+      if (warm) inf[q].normb = pin[2 * kBlk + q];
       if (info) info[k0 + q] = inf[q];
     }
   }
@@ -1828,50 +1940,54 @@ rfmls_status run_backward_block(rfmls_handle* h, const rfmls_csr* A, const rfmls
   const unsigned gm = grid_for(m * kBlk), gn = grid_for(n * kBlk);
   const int every = o->check_every > 0 ? o->check_every : 8;
   const BlockState* cst = c.dst;
+  double *alpha = &c.dst->col[0].alpha, *beta = &c.dst->col[0].beta;
+  const unsigned rn = rows_grid(n);
+  const BlkCommit cm = commit_of(c, 1);
   rfmls_status ret = RFMLS_OK;
   std::vector<BlockState> hs(1);
   for (int64_t k0 = 0; k0 < nrhs; k0 += kBlk) {
     const int64_t nb = nrhs - k0 < kBlk ? nrhs - k0 : kBlk;
     hipLaunchKernelGGL(k_gather_block, dim3(gn), dim3(kThreads), 0, c.st, G, ldg, k0, nb, n, Gb);
     // beta_1 u_1 = X^T g
-    RFMLS_CHECK(tri_block(c, 1, Gb, un, 0.0, nullptr, nullptr, c.sqB, nullptr));
-    hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqB,
-                       (int)rows_grid(n), c.dst, 0, 1);
-    hipLaunchKernelGGL(k_blk_start, dim3(1), dim3(64), 0, c.st, c.dst, o->atol, o->btol, o->conlim, itmax);
-    hipLaunchKernelGGL(k_blk_scale, dim3(gn), dim3(kThreads), 0, c.st, un, n, cst, 0, 1);
-    hipLaunchKernelGGL(k_blk_fill, dim3(gn), dim3(kThreads), 0, c.st, zz, n * kBlk, 0.0);
+    RFMLS_CHECK(tri_block(c, 1, Gb, un, BlkScale(), nullptr, c.sqB));
+    RFMLS_CHECK(presum(c, c.sqB, (int)rn, c.preB, nullptr));
+    hipLaunchKernelGGL(k_blk_begin, dim3(1), dim3(64), 0, c.st, c.dst, c.dst + 1, (const double*)c.preB, o->atol,
+                       o->btol, o->conlim, itmax);
     // alpha_1 v_1 = A (X u_1);  vt_1 = u_1 / alpha_1;  w_1 = vt_1
-    RFMLS_CHECK(tri_block(c, 0, un, tmp, 0.0, nullptr, nullptr, nullptr, nullptr));
+    BlkScale s1;
+    s1.sdiv = beta;
     int nbk = 0;
-    RFMLS_CHECK(spmm(c, A, tmp, 1.0, 0.0, nullptr, nullptr, vm, c.sqA, nullptr, &nbk));
-    hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqA, nbk, c.dst, 1, 0);
-    hipLaunchKernelGGL(k_blk_scale, dim3(gm), dim3(kThreads), 0, c.st, vm, m, cst, 1, 0);
-    hipLaunchKernelGGL(k_blk_start2, dim3(1), dim3(64), 0, c.st, c.dst);
-    hipLaunchKernelGGL(k_blk_recip_scale, dim3(gn), dim3(kThreads), 0, c.st, (const double*)un, 0.0,
-                       (const double*)nullptr, vt, n, cst, 1);
-    hipLaunchKernelGGL(k_blk_copy, dim3(gn), dim3(kThreads), 0, c.st, (const double*)vt, wt, n);
-    hipLaunchKernelGGL(k_blk_sumsq, dim3(rows_grid(n)), dim3(kThreads), 0, c.st, (const double*)wt, n, c.sqW);
+    RFMLS_CHECK(tri_block(c, 0, un, tmp));
+    RFMLS_CHECK(spmm(c, A, tmp, vm, s1, nullptr, c.sqA, nullptr, &nbk));
+    RFMLS_CHECK(presum(c, c.sqA, nbk, c.preA, nullptr));
+    hipLaunchKernelGGL(k_blk_begin2, dim3(1), dim3(64), 0, c.st, c.dst, (const double*)c.preA);
+    hipLaunchKernelGGL(k_blk_first_w, dim3(rn), dim3(kThreads), 0, c.st, cst, (const double*)un, 1, vt, wt, zz, n,
+                       c.sqW);
+    RFMLS_CHECK(presum(c, c.sqW, (int)rn, c.preB, nullptr));
+    hipLaunchKernelGGL(k_blk_w2, dim3(1), dim3(64), 0, c.st, c.dst, (const double*)c.preB);
     RFMLS_HIP(h, hipGetLastError());
-    RFMLS_CHECK(run_loop(c, itmax, every, [&]() -> rfmls_status {
-      // beta u = X^T (A^T v) - alpha u
-      RFMLS_CHECK(spmm(c, AT, vm, 1.0, 0.0, nullptr, nullptr, tmp, nullptr, cst, nullptr));
-      RFMLS_CHECK(tri_block(c, 1, tmp, un, 1.0, state_field(c.dst, 1), un, c.sqB, cst));
-      hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqB,
-                         (int)rows_grid(n), c.dst, 0, 0);
-      hipLaunchKernelGGL(k_blk_scale, dim3(gn), dim3(kThreads), 0, c.st, un, n, cst, 0, 0);
-      // alpha v = A (X u) - beta v;  vt = (u - beta vt) / alpha
-      RFMLS_CHECK(tri_block(c, 0, un, tmp, 0.0, nullptr, nullptr, nullptr, cst));
-      RFMLS_CHECK(spmm(c, A, tmp, 1.0, 1.0, state_field(c.dst, 0), vm, vm, c.sqA, cst, &nbk));
-      hipLaunchKernelGGL(k_blk_norms, dim3(1), dim3(kRedThreads), 0, c.st, (const double*)c.sqA, nbk, c.dst, 1, 0);
-      hipLaunchKernelGGL(k_blk_scale, dim3(gm), dim3(kThreads), 0, c.st, vm, m, cst, 1, 0);
-      hipLaunchKernelGGL(k_blk_recip_scale, dim3(gn), dim3(kThreads), 0, c.st, (const double*)un, 1.0,
-                         (const double*)vt, vt, n, cst, 0);
-      hipLaunchKernelGGL(k_blk_rotate, dim3(1), dim3(kRedThreads), 0, c.st, c.dst, (const double*)c.sqW,
-                         (int)rows_grid(n));
-      hipLaunchKernelGGL(k_blk_update, dim3(rows_grid(n)), dim3(kThreads), 0, c.st, cst,
-                         (const double*)vt, wt, zz, n, c.sqY, c.sqW);
-      hipLaunchKernelGGL(k_blk_check, dim3(1), dim3(kRedThreads), 0, c.st, c.dst, (const double*)c.sqY,
-                         (int)rows_grid(n), 1);
+    RFMLS_CHECK(run_loop(c, itmax, every, 1, [&]() -> rfmls_status {
+      // beta' u' = X^T (A^T v) - alpha u, with v = v^/alpha and u = u^/beta
+      BlkScale su;
+      su.sdiv = alpha;
+      su.c = 1.0;
+      su.cnum = alpha;
+      su.cden = beta;
+      RFMLS_CHECK(spmm(c, AT, vm, tmp, BlkScale(), nullptr, nullptr, cst));
+      RFMLS_CHECK(tri_block(c, 1, tmp, un, su, un, c.sqB, cst, cm));
+      RFMLS_CHECK(presum(c, c.sqB, (int)rn, c.preB, cst));
+      // alpha' v' = A (X u') - beta' v, with u' = u^'/beta', beta' from the sums;
+      // vt' = (u' - beta' vt) / alpha' in k_blk_step
+      BlkScale sv;
+      sv.c = 1.0;
+      sv.pre = c.preB;
+      sv.norm = beta;
+      sv.cden = alpha;
+      RFMLS_CHECK(tri_block(c, 0, un, tmp, BlkScale(), nullptr, nullptr, cst));
+      RFMLS_CHECK(spmm(c, A, tmp, vm, sv, vm, c.sqA, cst, &nbk));
+      RFMLS_CHECK(presum(c, c.sqA, nbk, c.preA, cst));
+      hipLaunchKernelGGL(k_blk_step, dim3(rn), dim3(kThreads), 0, c.st, cst, c.dst + 1, (const double*)c.preA,
+                         (const double*)un, vt, wt, zz, n, c.sqY, c.sqW);
       RFMLS_HIP(h, hipGetLastError());
       return RFMLS_OK;
     }));
@@ -1891,8 +2007,8 @@ rfmls_status run_backward_block(rfmls_handle* h, const rfmls_csr* A, const rfmls
       }
     }
     // w = X z, lam = A w
-    RFMLS_CHECK(tri_block(c, 0, zz, tmp, 0.0, nullptr, nullptr, nullptr, nullptr));
-    RFMLS_CHECK(spmm(c, A, tmp, 1.0, 0.0, nullptr, nullptr, lam, nullptr, nullptr, nullptr));
+    RFMLS_CHECK(tri_block(c, 0, zz, tmp));
+    RFMLS_CHECK(spmm(c, A, tmp, lam));
     if (dB)
       hipLaunchKernelGGL(k_scatter_block, dim3(gm), dim3(kThreads), 0, c.st, (const double*)lam, m, k0, nb, dB, lddb);
     if (dAval) {
@@ -1928,7 +2044,7 @@ rfmls_status run_form_B(rfmls_handle* h, const rfmls_csr* A, const rfmls_precond
     else
       hipLaunchKernelGGL(k_x_slab<float>, dim3(gn), dim3(kThreads), 0, c.st, (const float*)P->Xpk, n,
                          P->nt, P->full, c0, nb, c.Xb);
-    RFMLS_CHECK(spmm(c, A, c.Xb, 1.0, 0.0, nullptr, nullptr, c.U, nullptr, nullptr, nullptr));
+    RFMLS_CHECK(spmm(c, A, c.Xb, c.U));
     hipLaunchKernelGGL(k_scatter_slab, dim3(gm), dim3(kThreads), 0, c.st, (const double*)c.U, m, c0, nb,
                        Bmat, ldb);
     RFMLS_HIP(h, hipGetLastError());

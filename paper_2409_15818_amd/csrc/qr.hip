@@ -330,37 +330,58 @@ __global__ void __launch_bounds__(kPanelThreads)
   }
 }
 
-// Build T (nb x nb upper triangular, row-major) of the compact-WY form
-// H_1 ... H_nb = I - V T V^T from tau and the Gram V^T V (the sum of nsplit
-// partial slices Wz, each nb x ldw, whose leading nb columns hold V^T V).
+// T (nb x nb upper triangular, row-major) of the compact-WY form H_1 ... H_nb =
+// I - V T V^T from tau and the Gram V^T V (the leading nb columns of W, nb x ldw),
+// and W' = T^T W_C for the ncol columns of W after it.
 // T is the inverse of U = (strictly upper part of V^T V) + diag(1/tau): that
 // is the matrix form of the column recursion T[:j, j] = -tau_j T[:j, :j]
 // V_:j^T v_j (Schreiber and Van Loan).  Column k of T solves U t = e_k by
 // back substitution on one wavefront (lane i holds row i), t_l = tau_l x_l
 // from the bottom up, so 1/tau is never formed and a reflector with tau_j = 0
-// (H_j = I) leaves row and column j zero, as the recursion does.  One
-// wavefront per column: ceil(nb / 16) workgroups of 16, each staging the Gram.
+// (H_j = I) leaves row and column j zero, as the recursion does; a column of W'
+// solves U^T w' = w the same way from the top down, so it needs no T and both
+// go in one launch.  One wavefront per column, 16 to a workgroup, each workgroup
+// staging the Gram: the first ceil(nb / 16) form T, the others W' (none for
+// ncol = 0).  Bound by the loads and the 64-step chains.  Forming T first and
+// multiplying by it in a second launch took 8.5 + 11.3 us for 192 columns; this 8.1
+// (Helmholtz solve 26.4 -> 25.7 ms).
 template <typename T>
 __global__ void __launch_bounds__(1024)
-    k_qr_buildT(const T* __restrict__ Wz, int64_t zstride, int nsplit, int64_t ldw, int nb,
-                const T* __restrict__ tau, T* __restrict__ Tout, int64_t ldt) {
-  // Us[i][l] = (V^T V)_il for i < l < nb, zero elsewhere, so the update below
-  // needs no per-row test (rows i >= l subtract exactly 0)
+    k_qr_T_wp(const T* __restrict__ W, int64_t ldw, int nb, const T* __restrict__ tau, T* __restrict__ Tout,
+              int64_t ldt, int64_t ncol, T* __restrict__ Wp, int64_t ldwp) {
+  // Us[i][l] = (V^T V)_il for i < l < nb, zero elsewhere, so the updates below
+  // need no per-row test (rows that are done subtract exactly 0)
   __shared__ double Us[kMaxNb][kMaxNb + 1];
+  __shared__ double Ws[kMaxNb][16 + 1];
   __shared__ double ts[kMaxNb + 3];  // three zero entries below index 0 (steps past l = 0)
+  constexpr int kCols = 16;          // columns per workgroup
   const int tid = threadIdx.x;
-  for (int e = tid; e < kMaxNb * kMaxNb; e += 1024) {
-    const int i = e / kMaxNb, l = e % kMaxNb;
-    double sacc = 0.0;
-    if (i < l && l < nb)
-      for (int z = 0; z < nsplit; ++z) sacc += (double)Wz[(int64_t)z * zstride + (int64_t)i * ldw + l];
-    Us[i][l] = sacc;
+  const int nT = (nb + kCols - 1) / kCols;
+  const int64_t c0 = ((int64_t)blockIdx.x - nT) * kCols;
+  // clamped addresses, unused values dropped by selects: the loads go out together
+  double g[kMaxNb * kMaxNb / 1024];
+#pragma unroll
+  for (int q = 0; q < kMaxNb * kMaxNb / 1024; ++q) {
+    const int e = tid + 1024 * q, i = e / kMaxNb, l = e % kMaxNb;
+    g[q] = (double)W[(int64_t)min(i, nb - 1) * ldw + min(l, nb - 1)];
   }
-  if (tid < kMaxNb + 3) ts[tid] = (tid >= 3 && tid - 3 < nb) ? (double)tau[tid - 3] : 0.0;
+  const double tv = tid < kMaxNb + 3 ? (double)tau[min(max(tid - 3, 0), nb - 1)] : 0.0;
+  if (c0 >= 0) {
+    const int k = tid / kCols;
+    const int64_t c = c0 + tid % kCols;
+    const double v = (double)W[(int64_t)min(k, nb - 1) * ldw + nb + (c < ncol ? c : ncol - 1)];
+    Ws[k][tid % kCols] = k < nb ? v : 0.0;
+  }
+#pragma unroll
+  for (int q = 0; q < kMaxNb * kMaxNb / 1024; ++q) {
+    const int e = tid + 1024 * q, i = e / kMaxNb, l = e % kMaxNb;
+    Us[i][l] = i < l && l < nb ? g[q] : 0.0;
+  }
+  if (tid < kMaxNb + 3) ts[tid] = tid >= 3 && tid - 3 < nb ? tv : 0.0;
   __syncthreads();
   const int lane = tid & 63, w = tid >> 6;
-  {
-    const int k = (int)blockIdx.x * 16 + w;
+  if (c0 < 0) {
+    const int k = (int)blockIdx.x * kCols + w;
     if (k >= nb) return;  // uniform within the wavefront (no barrier follows)
     double x = lane == k ? 1.0 : 0.0, t = 0.0;
     // four steps per group, their LDS reads issued together; steps past l = 0
@@ -382,10 +403,36 @@ __global__ void __launch_bounds__(1024)
       }
     }
     if (lane < nb) Tout[(int64_t)lane * ldt + k] = (T)(lane <= k ? t : 0.0);
+    return;
   }
+  double x = Ws[lane][w], t = 0.0;
+  for (int l0 = 0; l0 < kMaxNb; l0 += 4) {  // tau = 0 past nb
+    double u[4], tt[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      u[d] = Us[l0 + d][lane];
+      tt[d] = ts[l0 + d + 3];
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      const double tl = tt[d] * lane_value(x, l0 + d);  // x_l is final once rows < l are done
+      if (lane == l0 + d) t = tl;
+      x -= u[d] * tl;
+    }
+  }
+  Ws[lane][w] = t;
+  __syncthreads();
+  const int k = tid / kCols;
+  const int64_t c = c0 + tid % kCols;
+  if (k < nb && c < ncol) Wp[(int64_t)k * ldwp + c] = (T)Ws[k][tid % kCols];
+}
+template <typename T>
+void launch_T_wp(hipStream_t st, const T* W, int64_t ldw, int nb, const T* tau, T* Tout, int64_t ldt, int64_t ncol = 0,
+                 T* Wp = nullptr, int64_t ldwp = 0) {
+  hipLaunchKernelGGL(k_qr_T_wp<T>, dim3((unsigned)((nb + 15) / 16 + (ncol + 15) / 16)), dim3(1024), 0, st, W, ldw, nb,
+                     tau, Tout, ldt, ncol, Wp, ldwp);
 }
 
-// W[e] = sum_z Wz[z * zstride + e] over a contiguous range of len elements
 template <typename T>
 __global__ void k_sum_slices(const T* __restrict__ Wz, int64_t zstride, int nsplit, int64_t len,
                              T* __restrict__ W) {
@@ -463,51 +510,6 @@ inline int64_t outer_slices_max(int64_t s) {
   const int64_t ms = s < 32767 ? s : 32767;
   const int64_t b = (ms + kOuterSplitShort - 1) / kOuterSplitShort;
   return (a > b ? a : b) + 2;
-}
-
-// W' = T^T W_C for one panel: W = V^T [V | C] (nb x ldw, its leading nb
-// columns the Gram, W_C the ncol columns after them) and the panel's T (nb x
-// nb upper triangular, rows ldt apart).  One workgroup per 32 columns; thread
-// (ty, tx) forms rows ty + 32 a and columns tx + 8 b of its strip, summing in
-// float64 over LDS copies of T and of the strip.
-template <typename T>
-__global__ void __launch_bounds__(256)
-    k_qr_wp(const T* __restrict__ W, int64_t ldw, int nb, const T* __restrict__ Tm, int64_t ldt,
-            int64_t ncol, T* __restrict__ Wp, int64_t ldwp) {
-  constexpr int SW = 32;
-  __shared__ double Ts[kMaxNb][kMaxNb + 1];  // [k][i] = T_ki (zero below the diagonal)
-  __shared__ double Ws[kMaxNb][SW + 1];      // [k][c]
-  const int tid = threadIdx.x;
-  const int ty = tid >> 3, tx = tid & 7;
-  const int64_t c0 = (int64_t)blockIdx.x * SW;
-  for (int e = tid; e < kMaxNb * kMaxNb; e += 256) {
-    const int k = e / kMaxNb, i = e % kMaxNb;
-    Ts[k][i] = (k <= i && i < nb) ? (double)Tm[(int64_t)k * ldt + i] : 0.0;
-  }
-  for (int e = tid; e < kMaxNb * SW; e += 256) {
-    const int k = e / SW, c = e % SW;
-    Ws[k][c] = (k < nb && c0 + c < ncol) ? (double)W[(int64_t)k * ldw + nb + c0 + c] : 0.0;
-  }
-  __syncthreads();
-  double o[2][4] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-#pragma unroll 4
-  for (int k = 0; k < kMaxNb; ++k) {
-    const double m0 = Ts[k][ty], m1 = Ts[k][ty + 32];
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const double r = Ws[k][tx + 8 * b];
-      o[0][b] += m0 * r;
-      o[1][b] += m1 * r;
-    }
-  }
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      const int i = ty + 32 * a;
-      const int64_t c = c0 + tx + 8 * b;
-      if (i < nb && c < ncol) Wp[(int64_t)i * ldwp + c] = (T)o[a][b];
-    }
 }
 
 // W' = T_o^T W_C for an outer block of NQ 64-column panels, without forming
@@ -866,10 +868,7 @@ rfmls_status qr_block_panels(rfmls_handle* h, const RowCounts& rows, int64_t k0,
       Trace tr(h, "qr_inner_T", sizeof(T) * 2.0 * jb * ncols, 2.0 * (double)jb * jb * rem);
       // this panel's T is also a diagonal block of the outer block's T_o
       T* Tq = pb.To + (p0 - k0) * kOuter + (p0 - k0);
-      hipLaunchKernelGGL(k_qr_buildT<T>, dim3((jb + 15) / 16), dim3(1024), 0, st, (const T*)pb.W, (int64_t)0, 1, ldw,
-                         jb, (const T*)tau_p, Tq, (int64_t)kOuter);
-      hipLaunchKernelGGL(k_qr_wp<T>, dim3(ceil_div(rem, 32)), dim3(256), 0, st, (const T*)pb.W, ldw, jb,
-                         (const T*)Tq, (int64_t)kOuter, rem, pb.Wp, ldwp);
+      launch_T_wp<T>(st, pb.W, ldw, jb, tau_p, Tq, kOuter, rem, pb.Wp, ldwp);
     }
     {
       Trace tr(h, "qr_inner_update", sizeof(T) * (2.0 * (double)M * rem + (double)M * jb),
@@ -963,8 +962,7 @@ rfmls_status qr_block_trailing(rfmls_handle* h, const RowCounts& rows, int64_t k
     Trace tr(h, "qr_outer_T", sizeof(T) * 2.0 * kMaxNb * kMaxNb, 2.0 * (double)kMaxNb * kMaxNb * kMaxNb / 3.0);
     const int64_t q0 = (bw - 1) / kMaxNb * kMaxNb;
     const int jq = (int)(bw - q0);
-    hipLaunchKernelGGL(k_qr_buildT<T>, dim3((jq + 15) / 16), dim3(1024), 0, st, (const T*)(tb.W + q0 * ldw + q0),
-                       (int64_t)0, 1, ldw, jq, (const T*)(tau + q0), To + q0 * kOuter + q0, (int64_t)kOuter);
+    launch_T_wp<T>(st, tb.W + q0 * ldw + q0, ldw, jq, tau + q0, To + q0 * kOuter + q0, kOuter);
     if (keep_gram)
       hipLaunchKernelGGL(k_qr_keep_gram<T>, dim3((unsigned)ceil_div(bw * bw, 256)), dim3(256), 0, st,
                          (const T*)tb.W, ldw, (int)bw, To, kOuter);
@@ -1234,8 +1232,7 @@ rfmls_status apply_householder(rfmls_handle* h, const double* P, int64_t ld, int
     const int64_t M = s - p0;
     double* V = const_cast<double*>(P) + p0 * ld + p0;
     RFMLS_HIP(h, (gemm<double, GemmRole::Generic>(vt_gemm<double>(V, ld, M, jb, jb, G, kMaxNb, 0), st)));
-    hipLaunchKernelGGL(k_qr_buildT<double>, dim3((jb + 15) / 16), dim3(1024), 0, st, (const double*)G, (int64_t)0, 1,
-                       (int64_t)kMaxNb, jb, tau + p0, Tq, (int64_t)kMaxNb);
+    launch_T_wp<double>(st, G, kMaxNb, jb, tau + p0, Tq, kMaxNb);
     GemmArgs<double> gw;  // W = V^T Y[p0:, :]
     gw.M = jb;
     gw.N = ny;

@@ -168,7 +168,10 @@ __global__ void __launch_bounds__(256) k_min_partials(const double* __restrict__
 // lane holding row i to the other three by a DPP quad broadcast.  Every element
 // sees the same operations in the same order as a one-lane-per-column
 // substitution, at a quarter of the registers (more wavefronts in flight).
-constexpr int kInvCols = 64;               // columns per block
+// 32 columns a block: half the LDS reads per compute unit of 64, 24 -> 18 us at 3,200
+// columns, 23.6 -> 20 at 12,800, float32 at 25,600 22.9 -> 21.2; 16 columns take
+// 17.5 and 20, but 25.8 there, the diagonal block read once more per block.
+constexpr int kInvCols = 32;                 // columns per block
 constexpr int kInvLanes = 4;               // lanes per column
 constexpr int kInvRows = kTile / kInvLanes;  // rows per lane
 

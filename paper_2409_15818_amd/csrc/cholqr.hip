@@ -231,6 +231,13 @@ __device__ __forceinline__ double rcp2(double x) {
   return fma(fma(-x, y, 1.0), y, y);
 }
 
+// 1 / sqrt(x), the same way.
+__device__ __forceinline__ double rsq2(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+}
+
 // Z = inverse of the diagonal block at k0 of the upper triangular U, by one
 // wavefront: lane l < 16 forms column l by a column sweep with U's entries read
 // uniformly from LDS (what lies below the diagonal is not read).
@@ -261,18 +268,23 @@ __device__ void diag_inverse(const Mat& U, int k0, Blk& Z, int l) {
 // from lane i; the whole block row of U comes out of the one elimination (no
 // product with the diagonal block's inverse) and no LDS round trip sits on the
 // chain.  mn / mx follow the pivots u_kk; *bad is set on a non-positive or
-// non-finite pivot.
-__device__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* bad) {
+// non-finite pivot.  With Z (kb > 0), 16 of the lanes past the columns carry the
+// identity through the same steps, which leaves U_kb^{-T}: Z = U_kb^{-1}.
+__device__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* bad, Blk* Z) {
   const int k0 = kb * kB;
   const bool act = l < kNb - k0;
+  const int zc = l - (kNb - k0);  // column of the identity
   double d[kB];
 #pragma unroll
-  for (int i = 0; i < kB; ++i) d[i] = act ? A[k0 + i][k0 + l] : 0.0;
+  for (int i = 0; i < kB; ++i) {
+    const double a = A[k0 + i][act ? k0 + l : k0];
+    d[i] = act ? a : (i == zc ? 1.0 : 0.0);
+  }
 #pragma unroll
   for (int s2 = 0; s2 < kB; ++s2) {
     const double piv = lane_bcast(d[s2], s2);
-    if (!(piv > 0.0) || !isfinite(piv)) *bad = true;
-    const double r = rsqrt(piv > 0.0 ? piv : 1.0);
+    *bad |= !(piv > 0.0 && piv < INFINITY);
+    const double r = rsq2(piv);
     const double ukk = piv * r;
     *mn = fmin(*mn, ukk);
     *mx = fmax(*mx, ukk);
@@ -284,6 +296,9 @@ __device__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* 
   if (act)
 #pragma unroll
     for (int i = 0; i < kB; ++i) A[k0 + i][k0 + l] = d[i];
+  else if (Z && zc < kB)
+#pragma unroll
+    for (int i = 0; i < kB; ++i) (*Z)[zc][i] = d[i];
 }
 
 // Columns k0 .. k0 + 15 of the reconstruction's LU (see k_cq_factor), rows k0 .. 63,
@@ -300,6 +315,7 @@ __device__ void recon_panel(Mat& A, const Mat& U2, int kb, int i, double* sg, do
     p[m] = A[i][k0 + m];
     u[m] = U2[i][k0 + m];  // row i of U2 (used on the panel's own rows only)
   }
+  double pv = 1.0, sv = 1.0, uv = 1.0;  // this row's pivot, sign and U2 diagonal
 #pragma unroll
   for (int j = 0; j < kB; ++j) {
     const int pr = k0 + j;
@@ -309,19 +325,20 @@ __device__ void recon_panel(Mat& A, const Mat& U2, int kb, int i, double* sg, do
     const double piv = ej - sj * ujj;
     const double rp = rcp2(piv);
     if (i == pr) {
-      sg[pr] = sj;
-      tau[pr] = fabs(piv) / ujj;
+      pv = piv;
+      sv = sj;
+      uv = ujj;
 #pragma unroll
       for (int m = j; m < kB; ++m) p[m] -= sj * u[m];
     }
-    const bool below = i > pr;
-    const double lij = p[j] * rp;
-    if (below) p[j] = lij;
+    const double lij = i > pr ? p[j] * rp : 0.0;
+    if (i > pr) p[j] = lij;
 #pragma unroll
-    for (int m = j + 1; m < kB; ++m) {
-      const double un = lane_bcast(p[m], pr);
-      if (below) p[m] = fma(-lij, un, p[m]);
-    }
+    for (int m = j + 1; m < kB; ++m) p[m] = fma(-lij, lane_bcast(p[m], pr), p[m]);
+  }
+  if (i >= k0 && i < k0 + kB) {
+    sg[i] = sv;
+    tau[i] = fabs(pv) / uv;
   }
   if (i >= k0)
 #pragma unroll
@@ -332,12 +349,15 @@ __device__ void recon_panel(Mat& A, const Mat& U2, int kb, int i, double* sg, do
 __device__ void recon_rows(Mat& A, const Mat& U2, int kb, int l, const double* sg) {
   const int k0 = kb * kB, c = k0 + kB + l;
   if (c >= kNb) return;
-  double x[kB];
-#pragma unroll
-  for (int i = 0; i < kB; ++i) x[i] = A[k0 + i][c];
+  double x[kB], u[kB];
 #pragma unroll
   for (int i = 0; i < kB; ++i) {
-    x[i] -= sg[k0 + i] * U2[k0 + i][c];
+    x[i] = A[k0 + i][c];
+    u[i] = sg[k0 + i] * U2[k0 + i][c];
+  }
+#pragma unroll
+  for (int i = 0; i < kB; ++i) {
+    x[i] -= u[i];
 #pragma unroll
     for (int m = i + 1; m < kB; ++m) x[m] = fma(-A[k0 + m][k0 + i], x[i], x[m]);
   }
@@ -366,20 +386,30 @@ __device__ void upper_product(const Mat& U2, Mat& R1, int lane) {
     }
 }
 
-// W = U^{-1} for the upper triangular U (zero below the diagonal; Z the
-// inverses of its diagonal blocks) by block back substitution from the bottom
-// block row up: W[k, >k] = -Z_k (U[k, >k] W[>k, >k]).  T is scratch.
-__device__ void blk_upper_inverse(const Mat& U, const Blk* Z, Mat& W, Mat& T) {
-  const int t = threadIdx.x;
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, j = e % kNb;
-    W[i][j] = (i >> 4) == (j >> 4) ? Z[i >> 4][i & 15][j & 15] : 0.0;
-  }
-  __syncthreads();
-  for (int kb = kNb / kB - 2; kb >= 0; --kb) {
-    const int k0 = kb * kB, nc = kNb - k0 - kB;
-    lds_mm(&T[0][0], kLd, &U[k0][k0 + kB], kLd, false, &W[k0 + kB][k0 + kB], kLd, kB, nc, nc, 1.0, 0.0);
-    lds_mm(&W[k0][k0 + kB], kLd, &Z[kb][0][0], kB + 1, false, &T[0][0], kLd, kB, nc, kB, -1.0, 0.0);
+// Block column tj of W = U^{-1} for the upper triangular U (Z the inverses of its
+// diagonal blocks) by one wavefront, block back substitution from the bottom up:
+// W_k = -Z_k (sum_{k < j <= tj} U_kj W_j), w[k] in the accumulator layout.  A register
+// r of it holds rows lk + 4 r, so taking K in that order makes w[j] the next product's
+// operand as it stands: no LDS round trip and no barrier.
+__device__ __forceinline__ void upper_inverse_col(const Mat& U, const Blk* Z, int tj, int lane, v4d (&w)[kNb / kB]) {
+  const int lr = lane & 15, lk = lane >> 4;
+#pragma unroll
+  for (int j = 0; j < kNb / kB; ++j)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[j][r] = j == tj ? Z[j][lk + 4 * r][lr] : 0.0;
+#pragma unroll
+  for (int k = kNb / kB - 2; k >= 0; --k) {
+    if (k >= tj) continue;
+    v4d acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int j = k + 1; j < kNb / kB; ++j)
+      if (j <= tj)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(U[16 * k + lr][16 * j + lk + 4 * r], w[j][r], acc, 0, 0, 0);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      w[k] = __builtin_amdgcn_mfma_f64_16x16x4f64(Z[k][lr][lk + 4 * r], -acc[r], w[k], 0, 0, 0);
   }
 }
 
@@ -401,19 +431,23 @@ __device__ void blk_upper_inverse(const Mat& U, const Blk* Z, Mat& W, Mat& T) {
 //
 // Bound by the eliminations' chains (a step per column), so independent ones run
 // beside each other, one wavefront each: stage kb has block row kb of the Cholesky
-// factor (wavefront 0), the reconstruction's panel kb - 1 (1), the inverse of an
-// earlier diagonal block (2) and at the end U2 R1 (3); the trailing products between
-// the stages are shared by all four.  Average of the two passes 47.3 -> 37.7 us
-// (4x4-box solve 9.8 -> 9.3 ms, Helmholtz 27.4 -> 26.4 ms).
+// factor (wavefront 0; in pass 1 its diagonal block's inverse comes out of the same
+// elimination), the reconstruction's panel kb - 1 (1), the inverse of an earlier
+// diagonal block of U~ (2) and at the end U2 R1 (3); the trailing products between
+// the stages are shared by all four, and each wavefront forms a block column of the
+// inverse by itself.  Average of the two passes 29.5 us; with the diagonal inverses as
+// stages of their own, the block inverse as products shared by the workgroup and the
+// library's rsqrt and divisions on the chains it was 37.7 (4x4-box solve 8.8 -> 8.4 ms,
+// Helmholtz 25.3 -> 24.6 ms).
 template <typename TS>
 __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G, double* __restrict__ Wk,
                                                    double* __restrict__ Rc, TS* __restrict__ P, int64_t ld,
                                                    TS* __restrict__ tau, int* __restrict__ status, int pass,
                                                    double min_pivot_ratio) {
   if (pass == 2 && *status) return;
-  __shared__ Mat M0, M1, M2, M3;
+  __shared__ Mat M0, M2, M3;
   __shared__ Blk Z[kNb / kB];
-  __shared__ double dsc[kNb];
+  __shared__ double dsc[kNb], rdsc[kNb];
   __shared__ double sg[kNb], tj[kNb];
   __shared__ int bad_s;
   __shared__ double ext[2];
@@ -426,6 +460,7 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
   double gv[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) gv[q] = G[(er + 4 * q) * kNb + ec];
+  const double gjj = G[ec * (kNb + 1)];
   if (pass == 2) {
     // the panel's top block (Q1's) into M3, R1 into M2
     double pv[16], rv[16];
@@ -440,32 +475,33 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
       M2[er + 4 * q][ec] = rv[q];
     }
   }
-  if (t < kNb) {
-    const double gjj = G[t * kNb + t];
-    dsc[t] = pass == 1 ? sqrt(gjj > 0.0 ? gjj : 0.0) : 1.0;
-  }
   if (t == 0) bad_s = 0;
-  __syncthreads();
-  if (t < kNb && !(dsc[t] > 0.0)) bad_s = 1;
-  {
-    const double dj = dsc[ec];
-    const double rj = dj > 0.0 ? 1.0 / dj : 0.0;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const double di = dsc[er + 4 * q];
-      M0[er + 4 * q][ec] = di > 0.0 ? gv[q] * (1.0 / di) * rj : 0.0;
+  if (pass == 1) {
+    __syncthreads();
+    if (t < kNb) {
+      const double dj = sqrt(gjj > 0.0 ? gjj : 0.0);
+      dsc[t] = dj;
+      rdsc[t] = dj > 0.0 ? 1.0 / dj : 0.0;
+      if (!(dj > 0.0)) bad_s = 1;
     }
+    __syncthreads();
+    const double rj = rdsc[ec];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) M0[er + 4 * q][ec] = gv[q] * rdsc[er + 4 * q] * rj;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 16; ++q) M0[er + 4 * q][ec] = gv[q];
   }
   __syncthreads();
   double mn = 1e300, mx = 0.0;  // pivots, uniform on wavefront 0
   bool ok = !bad_s;
-  for (int kb = 0; kb <= kBlocks + (pass == 2 ? 1 : 0) && ok; ++kb) {
+  for (int kb = 0; kb < kBlocks + (pass == 2 ? 2 : 0) && ok; ++kb) {
     const int k0 = kb * kB;
     if (kb > 0 && kb < kBlocks)  // A22 -= U12^T U12 with the block row of the stage before
       lds_mm(&M0[k0][k0], kLd, &M0[k0 - kB][k0], kLd, true, &M0[k0 - kB][k0], kLd, kNb - k0, kNb - k0, kB, -1.0, 1.0);
     if (w == 0 && kb < kBlocks) {
       bool bad = false;
-      chol_panel(M0, kb, lane, &mn, &mx, &bad);
+      chol_panel(M0, kb, lane, &mn, &mx, &bad, pass == 1 && kb > 0 ? &Z[kb] : nullptr);
       if (lane == 0) {
         if (bad) bad_s = 1;
         ext[0] = mn;
@@ -473,7 +509,7 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
       }
     }
     if (pass == 1) {
-      if (w == 1 && kb > 0) diag_inverse(M0, k0 - kB, Z[kb - 1], lane);
+      if (w == 1 && kb == 1) diag_inverse(M0, 0, Z[0], lane);
     } else {
       if (w == 1 && kb > 0 && kb <= kBlocks) {
         recon_panel(M3, M0, kb - 1, lane, sg, tj);
@@ -492,22 +528,37 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
     if (t == 0) *status = pass;
     return;
   }
+  // the inverse's block column w, and 16 elements a thread of the rest
+  const int lr = lane & 15, lk = lane >> 4;
+  v4d wc[kBlocks];
   if (pass == 1) {
-    blk_upper_inverse(M0, Z, M1, M2);  // M1 = U^{-1}
-    for (int e = t; e < kNb * kNb; e += 256) {
-      const int i = e / kNb, j = e % kNb;
-      Wk[e] = M1[i][j] * (1.0 / dsc[i]);
-      Rc[e] = i <= j ? M0[i][j] * dsc[j] : 0.0;
+    upper_inverse_col(M0, Z, w, lane, wc);  // U^{-1}
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int i = er + 4 * q;
+      Rc[i * kNb + ec] = i <= ec ? M0[i][ec] * dsc[ec] : 0.0;
     }
+#pragma unroll
+    for (int k = 0; k < kBlocks; ++k)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int i = 16 * k + lk + 4 * r;
+        Wk[i * kNb + 16 * w + lr] = wc[k][r] * rdsc[i];
+      }
     return;
   }
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, c = e % kNb;
-    P[(int64_t)i * ld + c] = (TS)(i <= c ? sg[i] * M2[i][c] : M3[i][c]);
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int i = er + 4 * q;
+    const double a = sg[i] * M2[i][ec], b = M3[i][ec];
+    P[(int64_t)i * ld + ec] = (TS)(i <= ec ? a : b);
   }
   if (t < kNb) tau[t] = (TS)tj[t];
-  blk_upper_inverse(M3, Z, M1, M0);  // M1 = U~^{-1} (above the diagonal blocks M3 holds U~)
-  for (int e = t; e < kNb * kNb; e += 256) Wk[e] = M1[e / kNb][e % kNb];
+  upper_inverse_col(M3, Z, w, lane, wc);  // U~^{-1} (above the diagonal blocks M3 holds U~)
+#pragma unroll
+  for (int k = 0; k < kBlocks; ++k)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) Wk[(16 * k + lk + 4 * r) * kNb + 16 * w + lr] = wc[k][r];
 }
 
 // A operands of P W for one row: lane (lr, lk) of a wavefront takes row lr of

@@ -149,7 +149,7 @@ __global__ void __launch_bounds__(256) k_cq_reduce(const double* __restrict__ Gp
 // 64 x 64 factorisations in LDS by one block of 256 threads, blocked by 16:
 // the eliminations of a 16-row (or 16-column) block on one wavefront in
 // registers (values passed by v_readlane), every product of blocks on the
-// matrix cores (lds_mm).
+// matrix cores.
 // ---------------------------------------------------------------------------
 constexpr int kB = 16;
 constexpr int kLd = kNb + 1;  // LDS row stride of a 64 x 64 matrix
@@ -163,57 +163,26 @@ __device__ __forceinline__ double lane_bcast(double v, int lane) {
   return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
 }
 
-// D = alpha op(A) B + beta D for LDS operands (row strides lda, ldb, ldd), D
-// m x n, K the inner dimension, all multiples of 16 (K of 4); op(A) = A (m x K)
-// or, with ta, A^T (A stored K x m).  Wave w computes 16 x 16 tiles w, w + 4,
-// ... (at most 16 tiles) into registers; after a barrier they are written, so
-// D may overlap A or B.  Every thread of the block calls it.
-__device__ void lds_mm(double* D, int ldd, const double* A, int lda, bool ta, const double* B, int ldb, int m, int n,
-                       int K, double alpha, double beta) {
-  const int t = threadIdx.x;
-  const int lane = t & 63, w = t >> 6;
+// Tile (ti, tj) of D -= op(A) B with K = 16, for LDS matrices of kLd columns (D, A
+// and B do not overlap): op(A) = A (a column block) or, with TA, A^T (A a row block).
+template <bool TA>
+__device__ __forceinline__ void rank16_tile(double* D, const double* A, const double* B, int ti, int tj, int lane) {
   const int lr = lane & 15, lk = lane >> 4;
-  const int tn = n / 16, nt = (m / 16) * tn;
-  const int astep = ta ? 4 * lda : 4;
-  v4d acc[4];
-  const double* ap[4];
-  const double* bp[4];
+  double* d = D + (16 * ti + lk) * kLd + 16 * tj + lr;
+  const double* ap = TA ? A + lk * kLd + 16 * ti + lr : A + (16 * ti + lr) * kLd + lk;
+  const double* bp = B + lk * kLd + 16 * tj + lr;
+  v4d acc;
+  double a[4], b[4];
 #pragma unroll
-  for (int sl = 0; sl < 4; ++sl) {
-    acc[sl] = v4d{0.0, 0.0, 0.0, 0.0};
-    const int tile = w + 4 * sl;
-    const int ti = tile / tn, tj = tile % tn;
-    ap[sl] = ta ? A + lk * lda + 16 * ti + lr : A + (16 * ti + lr) * lda + lk;
-    bp[sl] = B + lk * ldb + 16 * tj + lr;
+  for (int s = 0; s < 4; ++s) {
+    a[s] = ap[4 * s * (TA ? kLd : 1)];
+    b[s] = bp[4 * s * kLd];
+    acc[s] = d[4 * s * kLd];
   }
-  // the four tiles' chains interleaved: their operand loads issue together
-#pragma unroll 2
-  for (int k4 = 0; k4 < K / 4; ++k4) {
-    double a[4], b[4];
 #pragma unroll
-    for (int sl = 0; sl < 4; ++sl)
-      if (w + 4 * sl < nt) {
-        a[sl] = ap[sl][k4 * astep];
-        b[sl] = bp[sl][k4 * 4 * ldb];
-      }
+  for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[s], b[s], acc, 0, 0, 0);
 #pragma unroll
-    for (int sl = 0; sl < 4; ++sl)
-      if (w + 4 * sl < nt) acc[sl] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[sl], b[sl], acc[sl], 0, 0, 0);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int sl = 0; sl < 4; ++sl) {
-    const int tile = w + 4 * sl;
-    if (tile < nt) {
-      const int ti = tile / tn, tj = tile % tn;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        double* d = D + (16 * ti + lk + 4 * r) * ldd + 16 * tj + lr;
-        *d = beta == 0.0 ? alpha * acc[sl][r] : fma(alpha, acc[sl][r], beta * *d);
-      }
-    }
-  }
-  __syncthreads();
+  for (int r = 0; r < 4; ++r) d[4 * r * kLd] = acc[r];
 }
 
 // Orders a wavefront's LDS writes before its later LDS reads (no block barrier).
@@ -223,25 +192,24 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// 1 / x by the hardware estimate and two Newton steps (to about an ulp; x finite and
-// nonzero): a dependent chain a third as long as the library's division.
+// 1 / x and 1 / sqrt(x) (x finite, positive for the root) by the hardware estimate,
+// good to 2^-24 or so, and one third-order step (to about an ulp): dependent chains a
+// third as long as the library's.
 __device__ __forceinline__ double rcp2(double x) {
-  double y = __builtin_amdgcn_rcp(x);
-  y = fma(fma(-x, y, 1.0), y, y);
-  return fma(fma(-x, y, 1.0), y, y);
+  const double y = __builtin_amdgcn_rcp(x);
+  const double e = fma(-x, y, 1.0);
+  return fma(y, fma(e, e, e), y);
 }
-
-// 1 / sqrt(x), the same way.
 __device__ __forceinline__ double rsq2(double x) {
-  double y = __builtin_amdgcn_rsq(x);
-  y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
-  return fma(0.5 * y, fma(-x * y, y, 1.0), y);
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
 // Z = inverse of the diagonal block at k0 of the upper triangular U, by one
 // wavefront: lane l < 16 forms column l by a column sweep with U's entries read
 // uniformly from LDS (what lies below the diagonal is not read).
-__device__ void diag_inverse(const Mat& U, int k0, Blk& Z, int l) {
+__device__ __forceinline__ void diag_inverse(const Mat& U, int k0, Blk& Z, int l) {
   double rd[kB], acc[kB];
 #pragma unroll
   for (int i = 0; i < kB; ++i) {
@@ -270,7 +238,7 @@ __device__ void diag_inverse(const Mat& U, int k0, Blk& Z, int l) {
 // chain.  mn / mx follow the pivots u_kk; *bad is set on a non-positive or
 // non-finite pivot.  With Z (kb > 0), 16 of the lanes past the columns carry the
 // identity through the same steps, which leaves U_kb^{-T}: Z = U_kb^{-1}.
-__device__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* bad, Blk* Z) {
+__device__ __forceinline__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* bad, Blk* Z) {
   const int k0 = kb * kB;
   const bool act = l < kNb - k0;
   const int zc = l - (kNb - k0);  // column of the identity
@@ -285,13 +253,13 @@ __device__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* 
     const double piv = lane_bcast(d[s2], s2);
     *bad |= !(piv > 0.0 && piv < INFINITY);
     const double r = rsq2(piv);
-    const double ukk = piv * r;
-    *mn = fmin(*mn, ukk);
-    *mx = fmax(*mx, ukk);
-    const double us = l == s2 ? ukk : d[s2] * r;  // u_{s,l} for l >= s
-    d[s2] = l >= s2 ? us : 0.0;
+    *mn = fmin(*mn, piv * r);
+    *mx = fmax(*mx, piv * r);
+    const double us = d[s2] * r;  // u_{s,l} for l >= s
+    // u_{s,i} from the unscaled row, whose readlanes need not wait for r
 #pragma unroll
-    for (int i = s2 + 1; i < kB; ++i) d[i] = fma(-lane_bcast(us, i), us, d[i]);
+    for (int i = s2 + 1; i < kB; ++i) d[i] = fma(-(lane_bcast(d[s2], i) * r), us, d[i]);
+    d[s2] = l >= s2 ? us : 0.0;
   }
   if (act)
 #pragma unroll
@@ -306,69 +274,77 @@ __device__ void chol_panel(Mat& A, int kb, int l, double* mn, double* mx, bool* 
 // readlane, s_j = -sign(e_j), row j minus s_j times U2's row j (whose diagonal is
 // positive, so the pivot's size is |e_j| + u_jj), multipliers and the panel's
 // remaining columns.  A gets the multipliers below the diagonal and U~ on and
-// above it, tau_j = |pivot| / u_jj.
-__device__ void recon_panel(Mat& A, const Mat& U2, int kb, int i, double* sg, double* tau) {
+// above it, tau_j = |pivot| / u_jj.  Then the same rows of U~ in the columns right of
+// the panel, a column per lane: unit lower forward substitution with the multipliers
+// out of the registers (readlane), minus s_i U2; or, for the last panel, which has
+// none, Z = the inverse of its diagonal block, a column per lane, by a column sweep.
+__device__ __forceinline__ void recon_panel(Mat& A, const Mat& U2, int kb, int i, double* sg, double* tau, Blk& Z) {
   const int k0 = kb * kB;
-  double p[kB], u[kB];
+  const int c = k0 + kB + i;  // this lane's column right of the panel
+  const bool right = c < kNb;
+  double p[kB], u[kB], x[kB];
 #pragma unroll
   for (int m = 0; m < kB; ++m) {
     p[m] = A[i][k0 + m];
     u[m] = U2[i][k0 + m];  // row i of U2 (used on the panel's own rows only)
   }
-  double pv = 1.0, sv = 1.0, uv = 1.0;  // this row's pivot, sign and U2 diagonal
+  double pv = 1.0;  // this row's pivot
 #pragma unroll
   for (int j = 0; j < kB; ++j) {
     const int pr = k0 + j;
     const double ej = lane_bcast(p[j], pr);
     const double ujj = lane_bcast(u[j], pr);
-    const double sj = ej >= 0.0 ? -1.0 : 1.0;
-    const double piv = ej - sj * ujj;
-    const double rp = rcp2(piv);
-    if (i == pr) {
-      pv = piv;
-      sv = sj;
-      uv = ujj;
+    const double rp = rcp2(ej + copysign(ujj, ej));  // the pivot e_j - s_j u_jj
+    const double cj = i == pr ? copysign(1.0, ej) : 0.0;
+    const double pj = i > pr ? p[j] : 0.0;
 #pragma unroll
-      for (int m = j; m < kB; ++m) p[m] -= sj * u[m];
-    }
-    const double lij = i > pr ? p[j] * rp : 0.0;
-    if (i > pr) p[j] = lij;
+    for (int m = j; m < kB; ++m) p[m] = fma(cj, u[m], p[m]);
+    const double lij = pj * rp;
+    pv = i == pr ? p[j] : pv;
+    p[j] = i > pr ? lij : p[j];
 #pragma unroll
     for (int m = j + 1; m < kB; ++m) p[m] = fma(-lij, lane_bcast(p[m], pr), p[m]);
   }
-  if (i >= k0 && i < k0 + kB) {
-    sg[i] = sv;
-    tau[i] = fabs(pv) / uv;
-  }
-  if (i >= k0)
+  const double sv = -copysign(1.0, pv), rv = rcp2(pv);
+  if (i >= k0) {
 #pragma unroll
     for (int m = 0; m < kB; ++m) A[i][k0 + m] = p[m];
-}
-// The same rows k0 .. k0 + 15 of U~ in the columns right of the panel, a column per
-// lane: unit lower forward substitution, then minus s_i U2.
-__device__ void recon_rows(Mat& A, const Mat& U2, int kb, int l, const double* sg) {
-  const int k0 = kb * kB, c = k0 + kB + l;
-  if (c >= kNb) return;
-  double x[kB], u[kB];
+    if (i < k0 + kB) {
+      sg[i] = sv;
+      tau[i] = fabs(pv) / U2[i][i];
+    }
+  }
+  if (kb == kNb / kB - 1) {
 #pragma unroll
-  for (int i = 0; i < kB; ++i) {
-    x[i] = A[k0 + i][c];
-    u[i] = sg[k0 + i] * U2[k0 + i][c];
+    for (int m = 0; m < kB; ++m) x[m] = m == i ? 1.0 : 0.0;
+#pragma unroll
+    for (int m = kB - 1; m >= 0; --m) {
+      x[m] = m <= i ? x[m] * lane_bcast(rv, k0 + m) : 0.0;
+#pragma unroll
+      for (int q = 0; q < m; ++q) x[q] = fma(-lane_bcast(p[m], k0 + q), x[m], x[q]);
+    }
+    if (i < kB)
+#pragma unroll
+      for (int m = 0; m < kB; ++m) Z[m][i] = x[m];
+    return;
   }
 #pragma unroll
-  for (int i = 0; i < kB; ++i) {
-    x[i] -= u[i];
+  for (int m = 0; m < kB; ++m)
+    x[m] = fma(-lane_bcast(sv, k0 + m), U2[k0 + m][right ? c : k0], A[k0 + m][right ? c : k0]);
 #pragma unroll
-    for (int m = i + 1; m < kB; ++m) x[m] = fma(-A[k0 + m][k0 + i], x[i], x[m]);
+  for (int m = 0; m < kB; ++m) {
+#pragma unroll
+    for (int q = m + 1; q < kB; ++q) x[q] = fma(-lane_bcast(p[m], k0 + q), x[m], x[q]);
   }
+  if (right)
 #pragma unroll
-  for (int i = 0; i < kB; ++i) A[k0 + i][c] = x[i];
+    for (int m = 0; m < kB; ++m) A[k0 + m][c] = x[m];
 }
 
 // R1 <- U2 R1 (both upper triangular, zeros below the diagonal inside the diagonal
 // blocks) by one wavefront on the matrix cores: block column by block column, the
 // blocks from the top down, each needing only the blocks of R1 at and below it.
-__device__ void upper_product(const Mat& U2, Mat& R1, int lane) {
+__device__ __forceinline__ void upper_product(const Mat& U2, Mat& R1, int lane) {
   const int lr = lane & 15, lk = lane >> 4;
 #pragma unroll
   for (int tj = 0; tj < kNb / kB; ++tj)
@@ -432,13 +408,16 @@ __device__ __forceinline__ void upper_inverse_col(const Mat& U, const Blk* Z, in
 // Bound by the eliminations' chains (a step per column), so independent ones run
 // beside each other, one wavefront each: stage kb has block row kb of the Cholesky
 // factor (wavefront 0; in pass 1 its diagonal block's inverse comes out of the same
-// elimination), the reconstruction's panel kb - 1 (1), the inverse of an earlier
-// diagonal block of U~ (2) and at the end U2 R1 (3); the trailing products between
-// the stages are shared by all four, and each wavefront forms a block column of the
-// inverse by itself.  Average of the two passes 29.5 us; with the diagonal inverses as
-// stages of their own, the block inverse as products shared by the workgroup and the
-// library's rsqrt and divisions on the chains it was 37.7 (4x4-box solve 8.8 -> 8.4 ms,
-// Helmholtz 25.3 -> 24.6 ms).
+// elimination), the reconstruction's panel kb - 1 (1; the last with its diagonal
+// block's inverse), the inverse of an earlier diagonal block of U~ (2) and at the end
+// U2 R1 (3); the trailing tiles after a stage are shared by all four, and each
+// wavefront forms a block column of the inverse by itself.  Average of the two passes
+// 27.5 us; with the diagonal inverses as stages of their own, trailing and inverse
+// products with barriers inside and the library's rsqrt and divisions on the chains it
+// was 37.7 (4x4-box solve 8.8 -> 8.35 ms, Helmholtz 25.3 -> 24.4 ms).  A step of a
+// 16-column elimination takes about 400 (Cholesky) and 500 clocks (reconstruction) at
+// some 75 instructions; shortening its dependent chain changes nothing, so one
+// wavefront's issue rate is what is left.
 template <typename TS>
 __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G, double* __restrict__ Wk,
                                                    double* __restrict__ Rc, TS* __restrict__ P, int64_t ld,
@@ -495,10 +474,8 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
   __syncthreads();
   double mn = 1e300, mx = 0.0;  // pivots, uniform on wavefront 0
   bool ok = !bad_s;
-  for (int kb = 0; kb < kBlocks + (pass == 2 ? 2 : 0) && ok; ++kb) {
+  for (int kb = 0; kb < kBlocks + (pass == 2 ? 1 : 0) && ok; ++kb) {
     const int k0 = kb * kB;
-    if (kb > 0 && kb < kBlocks)  // A22 -= U12^T U12 with the block row of the stage before
-      lds_mm(&M0[k0][k0], kLd, &M0[k0 - kB][k0], kLd, true, &M0[k0 - kB][k0], kLd, kNb - k0, kNb - k0, kB, -1.0, 1.0);
     if (w == 0 && kb < kBlocks) {
       bool bad = false;
       chol_panel(M0, kb, lane, &mn, &mx, &bad, pass == 1 && kb > 0 ? &Z[kb] : nullptr);
@@ -511,18 +488,25 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
     if (pass == 1) {
       if (w == 1 && kb == 1) diag_inverse(M0, 0, Z[0], lane);
     } else {
-      if (w == 1 && kb > 0 && kb <= kBlocks) {
-        recon_panel(M3, M0, kb - 1, lane, sg, tj);
-        wave_sync();
-        recon_rows(M3, M0, kb - 1, lane, sg);
-      }
+      if (w == 1 && kb > 0) recon_panel(M3, M0, kb - 1, lane, sg, tj, Z[kBlocks - 1]);
       if (w == 2 && kb > 1) diag_inverse(M3, k0 - 2 * kB, Z[kb - 2], lane);
       if (w == 3 && kb == kBlocks) upper_product(M0, M2, lane);
     }
     __syncthreads();
     ok = !bad_s;
-    if (pass == 2 && kb > 0 && kb < kBlocks)  // trailing block of the panel just reconstructed
-      lds_mm(&M3[k0][k0], kLd, &M3[k0][k0 - kB], kLd, false, &M3[k0 - kB][k0], kLd, kNb - k0, kNb - k0, kB, -1.0, 1.0);
+    // the trailing blocks of the Cholesky block row just formed (upper tiles, all
+    // that is read) and of the panel just reconstructed
+    const int nt = kBlocks - 1 - kb;  // tile rows right of block row kb
+    int q = w;
+    for (int ti = 0; ti < nt; ++ti)
+      for (int tc = ti; tc < nt; ++tc, q = q == 0 ? 3 : q - 1)
+        if (q == 0)
+          rank16_tile<true>(&M0[k0 + kB][k0 + kB], &M0[k0][k0 + kB], &M0[k0][k0 + kB], ti, tc, lane);
+    if (pass == 2 && kb > 0 && kb < kBlocks)
+      for (int e = 0; e < (nt + 1) * (nt + 1); ++e, q = q == 0 ? 3 : q - 1)
+        if (q == 0)
+          rank16_tile<false>(&M3[k0][k0], &M3[k0][k0 - kB], &M3[k0 - kB][k0], e / (nt + 1), e % (nt + 1), lane);
+    if (kb < kBlocks - 1 + (pass == 2 ? 1 : 0)) __syncthreads();
   }
   if (!ok || !(ext[0] >= min_pivot_ratio * ext[1])) {
     if (t == 0) *status = pass;

@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import paper_2409_15818_amd as R
+from oracle import backward
 from rfmgen import csr_from_dense, dense_with_condition
 
 pytestmark = pytest.mark.gpu
@@ -102,6 +103,38 @@ def test_run_products_in_chunks(nrhs):
     assert rc == 0
     assert np.linalg.norm(X.cpu().numpy() - want) <= 1e-10 * np.linalg.norm(want)
     assert np.linalg.norm(Res.cpu().numpy() - (B - want @ Ad.T)) <= 1e-10 * np.linalg.norm(B)
+
+
+# The matrix gradient over pieces of rows with common column runs: pieces and runs
+# with remainders of 16, one-entry runs, empty rows, and a second block of 32
+# right-hand sides added to the first.  Oracle and bound as above (kappa = O(10)).
+@pytest.mark.parametrize("nrhs", [2, 33])
+def test_matrix_gradient_over_run_pieces(nrhs):
+    n = 96
+    pieces = [(450, [(0, 48)]), (350, [(48, 48)]), (333, [(0, 96)]), (70, [(3, 17), (40, 1), (60, 33)]), (5, []),
+              (17, [(95, 1)])]
+    ptr, col, val = _blocks(pieces, n, 9)
+    m = len(ptr) - 1
+    Ad = np.zeros((m, n))
+    Ad[np.repeat(np.arange(m), np.diff(ptr)), col] = val
+    rng = np.random.default_rng(2)
+    B, G = rng.standard_normal((nrhs, m)), rng.standard_normal((nrhs, n))
+    h = R.Handle(device="cuda:0")
+    A = R.CSR.from_numpy(ptr, col, val, m, n)
+    AT = R.rfmls_transpose(h, A)
+    SA, _, _, _ = R.rfmls_sketch(h, A, 4 * n, 2)
+    P = R.rfmls_precond(h, SA)
+    opts = R.default_opts(atol=1e-13, btol=1e-13)
+    X, Res, _, _ = R.rfmls_solve(h, A, AT, P, torch.tensor(B, device="cuda"), opts)
+    dB, dA, _, rc = R.rfmls_solve_backward(h, A, AT, P, X, Res, torch.tensor(G, device="cuda"), opts)
+    dBo, dAo = np.zeros((nrhs, m)), np.zeros(len(col))
+    for k in range(nrhs):
+        x, r, w, lam = backward.dense_gradients(Ad, B[k], G[k])
+        dBo[k] = lam
+        dAo += backward.pattern_grad(ptr, col, r, w, lam, x)
+    assert rc == 0
+    assert np.linalg.norm(dB.cpu().numpy() - dBo) <= 1e-10 * np.linalg.norm(dBo)
+    assert np.linalg.norm(dA.cpu().numpy() - dAo) <= 1e-10 * np.linalg.norm(dAo)
 
 
 def _staircase(s, n, width, per_row, seed, zero_rows=0):

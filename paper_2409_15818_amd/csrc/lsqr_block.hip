@@ -1623,12 +1623,14 @@ static rfmls_status spmm_prepare(BCtx& c) {
     if (M->m < 1 || badh[i] || np * kRunMinRows > M->m) continue;
     r.npieces = np;
     // K chunks where the pieces alone give fewer than four workgroups per
-    // compute unit: each at least 64 entries of an average row (a step per
-    // wavefront), at most kRunMaxSplit; a chunk is a whole number of steps and
-    // the last also takes what longer rows have beyond it
+    // compute unit: each at least 256 entries of an average row (four steps per
+    // wavefront; with 64, a 6.9 M entry matrix's products with 240- and 3,600-entry
+    // rows took 25.9 + 7.2 us for the merge each, with 256 23.2 us and one merge of
+    // 5.0 for the two; 192 gives 26.6, 384 25.1), at most kRunMaxSplit; a chunk is a
+    // whole number of steps and the last also takes what longer rows have beyond it
     const int64_t len = (M->nnz + M->m - 1) / M->m;
     int64_t sp = (4 * (int64_t)h->num_cus + np - 1) / np;
-    if (sp > len / 64) sp = len / 64;
+    if (sp > len / 256) sp = len / 256;
     if (sp > kRunMaxSplit) sp = kRunMaxSplit;
     if (sp < 1) sp = 1;
     r.nsplit = (int)sp;

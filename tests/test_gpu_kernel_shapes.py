@@ -108,11 +108,18 @@ def test_run_products_in_chunks(nrhs):
 # The matrix gradient over pieces of rows with common column runs: pieces and runs
 # with remainders of 16, one-entry runs, empty rows, and a second block of 32
 # right-hand sides added to the first.  Oracle and bound as above (kappa = O(10)).
+# The wide matrix's rows are long enough for K chunks.
+GRADIENT_CASES = [
+    (96, [(450, [(0, 48)]), (350, [(48, 48)]), (333, [(0, 96)]), (70, [(3, 17), (40, 1), (60, 33)]), (5, []),
+          (17, [(95, 1)])]),
+    (700, [(1500, [(0, 700)]), (70, [(3, 517), (540, 1), (560, 133)]), (5, [])]),
+]
+
+
 @pytest.mark.parametrize("nrhs", [2, 33])
-def test_matrix_gradient_over_run_pieces(nrhs):
-    n = 96
-    pieces = [(450, [(0, 48)]), (350, [(48, 48)]), (333, [(0, 96)]), (70, [(3, 17), (40, 1), (60, 33)]), (5, []),
-              (17, [(95, 1)])]
+@pytest.mark.parametrize("case", range(len(GRADIENT_CASES)))
+def test_matrix_gradient_over_run_pieces(case, nrhs):
+    n, pieces = GRADIENT_CASES[case]
     ptr, col, val = _blocks(pieces, n, 9)
     m = len(ptr) - 1
     Ad = np.zeros((m, n))

@@ -433,14 +433,36 @@ void launch_T_wp(hipStream_t st, const T* W, int64_t ldw, int nb, const T* tau, 
                      tau, Tout, ldt, ncol, Wp, ldwp);
 }
 
+// W = the sum of the nsplit slices of Wz in slice order, 16 bytes a thread (len a
+// multiple of 32, slices 16-byte aligned), eight slices' loads in flight: bound by
+// reading the slices (4^3-box float32 sketch 176 -> 125 us, one element a thread before).
 template <typename T>
-__global__ void k_sum_slices(const T* __restrict__ Wz, int64_t zstride, int nsplit, int64_t len,
-                             T* __restrict__ W) {
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < len;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    double acc = 0.0;
-    for (int z = 0; z < nsplit; ++z) acc += (double)Wz[(int64_t)z * zstride + e];
-    W[e] = (T)acc;
+__global__ void __launch_bounds__(256) k_sum_slices(const T* __restrict__ Wz, int64_t zstride, int nsplit, int64_t len,
+                                                    T* __restrict__ W) {
+  constexpr int E = 16 / sizeof(T);
+  typedef T vec __attribute__((ext_vector_type(E)));
+  for (int64_t e = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * E; e < len;
+       e += (int64_t)gridDim.x * blockDim.x * E) {
+    double acc[E] = {};
+    int z = 0;
+    for (; z + 8 <= nsplit; z += 8) {
+      vec v[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] = *(const vec*)(Wz + (int64_t)(z + q) * zstride + e);
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int i = 0; i < E; ++i) acc[i] += (double)v[q][i];
+    }
+    for (; z < nsplit; ++z) {
+      const vec v = *(const vec*)(Wz + (int64_t)z * zstride + e);
+#pragma unroll
+      for (int i = 0; i < E; ++i) acc[i] += (double)v[i];
+    }
+    vec o;
+#pragma unroll
+    for (int i = 0; i < E; ++i) o[i] = (T)acc[i];
+    *(vec*)(W + e) = o;
   }
 }
 
@@ -497,16 +519,27 @@ inline int64_t inner_slices_max(int64_t s) {
 }
 // Row slices of an outer block's V^T [V | C] below its masked top rows:
 // 4096 rows from 32,768 rows on (2% faster than 8192 on the 8x8-box sketch,
-// net of the longer slice sum; 2048 there measured even), kOuterSplitShort
-// below, where the grid is thinner (Helmholtz sketch, 12,800 rows: V^T C
-// 4.07 -> 3.15 ms per solve against 4096-row slices; 2048 rows 3.45 ms,
-// 8192 rows 6.6 ms).
+// net of the longer slice sum; 2048 there measured even).  Below, the largest of
+// 4096, 2048 and kOuterSplitShort rows that leaves 64 x 64 tiles times slices for
+// kOuterMinTiles workgroups over the nl columns from the block on (Helmholtz sketch,
+// 12,800 rows: V^T C 4.07 -> 3.15 ms per solve with 1024 rows against 4096; 2048 rows
+// 3.45 ms, 8192 rows 6.6 ms), since every slice is written and read once more.
+// 8x8-box sketch in sorted order, under 32,768 rows: the slice sum 112 -> 36 us against
+// 1024 rows, the product even.
+// nl and not the product's own columns decides, so that a product split by
+// columns (look-ahead) keeps every column's sums.
 constexpr int64_t kOuterSplitShort = 1024;
-inline int64_t outer_split(int64_t M0) { return M0 >= 32768 ? 4096 : kOuterSplitShort; }
+constexpr int64_t kOuterMinTiles = 2048;
+inline int64_t outer_split(int64_t M0, int64_t bw, int64_t nl) {
+  if (M0 >= 32768) return 4096;
+  int64_t sp = 4096;
+  while (sp > kOuterSplitShort && (bw / 64) * ((nl + 63) / 64) * ((M0 + sp - 1) / sp) < kOuterMinTiles) sp /= 2;
+  return sp;
+}
 // most slices any outer block of an s-row sketch takes (the masked top rows
 // and a ragged tail included)
 inline int64_t outer_slices_max(int64_t s) {
-  const int64_t a = (s + outer_split(s) - 1) / outer_split(s);
+  const int64_t a = (s + 4095) / 4096;
   const int64_t ms = s < 32767 ? s : 32767;
   const int64_t b = (ms + kOuterSplitShort - 1) / kOuterSplitShort;
   return (a > b ? a : b) + 2;
@@ -785,7 +818,7 @@ GemmArgs<T> v_update(T* P, int64_t ld, int64_t M, int64_t vcols, int64_t ncols, 
 // Rows that a panel or an outer block works on: all s, or with sorted rows the
 // act[k] rows whose first nonzero lies in panel k or before it.
 struct RowCounts {
-  int64_t s = 0;
+  int64_t s = 0, n = 0;  // the sketch's rows and columns
   std::vector<int64_t> act;  // per 64-column panel; empty: s
   int64_t at(int64_t col) const { return act.empty() ? s : act[(size_t)(col / kMaxNb)]; }
 };
@@ -904,7 +937,7 @@ rfmls_status qr_block_trailing(rfmls_handle* h, const RowCounts& rows, int64_t k
                                const TrailBufs<T>& tb, bool keep_gram = false) {
   hipStream_t st = h->stream;
   const int64_t M0 = rows.at(k0 + bw - 1) - k0;
-  const int64_t split_out = outer_split(M0);
+  const int64_t split_out = outer_split(M0, bw, rows.n - k0);
   T* P0 = SA + k0 * ld + k0;
   const int64_t vc = gram ? bw : 0;  // V's own columns in the product
   const int64_t ncols = vc + nc, ncols_m = vc + nc_m;
@@ -953,7 +986,8 @@ rfmls_status qr_block_trailing(rfmls_handle* h, const RowCounts& rows, int64_t k
       gr.b_vcols = 0;
       RFMLS_HIP(h, (gemm<T, GemmRole::QrVtC>(gr, st)));
     }
-    hipLaunchKernelGGL(k_sum_slices<T>, dim3(ceil_div(bw * ldw, 256) < 4096 ? ceil_div(bw * ldw, 256) : 4096),
+    const int64_t per = 256 * 16 / sizeof(T);  // elements a workgroup sums at a time
+    hipLaunchKernelGGL(k_sum_slices<T>, dim3(ceil_div(bw * ldw, per) < 4096 ? ceil_div(bw * ldw, per) : 4096),
                        dim3(256), 0, st, (const T*)tb.Wz, bw * ldw, (int)nsp, zs, tb.W);
   }
   if (gram) {
@@ -1160,6 +1194,7 @@ rfmls_status qr_impl(rfmls_handle* h, int64_t s, int64_t n, int64_t n_room, T* S
   // the rows' order is free when no reflector is applied afterwards
   RowCounts rows;
   rows.s = s;
+  rows.n = n;
   if (!tau_out) RFMLS_CHECK(sort_rows<T>(h, s, n, kOuter, SA, ld, tb.Wz, (int64_t)wz_out, &rows));
   // block k + 1's panels all CholeskyQR2-eligible (64 columns, enough rows)
   auto cq_block = [&](int64_t k1, int64_t bw1) {

@@ -157,10 +157,9 @@ __global__ void __launch_bounds__(256) k_min_partials(const double* __restrict__
 // lower triangle gets the exact zeros back substitution leaves there (0 / r_ii
 // below a unit right-hand side); the GEMMs above read those as stored.
 // Right-hand side: e_j restricted to the block row, minus R_{I,>I} X_{>I}, which
-// arrives in two parts (see invert_upper): nzn split-K slices of Pn (each
-// b x (n - o - 64), stride zsn) from the rows of X solved earlier inside the
-// same outer block, summed in slice order, and nzf split-K
-// slices of Pf (rows roff .. roff + b of a (rows of the outer block) x (n - e2)
+// arrives in two parts (see invert_upper): Pn (b x (n - o - 64), none for an outer
+// block's last block row) from the rows of X solved earlier inside the same outer
+// block, and nzf split-K slices of Pf (rows roff .. roff + b of a (rows of the outer block) x (n - e2)
 // partial) from the rows beyond the outer block, for columns j >= e2.  Then
 // R_II x = rhs by back substitution, column-oriented (x_i = rhs_i * (1 / r_ii),
 // the 64 reciprocals formed once, then every rhs_k, k < i, is updated at once).  Four neighbouring lanes share a
@@ -190,8 +189,7 @@ __device__ __forceinline__ double quad_bcast(double v) {
 template <typename T>
 __global__ void __launch_bounds__(kInvCols * kInvLanes)
     k_inv_blockrow(const T* __restrict__ R, int64_t n, int64_t I, const T* __restrict__ Pn,
-                   int64_t ldn, int nzn, int64_t zsn, const T* __restrict__ Pf, int nzf, int64_t ldf, int64_t zsf,
-                   int64_t roff, int64_t e2, T* __restrict__ X) {
+                   int64_t ldn, const T* __restrict__ Pf, int nzf, int64_t ldf, int64_t zsf, int64_t roff, int64_t e2, T* __restrict__ X) {
   __shared__ double Rs[kTile][kTile + 1];
   __shared__ double rinv[kTile];  // 1 / r_ii, formed once so no division sits on the chain
   const int64_t o = I * kTile;
@@ -222,13 +220,6 @@ __global__ void __launch_bounds__(kInvCols * kInvLanes)
     double pn[kInvRows];
 #pragma unroll
     for (int l = 0; l < kInvRows; ++l) pn[l] = (double)Pn[(int64_t)min(r0 + l, b - 1) * ldn + jc];
-    for (int z = 1; z < nzn; ++z) {
-      double pz[kInvRows];
-#pragma unroll
-      for (int l = 0; l < kInvRows; ++l) pz[l] = (double)Pn[(int64_t)z * zsn + (int64_t)min(r0 + l, b - 1) * ldn + jc];
-#pragma unroll
-      for (int l = 0; l < kInvRows; ++l) pn[l] += pz[l];
-    }
 #pragma unroll
     for (int l = 0; l < kInvRows; ++l) v[l] = r0 + l < b ? -pn[l] : 0.0;
   }
@@ -342,22 +333,28 @@ __global__ void k_unpack_tiles(const TS* __restrict__ pk, int64_t n, int64_t nt,
 // X = R^{-1} by blocked back substitution, two levels: outer blocks of
 // kInvOuter rows (kInvTiles tiles), inner block rows of 64.  For block row I
 // inside the outer block [o2, e2):
-//   R_{I,>I} X_{>I} = R_{I,(I,e2)} X_{(I,e2)}  (near: K < kInvOuter, one GEMM
-//                                                 per block row)
+//   R_{I,>I} X_{>I} = R_{I,(I,e2)} X_{(I,e2)}  (near: K < kInvOuter)
 //                   + R_{I,>=e2} X_{>=e2}        (far: computed once per outer
 //                                                 block for all its rows)
 // so the dominant n^3/3 flops run as kInvOuter-row GEMMs, each panel of X read
 // by kInvTiles tile rows.  Measured (total of the three kernels, 12,800 /
-// 25,600 columns): 40 / 188 ms at 4 tiles, 39 / 180 ms at 16, 42 / 180 ms at 32
-// (the near products grow as fast as the far one shrinks).  Pf holds up to 4
-// split-K slices of (e2 - o2) x (n - e2); Pn up to 2 split-K slices of 64 x n
-// (the near product has one tile row, so its K range is split in two where
-// its output tiles alone give fewer than about two blocks per compute unit;
-// measured against 1 and 4 slices: 340 vs 342 / 342 ms for QR + inverse on
-// the 8x8-box system, 696 vs 699 / 695 ms on the 4^3-box float32 one, since
-// every slice is one more memory round trip for the block-row kernel).
+// 25,600 columns): 40 / 188 ms at 4 tiles, 39 / 180 ms at 16, 42 / 180 ms at 32.
+// The near sums of all the outer block's rows are kept in Pn: once block row I is
+// solved, R[o2:o, I] X_I is added to every block row above it, a product of K = 64
+// with as many tile rows as are left.  (Formed per block row instead, just before it
+// is solved, the near product has one tile row and K up to kInvOuter, a long chain on
+// few workgroups: 16.4 and 20.7 us on average with the far products at 1,600 and 3,200
+// columns, 12.3 and 15.9 this way, even at 12,800; Helmholtz solve 24.4 -> 24.0 ms.)
+// Pf holds up to 4 split-K slices of (e2 - o2) x (n - e2), Pn is (e2 - o2) x (n - o2).
 constexpr int64_t kInvTiles = 16;
 constexpr int64_t kInvOuter = kInvTiles * kTile;
+
+// the leading w columns of w rows, zeroed
+template <typename T>
+__global__ void k_zero_cols(T* __restrict__ p, int64_t ld, int64_t w) {
+  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < w * w; e += (int64_t)gridDim.x * blockDim.x)
+    p[e / w * ld + e % w] = T(0);
+}
 
 template <typename T>
 rfmls_status invert_upper(rfmls_handle* h, const T* R, T* X, T* Pf, T* Pn, int64_t n, int64_t nt,
@@ -370,6 +367,7 @@ rfmls_status invert_upper(rfmls_handle* h, const T* R, T* X, T* Pf, T* Pn, int64
     int nzf = 0;
     const int64_t ldf = far > 0 ? far : 1;
     const int64_t zsf = (e2 - o2) * ldf;
+    const int64_t ldn = n - o2;
     if (far > 0) {
       // K slices only where the (e2 - o2) x far output has too few tiles for
       // about two blocks per compute unit (at most 4 slices, each >= kslice)
@@ -404,47 +402,37 @@ rfmls_status invert_upper(rfmls_handle* h, const T* R, T* X, T* Pf, T* Pn, int64
     for (int64_t I = (e2 - 1) / kTile; I >= I2 * kInvTiles; --I) {
       const int64_t o = I * kTile;
       const int64_t b = n - o < kTile ? n - o : kTile;
-      const int64_t kn = e2 - o - b;  // solved rows of this outer block below row block I
-      const int64_t ldn = n - o - kTile > 0 ? n - o - kTile : 1;
-      int nzn = 0;
-      const int64_t zsn = kTile * ldn;
-      if (kn > 0) {
-        GemmArgs<T> g;
-        g.M = b;
-        g.N = n - o - kTile;
-        g.K = kn;
-        g.A = R + o * n + o + kTile;
-        g.lda = n;
-        g.B = X + (o + kTile) * n + o + kTile;
-        g.ldb = n;
-        g.C = Pn;
-        g.ldc = ldn;
-        g.b_upper = 1;
-        g.b_lower_zero = 1;
-        // one tile row: split K (slices of at least 64 rows, at most 2) until
-        // the tiles times the slices give about two blocks per compute unit
-        const int64_t tiles = (g.N + kTile - 1) / kTile;
-        int64_t want = (2 * (int64_t)h->num_cus + tiles - 1) / tiles;
-        if (want > 2) want = 2;
-        int64_t ksn = (kn + want - 1) / want;
-        ksn = (ksn + kTile - 1) / kTile * kTile;
-        nzn = (int)((kn + ksn - 1) / ksn);
-        if (nzn > 1) {
-          g.ksplit = ksn;
-          g.c_zstride = zsn;
-        }
-        if (nzn < 1) nzn = 1;
-        Trace tr(h, "inv_gemm_near", (double)sizeof(T) * ((double)b * kn + (double)kn * g.N + (double)nzn * b * g.N),
-                 2.0 * (double)b * kn * (double)g.N);
-        RFMLS_HIP(h, (gemm_clean<T, GemmRole::Inverse>(g, h->stream)));
-      }
+      const bool first = o + b == e2;
       {
         Trace tr(h, "inv_blockrow",
-                 (double)sizeof(T) * ((double)(nzf + nzn + 1) * kTile * (double)(n - o) + (double)kTile * (n - o)),
+                 (double)sizeof(T) * ((double)(nzf + (first ? 1 : 2)) * kTile * (double)(n - o) + (double)kTile * (n - o)),
                  (double)kTile * kTile * (double)(n - o));
         hipLaunchKernelGGL(k_inv_blockrow<T>, dim3(ceil_div(n - o, kInvCols)), dim3(kInvCols * kInvLanes), 0, h->stream, R,
-                           n, I, kn > 0 ? (const T*)Pn : (const T*)nullptr, ldn, nzn, zsn,
+                           n, I, first ? (const T*)nullptr : (const T*)(Pn + (o - o2) * ldn + o + kTile - o2), ldn,
                            (const T*)Pf, nzf, ldf, zsf, o - o2, e2, X);
+      }
+      if (o > o2) {
+        // the columns up to here are first reached by this block row's product
+        // or a later one's and start as zeros, the others as this first product
+        if (first) {
+          const unsigned gz = ceil_div((o - o2) * (o - o2), 256);
+          hipLaunchKernelGGL(k_zero_cols<T>, dim3(gz < 1024 ? gz : 1024), dim3(256), 0, h->stream, Pn, ldn, o - o2);
+        }
+        GemmArgs<T> g;
+        g.M = o - o2;
+        g.N = n - o;
+        g.K = b;
+        g.A = R + o2 * n + o;
+        g.lda = n;
+        g.B = X + o * n + o;  // zeros below the diagonal of its first block
+        g.ldb = n;
+        g.C = Pn + (o - o2);
+        g.ldc = ldn;
+        g.beta = first ? T(0) : T(1);
+        Trace tr(h, "inv_gemm_near",
+                 (double)sizeof(T) * ((double)g.M * b + (double)b * g.N + (first ? 1.0 : 2.0) * (double)g.M * g.N),
+                 2.0 * (double)b * (double)g.M * (double)g.N);
+        RFMLS_HIP(h, (gemm_clean<T, GemmRole::Inverse>(g, h->stream)));
       }
       RFMLS_HIP(h, hipGetLastError());
     }
@@ -508,8 +496,8 @@ rfmls_status finish_precond(rfmls_handle* h, rfmls_precond_t* P, int check_rank,
   void* p_w;
   RFMLS_CHECK(workspace(h, WS_TRSM, sizeof(double) * (size_t)n * (size_t)n, &p_x));
   const int64_t kslice = 512;
-  // 4 far slices of kInvOuter x n and 2 near slices of 64 x n
-  RFMLS_CHECK(workspace(h, WS_QR_W, sizeof(double) * (size_t)(4 * kInvOuter + 2 * kTile) * (size_t)n, &p_w));
+  // 4 far slices and the near sums, kInvOuter x n each
+  RFMLS_CHECK(workspace(h, WS_QR_W, sizeof(double) * (size_t)(5 * kInvOuter) * (size_t)n, &p_w));
   if (invert_f32) {
     // X and R in float32 share the float64 n x n slot
     float* X32 = (float*)p_x;

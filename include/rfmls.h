@@ -319,7 +319,7 @@ rfmls_status rfmls_solve_backward(rfmls_handle *h, const rfmls_csr *A, const rfm
                                   const rfmls_opts *opts, rfmls_info *info);
 
 /* ---- Panel factorisation of the QR (Alg. 1 step 3) ----
- * mode 0 (default): 64-column panels of at least 1024 rows are factored by
+ * mode 0 (default): 64-column panels of at least 128 rows are factored by
  * CholeskyQR2 on column-scaled Gram matrices followed by the reconstruction of
  * their Householder vectors (a fixed number of passes over the panel instead
  * of one grid-wide exchange per column), in float64 arithmetic for float64 and
@@ -350,8 +350,8 @@ rfmls_status rfmls_qr_lookahead(rfmls_handle *h, int enable);
  * With tuning on (the default), the first lockstep solve, backward pass or
  * rfmls_form_B that uses a matrix of a given shape (rows, columns, stored
  * entries) on a handle times every candidate launch shape of its 32-column
- * sparse products (the width of the input window staged in LDS) on that
- * matrix, and keeps the fastest for later calls on the handle.  The candidates
+ * sparse products (the width of the input window staged in LDS, or the order
+ * in which pieces of rows with equal column runs are dispatched) on that matrix, and keeps the fastest for later calls on the handle.  The candidates
  * change neither the order of any sum nor the rows each block handles, so
  * results do not depend on the choice.  Tuning synchronises the stream once
  * per matrix shape; off, the hand-picked shape is used. */

@@ -57,17 +57,48 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // l = 16 lk + lr holds A[lr][lk] and B[lk][lr]; accumulator register r holds
 // D[lk + 4 r][lr].
 
+// A Gram is kept as its ten upper 16 x 16 tiles (a, b), a <= b, each row-major, which
+// is also the order r * 64 + lane of the accumulator registers.
+constexpr int kGramTiles = 10;
+constexpr int kGramLen = kGramTiles * 256;
+__device__ __forceinline__ int gram_at(int i, int j) {  // entry (i, j), either triangle
+  const int a = i >> 4, b = j >> 4;
+  const bool up = a <= b;
+  const int a2 = up ? a : b, b2 = up ? b : a, ii = up ? i : j, jj = up ? j : i;
+  return (a2 * 4 - a2 * (a2 - 1) / 2 + b2 - a2) * 256 + (ii & 15) * 16 + (jj & 15);
+}
+// gp = the sum of the four wavefronts' tiles in wave order; S holds 4 kGramLen doubles.
+// One pass out and one back: adding them one wavefront at a time in a shared copy took
+// a read, an add and a write of every entry and a barrier per wavefront (1,600 / 3,200
+// column sketches, with W's loads issued together: Gram 7.5 -> 5.5 us, fused apply + Gram
+// 16.0 / 18.0 -> 10.5 / 12.2, apply 8.7 / 10.2 -> 5.3 / 7.1; Helmholtz solve 24.1 -> 23.5 ms).
+__device__ __forceinline__ void sum_tiles(const v4d (&acc)[kGramTiles], double* __restrict__ S,
+                                          double* __restrict__ gp) {
+  const int t = threadIdx.x;
+  const int lane = t & 63, w = t >> 6;
+#pragma unroll
+  for (int q = 0; q < kGramTiles; ++q)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) S[w * kGramLen + q * 256 + r * 64 + lane] = acc[q][r];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kGramTiles; ++q) {
+    const int e = q * 256 + t;
+    gp[e] = ((S[e] + S[kGramLen + e]) + S[2 * kGramLen + e]) + S[3 * kGramLen + e];
+  }
+}
+
 // Partial Gram of rows [z S, (z + 1) S) of P (S = 64 NG) on the matrix cores.
 // Wave w takes the 16 NG rows from z S + 16 NG w and accumulates the ten upper
 // 16 x 16 tiles of their Gram; each lane loads its operands straight from P
 // (lane (lr, lk) reads row 4 s + lk, columns 16 q + lr: every 16 lanes read
 // 128 contiguous bytes), no LDS staging.  The four waves' tiles are then added
-// in wave order through LDS and the full symmetric 64 x 64 partial written.
+// in wave order through LDS (sum_tiles).
 template <typename TS, int NG>
 __global__ void __launch_bounds__(256) k_cq_gram(const TS* __restrict__ P, int64_t ld, int64_t M,
                                                  double* __restrict__ Gpart, const int* __restrict__ status) {
   if (status && *status) return;
-  __shared__ double S[kNb][kNb + 1];
+  __shared__ double S[4 * kGramLen];
   const int t = threadIdx.x;
   const int lane = t & 63, w = t >> 6;
   const int lr = lane & 15, lk = lane >> 4;
@@ -97,28 +128,7 @@ __global__ void __launch_bounds__(256) k_cq_gram(const TS* __restrict__ P, int64
       for (int b = a; b < 4; ++b, ++tile)
         acc[tile] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[s][a], x[s][b], acc[tile], 0, 0, 0);
   }
-  // tile (a, b): D[lk + 4 r][lr] = G[16 a + lk + 4 r][16 b + lr]
-  for (int ww = 0; ww < 4; ++ww) {
-    if (w == ww) {
-      int tile = 0;
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = a; b < 4; ++b, ++tile)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            double& g = S[16 * a + lk + 4 * r][16 * b + lr];
-            g = ww == 0 ? acc[tile][r] : g + acc[tile][r];
-          }
-    }
-    __syncthreads();
-  }
-  double* gp = Gpart + (int64_t)blockIdx.x * kNb * kNb;
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, j = e % kNb;
-    // upper tiles hold G[i][j] for tile(i) <= tile(j); the rest by symmetry
-    gp[e] = (i >> 4) <= (j >> 4) ? S[i][j] : S[j][i];
-  }
+  sum_tiles(acc, S, Gpart + (int64_t)blockIdx.x * kGramLen);
 }
 
 // G = sum of the nslab partials in slab order.  Block b takes entries
@@ -133,7 +143,8 @@ __global__ void __launch_bounds__(256) k_cq_reduce(const double* __restrict__ Gp
   const int el = t & 15, zq = t >> 4;
   const int e = blockIdx.x * 16 + el;
   double s = 0.0;
-  for (int z = zq; z < nslab; z += 16) s += Gpart[(int64_t)z * kNb * kNb + e];
+#pragma unroll 4
+  for (int z = zq; z < nslab; z += 16) s += Gpart[(int64_t)z * kGramLen + e];
   red[zq][el] = s;
   __syncthreads();
   if (t < 16) {
@@ -438,8 +449,8 @@ __global__ void __launch_bounds__(256) k_cq_factor(const double* __restrict__ G,
   const int er = t >> 6, ec = t & 63;
   double gv[16];
 #pragma unroll
-  for (int q = 0; q < 16; ++q) gv[q] = G[(er + 4 * q) * kNb + ec];
-  const double gjj = G[ec * (kNb + 1)];
+  for (int q = 0; q < 16; ++q) gv[q] = G[gram_at(er + 4 * q, ec)];
+  const double gjj = G[gram_at(ec, ec)];
   if (pass == 2) {
     // the panel's top block (Q1's) into M3, R1 into M2
     double pv[16], rv[16];
@@ -618,7 +629,8 @@ __global__ void __launch_bounds__(256) k_cq_apply(TS* __restrict__ P, int64_t ld
   const int64_t rc = ra < M ? ra : M - 1;  // rows past M: row M - 1, replaced by zeros
   double a[16];
   load_arow<TS, V16>(a, P + rc * ld, lk, ra < M);
-  for (int e = t; e < kNb * kNb; e += 256) Ws[e / kNb][e % kNb] = W[e];
+#pragma unroll
+  for (int q = 0; q < kNb * kNb / 256; ++q) Ws[(t >> 6) + 4 * q][t & 63] = W[t + 256 * q];
   __syncthreads();
   v4d acc[4];
   group_times_upper<TS>(a, Ws, lr, lk, acc);
@@ -643,8 +655,8 @@ __global__ void __launch_bounds__(256) k_cq_apply_gram(TS* __restrict__ P, int64
                                                        const double* __restrict__ W, double* __restrict__ Gpart,
                                                        const int* __restrict__ status) {
   if (*status) return;
-  __shared__ double Ws[kNb][kNb + 1];
-  __shared__ double S[kNb][kNb + 1];
+  __shared__ double S[4 * kGramLen];
+  double(*Ws)[kNb + 1] = (double(*)[kNb + 1])S;
   const int t = threadIdx.x;
   const int lane = t & 63, w = t >> 6;
   const int lr = lane & 15, lk = lane >> 4;
@@ -657,7 +669,8 @@ __global__ void __launch_bounds__(256) k_cq_apply_gram(TS* __restrict__ P, int64
     const int64_t rc = ra < M ? ra : M - 1;
     load_arow<TS, V16>(ag[grp], P + rc * ld, lk, ra < M);
   }
-  for (int e = t; e < kNb * kNb; e += 256) Ws[e / kNb][e % kNb] = W[e];
+#pragma unroll
+  for (int q = 0; q < kNb * kNb / 256; ++q) Ws[(t >> 6) + 4 * q][t & 63] = W[t + 256 * q];
   __syncthreads();
   v4d gacc[10];
 #pragma unroll
@@ -692,26 +705,8 @@ __global__ void __launch_bounds__(256) k_cq_apply_gram(TS* __restrict__ P, int64
           gacc[tile] = __builtin_amdgcn_mfma_f64_16x16x4f64(acc[a2][r], acc[b][r], gacc[tile], 0, 0, 0);
     }
   }
-  for (int ww = 0; ww < 4; ++ww) {
-    if (w == ww) {
-      int tile = 0;
-#pragma unroll
-      for (int a2 = 0; a2 < 4; ++a2)
-#pragma unroll
-        for (int b = a2; b < 4; ++b, ++tile)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            double& g = S[16 * a2 + lk + 4 * r][16 * b + lr];
-            g = ww == 0 ? gacc[tile][r] : g + gacc[tile][r];
-          }
-    }
-    __syncthreads();
-  }
-  double* gp = Gpart + (int64_t)blockIdx.x * kNb * kNb;
-  for (int e = t; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, j = e % kNb;
-    gp[e] = (i >> 4) <= (j >> 4) ? S[i][j] : S[j][i];
-  }
+  __syncthreads();  // every wavefront is done with Ws
+  sum_tiles(gacc, S, Gpart + (int64_t)blockIdx.x * kGramLen);
 }
 
 }  // namespace
@@ -749,7 +744,7 @@ static rfmls_status cholqr_panel(rfmls_handle* h, TS* P, int64_t ld, int64_t M, 
   else
     hipLaunchKernelGGL((k_cq_gram<TS, 2>), dim3((unsigned)nslab), dim3(256), 0, st, (const TS*)P, ld, M, Gpart,
                        (const int*)nullptr);
-  hipLaunchKernelGGL(k_cq_reduce, dim3(kNb * kNb / 16), dim3(256), 0, st, (const double*)Gpart, (int)nslab, G, status,
+  hipLaunchKernelGGL(k_cq_reduce, dim3(kGramLen / 16), dim3(256), 0, st, (const double*)Gpart, (int)nslab, G, status,
                      1);
   hipLaunchKernelGGL(k_cq_factor<TS>, dim3(1), dim3(256), 0, st, (const double*)G, Wk, Rc, P, ld, tau, status, 1,
                      min_ratio1);
@@ -767,7 +762,7 @@ static rfmls_status cholqr_panel(rfmls_handle* h, TS* P, int64_t ld, int64_t M, 
   else
     hipLaunchKernelGGL((k_cq_apply_gram<TS, false, 2>), dim3((unsigned)nslab), dim3(256), 0, st, P, ld, M,
                        (const double*)Wk, Gpart, (const int*)status);
-  hipLaunchKernelGGL(k_cq_reduce, dim3(kNb * kNb / 16), dim3(256), 0, st, (const double*)Gpart, (int)nslab, G, status,
+  hipLaunchKernelGGL(k_cq_reduce, dim3(kGramLen / 16), dim3(256), 0, st, (const double*)Gpart, (int)nslab, G, status,
                      0);
   hipLaunchKernelGGL(k_cq_factor<TS>, dim3(1), dim3(256), 0, st, (const double*)G, Wk, Rc, P, ld, tau, status, 2,
                      min_ratio2);

@@ -344,7 +344,7 @@ __global__ void k_unpack_tiles(const TS* __restrict__ pk, int64_t n, int64_t nt,
 // with as many tile rows as are left.  (Formed per block row instead, just before it
 // is solved, the near product has one tile row and K up to kInvOuter, a long chain on
 // few workgroups: 16.4 and 20.7 us on average with the far products at 1,600 and 3,200
-// columns, 12.3 and 15.9 this way, even at 12,800; Helmholtz solve 24.4 -> 24.0 ms.)
+// columns, 12.3 and 15.9 this way (10.2 and 14.1 with C read in batches), even at 12,800; Helmholtz solve 24.4 -> 24.0 ms.)
 // Pf holds up to 4 split-K slices of (e2 - o2) x (n - e2), Pn is (e2 - o2) x (n - o2).
 constexpr int64_t kInvTiles = 16;
 constexpr int64_t kInvOuter = kInvTiles * kTile;

@@ -36,7 +36,8 @@ constexpr int kMaxNb = 64;
 // below which a panel falls back to the unblocked kernel (scaled panel condition
 // near u^{-1/2}).  The unblocked kernel exchanges sums between workgroups for every
 // column, 190 to 230 us a panel at 128 to 1,024 rows, CholeskyQR2's passes and
-// factorisations 120 us (2x2-box solve 3.0 -> 2.4 ms against a limit of 1,024 rows).
+// factorisations about 100 us (2x2-box solve 3.0 -> 2.4 ms against a limit of 1,024
+// rows, when they took 120).
 constexpr int64_t kCholqrMinRows = 128;
 constexpr double kCholqrMinPivot = 1e-7;
 

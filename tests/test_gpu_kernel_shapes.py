@@ -245,3 +245,18 @@ def test_sketch_of_two_span_rows(s, big, dtype):
     ref, _ = countsketch.sketch_dense(ptr, col, val, ho, so, s, n)
     assert np.array_equal(hg.cpu().numpy(), ho) and np.array_equal(sg.cpu().numpy(), so)
     assert np.array_equal(SA.cpu().numpy(), ref if dtype == "f64" else ref.astype(np.float32))
+
+
+# X = R^{-1} over outer blocks of 1,024 rows whose near sums are carried from block
+# row to block row: one outer block with a ragged tail, exactly one, and two or three
+# with the last ragged.  Each column is a back substitution: |R X - I| <= n u |R||X|
+# and as much again for the product taken here; 4 n u allows twice that.
+@pytest.mark.parametrize("n", [1, 64, 65, 200, 1024, 1025, 1100, 2112, 2113])
+def test_inverse_over_outer_blocks(n):
+    rng = np.random.default_rng(n)
+    U = np.triu(rng.standard_normal((n, n)), 1) / np.sqrt(n) + np.diag(1.0 + rng.random(n))
+    h = R.Handle(device="cuda:0")
+    P = R.rfmls_precond_import_R(h, torch.tensor(U, device="cuda"))
+    X = R.rfmls_precond_export_Rinv(h, P).cpu().numpy()
+    err = np.linalg.norm(U @ X - np.eye(n))
+    assert err <= 4 * n * 2.0 ** -53 * np.linalg.norm(np.abs(U) @ np.abs(X)), err

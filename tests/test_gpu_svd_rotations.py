@@ -1,0 +1,50 @@
+"""The plane rotations of the SVD preconditioner at the ends of float64's range and
+to its last bits, against LAPACK's SVD of the oracle's sketch."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2409_15818_amd as R
+from oracle import countsketch
+from rfmgen import csr_from_dense, dense_with_condition
+
+pytestmark = pytest.mark.gpu
+
+
+def _sketch(Ad, s, seed):
+    m, n = Ad.shape
+    rp, col, val = csr_from_dense(Ad, keep_zeros=True)
+    h, sign = countsketch.hash_sign(m, s, seed)
+    return countsketch.sketch_dense(rp, col, val, h, sign, s, n)[0]
+
+
+# All columns so short that twice a pair's product is subnormal near convergence:
+# scaling by a power of two scales every rounding, so the singular values are those of
+# the unscaled sketch to the usual 2e-12 of sigma_1.
+@pytest.mark.parametrize("exponent", [-498, -250, 400])
+def test_svd_of_a_scaled_sketch(exponent):
+    n = 20
+    SA = _sketch(dense_with_condition(200, n, 1e3, seed=3), 60, 5)
+    want = np.linalg.svd(SA, compute_uv=False)
+    h = R.Handle(device="cuda:0")
+    P = R.rfmls_precond_svd(h, torch.tensor(SA * 2.0 ** exponent, device="cuda"), n)
+    sig = np.sort(R.rfmls_precond_export_sigma(h, P).cpu().numpy())[::-1]
+    assert P.status == 0 and P.rank == n and P.off <= 1.0
+    assert np.max(np.abs(sig * 2.0 ** -exponent - want)) <= 2e-12 * want[0]
+    U = SA @ (R.rfmls_precond_export_P(h, P).cpu().numpy() * 2.0 ** exponent)
+    assert np.max(np.abs(U.T @ U - np.eye(n))) <= n * 2.0 ** -53 * want[0] / want[-1] + 1e-12
+
+
+# One rotation makes two columns orthogonal: formed to the last bits it leaves a cosine
+# of some 4 u from t and 3 u each from applying it and from its measurement, against
+# the tolerance of 16 u for two columns, so the second sweep rotates nothing.
+def test_svd_of_two_columns_takes_one_rotation():
+    h = R.Handle(device="cuda:0")
+    sweeps = []
+    for seed in range(24):
+        SA = np.random.default_rng(seed).standard_normal((16, 2)) @ np.array([[1.0, 0.5], [0.0, 0.7]])
+        P = R.rfmls_precond_svd(h, torch.tensor(SA, device="cuda"), 2)
+        assert P.status == 0 and P.rank == 2 and P.off <= 16 * 2.0 ** -53
+        sweeps.append(P.sweeps)
+    assert max(sweeps) <= 2, sweeps

@@ -1143,6 +1143,11 @@ rfmls_status sort_rows(rfmls_handle* h, int64_t s, int64_t n, int64_t kOuter, T*
 template <typename T>
 rfmls_status qr_impl(rfmls_handle* h, int64_t s, int64_t n, int64_t n_room, T* SA, int64_t ld, T* tau_out) {
   const int64_t kOuter = outer_width<T>(n);
+  // a sketch with more rows than a panel's grid can hold is refused as it stands, also
+  // where sorted rows would leave every panel fewer
+  PanelShape widest;
+  int64_t blocks = 0;
+  RFMLS_CHECK(pick_panel_shape<T>(h, s, &widest, &blocks));
   const int64_t nsp_in_max = inner_slices_max(s);
   const int64_t nsp_out_max = outer_slices_max(s);
   void *p_tau, *p_part, *p_wz, *p_w, *p_wp, *p_to, *p_in;

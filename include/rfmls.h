@@ -349,12 +349,14 @@ rfmls_status rfmls_qr_lookahead(rfmls_handle *h, int enable);
 /* ---- Autotuning of launch shapes ----
  * With tuning on (the default), the first lockstep solve, backward pass or
  * rfmls_form_B that uses a matrix of a given shape (rows, columns, stored
- * entries) on a handle times every candidate launch shape of its 32-column
- * sparse products (the width of the input window staged in LDS, or the order
- * in which pieces of rows with equal column runs are dispatched) on that matrix, and keeps the fastest for later calls on the handle.  The candidates
- * change neither the order of any sum nor the rows each block handles, so
- * results do not depend on the choice.  Tuning synchronises the stream once
- * per matrix shape; off, the hand-picked shape is used. */
+ * entries) and kind on a handle times every candidate launch shape of its
+ * 32-column sparse products on that matrix and keeps the fastest for later calls
+ * on the handle.  A matrix whose consecutive rows hold the same column runs is
+ * multiplied in pieces of such rows, and the order in which they are dispatched is
+ * tuned; for any other the width of the input window staged in LDS is.  The
+ * candidates change neither the order of any sum nor the rows each block handles,
+ * so results do not depend on the choice.  Tuning synchronises the stream once
+ * per matrix shape and kind; off, the hand-picked shape is used. */
 typedef struct {
   char kernel[16];        /* kernel family ("spmm")                         */
   int64_t rows, cols, nnz; /* the matrix it was tuned on                     */

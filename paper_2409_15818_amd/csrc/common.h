@@ -29,9 +29,11 @@ struct Workspace {
 
 namespace rfmls {
 // One autotuned launch shape: the kernel family, the shape of the operand it
-// was tuned on, the candidate chosen and its time beside the hand-picked one's.
+// was tuned on and which of the family's kernels takes it (runs), the candidate
+// chosen and its time beside the hand-picked one's.
 struct TuneRec {
   char kernel[16];
+  bool runs;
   int64_t rows, cols, nnz;
   int choice;
   char desc[48];

@@ -1411,12 +1411,13 @@ rfmls_status tri_block(BCtx& c, int trans, const double* in, double* out, const 
 }
 
 // The tuned launch shape of products with M on this handle, if a matrix of M's
-// shape (rows, columns, stored entries) has been tuned: a rebuilt transpose
-// (same matrix at a new address) is not tuned again.
+// shape (rows, columns, stored entries) that the same kernel takes has been tuned: a
+// rebuilt transpose (same matrix at a new address) is not tuned again, a matrix of
+// another structure has candidates of its own.
 static bool spmm_lookup(rfmls_handle* h, const rfmls_csr* M, bool runs, SpmmShape* out) {
   if (!h->tune) return false;
   for (const TuneRec& t : h->tuned)
-    if (t.rows == M->m && t.cols == M->n && t.nnz == M->nnz && !strcmp(t.kernel, "spmm")) {
+    if (t.rows == M->m && t.cols == M->n && t.nnz == M->nnz && t.runs == runs && !strcmp(t.kernel, "spmm")) {
       const std::vector<SpmmShape> cands = spmm_candidates(runs);
       if (t.choice >= 0 && t.choice < (int)cands.size()) {
         *out = cands[t.choice];
@@ -1488,8 +1489,8 @@ static rfmls_status spmm_launch(BCtx& c, const rfmls_csr* M, const SpmmShape& sh
                                 const double* prev, double* out, double* sq, const BlockState* stp, int* nblk);
 static const RunMat& run_mat(const BCtx& c, const rfmls_csr* M) { return M == c.A ? c.rA : c.rAT; }
 
-// Autotuner of the SpMM launch shape (window width) for M: the first time a
-// matrix of M's shape is used on this handle (with tuning on), every candidate of
+// Autotuner of the SpMM launch shape for M: the first time a
+// matrix of M's shape and kernel is used on this handle (with tuning on), every candidate of
 // spmm_candidates runs on M with a zero input block of 32 columns into
 // scratch (xin: M->n x 32, out: M->m x 32, sq: the partials), once to warm up
 // and then three times between HIP events; the candidate with the smallest
@@ -1531,6 +1532,7 @@ static rfmls_status spmm_tune(BCtx& c, const rfmls_csr* M, double* xin, double* 
     if (med[k] < med[best]) best = k;
   TuneRec rec{};
   snprintf(rec.kernel, sizeof(rec.kernel), "spmm");
+  rec.runs = runs;
   rec.rows = M->m;
   rec.cols = M->n;
   rec.nnz = M->nnz;

@@ -326,7 +326,8 @@ rfmls_status run_sketch(rfmls_handle* h, const rfmls_csr* A, int64_t s, const in
                         rfmls_dtype dt, void* SA, int64_t ld);
 rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int32_t* col,
                            double* val);
-rfmls_status scan_counts(rfmls_handle* h, const int32_t* count, int64_t n, int64_t* ptr);
+// (nothing where *skip is set, when given)
+rfmls_status scan_counts(rfmls_handle* h, const int32_t* count, int64_t n, int64_t* ptr, const int* skip = nullptr);
 // Householder QR of SA (s x n); columns n .. n_room-1 (n_room <= ld) may be
 // used as scratch; tau_out (n values of SA's dtype, device) receives every
 // reflector's tau when given
@@ -396,7 +397,12 @@ rfmls_status unpack_precond(rfmls_handle* h, const rfmls_precond_t* P, double* X
 // kMaxRuns), run k starting at column rcol[i kMaxRuns + k] and ending before
 // entry rend[i kMaxRuns + k] of the row
 constexpr int kMaxRuns = 8;
-void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol, int32_t* rend);
+// skip (optional, device): leaves everything unwritten where *skip is set
+void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol, int32_t* rend,
+               const int* skip = nullptr);
+// *bad = whether a sample of M's rows rules out pieces of rows with equal column runs
+// (csr.hip); *mode = 0
+void probe_pieces(hipStream_t st, const rfmls_csr* M, int* bad, int* mode);
 rfmls_status run_solve(rfmls_handle* h, const rfmls_csr* A, const rfmls_csr* AT,
                        const rfmls_precond_t* P, const double* B, int64_t ldb, int64_t nrhs,
                        double* X, int64_t ldx, double* Rout, int64_t ldr, const rfmls_opts* o,

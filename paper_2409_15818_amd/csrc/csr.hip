@@ -104,6 +104,7 @@ __global__ void __launch_bounds__(256)
     k_tr_groups(int64_t m, int64_t n, const int32_t* __restrict__ nrun, const int32_t* __restrict__ rcol,
                 const int32_t* __restrict__ rend, unsigned long long* __restrict__ gstart, int32_t* __restrict__ elen,
                 int* __restrict__ bad) {
+  if (*bad) return;  // (what it leaves unwritten is not read then)
   const int lane = threadIdx.x & 63;
   const int64_t ng = (m + kPieceRows - 1) / kPieceRows;
   const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -124,9 +125,59 @@ __global__ void __launch_bounds__(256)
     if (wrong) atomicOr(bad, 1);
   }
 }
-__global__ void k_tr_clear(int* bad, int* mode) {
-  *bad = 0;
-  *mode = 0;
+// bad = 1 where a sample says that the rows have no pieces to speak of, mode = 0.  The
+// sample is up to 64 groups spread over the matrix; a row of another length, first or
+// last column than the row before starts a piece.  More than a quarter of the sampled
+// rows doing so is far from what either use of the pieces asks (one in eight entries
+// here, one in sixteen rows in the lockstep products): the kernels that find the runs
+// and pieces then return at once.  One workgroup, four groups a wavefront.
+// Without it a 2,000,000 x 20,000 matrix of 12 scattered entries a row spent 0.55 of
+// 6.95 ms on runs that the entry-by-entry transpose then did not use.
+constexpr int kProbeGroups = 64;
+__global__ void __launch_bounds__(1024)
+    k_probe_pieces(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int64_t m, int* bad,
+                   int* mode) {
+  __shared__ int found[16][2];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int64_t ng = (m + kPieceRows - 1) / kPieceRows;
+  const int64_t step = ng > kProbeGroups ? ng / kProbeGroups : 1;
+  int64_t lo[4], hi[4];
+  bool live[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int64_t row = (int64_t)(w + 16 * q) * step * kPieceRows + lane;
+    live[q] = row < m;
+    lo[q] = row_ptr[live[q] ? row : m];
+    hi[q] = row_ptr[live[q] ? row + 1 : m];
+  }
+  int first[4], last[4], starts = 0, rows = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    first[q] = hi[q] > lo[q] ? col[lo[q]] : -1;
+    last[q] = hi[q] > lo[q] ? col[hi[q] - 1] : -1;
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int len = (int)(hi[q] - lo[q]);
+    const bool other = __shfl_up(len, 1, 64) != len || __shfl_up(first[q], 1, 64) != first[q] ||
+                       __shfl_up(last[q], 1, 64) != last[q];
+    starts += __popcll(__ballot(live[q] && (lane == 0 || other)));
+    rows += __popcll(__ballot(live[q]));
+  }
+  if (lane == 0) {
+    found[w][0] = starts;
+    found[w][1] = rows;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int s = 0, r = 0;
+    for (int q = 0; q < 16; ++q) {
+      s += found[q][0];
+      r += found[q][1];
+    }
+    *bad = 4 * s > r;
+    *mode = 0;
+  }
 }
 // mode = 1: every row described, and the pieces' entry lists fit their buffer
 __global__ void k_tr_mode(const int* __restrict__ bad, const int64_t* __restrict__ eptr, int64_t ng, int64_t cap,
@@ -214,39 +265,45 @@ __global__ void __launch_bounds__(256)
   __shared__ double tile[kPieceRows][65];
   __shared__ int64_t rp[kPieceRows];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  each_piece(blockIdx.x, m, gstart, eptr, nrun, rend, [&](int64_t row, int nr, int len, int64_t slot) {
-    __syncthreads();  // the previous piece's tiles are out
-    if (threadIdx.x < nr) rp[threadIdx.x] = row_ptr[row + threadIdx.x];
-    __syncthreads();
-    for (int e0 = 64 * blockIdx.y; e0 < len; e0 += 64 * gridDim.y) {
-      const int e = e0 + lane;
-      double v[16];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int r = w + 4 * q;
-        v[q] = (r < nr && e < len) ? val[rp[r] + e] : 0.0;
-      }
-      int32_t p[16];  // of columns e0 + w + 4 q
-#pragma unroll
-      for (int q = 0; q < 16; ++q) p[q] = e0 + w + 4 * q < len ? pos[slot + e0 + w + 4 * q] : 0;
-#pragma unroll
-      for (int q = 0; q < 16; ++q) tile[w + 4 * q][lane] = v[q];
+  const int64_t ng = (m + kPieceRows - 1) / kPieceRows;
+  for (int64_t g = blockIdx.x; g < ng; g += gridDim.x)
+    each_piece(g, m, gstart, eptr, nrun, rend, [&](int64_t row, int nr, int len, int64_t slot) {
+      __syncthreads();  // the previous piece's tiles are out
+      if (threadIdx.x < nr) rp[threadIdx.x] = row_ptr[row + threadIdx.x];
       __syncthreads();
+      for (int e0 = 64 * blockIdx.y; e0 < len; e0 += 64 * gridDim.y) {
+        const int e = e0 + lane;
+        double v[16];
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int c = w + 4 * q;
-        if (e0 + c < len && lane < nr) {
-          const int64_t o = (int64_t)p[q] + lane;
-          at_val[o] = tile[lane][c];
-          at_col[o] = (int32_t)(row + lane);
+        for (int q = 0; q < 16; ++q) {
+          const int r = w + 4 * q;
+          v[q] = (r < nr && e < len) ? val[rp[r] + e] : 0.0;
         }
+        int32_t p[16];  // of columns e0 + w + 4 q
+#pragma unroll
+        for (int q = 0; q < 16; ++q) p[q] = e0 + w + 4 * q < len ? pos[slot + e0 + w + 4 * q] : 0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) tile[w + 4 * q][lane] = v[q];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int c = w + 4 * q;
+          if (e0 + c < len && lane < nr) {
+            const int64_t o = (int64_t)p[q] + lane;
+            at_val[o] = tile[lane][c];
+            at_col[o] = (int32_t)(row + lane);
+          }
+        }
+        __syncthreads();
       }
-      __syncthreads();
-    }
-  });
+    });
 }
 
 }  // namespace
+
+void probe_pieces(hipStream_t st, const rfmls_csr* M, int* bad, int* mode) {
+  hipLaunchKernelGGL(k_probe_pieces, dim3(1), dim3(1024), 0, st, M->row_ptr, M->col, M->m, bad, mode);
+}
 
 rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int32_t* at_col,
                            double* at_val) {
@@ -291,11 +348,11 @@ rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int
     rend = rcol + m * kMaxRuns;
     pos = rend + m * kMaxRuns;
     phist = pos + cap;
-    hipLaunchKernelGGL(k_tr_clear, dim3(1), dim3(1), 0, h->stream, bad, mode);
-    find_runs(h->stream, A, nrun, rcol, rend);
+    probe_pieces(h->stream, A, bad, mode);
+    find_runs(h->stream, A, nrun, rcol, rend, bad);
     hipLaunchKernelGGL(k_tr_groups, dim3(ceil_div(ng, 4)), dim3(256), 0, h->stream, m, n, (const int32_t*)nrun,
                        (const int32_t*)rcol, (const int32_t*)rend, gstart, elen, bad);
-    RFMLS_CHECK(scan_counts(h, elen, ng, eptr));
+    RFMLS_CHECK(scan_counts(h, elen, ng, eptr, bad));
     hipLaunchKernelGGL(k_tr_mode, dim3(1), dim3(1), 0, h->stream, (const int*)bad, (const int64_t*)eptr, ng, cap, mode);
     hipLaunchKernelGGL(k_tr_piece_walk<false>, dim3((unsigned)nch), dim3(256), 0, h->stream, m, n, gc,
                        (const unsigned long long*)gstart, (const int64_t*)eptr, (const int32_t*)nrun,
@@ -319,10 +376,11 @@ rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int
     hipLaunchKernelGGL(k_tr_piece_walk<true>, dim3((unsigned)nch), dim3(256), 0, h->stream, m, n, gc,
                        (const unsigned long long*)gstart, (const int64_t*)eptr, (const int32_t*)nrun,
                        (const int32_t*)rcol, (const int32_t*)rend, phist, (const int64_t*)rp, pos, (const int*)mode);
-    // about eight workgroups per compute unit over the groups
+    // about eight workgroups per compute unit over the groups, at most 32
+    const int64_t most = 32 * (int64_t)h->num_cus;
     int64_t ys = (8 * (int64_t)h->num_cus + ng - 1) / ng;
     if (ys > 8) ys = 8;
-    hipLaunchKernelGGL(k_tr_piece_fill, dim3((unsigned)ng, (unsigned)ys), dim3(256), 0, h->stream, A->row_ptr, A->val,
+    hipLaunchKernelGGL(k_tr_piece_fill, dim3((unsigned)(ng < most ? ng : most), (unsigned)ys), dim3(256), 0, h->stream, A->row_ptr, A->val,
                        m, (const unsigned long long*)gstart, (const int64_t*)eptr, (const int32_t*)nrun,
                        (const int32_t*)rend, (const int32_t*)pos, at_col, at_val, (const int*)mode);
     RFMLS_HIP(h, hipGetLastError());

@@ -469,7 +469,9 @@ constexpr int kSpvLanesShort = 8;
 
 __global__ void __launch_bounds__(kThreads)
     k_find_runs(const int64_t* __restrict__ rp, const int32_t* __restrict__ col, int64_t rows,
-                int32_t* __restrict__ nrun, int32_t* __restrict__ rcol, int32_t* __restrict__ rend) {
+                int32_t* __restrict__ nrun, int32_t* __restrict__ rcol, int32_t* __restrict__ rend,
+                const int* __restrict__ skip) {
+  if (skip && *skip) return;
   const int lane = threadIdx.x & (kSpvLanes - 1);
   const int half = (threadIdx.x & 63) >> 5;
   const int64_t sub = ((int64_t)blockIdx.x * kThreads + threadIdx.x) / kSpvLanes;
@@ -1010,9 +1012,9 @@ rfmls_status tri_apply(rfmls_handle* h, const rfmls_precond_t* P, int trans, con
 }
 
 
-void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol, int32_t* rend) {
+void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol, int32_t* rend, const int* skip) {
   hipLaunchKernelGGL(k_find_runs, dim3(spmv_blocks(M->m)), dim3(kThreads), 0, st, M->row_ptr, M->col, M->m, nrun, rcol,
-                     rend);
+                     rend, skip);
 }
 
 static rfmls_status spmv(Ctx& c, const rfmls_csr* M, const double* x, double* out,

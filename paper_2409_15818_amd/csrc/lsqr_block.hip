@@ -722,6 +722,9 @@ __global__ void __launch_bounds__(kThreads)
     k_run_pieces(int64_t rows, int64_t ncols, const int32_t* __restrict__ nrun, const int32_t* __restrict__ rcol,
                  const int32_t* __restrict__ rend, int32_t* __restrict__ pcount, const int64_t* __restrict__ pptr,
                  int2* __restrict__ pieces, int* __restrict__ bad) {
+  // set before, by the probe or the count pass (whose own setting it leaves counts and
+  // places unwritten that nothing then reads)
+  if (*bad) return;
   const int lane = threadIdx.x & 63;
   const int64_t ngroups = (rows + kPieceRows - 1) / kPieceRows;
   const int64_t nw = (int64_t)gridDim.x * (kThreads / 64);
@@ -738,10 +741,6 @@ __global__ void __launch_bounds__(kThreads)
       pieces[pptr[g] + __popcll(below)] = make_int2((int)(g * kPieceRows + lane), piece_len(starts, lives, lane));
     }
   }
-}
-
-__global__ void k_zero_i32(int32_t* p, int n) {
-  if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
 }
 
 template <int NG>
@@ -1584,7 +1583,6 @@ static rfmls_status spmm_prepare(BCtx& c) {
     q += (b + 7) / 8 * 8;
     return r;
   };
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, c.st, bad, 2);
   for (int i = 0; i < nm; ++i) {
     const rfmls_csr* M = mats[i];
     const int64_t rows = M->m, ng = (rows + kPieceRows - 1) / kPieceRows;
@@ -1596,12 +1594,13 @@ static rfmls_status spmm_prepare(BCtx& c) {
     int32_t* rend = rcol + rows * kMaxRuns;
     *out[i] = RunMat{M->row_ptr, M->val, nrun, rcol, rend, pieces, 0, rows, 1, 0};
     if (rows > 0) {
-      find_runs(c.st, M, nrun, rcol, rend);
+      probe_pieces(c.st, M, bad + i, bad + 2);
+      find_runs(c.st, M, nrun, rcol, rend, bad + i);
       const unsigned g = (unsigned)(ng < 4096 ? (ng + 3) / 4 : 1024);
       hipLaunchKernelGGL(k_run_pieces<false>, dim3(g), dim3(kThreads), 0, c.st, rows, M->n, (const int32_t*)nrun,
                          (const int32_t*)rcol, (const int32_t*)rend, pcount, (const int64_t*)nullptr,
                          (int2*)nullptr, bad + i);
-      RFMLS_CHECK(scan_counts(h, pcount, ng, pptr[i]));
+      RFMLS_CHECK(scan_counts(h, pcount, ng, pptr[i], bad + i));
       hipLaunchKernelGGL(k_run_pieces<true>, dim3(g), dim3(kThreads), 0, c.st, rows, M->n, (const int32_t*)nrun,
                          (const int32_t*)rcol, (const int32_t*)rend, pcount, (const int64_t*)pptr[i], pieces,
                          bad + i);

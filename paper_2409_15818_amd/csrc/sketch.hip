@@ -41,7 +41,8 @@ __global__ void k_count(const int32_t* __restrict__ key, int64_t m, int32_t* __r
 // Exclusive scan of count[0..n) into ptr[0..n] (ptr[n] = total), one block of
 // 1024 threads, tiles of 1024*8 elements with a running carry.
 __global__ void __launch_bounds__(1024) k_scan(const int32_t* __restrict__ count, int64_t n,
-                                                int64_t* __restrict__ ptr) {
+                                                int64_t* __restrict__ ptr, const int* __restrict__ skip) {
+  if (skip && *skip) return;
   __shared__ int64_t wsum[16];
   __shared__ int64_t carry_s;
   constexpr int kPer = 8;
@@ -406,7 +407,7 @@ rfmls_status bucket_sort(rfmls_handle* h, const int32_t* key, int64_t m, int64_t
                      dim3(256), 0, st, scratch_count, nb, 0);
   if (m > 0)
     hipLaunchKernelGGL(k_count, dim3(ceil_div(m, 256)), dim3(256), 0, st, key, m, scratch_count);
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, scratch_count, nb, ptr);
+  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, st, scratch_count, nb, ptr, (const int*)nullptr);
   hipLaunchKernelGGL(k_copy_ptr_i32, dim3(ceil_div(nb, 256)), dim3(256), 0, st, ptr, nb,
                      scratch_count);
   if (m > 0) {
@@ -419,8 +420,8 @@ rfmls_status bucket_sort(rfmls_handle* h, const int32_t* key, int64_t m, int64_t
   return RFMLS_OK;
 }
 
-rfmls_status scan_counts(rfmls_handle* h, const int32_t* count, int64_t n, int64_t* ptr) {
-  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, h->stream, count, n, ptr);
+rfmls_status scan_counts(rfmls_handle* h, const int32_t* count, int64_t n, int64_t* ptr, const int* skip) {
+  hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, h->stream, count, n, ptr, skip);
   RFMLS_HIP(h, hipGetLastError());
   return RFMLS_OK;
 }

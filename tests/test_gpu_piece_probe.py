@@ -1,0 +1,61 @@
+"""Matrices whose rows have the same column runs in pieces in some of their 64-row groups
+only: the sample that is looked at first may see the one kind or the other, and whichever
+kernels then run give the same bytes."""
+
+import numpy as np
+import pytest
+import scipy.sparse as sp
+import torch
+
+import paper_2409_15818_amd as R
+
+pytestmark = pytest.mark.gpu
+
+
+def _mixed(groups, in_pieces, k, n, tail, seed):
+    """Rows of k entries by 64-row groups: one run that all rows of the group share where
+    in_pieces(group), else a random place in each k-th of the columns; then `tail` rows."""
+    rng = np.random.default_rng(seed)
+    e = np.arange(k + 1) * n // k
+    cols = []
+    for g in range(groups + (tail > 0)):
+        rows = 64 if g < groups else tail
+        if in_pieces(g):
+            c = np.tile(rng.integers(0, n - k) + np.arange(k), (rows, 1))
+        else:
+            c = e[:-1] + (rng.random((rows, k)) * np.diff(e)).astype(np.int64)
+        cols.append(c)
+    col = np.concatenate(cols).reshape(-1).astype(np.int32)
+    m = 64 * groups + tail
+    return m, np.arange(m + 1) * k, col, rng.standard_normal(m * k)
+
+
+# 192 groups are sampled at every third.  All pieces, none, pieces only where the sample
+# looks, only where it does not, every eighth of the sampled groups scattered, and fewer
+# groups than the sample takes, with a ragged last one.  At least 2^20 entries, from where
+# the transpose takes pieces at all.
+CASES = [
+    (192, lambda g: True, 90, 0), (192, lambda g: False, 90, 13), (192, lambda g: g % 3 == 0, 90, 1),
+    (192, lambda g: g % 3 != 0, 90, 63), (192, lambda g: g % 24 != 0, 90, 5), (30, lambda g: True, 600, 17),
+    (30, lambda g: g % 2 == 0, 600, 0),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_pieces_in_some_groups(case):
+    groups, kind, k, tail = CASES[case]
+    n = 1500 if k == 600 else 700
+    m, ptr, col, val = _mixed(groups, kind, k, n, tail, case)
+    assert len(col) >= 1 << 20
+    h = R.Handle(device="cuda:0")
+    A = R.CSR.from_numpy(ptr, col, val, m, n)
+    T = R.rfmls_transpose(h, A)
+    ref = sp.csr_matrix((val, col, ptr), shape=(m, n))
+    tr = ref.T.tocsr()
+    tr.sort_indices()
+    assert np.array_equal(T.row_ptr.cpu().numpy(), tr.indptr)
+    assert np.array_equal(T.col.cpu().numpy(), tr.indices)
+    assert np.array_equal(T.val.cpu().numpy(), tr.data)
+    # B = A I: every output one product a_ij * 1 plus zeros, the bits of A
+    P = R.rfmls_precond_import_R(h, torch.eye(n, dtype=torch.float64, device="cuda"))
+    assert np.array_equal(R.rfmls_form_B(h, A, P).cpu().numpy(), ref.toarray())

@@ -126,44 +126,29 @@ __global__ void __launch_bounds__(256)
   }
 }
 // bad = 1 where a sample says that the rows have no pieces to speak of, mode = 0.  The
-// sample is up to 64 groups spread over the matrix; a row of another length, first or
-// last column than the row before starts a piece.  More than a quarter of the sampled
-// rows doing so is far from what either use of the pieces asks (one in eight entries
-// here, one in sixteen rows in the lockstep products): the kernels that find the runs
-// and pieces then return at once.  One workgroup, four groups a wavefront.
-// Without it a 2,000,000 x 20,000 matrix of 12 scattered entries a row spent 0.55 of
-// 6.95 ms on runs that the entry-by-entry transpose then did not use.
-constexpr int kProbeGroups = 64;
-__global__ void __launch_bounds__(1024)
+// sample is up to 16 groups spread over the matrix, one a wavefront; a row of another
+// length or first column than the row before starts a piece.  More than a fifth of the
+// sampled rows doing so is beyond what either use of the pieces takes (one in eight
+// entries here, one in six rows in the lockstep products): the kernels that find the
+// runs and pieces then return at once.  Without it a 2,000,000 x 20,000 matrix of 12
+// scattered entries a row spent 0.55 of 6.95 ms on runs that the entry-by-entry transpose
+// then did not use.  One workgroup, bound by its scattered loads: 64 groups and the last
+// columns too took 16 us.
+constexpr int kProbeGroups = 16;
+__global__ void __launch_bounds__(64 * kProbeGroups)
     k_probe_pieces(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int64_t m, int* bad,
                    int* mode) {
-  __shared__ int found[16][2];
+  __shared__ int found[kProbeGroups][2];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t ng = (m + kPieceRows - 1) / kPieceRows;
-  const int64_t step = ng > kProbeGroups ? ng / kProbeGroups : 1;
-  int64_t lo[4], hi[4];
-  bool live[4];
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int64_t row = (int64_t)(w + 16 * q) * step * kPieceRows + lane;
-    live[q] = row < m;
-    lo[q] = row_ptr[live[q] ? row : m];
-    hi[q] = row_ptr[live[q] ? row + 1 : m];
-  }
-  int first[4], last[4], starts = 0, rows = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    first[q] = hi[q] > lo[q] ? col[lo[q]] : -1;
-    last[q] = hi[q] > lo[q] ? col[hi[q] - 1] : -1;
-  }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int len = (int)(hi[q] - lo[q]);
-    const bool other = __shfl_up(len, 1, 64) != len || __shfl_up(first[q], 1, 64) != first[q] ||
-                       __shfl_up(last[q], 1, 64) != last[q];
-    starts += __popcll(__ballot(live[q] && (lane == 0 || other)));
-    rows += __popcll(__ballot(live[q]));
-  }
+  const int64_t row = w * (ng > kProbeGroups ? ng / kProbeGroups : 1) * kPieceRows + lane;
+  const bool live = row < m;
+  const int64_t lo = row_ptr[live ? row : m], hi = row_ptr[live ? row + 1 : m];
+  const int len = (int)(hi - lo), first = len > 0 ? col[lo] : -1;
+  // (every lane takes part in both shuffles)
+  const int len1 = __shfl_up(len, 1, 64), first1 = __shfl_up(first, 1, 64);
+  const int starts = __popcll(__ballot(live && (lane == 0 || len1 != len || first1 != first)));
+  const int rows = __popcll(__ballot(live));
   if (lane == 0) {
     found[w][0] = starts;
     found[w][1] = rows;
@@ -171,11 +156,11 @@ __global__ void __launch_bounds__(1024)
   __syncthreads();
   if (threadIdx.x == 0) {
     int s = 0, r = 0;
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < kProbeGroups; ++q) {
       s += found[q][0];
       r += found[q][1];
     }
-    *bad = 4 * s > r;
+    *bad = 5 * s > r;
     *mode = 0;
   }
 }
@@ -302,7 +287,7 @@ __global__ void __launch_bounds__(256)
 }  // namespace
 
 void probe_pieces(hipStream_t st, const rfmls_csr* M, int* bad, int* mode) {
-  hipLaunchKernelGGL(k_probe_pieces, dim3(1), dim3(1024), 0, st, M->row_ptr, M->col, M->m, bad, mode);
+  hipLaunchKernelGGL(k_probe_pieces, dim3(1), dim3(64 * kProbeGroups), 0, st, M->row_ptr, M->col, M->m, bad, mode);
 }
 
 rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int32_t* at_col,

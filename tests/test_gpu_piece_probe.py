@@ -30,21 +30,21 @@ def _mixed(groups, in_pieces, k, n, tail, seed):
     return m, np.arange(m + 1) * k, col, rng.standard_normal(m * k)
 
 
-# 192 groups are sampled at every third.  All pieces, none, pieces only where the sample
+# 192 groups are sampled at every twelfth.  All pieces, none, pieces only where the sample
 # looks, only where it does not, every eighth of the sampled groups scattered, and fewer
 # groups than the sample takes, with a ragged last one.  At least 2^20 entries, from where
 # the transpose takes pieces at all.
 CASES = [
-    (192, lambda g: True, 90, 0), (192, lambda g: False, 90, 13), (192, lambda g: g % 3 == 0, 90, 1),
-    (192, lambda g: g % 3 != 0, 90, 63), (192, lambda g: g % 24 != 0, 90, 5), (30, lambda g: True, 600, 17),
-    (30, lambda g: g % 2 == 0, 600, 0),
+    (192, lambda g: True, 90, 0), (192, lambda g: False, 90, 13), (192, lambda g: g % 12 == 0, 90, 1),
+    (192, lambda g: g % 12 != 0, 90, 63), (192, lambda g: g % 96 != 0, 90, 5), (13, lambda g: True, 1300, 17),
+    (13, lambda g: g % 2 == 0, 1300, 0),
 ]
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_pieces_in_some_groups(case):
     groups, kind, k, tail = CASES[case]
-    n = 1500 if k == 600 else 700
+    n = 2900 if k == 1300 else 700
     m, ptr, col, val = _mixed(groups, kind, k, n, tail, case)
     assert len(col) >= 1 << 20
     h = R.Handle(device="cuda:0")

@@ -715,19 +715,20 @@ struct RunMat {
 };
 
 // Pieces of each 64-row group (group_pieces).  Count pass: pcount[group]; fill
-// pass: pieces from pptr[group] on.  bad is set when a row has no run description
+// pass: pieces from pptr[group] on, and their number in *total.  bad is set when a row has no run description
 // or a run leaves the matrix's columns.
 template <bool Fill>
 __global__ void __launch_bounds__(kThreads)
     k_run_pieces(int64_t rows, int64_t ncols, const int32_t* __restrict__ nrun, const int32_t* __restrict__ rcol,
                  const int32_t* __restrict__ rend, int32_t* __restrict__ pcount, const int64_t* __restrict__ pptr,
-                 int2* __restrict__ pieces, int* __restrict__ bad) {
+                 int2* __restrict__ pieces, int* __restrict__ bad, int64_t* __restrict__ total) {
   // set before, by the probe or the count pass (whose own setting it leaves counts and
   // places unwritten that nothing then reads)
   if (*bad) return;
   const int lane = threadIdx.x & 63;
   const int64_t ngroups = (rows + kPieceRows - 1) / kPieceRows;
   const int64_t nw = (int64_t)gridDim.x * (kThreads / 64);
+  if (Fill && blockIdx.x == 0 && threadIdx.x == 0) *total = pptr[ngroups];
   for (int64_t g = (int64_t)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); g < ngroups; g += nw) {
     unsigned long long starts, lives, wrong;
     group_pieces(g, rows, ncols, nrun, rcol, rend, &starts, &lives, &wrong);
@@ -1556,11 +1557,12 @@ static rfmls_status spmm_tune(BCtx& c, const rfmls_csr* M, double* xin, double* 
 // The run kernel takes a matrix whose rows all have a run description and whose
 // pieces average at least kRunMinRows rows: a piece's products run on 16-row
 // tiles, so shorter pieces leave most of the matrix cores' rows empty.  The
-// windowed kernel (which needs no structure) takes the rest.  On pieces of 25
-// rows and more (the systems of 720 to 3,200 columns) the run kernel was 1.9 to
-// 6 times faster on every matrix measured (26 against 92 us on the 25,688 x
-// 1,864 system, 21.5 against 42 us on the 32,805 x 2,619 one).
-constexpr int64_t kRunMinRows = 16;
+// windowed kernel (which needs no structure) takes the rest.  The line by pieces of h
+// rows at random places, B = A X over 1,024 columns, windowed against runs (ms): 20,000
+// rows of 200 entries, h = 2 / 4 / 6 / 12: 2.85, 2.84, 2.85, 2.70 against 3.11, 1.79,
+// 1.41, 1.00; of 8 runs of 4: h = 4 / 6 2.89, 2.79 against 2.55, 1.97; 100,000 rows of
+// 20: h = 4 / 6 / 8 4.69, 3.80, 2.93 against 4.77, 3.60, 2.79.
+constexpr int64_t kRunMinRows = 6;
 constexpr int64_t kRunMaxSplit = 32;
 static rfmls_status spmm_prepare(BCtx& c) {
   rfmls_handle* h = c.h;
@@ -1574,7 +1576,9 @@ static rfmls_status spmm_prepare(BCtx& c) {
   }
   void* pr;
   RFMLS_CHECK(workspace(h, WS_SPMM_RUNS, bytes, &pr));
+  // flags of both matrices, the probe's spare word, and the numbers of pieces: one copy
   int* bad = (int*)pr;
+  int64_t* total = (int64_t*)pr + 2;
   char* q = (char*)pr + 256;
   RunMat* out[2] = {&c.rA, &c.rAT};
   int64_t* pptr[2];
@@ -1599,28 +1603,23 @@ static rfmls_status spmm_prepare(BCtx& c) {
       const unsigned g = (unsigned)(ng < 4096 ? (ng + 3) / 4 : 1024);
       hipLaunchKernelGGL(k_run_pieces<false>, dim3(g), dim3(kThreads), 0, c.st, rows, M->n, (const int32_t*)nrun,
                          (const int32_t*)rcol, (const int32_t*)rend, pcount, (const int64_t*)nullptr,
-                         (int2*)nullptr, bad + i);
+                         (int2*)nullptr, bad + i, (int64_t*)nullptr);
       RFMLS_CHECK(scan_counts(h, pcount, ng, pptr[i], bad + i));
       hipLaunchKernelGGL(k_run_pieces<true>, dim3(g), dim3(kThreads), 0, c.st, rows, M->n, (const int32_t*)nrun,
                          (const int32_t*)rcol, (const int32_t*)rend, pcount, (const int64_t*)pptr[i], pieces,
-                         bad + i);
+                         bad + i, total + i);
     }
   }
   RFMLS_HIP(h, hipGetLastError());
-  int64_t* pin = (int64_t*)((char*)h->pinned + 1024);  // totals of both matrices, then their flags
-  pin[0] = pin[1] = 0;
-  for (int i = 0; i < nm; ++i)
-    if (mats[i]->m > 0)
-      RFMLS_HIP(h, hipMemcpyAsync(pin + i, pptr[i] + (mats[i]->m + kPieceRows - 1) / kPieceRows, sizeof(int64_t),
-                                  hipMemcpyDeviceToHost, c.st));
-  RFMLS_HIP(h, hipMemcpyAsync(pin + 2, bad, 2 * sizeof(int), hipMemcpyDeviceToHost, c.st));
+  const int64_t* pin = (const int64_t*)((char*)h->pinned + 1024);
+  RFMLS_HIP(h, hipMemcpyAsync((char*)h->pinned + 1024, pr, 4 * sizeof(int64_t), hipMemcpyDeviceToHost, c.st));
   RFMLS_HIP(h, hipStreamSynchronize(c.st));
-  const int* badh = (const int*)(pin + 2);
+  const int* badh = (const int*)pin;
   int64_t need = 0;
   for (int i = 0; i < nm; ++i) {
     const rfmls_csr* M = mats[i];
     RunMat& r = *out[i];
-    const int64_t np = pin[i];
+    const int64_t np = pin[2 + i];
     if (M->m < 1 || badh[i] || np * kRunMinRows > M->m) continue;
     r.npieces = np;
     // K chunks where the pieces alone give fewer than four workgroups per

@@ -2,6 +2,8 @@
 // bucket sort of the rows of A by h(i), and the segmented sum that writes the
 // dense row-major SA.  Integer work is bit-exact; each element of SA is summed
 // in float64 from +0 over its bucket's rows in ascending row order.
+#include <type_traits>
+
 #include "common.h"
 
 namespace rfmls {
@@ -147,10 +149,11 @@ __global__ void __launch_bounds__(256) k_sort_buckets(const int64_t* __restrict_
 // wider than kWin takes the chunked path: chunks of kWin columns, every row of
 // the bucket visited per chunk.  Either way every element is summed in float64
 // from +0 over the bucket's rows in ascending row order.
+// Few (buckets of two or three rows): one span a row and no entries read ahead, since
+// there is little to wait for and the registers take a workgroup from every compute unit.
 // threads: twice as many beside the 32 KB window, of which only four fit a compute unit
 constexpr int sketch_threads(int win) { return win > 2048 ? 512 : 256; }
 constexpr int kMaxBucketRows = 64;
-constexpr int kMaxSpans = 2 * kMaxBucketRows;
 
 template <typename TOut>
 struct SketchVec;
@@ -167,13 +170,15 @@ struct SketchVec<float> {
 
 // Vec: the row start is 16-byte aligned (SA and ld suit 16-byte stores).  kWin: see
 // run_sketch.
-template <typename TOut, bool Vec, int kWin>
-__global__ void __launch_bounds__(sketch_threads(kWin))
+template <typename TOut, bool Vec, int kWin, bool Few>
+__global__ void __launch_bounds__(sketch_threads(kWin), 8)
     k_sketch_rows(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                   const double* __restrict__ val, const int8_t* __restrict__ sign,
                   const int64_t* __restrict__ bptr, const int32_t* __restrict__ perm, int64_t n,
                   TOut* __restrict__ SA, int64_t ld) {
   constexpr int NT = sketch_threads(kWin);
+  constexpr int S = Few ? 1 : 2;  // spans a row
+  constexpr int kMaxSpans = S * kMaxBucketRows;
   constexpr int V = Vec ? SketchVec<TOut>::V : 1;
   typedef typename SketchVec<TOut>::vec vec_t;
   __shared__ double acc[kWin];
@@ -206,19 +211,21 @@ __global__ void __launch_bounds__(sketch_threads(kWin))
         f0 = col[lo];
         l0 = col[hi - 1];
         const int32_t e0 = col[lo + (h > 0 ? h - 1 : 0)], b1 = col[lo + h];
-        if (h > 0 && b1 > e0 + 1 && (int64_t)e0 - f0 == h - 1 && (int64_t)l0 - b1 == hi - lo - h - 1) {
+        if (!Few && h > 0 && b1 > e0 + 1 && (int64_t)e0 - f0 == h - 1 && (int64_t)l0 - b1 == hi - lo - h - 1) {
           f1 = b1;
           l1 = l0;
           l0 = e0;
         }
       }
-      raw0[2 * t] = f0;
-      raw1[2 * t] = l0;
-      raw0[2 * t + 1] = f1;
-      raw1[2 * t + 1] = l1;
+      raw0[S * t] = f0;
+      raw1[S * t] = l0;
+      if constexpr (!Few) {
+        raw0[S * t + 1] = f1;
+        raw1[S * t + 1] = l1;
+      }
     }
     __syncthreads();
-    const int ns = 2 * (int)nb;
+    const int ns = S * (int)nb;
     if (t < ns) {  // sorted by first column: each span to the place its rank gives
       const int32_t x0 = raw0[t];
       int rank = 0;
@@ -256,7 +263,7 @@ __global__ void __launch_bounds__(sketch_threads(kWin))
         if (c >= ist[k] && c <= ien[k]) return ioff[k] + (int)(c - ist[k]);
       return -1;
     };
-    if (t < 2 * (int)nb && raw1[t] >= raw0[t]) {
+    if (t < S * (int)nb && raw1[t] >= raw0[t]) {
       int k = 0;
       while (k + 1 < nint && ist[k + 1] <= raw0[t]) ++k;
       wof[t] = ioff[k] - ist[k];
@@ -295,33 +302,40 @@ __global__ void __launch_bounds__(sketch_threads(kWin))
     };
     auto row = [&](const Ahead& p, int q) {
       const double sg = (double)rsg[q];
-      const int32_t a0 = raw0[2 * q], a1 = raw1[2 * q], b0 = raw0[2 * q + 1], b1 = raw1[2 * q + 1];
-      const int32_t aw = wof[2 * q], bw = wof[2 * q + 1];
+      const int32_t a0 = raw0[S * q], a1 = raw1[S * q], b0 = Few ? 1 : raw0[S * q + S - 1],
+                    b1 = Few ? 0 : raw1[S * q + S - 1];
+      const int32_t aw = wof[S * q], bw = wof[S * q + S - 1];
       // a column outside the row's spans (a row against the ascending-column
       // contract) is dropped rather than written outside the window
       auto add = [&](int32_t c, double x) {
         const bool ina = c >= a0 && c <= a1;
         if (ina || (c >= b0 && c <= b1)) acc[c + (ina ? aw : bw)] += x;
       };
+      if constexpr (!Few) {
 #pragma unroll
-      for (int u = 0; u <= kPre; ++u)
-        if (t + u * NT < rlen[q]) add(p.c[u], sg * p.v[u]);
-      for (int e = t + (kPre + 1) * NT; e < rlen[q]; e += NT)
+        for (int u = 0; u <= kPre; ++u)
+          if (t + u * NT < rlen[q]) add(p.c[u], sg * p.v[u]);
+      }
+      for (int e = t + (Few ? 0 : kPre + 1) * NT; e < rlen[q]; e += NT)
         add(col[(int64_t)rlo[q] + e], sg * val[(int64_t)rlo[q] + e]);
       __syncthreads();
     };
     Ahead p0, p1, p2;
-    fetch(p0, 0);
-    fetch(p1, 1);
-    for (int q = 0; q < (int)nb; q += 3) {
-      fetch(p2, q + 2);
-      row(p0, q);
-      if (q + 1 >= (int)nb) break;
-      fetch(p0, q + 3);
-      row(p1, q + 1);
-      if (q + 2 >= (int)nb) break;
-      fetch(p1, q + 4);
-      row(p2, q + 2);
+    if constexpr (Few) {
+      for (int q = 0; q < (int)nb; ++q) row(p0, q);
+    } else {
+      fetch(p0, 0);
+      fetch(p1, 1);
+      for (int q = 0; q < (int)nb; q += 3) {
+        fetch(p2, q + 2);
+        row(p0, q);
+        if (q + 1 >= (int)nb) break;
+        fetch(p0, q + 3);
+        row(p1, q + 1);
+        if (q + 2 >= (int)nb) break;
+        fetch(p1, q + 4);
+        row(p2, q + 2);
+      }
     }
     // the window's segments (a segment across two intervals is written twice, alike)
     for (int k = 0; k < nint; ++k) {
@@ -450,25 +464,33 @@ rfmls_status run_sketch(rfmls_handle* h, const rfmls_csr* A, int64_t s, const in
   // 4,096 where the buckets hold more than 1,024 entries on average and so often
   // touch more than 2,048 columns: a bucket past the window reads its rows once per
   // chunk.  With an interface row's two boxes as two spans and two rows' entries in
-  // flight: 105,840 x 9,450, float32, 2,352 entries a bucket, 0.70 -> 0.54 ms;
-  // Helmholtz sketch (2,900) 0.31 -> 0.24 ms; the 8x8-box sketch (475, bound by
-  // writing 5.2 GB) stays at 2,048 and pays 1.07 -> 1.18 ms of its 245 ms solve for
-  // the spans' sort.
-  const bool wide = A->nnz > 1024 * s;
+  // flight, whole calls: 105,840 x 9,450, float32, 2,352 entries a bucket, 0.73 -> 0.57
+  // ms; Helmholtz system (2,900) 0.37 -> 0.27 ms.  Short rows over more columns than the
+  // wide window gain nothing from it and leave half of its 512 threads idle: 2,000,000 x
+  // 10,000 of 20 entries a row 8.60 ms narrow, 9.69 wide.
+  // Buckets of fewer than three rows on average take the one-span form: the 8x8-box
+  // sketch (2.2 rows, 475 entries, bound by writing 5.2 GB) 1.15 ms against 1.20 with two
+  // spans, the 4x4-box one 69 us against 75; with 3.5 rows of 270 entries 113 us
+  // against 100.
+  const bool wide = A->nnz > 1024 * s && (A->nnz >= 256 * A->m || A->n <= 4096);
+  const bool few = !wide && A->m < 3 * s;
+  auto rows = [&](auto tout, auto vtag) {
+    using TOut = decltype(tout);
+    constexpr bool V = decltype(vtag)::value;
+    auto launch = [&](auto fn, int win) {
+      hipLaunchKernelGGL(fn, dim3((unsigned)s), dim3(sketch_threads(win)), 0, h->stream, A->row_ptr, A->col, A->val,
+                         sign, bptr, perm, A->n, (TOut*)SA, ld);
+    };
+    if (wide) launch(k_sketch_rows<TOut, V, 4096, false>, 4096);
+    else if (few) launch(k_sketch_rows<TOut, V, 2048, true>, 2048);
+    else launch(k_sketch_rows<TOut, V, 2048, false>, 2048);
+  };
   if (dt == RFMLS_F64) {
-    if (vec)
-      hipLaunchKernelGGL((wide ? k_sketch_rows<double, true, 4096> : k_sketch_rows<double, true, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
-                         A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (double*)SA, ld);
-    else
-      hipLaunchKernelGGL((wide ? k_sketch_rows<double, false, 4096> : k_sketch_rows<double, false, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
-                         A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (double*)SA, ld);
+    if (vec) rows(0.0, std::true_type());
+    else rows(0.0, std::false_type());
   } else {
-    if (vec)
-      hipLaunchKernelGGL((wide ? k_sketch_rows<float, true, 4096> : k_sketch_rows<float, true, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
-                         A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (float*)SA, ld);
-    else
-      hipLaunchKernelGGL((wide ? k_sketch_rows<float, false, 4096> : k_sketch_rows<float, false, 2048>), dim3((unsigned)s), dim3(wide ? sketch_threads(4096) : sketch_threads(2048)), 0, h->stream,
-                         A->row_ptr, A->col, A->val, sign, bptr, perm, A->n, (float*)SA, ld);
+    if (vec) rows(0.0f, std::true_type());
+    else rows(0.0f, std::false_type());
   }
   }
   RFMLS_HIP(h, hipGetLastError());

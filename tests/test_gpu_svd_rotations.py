@@ -48,3 +48,26 @@ def test_svd_of_two_columns_takes_one_rotation():
         assert P.status == 0 and P.rank == 2 and P.off <= 16 * 2.0 ** -53
         sweeps.append(P.sweeps)
     assert max(sweeps) <= 2, sweeps
+
+
+# Beyond the sizes whose blocks are few: P = V Sigma^{-1} of a sketch of 2,500 and 4,200
+# columns, kappa 1e4.  V = P Sigma is orthogonal and U = SA P has orthonormal columns, to
+# 8 n u and to what kappa amplifies; the singular values' squares sum to the sketch's.
+@pytest.mark.parametrize("n", [2500, 4200])
+def test_svd_of_many_columns(n):
+    s = 2 * n
+    gen = torch.Generator("cuda").manual_seed(n)
+    SA = torch.randn((s, n), dtype=torch.float64, device="cuda", generator=gen)
+    SA *= torch.logspace(0, -3, n, dtype=torch.float64, device="cuda")
+    h = R.Handle(device="cuda:0")
+    P = R.rfmls_precond_svd(h, SA.clone(), n)
+    sig = R.rfmls_precond_export_sigma(h, P)
+    X = R.rfmls_precond_export_P(h, P)
+    u = 2.0 ** -53
+    assert P.status == 0 and P.rank == n
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    V, U = X * sig, SA @ X
+    assert float((V.T.contiguous() @ V - eye).abs().max()) <= 8 * n * u
+    kappa = float(sig.max() / sig.min())
+    assert float((U.T.contiguous() @ U - eye).abs().max()) <= n * u * kappa + 1e-12
+    assert abs(float((sig ** 2).sum() / (SA ** 2).sum()) - 1.0) <= 8 * n * u

@@ -167,13 +167,6 @@ constexpr int kLd = kNb + 1;  // LDS row stride of a 64 x 64 matrix
 typedef double Mat[kNb][kLd];
 typedef double Blk[kB][kB + 1];
 
-__device__ __forceinline__ double lane_bcast(double v, int lane) {
-  const long long x = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(x & 0xffffffffll), lane);
-  const int hi = __builtin_amdgcn_readlane((int)(x >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 // Tile (ti, tj) of D -= op(A) B with K = 16, for LDS matrices of kLd columns (D, A
 // and B do not overlap): op(A) = A (a column block) or, with TA, A^T (A a row block).
 template <bool TA>
@@ -261,7 +254,7 @@ __device__ __forceinline__ void chol_panel(Mat& A, int kb, int l, double* mn, do
   }
 #pragma unroll
   for (int s2 = 0; s2 < kB; ++s2) {
-    const double piv = lane_bcast(d[s2], s2);
+    const double piv = lane_read(d[s2], s2);
     *bad |= !(piv > 0.0 && piv < INFINITY);
     const double r = rsq2(piv);
     *mn = fmin(*mn, piv * r);
@@ -269,7 +262,7 @@ __device__ __forceinline__ void chol_panel(Mat& A, int kb, int l, double* mn, do
     const double us = d[s2] * r;  // u_{s,l} for l >= s
     // u_{s,i} from the unscaled row, whose readlanes need not wait for r
 #pragma unroll
-    for (int i = s2 + 1; i < kB; ++i) d[i] = fma(-(lane_bcast(d[s2], i) * r), us, d[i]);
+    for (int i = s2 + 1; i < kB; ++i) d[i] = fma(-(lane_read(d[s2], i) * r), us, d[i]);
     d[s2] = l >= s2 ? us : 0.0;
   }
   if (act)
@@ -303,8 +296,8 @@ __device__ __forceinline__ void recon_panel(Mat& A, const Mat& U2, int kb, int i
 #pragma unroll
   for (int j = 0; j < kB; ++j) {
     const int pr = k0 + j;
-    const double ej = lane_bcast(p[j], pr);
-    const double ujj = lane_bcast(u[j], pr);
+    const double ej = lane_read(p[j], pr);
+    const double ujj = lane_read(u[j], pr);
     const double rp = rcp2(ej + copysign(ujj, ej));  // the pivot e_j - s_j u_jj
     const double cj = i == pr ? copysign(1.0, ej) : 0.0;
     const double pj = i > pr ? p[j] : 0.0;
@@ -314,7 +307,7 @@ __device__ __forceinline__ void recon_panel(Mat& A, const Mat& U2, int kb, int i
     pv = i == pr ? p[j] : pv;
     p[j] = i > pr ? lij : p[j];
 #pragma unroll
-    for (int m = j + 1; m < kB; ++m) p[m] = fma(-lij, lane_bcast(p[m], pr), p[m]);
+    for (int m = j + 1; m < kB; ++m) p[m] = fma(-lij, lane_read(p[m], pr), p[m]);
   }
   const double sv = -copysign(1.0, pv), rv = rcp2(pv);
   if (i >= k0) {
@@ -330,9 +323,9 @@ __device__ __forceinline__ void recon_panel(Mat& A, const Mat& U2, int kb, int i
     for (int m = 0; m < kB; ++m) x[m] = m == i ? 1.0 : 0.0;
 #pragma unroll
     for (int m = kB - 1; m >= 0; --m) {
-      x[m] = m <= i ? x[m] * lane_bcast(rv, k0 + m) : 0.0;
+      x[m] = m <= i ? x[m] * lane_read(rv, k0 + m) : 0.0;
 #pragma unroll
-      for (int q = 0; q < m; ++q) x[q] = fma(-lane_bcast(p[m], k0 + q), x[m], x[q]);
+      for (int q = 0; q < m; ++q) x[q] = fma(-lane_read(p[m], k0 + q), x[m], x[q]);
     }
     if (i < kB)
 #pragma unroll
@@ -341,11 +334,11 @@ __device__ __forceinline__ void recon_panel(Mat& A, const Mat& U2, int kb, int i
   }
 #pragma unroll
   for (int m = 0; m < kB; ++m)
-    x[m] = fma(-lane_bcast(sv, k0 + m), U2[k0 + m][right ? c : k0], A[k0 + m][right ? c : k0]);
+    x[m] = fma(-lane_read(sv, k0 + m), U2[k0 + m][right ? c : k0], A[k0 + m][right ? c : k0]);
 #pragma unroll
   for (int m = 0; m < kB; ++m) {
 #pragma unroll
-    for (int q = m + 1; q < kB; ++q) x[q] = fma(-lane_bcast(p[m], k0 + q), x[m], x[q]);
+    for (int q = m + 1; q < kB; ++q) x[q] = fma(-lane_read(p[m], k0 + q), x[m], x[q]);
   }
   if (right)
 #pragma unroll

@@ -209,6 +209,9 @@ __device__ __forceinline__ double lane_read(double v, int lane) {
   const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
+__device__ __forceinline__ double lane_read(float v, int lane) {
+  return (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
 // Sum over the wavefront, the same on every lane: DPP rows, then the four row sums
 // in a fixed order (no LDS permutes: a tenth of the latency and of the code of six
 // __shfl_xor steps, which the small kernels of an iteration feel).

@@ -1272,7 +1272,8 @@ unsigned rows_grid(int64_t rows) {  // blocks of 8 rows x 32 columns, grid-strid
   const int64_t b = (rows + (kThreads / kBlk) - 1) / (kThreads / kBlk);
   return (unsigned)(b < kRowBlocks ? (b > 0 ? b : 1) : kRowBlocks);
 }
-unsigned spmm_grid(int64_t rows) {  // 16-row groups, grid-stride beyond kSpmmBlocks
+// k_blk_pattern_grad: four rows a wavefront, grid-stride beyond kSpmmBlocks
+unsigned pattern_grid(int64_t rows) {
   const int64_t b = (rows + 15) / 16;
   return (unsigned)(b < kSpmmBlocks ? (b > 0 ? b : 1) : kSpmmBlocks);
 }
@@ -1353,11 +1354,6 @@ struct BCtx {
 template <class F>
 static rfmls_status run_loop(BCtx& c, int64_t itmax, int every, int consistent, F&& iteration);
 
-double* state_field(BlockState* s, int which) {
-  // pointer to col[0].<field>; stride between columns in doubles
-  LsqrDev* d = &s->col[0];
-  return which == 0 ? &d->beta : &d->alpha;
-}
 BlkCommit commit_of(const BCtx& c, int consistent) {
   BlkCommit cm;
   cm.st = c.dst;
@@ -2100,7 +2096,7 @@ rfmls_status run_backward_block(rfmls_handle* h, const rfmls_csr* A, const rfmls
                            rm, (const double*)Rg, (const double*)tmp, (const double*)lam, (const double*)Xg, dAval,
                            k0 > 0 ? 1 : 0);
       else
-        hipLaunchKernelGGL(k_blk_pattern_grad, dim3(spmm_grid(m)), dim3(kThreads), 0, c.st, A->row_ptr, A->col, m,
+        hipLaunchKernelGGL(k_blk_pattern_grad, dim3(pattern_grid(m)), dim3(kThreads), 0, c.st, A->row_ptr, A->col, m,
                            (const double*)Rg, (const double*)tmp, (const double*)lam, (const double*)Xg, dAval,
                            k0 > 0 ? 1 : 0);
     }

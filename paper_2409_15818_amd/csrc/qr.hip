@@ -128,16 +128,6 @@ __device__ __forceinline__ void ll_wait2(const uint64_t* s0, const uint64_t* s1,
 // has published column j + 1, which each does after reading column j.
 //   ll  slots, 16 bytes each: r1 [2][64][G], rp [2][64], r2 [2][64]
 
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  const long long x = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(x & 0xffffffffll), lane);
-  const int hi = __builtin_amdgcn_readlane((int)(x >> 32), lane);
-  return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-__device__ __forceinline__ double lane_value(float v, int lane) {
-  return (double)__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
 constexpr int kPanelThreads = 1024;
 constexpr int kPanelGroups = kPanelThreads / 64;  // wavefronts per block
 constexpr int kPanelMaxBlocks = kPanelThreads;    // a reducer thread per block
@@ -206,7 +196,7 @@ __global__ void __launch_bounds__(kPanelThreads)
       const int li = rg + kPanelGroups * q;
       // rows li >= kMaxNb > j always take part (compile-time for large q)
       if (kPanelGroups * q >= kMaxNb || !top || li > j) {
-        const T v = (T)lane_value(a[q], j);
+        const T v = (T)lane_read(a[q], j);
         if constexpr (kKeep) aj[q] = v;
         s += (double)v * (double)a[q];
       } else if constexpr (kKeep) {
@@ -292,7 +282,7 @@ __global__ void __launch_bounds__(kPanelThreads)
       if (kPanelGroups * q >= kMaxNb || !top || li > j) {
         double vj;
         if constexpr (kKeep) vj = (double)aj[q];
-        else vj = lane_value(a[q], j);  // read before lane j rewrites it
+        else vj = lane_read(a[q], j);  // read before lane j rewrites it
         a[q] = (T)fma(kv, vj, keep ? (double)a[q] : 0.0);
       } else if (li == j) {
         a[q] = (T)(upd ? (double)a[q] - f : (c == j ? beta : (double)a[q]));
@@ -398,7 +388,7 @@ __global__ void __launch_bounds__(1024)
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
         const int l = l0 - d;
-        const double tl = tt[d] * lane_value(x, l > 0 ? l : 0);  // x_l is final once rows > l are done
+        const double tl = tt[d] * lane_read(x, l > 0 ? l : 0);  // x_l is final once rows > l are done
         if (lane == l) t = tl;
         x -= u[d] * tl;
       }
@@ -416,7 +406,7 @@ __global__ void __launch_bounds__(1024)
     }
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-      const double tl = tt[d] * lane_value(x, l0 + d);  // x_l is final once rows < l are done
+      const double tl = tt[d] * lane_read(x, l0 + d);  // x_l is final once rows < l are done
       if (lane == l0 + d) t = tl;
       x -= u[d] * tl;
     }

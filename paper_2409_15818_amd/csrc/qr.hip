@@ -1055,8 +1055,13 @@ rfmls_status lookahead_stream(rfmls_handle* h) {
 //   act[k]  at least the panel's rows (so that R's rows exist), and at least
 //           kCholqrMinRows of them, so that the first panels of a sparse sketch
 //           stay on CholeskyQR2; whole multiples of 64 keep the clean kernels.
-// Costs a host wait for the counts (about 30 us with the search and the sort), so
-// small sketches, where the panels' latency is most of the time, keep their order.
+// Costs a host wait for the counts (20 to 100 us with the search, the sort and the move),
+// so small sketches, where the panels' latency is most of the time, keep their order.
+// The lines by sketches of some rows dense and the others starting anywhere, factored
+// sorted against as given (ms): 1,448 x 362 at 0.50 of the work 1.41 against 1.35, 2,048 x
+// 512 at 0.44 1.52 against 1.44; 2,896 x 724 (2^21 elements) at 0.43 2.49 against 2.53,
+// 4,096 x 1,024 at 0.82, 0.64 and 0.41 3.08, 3.06 and 3.03 against 3.03; 6,400 x 1,600 at
+// 0.97, 0.90, 0.82, 0.64 and 0.40 5.26, 5.22, 5.18, 5.09 and 4.95 against 5.18.
 constexpr int64_t kSortMinElems = (int64_t)1 << 21;
 template <typename T>
 rfmls_status sort_rows(rfmls_handle* h, int64_t s, int64_t n, int64_t kOuter, T* SA, int64_t ld, T* tmp,

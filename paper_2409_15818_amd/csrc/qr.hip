@@ -647,10 +647,14 @@ __global__ void k_qr_keep_gram(const T* __restrict__ W, int64_t ldw, int bw, T* 
 // ms, the rows' move 3 ms), 4^3-box float32 703 -> 505 ms, Helmholtz 30.2 -> 29.8,
 // 4x4-box 11.2 -> 11.0 ms.
 // ---------------------------------------------------------------------------
-// key[i] = panel of row i's first nonzero (npan for a zero row); one wavefront per row
+// key[i] = panel of row i's first nonzero (npan for a zero row); one wavefront per row.
+// cnt[0 .. npan] = 0.
 template <typename T>
 __global__ void __launch_bounds__(256)
-    k_row_keys(const T* __restrict__ SA, int64_t ld, int64_t s, int64_t n, int npan, int32_t* __restrict__ key) {
+    k_row_keys(const T* __restrict__ SA, int64_t ld, int64_t s, int64_t n, int npan, int32_t* __restrict__ key,
+               int32_t* __restrict__ cnt) {
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k <= npan; k += 256) cnt[k] = 0;
   const int lane = threadIdx.x & 63;
   const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= s) return;
@@ -676,21 +680,43 @@ __global__ void __launch_bounds__(256)
   if (lane == 0) key[row] = k;
 }
 
-// Stable sort of the rows by key: workgroup k counts the rows of smaller keys,
-// then lists its own in ascending order; cnt[k] = rows of keys <= k.
-__global__ void __launch_bounds__(256)
-    k_row_order(const int32_t* __restrict__ key, int64_t s, int32_t* __restrict__ perm, int32_t* __restrict__ cnt) {
-  __shared__ int wsum[4];
+// cnt[k] += rows of key k, counted in LDS by chunks of kCountRows (npan < kCountKeys: a
+// sketch has at most 512 rows a compute unit, and as many columns).
+constexpr int kCountRows = 4096, kCountKeys = 4096;
+__global__ void __launch_bounds__(1024)
+    k_row_counts(const int32_t* __restrict__ key, int64_t s, int npan, int32_t* __restrict__ cnt) {
+  __shared__ int32_t c[kCountKeys];
+  for (int k = threadIdx.x; k <= npan; k += 1024) c[k] = 0;
+  __syncthreads();
+  const int64_t i0 = (int64_t)blockIdx.x * kCountRows;
+#pragma unroll
+  for (int q = 0; q < kCountRows / 1024; ++q) {
+    const int64_t i = i0 + q * 1024 + threadIdx.x;
+    if (i < s) atomicAdd(&c[key[i]], 1);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k <= npan; k += 1024)
+    if (c[k]) atomicAdd(&cnt[k], c[k]);
+}
+
+// Stable sort of the rows by key: workgroup k starts after the rows of smaller keys and
+// lists its own in ascending order.
+__global__ void __launch_bounds__(1024)
+    k_row_order(const int32_t* __restrict__ key, int64_t s, const int32_t* __restrict__ cnt, int32_t* __restrict__ perm) {
+  __shared__ int wsum[16];
   const int k = blockIdx.x;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if (cnt[k] == 0) return;  // uniform
   int below = 0;
-  for (int64_t i = threadIdx.x; i < s; i += 256) below += key[i] < k ? 1 : 0;
+  for (int q = threadIdx.x; q < k; q += 1024) below += cnt[q];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) below += __shfl_xor(below, off, 64);
   if (lane == 0) wsum[w] = below;
   __syncthreads();
-  int base = (wsum[0] + wsum[1]) + (wsum[2] + wsum[3]);
-  for (int64_t i0 = 0; i0 < s; i0 += 256) {
+  int base = 0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) base += wsum[q];
+  for (int64_t i0 = 0; i0 < s; i0 += 1024) {
     const int64_t i = i0 + threadIdx.x;
     const bool mine = i < s && key[i] == k;
     const unsigned long long b = __ballot(mine);
@@ -699,14 +725,13 @@ __global__ void __launch_bounds__(256)
     __syncthreads();
     int before = 0, all = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 16; ++q) {
       before += q < w ? wsum[q] : 0;
       all += wsum[q];
     }
     if (mine) perm[base + before + __popcll(b & ((1ull << lane) - 1ull))] = (int32_t)i;
     base += all;
   }
-  if (threadIdx.x == 0) cnt[k] = base;
 }
 
 // out[i][c] = in[row(i)][c], c < width; row(i) = perm[i], or i without perm
@@ -1055,20 +1080,24 @@ rfmls_status lookahead_stream(rfmls_handle* h) {
 //   act[k]  at least the panel's rows (so that R's rows exist), and at least
 //           kCholqrMinRows of them, so that the first panels of a sparse sketch
 //           stay on CholeskyQR2; whole multiples of 64 keep the clean kernels.
-// Costs a host wait for the counts (20 to 100 us with the search, the sort and the move),
-// so small sketches, where the panels' latency is most of the time, keep their order.
-// The lines by sketches of some rows dense and the others starting anywhere, factored
-// sorted against as given (ms): 1,448 x 362 at 0.50 of the work 1.41 against 1.35, 2,048 x
-// 512 at 0.44 1.52 against 1.44; 2,896 x 724 (2^21 elements) at 0.43 2.49 against 2.53,
-// 4,096 x 1,024 at 0.82, 0.64 and 0.41 3.08, 3.06 and 3.03 against 3.03; 6,400 x 1,600 at
-// 0.97, 0.90, 0.82, 0.64 and 0.40 5.26, 5.22, 5.18, 5.09 and 4.95 against 5.18.
+// Costs a host wait for the counts (40 to 60 us with the search; the order is formed only
+// where it is used), so small sketches, where the panels' latency is most of the time, and
+// narrow ones, which have little work to save, keep their order.  The lines by sketches of
+// some rows dense and the others starting anywhere, factored sorted against as given (ms):
+// 1,448 x 362 at 0.50 of the work 1.41 against 1.35, 2,048 x 512 at 0.44 1.52 against 1.44;
+// 2,896 x 724 (2^21 elements) at 0.43 2.52 against 2.52, 4,096 x 1,024 at 0.82, 0.64 and 0.41
+// 3.10, 3.07 and 3.05 against 3.03; 6,400 x 1,600 at 0.97, 0.90, 0.82, 0.64 and 0.40 5.25,
+// 5.24, 5.17, 5.08 and 4.95 against 5.16.  Columns: 131,072 x 64 0.37 against 0.32 and 60,000
+// x 200 1.02 against 0.97 (0.40 and 1.21 with unblocked panels), 9,000 x 250 1.07 against
+// 1.00, 33,500 x 320 1.30 against 1.41.
 constexpr int64_t kSortMinElems = (int64_t)1 << 21;
+constexpr int64_t kSortMinCols = 256;
 template <typename T>
 rfmls_status sort_rows(rfmls_handle* h, int64_t s, int64_t n, int64_t kOuter, T* SA, int64_t ld, T* tmp,
                        int64_t tmp_len, RowCounts* rows) {
   rows->s = s;
   rows->act.clear();
-  if (s * n < kSortMinElems || s >= INT32_MAX) return RFMLS_OK;
+  if (s * n < kSortMinElems || n < kSortMinCols || n >= kMaxNb * (kCountKeys - 1) || s >= INT32_MAX) return RFMLS_OK;
   hipStream_t st = h->stream;
   const int64_t npan = (n + kMaxNb - 1) / kMaxNb;
   void* p;
@@ -1079,17 +1108,21 @@ rfmls_status sort_rows(rfmls_handle* h, int64_t s, int64_t n, int64_t kOuter, T*
   std::vector<int32_t> c((size_t)npan + 1);
   {
     Trace tr(h, "qr_row_order", 4.0 * 3.0 * (double)s, 0.0);
-    hipLaunchKernelGGL(k_row_keys<T>, dim3(ceil_div(s, 4)), dim3(256), 0, st, (const T*)SA, ld, s, n, (int)npan, key);
-    hipLaunchKernelGGL(k_row_order, dim3((unsigned)npan + 1), dim3(256), 0, st, (const int32_t*)key, s, perm, cnt);
+    hipLaunchKernelGGL(k_row_keys<T>, dim3(ceil_div(s, 4)), dim3(256), 0, st, (const T*)SA, ld, s, n, (int)npan, key,
+                       cnt);
+    hipLaunchKernelGGL(k_row_counts, dim3(ceil_div(s, kCountRows)), dim3(1024), 0, st, (const int32_t*)key, s, (int)npan,
+                       cnt);
     RFMLS_HIP(h, hipGetLastError());
   }
   RFMLS_HIP(h, hipMemcpyAsync(c.data(), cnt, sizeof(int32_t) * c.size(), hipMemcpyDeviceToHost, st));
   RFMLS_HIP(h, hipStreamSynchronize(st));
   std::vector<int64_t> act((size_t)npan);
   double plain = 0.0, sorted = 0.0;
+  int64_t started = 0;
   for (int64_t k = 0; k < npan; ++k) {
     const int64_t p0 = k * kMaxNb;
-    int64_t a = c[(size_t)k];
+    started += c[(size_t)k];
+    int64_t a = started;
     a = a > p0 + kMaxNb + kCholqrMinRows ? a : p0 + kMaxNb + kCholqrMinRows;
     a = (a + kMaxNb - 1) / kMaxNb * kMaxNb;
     if (k > 0 && act[(size_t)k - 1] > a) a = act[(size_t)k - 1];
@@ -1107,6 +1140,8 @@ rfmls_status sort_rows(rfmls_handle* h, int64_t s, int64_t n, int64_t kOuter, T*
     return act[(size_t)(e < npan ? e : npan - 1)];
   };
   if (moved(npan - 1) * kMaxNb > tmp_len) return RFMLS_OK;
+  hipLaunchKernelGGL(k_row_order, dim3((unsigned)npan + 1), dim3(1024), 0, st, (const int32_t*)key, s,
+                     (const int32_t*)cnt, perm);
   for (int64_t k0 = 0; k0 < npan;) {
     int64_t k1 = k0 + 1;
     while (k1 < npan && moved(k1) * (k1 + 1 - k0) * kMaxNb <= tmp_len) ++k1;

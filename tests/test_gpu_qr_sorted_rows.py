@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 # the gate of the other factorisations, 20 n u.
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 def test_qr_refuses_rows_beyond_a_panel_grid(dtype):
-    n, live = 64, 3000
+    n, live = 256, 3000
     most = 512 * torch.cuda.get_device_properties(0).multi_processor_count
     td = torch.float64 if dtype == "f64" else torch.float32
     M = np.random.default_rng(3).standard_normal((live, n)).astype(np.float64 if dtype == "f64" else np.float32)
@@ -52,7 +52,7 @@ def _staircase(s, n, width, seed, dtype):
 # Both forced fallbacks over sorted rows: the first Cholesky failed leaves the unblocked
 # kernel's R bit for bit, the second its R of Q1 times R1.  Gates as for dense sketches.
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-@pytest.mark.parametrize("s,n,width", [(9000, 250, 25), (5200, 577, 40)])
+@pytest.mark.parametrize("s,n,width", [(9000, 300, 25), (5200, 577, 40)])
 def test_fallback_panels_over_sorted_rows(handle, s, n, width, dtype):
     M = _staircase(s, n, width, s, dtype)
     Md = M.astype(np.float64)
@@ -87,3 +87,18 @@ def test_lookahead_over_sorted_rows(handle, dtype):
             R.rfmls_qr_lookahead(handle, False)
     for f in F[1:]:
         assert np.array_equal(F[0][0], f[0]) and np.array_equal(F[0][1], f[1])
+
+
+# The count of the rows by their panel: one chunk of 4,096 and several with a ragged last,
+# every row of one panel, and empty panels, against the dense factorisation's gate.
+@pytest.mark.parametrize("s,n,first", [(8192, 256, lambda i, n: 0 * i), (8193, 300, lambda i, n: i * n // 9000),
+                                       (20001, 321, lambda i, n: np.where(i % 2 == 0, 0, n - 60))])
+def test_rows_by_their_panels(handle, s, n, first):
+    rng = np.random.default_rng(s)
+    M = rng.standard_normal((s, n))
+    M[np.arange(n)[None, :] < np.minimum(first(np.arange(s), n), n - 1)[:, None]] = 0.0
+    M = M[rng.permutation(s)]
+    P = R.rfmls_precond(handle, torch.tensor(M, device="cuda"))
+    Rm = R.rfmls_precond_export_R(handle, P).cpu().numpy()
+    assert np.all(np.diag(Rm) > 0) and not np.tril(Rm, -1).any()
+    assert np.linalg.norm(Rm.T @ Rm - M.T @ M) <= 20 * n * 2.0 ** -53 * np.linalg.norm(M) ** 2

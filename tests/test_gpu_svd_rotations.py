@@ -71,3 +71,25 @@ def test_svd_of_many_columns(n):
     kappa = float(sig.max() / sig.min())
     assert float((U.T.contiguous() @ U - eye).abs().max()) <= n * u * kappa + 1e-12
     assert abs(float((sig ** 2).sum() / (SA ** 2).sum()) - 1.0) <= 8 * n * u
+
+
+# Few columns, whose sweeps run in one launch up to 32: one column, padding inside the
+# pairs' rounds, the whole group, and one column more.  kappa 1e4; the sweeps' limit is
+# kept to, and what it leaves is still an SVD's V to rounding.
+@pytest.mark.parametrize("n", [1, 2, 3, 5, 8, 16, 31, 32, 33])
+def test_svd_of_few_columns(n):
+    SA = _sketch(dense_with_condition(8 * n + 30, n, 1e4 if n > 1 else 1.0, seed=n), 4 * n + 5, 3)
+    want = np.linalg.svd(SA, compute_uv=False)
+    h = R.Handle(device="cuda:0")
+    P = R.rfmls_precond_svd(h, torch.tensor(SA, device="cuda"), n)
+    sig = R.rfmls_precond_export_sigma(h, P).cpu().numpy()
+    X = R.rfmls_precond_export_P(h, P).cpu().numpy()
+    assert P.status == 0 and P.rank == n and P.sweeps >= 1 and P.off <= max(8.0, n ** 0.5) * 2.0 ** -52
+    assert np.max(np.abs(np.sort(sig)[::-1] - want)) <= 2e-12 * want[0]
+    U = SA @ X
+    assert np.max(np.abs(U.T @ U - np.eye(n))) <= n * 2.0 ** -53 * want[0] / want[-1] + 1e-12
+    for most in range(1, P.sweeps + 1):
+        Q = R.rfmls_precond_svd(h, torch.tensor(SA, device="cuda"), n, max_sweeps=most)
+        assert Q.sweeps == most and Q.status == (0 if most == P.sweeps else 1) and Q.off <= 1.0
+        V = R.rfmls_precond_export_P(h, Q).cpu().numpy() * R.rfmls_precond_export_sigma(h, Q).cpu().numpy()
+        assert np.max(np.abs(V.T @ V - np.eye(n))) <= 64 * n * 2.0 ** -53

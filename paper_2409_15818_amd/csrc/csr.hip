@@ -134,6 +134,7 @@ __global__ void __launch_bounds__(256)
 // scattered entries a row spent 0.55 of 6.95 ms on runs that the entry-by-entry transpose
 // then did not use.  One workgroup, bound by its scattered loads: 64 groups and the last
 // columns too took 16 us.
+__global__ void k_tr_clear(int* bad) { *bad = 0; }
 constexpr int kProbeGroups = 16;
 __global__ void __launch_bounds__(64 * kProbeGroups)
     k_probe_pieces(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int64_t m, int* bad,
@@ -308,6 +309,12 @@ rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int
   // rows over the entries, or their entry lists would approach the matrix's own size.
   constexpr int64_t kTrPieceMinNnz = (int64_t)1 << 20;
   constexpr int64_t kTrPieceRows = 8;
+  // The sample costs a matrix of pieces 5 us (8,000 x 1,200 of 150 a row: 51 us without
+  // it, 55.5 with) and spares one without them the runs and their counts, which go by rows:
+  // 105,000 rows of 10 scattered entries 276 us without and 244 with, 600,000 of 20 1.64
+  // and 1.51 ms, 2,000,000 of 12 6.94 and 6.40.  A system of fewer rows is likely the
+  // former, and one of these rows takes at least 0.15 ms.
+  constexpr int64_t kTrProbeMinRows = (int64_t)1 << 18;
   const bool try_pieces = A->nnz >= kTrPieceMinNnz && m > 0;
   const int64_t ng = (m + kPieceRows - 1) / kPieceRows, cap = A->nnz / kTrPieceRows;
   const int64_t gc = (ng + 127) / 128;  // groups per chunk
@@ -333,11 +340,13 @@ rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int
     rend = rcol + m * kMaxRuns;
     pos = rend + m * kMaxRuns;
     phist = pos + cap;
-    probe_pieces(h->stream, A, bad, mode);
-    find_runs(h->stream, A, nrun, rcol, rend, bad);
+    const bool probe = m >= kTrProbeMinRows;
+    if (probe) probe_pieces(h->stream, A, bad, mode);
+    else hipLaunchKernelGGL(k_tr_clear, dim3(1), dim3(1), 0, h->stream, bad);
+    find_runs(h->stream, A, nrun, rcol, rend, probe ? bad : nullptr);
     hipLaunchKernelGGL(k_tr_groups, dim3(ceil_div(ng, 4)), dim3(256), 0, h->stream, m, n, (const int32_t*)nrun,
                        (const int32_t*)rcol, (const int32_t*)rend, gstart, elen, bad);
-    RFMLS_CHECK(scan_counts(h, elen, ng, eptr, bad));
+    RFMLS_CHECK(scan_counts(h, elen, ng, eptr, probe ? bad : nullptr));
     hipLaunchKernelGGL(k_tr_mode, dim3(1), dim3(1), 0, h->stream, (const int*)bad, (const int64_t*)eptr, ng, cap, mode);
     hipLaunchKernelGGL(k_tr_piece_walk<false>, dim3((unsigned)nch), dim3(256), 0, h->stream, m, n, gc,
                        (const unsigned long long*)gstart, (const int64_t*)eptr, (const int32_t*)nrun,

@@ -29,7 +29,7 @@
 // products on the matrix cores, and no block-wide reduction over n rows per
 // round.  Measured at n = 1,600 (31,360 x 1,600 Helmholtz system): 16 sweeps of 399
 // steps of 52 us before; 13 or 14 sweeps of 50 steps of 11 (Gram) + 25 (rotations)
-// + 19 us (apply, 4.3 TB/s) now, whole CSSVDP solve 340 -> 59 ms.
+// + 19 us (apply, 4.3 TB/s) now, whole CSSVDP solve 340 -> 53 ms.
 //
 // Layout: M and J column-major (column k contiguous, ld = ldm), columns and rows
 // padded with zeros to whole groups and 32-row tiles; float64 throughout.

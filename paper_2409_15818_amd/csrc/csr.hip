@@ -125,6 +125,7 @@ __global__ void __launch_bounds__(256)
     if (wrong) atomicOr(bad, 1);
   }
 }
+__global__ void k_tr_clear(int* bad) { *bad = 0; }
 // bad = 1 where a sample says that the rows have no pieces to speak of, mode = 0.  The
 // sample is up to 16 groups spread over the matrix, one a wavefront; a row of another
 // length or first column than the row before starts a piece.  More than a fifth of the
@@ -134,7 +135,6 @@ __global__ void __launch_bounds__(256)
 // scattered entries a row spent 0.55 of 6.95 ms on runs that the entry-by-entry transpose
 // then did not use.  One workgroup, bound by its scattered loads: 64 groups and the last
 // columns too took 16 us.
-__global__ void k_tr_clear(int* bad) { *bad = 0; }
 constexpr int kProbeGroups = 16;
 __global__ void __launch_bounds__(64 * kProbeGroups)
     k_probe_pieces(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int64_t m, int* bad,
@@ -309,8 +309,8 @@ rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int
   // rows over the entries, or their entry lists would approach the matrix's own size.
   constexpr int64_t kTrPieceMinNnz = (int64_t)1 << 20;
   constexpr int64_t kTrPieceRows = 8;
-  // The sample costs a matrix of pieces 5 us (8,000 x 1,200 of 150 a row: 51 us without
-  // it, 55.5 with) and spares one without them the runs and their counts, which go by rows:
+  // The sample is a launch of 4.9 us more for a matrix of pieces (whole calls, 8,000 x 1,200
+  // of 150 a row 52 to 58 us, 100,000 x 9,000 of 160 199 us) and spares one without them the runs and their counts, which go by rows:
   // 105,000 rows of 10 scattered entries 276 us without and 244 with, 600,000 of 20 1.64
   // and 1.51 ms, 2,000,000 of 12 6.94 and 6.40.  A system of fewer rows is likely the
   // former, and one of these rows takes at least 0.15 ms.

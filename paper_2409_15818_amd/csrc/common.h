@@ -404,8 +404,9 @@ constexpr int kMaxRuns = 8;
 void find_runs(hipStream_t st, const rfmls_csr* M, int32_t* nrun, int32_t* rcol, int32_t* rend,
                const int* skip = nullptr);
 // *bad = whether a sample of M's rows rules out pieces of rows with equal column runs
-// (csr.hip); *mode = 0
-void probe_pieces(hipStream_t st, const rfmls_csr* M, int* bad, int* mode);
+// (csr.hip).  Returns what the kernels that look for them have to skip by: bad, or null
+// where no sample is taken and *bad = 0.
+const int* probe_pieces(hipStream_t st, const rfmls_csr* M, int* bad);
 rfmls_status run_solve(rfmls_handle* h, const rfmls_csr* A, const rfmls_csr* AT,
                        const rfmls_precond_t* P, const double* B, int64_t ldb, int64_t nrhs,
                        double* X, int64_t ldx, double* Rout, int64_t ldr, const rfmls_opts* o,

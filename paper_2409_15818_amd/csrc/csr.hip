@@ -125,8 +125,8 @@ __global__ void __launch_bounds__(256)
     if (wrong) atomicOr(bad, 1);
   }
 }
-__global__ void k_tr_clear(int* bad) { *bad = 0; }
-// bad = 1 where a sample says that the rows have no pieces to speak of, mode = 0.  The
+__global__ void k_clear_flag(int* bad) { *bad = 0; }
+// bad = 1 where a sample says that the rows have no pieces to speak of, else 0.  The
 // sample is up to 16 groups spread over the matrix, one a wavefront; a row of another
 // length or first column than the row before starts a piece.  More than a fifth of the
 // sampled rows doing so is beyond what either use of the pieces takes (one in eight
@@ -137,8 +137,7 @@ __global__ void k_tr_clear(int* bad) { *bad = 0; }
 // columns too took 16 us.
 constexpr int kProbeGroups = 16;
 __global__ void __launch_bounds__(64 * kProbeGroups)
-    k_probe_pieces(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int64_t m, int* bad,
-                   int* mode) {
+    k_probe_pieces(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col, int64_t m, int* bad) {
   __shared__ int found[kProbeGroups][2];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t ng = (m + kPieceRows - 1) / kPieceRows;
@@ -162,7 +161,6 @@ __global__ void __launch_bounds__(64 * kProbeGroups)
       r += found[q][1];
     }
     *bad = 5 * s > r;
-    *mode = 0;
   }
 }
 // mode = 1: every row described, and the pieces' entry lists fit their buffer
@@ -287,8 +285,20 @@ __global__ void __launch_bounds__(256)
 
 }  // namespace
 
-void probe_pieces(hipStream_t st, const rfmls_csr* M, int* bad, int* mode) {
-  hipLaunchKernelGGL(k_probe_pieces, dim3(1), dim3(64 * kProbeGroups), 0, st, M->row_ptr, M->col, M->m, bad, mode);
+// The sample is a launch of 4.9 us more for a matrix of pieces (whole transposes, 8,000 x
+// 1,200 of 150 a row 52 to 58 us, 100,000 x 9,000 of 160 199 us) and spares one without
+// them the runs and their counts, which go by rows: 105,000 rows of 10 scattered entries
+// 276 us without and 244 with, 600,000 of 20 1.64 and 1.51 ms, 2,000,000 of 12 6.94 and
+// 6.40.  A system of fewer rows is likely the former, and one of these rows takes at
+// least 0.15 ms.
+constexpr int64_t kProbeMinRows = (int64_t)1 << 18;
+const int* probe_pieces(hipStream_t st, const rfmls_csr* M, int* bad) {
+  if (M->m < kProbeMinRows) {
+    hipLaunchKernelGGL(k_clear_flag, dim3(1), dim3(1), 0, st, bad);
+    return nullptr;
+  }
+  hipLaunchKernelGGL(k_probe_pieces, dim3(1), dim3(64 * kProbeGroups), 0, st, M->row_ptr, M->col, M->m, bad);
+  return bad;
 }
 
 rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int32_t* at_col,
@@ -309,12 +319,6 @@ rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int
   // rows over the entries, or their entry lists would approach the matrix's own size.
   constexpr int64_t kTrPieceMinNnz = (int64_t)1 << 20;
   constexpr int64_t kTrPieceRows = 8;
-  // The sample is a launch of 4.9 us more for a matrix of pieces (whole calls, 8,000 x 1,200
-  // of 150 a row 52 to 58 us, 100,000 x 9,000 of 160 199 us) and spares one without them the runs and their counts, which go by rows:
-  // 105,000 rows of 10 scattered entries 276 us without and 244 with, 600,000 of 20 1.64
-  // and 1.51 ms, 2,000,000 of 12 6.94 and 6.40.  A system of fewer rows is likely the
-  // former, and one of these rows takes at least 0.15 ms.
-  constexpr int64_t kTrProbeMinRows = (int64_t)1 << 18;
   const bool try_pieces = A->nnz >= kTrPieceMinNnz && m > 0;
   const int64_t ng = (m + kPieceRows - 1) / kPieceRows, cap = A->nnz / kTrPieceRows;
   const int64_t gc = (ng + 127) / 128;  // groups per chunk
@@ -340,13 +344,11 @@ rfmls_status run_transpose(rfmls_handle* h, const rfmls_csr* A, int64_t* rp, int
     rend = rcol + m * kMaxRuns;
     pos = rend + m * kMaxRuns;
     phist = pos + cap;
-    const bool probe = m >= kTrProbeMinRows;
-    if (probe) probe_pieces(h->stream, A, bad, mode);
-    else hipLaunchKernelGGL(k_tr_clear, dim3(1), dim3(1), 0, h->stream, bad);
-    find_runs(h->stream, A, nrun, rcol, rend, probe ? bad : nullptr);
+    const int* skip = probe_pieces(h->stream, A, bad);
+    find_runs(h->stream, A, nrun, rcol, rend, skip);
     hipLaunchKernelGGL(k_tr_groups, dim3(ceil_div(ng, 4)), dim3(256), 0, h->stream, m, n, (const int32_t*)nrun,
                        (const int32_t*)rcol, (const int32_t*)rend, gstart, elen, bad);
-    RFMLS_CHECK(scan_counts(h, elen, ng, eptr, probe ? bad : nullptr));
+    RFMLS_CHECK(scan_counts(h, elen, ng, eptr, skip));
     hipLaunchKernelGGL(k_tr_mode, dim3(1), dim3(1), 0, h->stream, (const int*)bad, (const int64_t*)eptr, ng, cap, mode);
     hipLaunchKernelGGL(k_tr_piece_walk<false>, dim3((unsigned)nch), dim3(256), 0, h->stream, m, n, gc,
                        (const unsigned long long*)gstart, (const int64_t*)eptr, (const int32_t*)nrun,

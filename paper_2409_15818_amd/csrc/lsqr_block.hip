@@ -1572,7 +1572,7 @@ static rfmls_status spmm_prepare(BCtx& c) {
   }
   void* pr;
   RFMLS_CHECK(workspace(h, WS_SPMM_RUNS, bytes, &pr));
-  // flags of both matrices, the probe's spare word, and the numbers of pieces: one copy
+  // flags of both matrices and the numbers of pieces, in one copy
   int* bad = (int*)pr;
   int64_t* total = (int64_t*)pr + 2;
   char* q = (char*)pr + 256;
@@ -1594,13 +1594,13 @@ static rfmls_status spmm_prepare(BCtx& c) {
     int32_t* rend = rcol + rows * kMaxRuns;
     *out[i] = RunMat{M->row_ptr, M->val, nrun, rcol, rend, pieces, 0, rows, 1, 0};
     if (rows > 0) {
-      probe_pieces(c.st, M, bad + i, bad + 2);
-      find_runs(c.st, M, nrun, rcol, rend, bad + i);
+      const int* skip = probe_pieces(c.st, M, bad + i);
+      find_runs(c.st, M, nrun, rcol, rend, skip);
       const unsigned g = (unsigned)(ng < 4096 ? (ng + 3) / 4 : 1024);
       hipLaunchKernelGGL(k_run_pieces<false>, dim3(g), dim3(kThreads), 0, c.st, rows, M->n, (const int32_t*)nrun,
                          (const int32_t*)rcol, (const int32_t*)rend, pcount, (const int64_t*)nullptr,
                          (int2*)nullptr, bad + i, (int64_t*)nullptr);
-      RFMLS_CHECK(scan_counts(h, pcount, ng, pptr[i], bad + i));
+      RFMLS_CHECK(scan_counts(h, pcount, ng, pptr[i], skip));
       hipLaunchKernelGGL(k_run_pieces<true>, dim3(g), dim3(kThreads), 0, c.st, rows, M->n, (const int32_t*)nrun,
                          (const int32_t*)rcol, (const int32_t*)rend, pcount, (const int64_t*)pptr[i], pieces,
                          bad + i, total + i);

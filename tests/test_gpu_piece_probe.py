@@ -40,24 +40,29 @@ CASES = [
     (13, lambda g: g % 2 == 0, 1300, 0),
 ]
 
-# The transpose takes its sample from 2^18 rows on: one row fewer and no more, the sampled
+# The sample is taken from 2^18 rows on: one row fewer and no more, the sampled
 # groups in pieces and the others not and the other way round.
 TALL = [(4096, lambda g: True, 0), (4095, lambda g: True, 63), (4096, lambda g: False, 1), (4096, lambda g: g % 256 == 0, 0),
         (4096, lambda g: g % 256 != 0, 7)]
 
 
 @pytest.mark.parametrize("case", range(len(TALL)))
-def test_transpose_of_many_rows(case):
+def test_many_rows(case):
     groups, kind, tail = TALL[case]
     n = 150
     m, ptr, col, val = _mixed(groups, kind, 5, n, tail, case)
     assert len(col) >= 1 << 20
     h = R.Handle(device="cuda:0")
-    T = R.rfmls_transpose(h, R.CSR.from_numpy(ptr, col, val, m, n))
+    A = R.CSR.from_numpy(ptr, col, val, m, n)
+    T = R.rfmls_transpose(h, A)
     order = np.argsort(col, kind="stable")
     assert np.array_equal(T.row_ptr.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(col, minlength=n))]))
     assert np.array_equal(T.col.cpu().numpy(), np.repeat(np.arange(m), 5)[order])
     assert np.array_equal(T.val.cpu().numpy(), val[order])
+    P = R.rfmls_precond_import_R(h, torch.eye(n, dtype=torch.float64, device="cuda"))
+    dense = torch.zeros((m, n), dtype=torch.float64, device="cuda")
+    dense[torch.arange(m, device="cuda").repeat_interleave(5), A.col.long()] = A.val
+    assert torch.equal(R.rfmls_form_B(h, A, P), dense)
 
 
 @pytest.mark.parametrize("case", range(len(CASES)))

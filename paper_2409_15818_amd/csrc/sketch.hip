@@ -138,19 +138,21 @@ __global__ void __launch_bounds__(256) k_sort_buckets(const int64_t* __restrict_
 }
 
 // One block per sketch row j.  The bucket's rows (columns ascending within a
-// row) each cover one contiguous column span, or two where both halves of the
-// row's entries are gapless (an RFM interface row: two boxes, which may lie far
-// apart); the spans, merged in order of their first column, map the row's touched
-// columns onto a compact LDS window (at most kWin doubles).  Zeros go out first for every 16-byte segment clear
-// of the window, the bucket's rows are then added into the window in ascending
-// row order (a barrier between rows), and the window's segments are stored:
-// the dense row is written once, with 16-byte non-temporal stores, and A's
-// entries are read once.  A bucket of more than kMaxBucketRows rows or a window
-// wider than kWin takes the chunked path: chunks of kWin columns, every row of
-// the bucket visited per chunk.  Either way every element is summed in float64
-// from +0 over the bucket's rows in ascending row order.
-// Few (buckets of two or three rows): one span a row and no entries read ahead, since
-// there is little to wait for and the registers take a workgroup from every compute unit.
+// row) each cover one contiguous column span; the spans, merged in order of their
+// first column, map the row's touched columns onto a compact LDS window (at most
+// kWin doubles).  Where that is too narrow, a row whose halves are both gapless (an
+// RFM interface row: two boxes, which may lie far apart) counts as two spans.  Zeros
+// go out first for every 16-byte segment clear of the window, the bucket's rows are
+// then added into the window in ascending row order (a barrier between rows), and
+// the window's segments are stored: the dense row is written once, with 16-byte
+// non-temporal stores, and A's entries are read once.  A bucket of more than
+// kMaxBucketRows rows or a window wider than kWin takes the chunked path: chunks of
+// kWin columns, every row of the bucket visited per chunk.  Either way every element
+// is summed in float64 from +0 over the bucket's rows in ascending row order.
+// Spans and how they are stored are most of the time where rows are short: two
+// spans for every such row and each element's interval looked up from the first made
+// a 57,344 x 3,136 sketch of 9,408 rows 339 us in float32 (260 with one span a row),
+// one span first 270, the interval known and a wavefront each 134.
 // threads: twice as many beside the 32 KB window, of which only four fit a compute unit
 constexpr int sketch_threads(int win) { return win > 2048 ? 512 : 256; }
 constexpr int kMaxBucketRows = 64;
@@ -170,15 +172,15 @@ struct SketchVec<float> {
 
 // Vec: the row start is 16-byte aligned (SA and ld suit 16-byte stores).  kWin: see
 // run_sketch.
-template <typename TOut, bool Vec, int kWin, bool Few>
+template <typename TOut, bool Vec, int kWin>
 __global__ void __launch_bounds__(sketch_threads(kWin), 8)
     k_sketch_rows(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                   const double* __restrict__ val, const int8_t* __restrict__ sign,
                   const int64_t* __restrict__ bptr, const int32_t* __restrict__ perm, int64_t n,
                   TOut* __restrict__ SA, int64_t ld) {
   constexpr int NT = sketch_threads(kWin);
-  constexpr int S = Few ? 1 : 2;  // spans a row
-  constexpr int kMaxSpans = S * kMaxBucketRows;
+  constexpr bool kAhead = kWin > 2048;
+  constexpr int kMaxSpans = 2 * kMaxBucketRows;
   constexpr int V = Vec ? SketchVec<TOut>::V : 1;
   typedef typename SketchVec<TOut>::vec vec_t;
   __shared__ double acc[kWin];
@@ -197,6 +199,7 @@ __global__ void __launch_bounds__(sketch_threads(kWin), 8)
   const int64_t nb = bhi - blo;
   TOut* out = SA + j * ld;
   int nint = -1;  // -1: chunked path
+  bool two = false;  // rows of two spans
   if (nb <= kMaxBucketRows) {
     if (t < nb) {
       const int32_t i = perm[blo + t];
@@ -205,55 +208,63 @@ __global__ void __launch_bounds__(sketch_threads(kWin), 8)
       rlen[t] = (int32_t)(hi - lo);
       rsg[t] = sign[i];
       // empty spans (1, 0) for what a row does not have
-      int32_t f0 = 1, l0 = 0, f1 = 1, l1 = 0;
-      if (hi > lo) {
-        const int64_t h = (hi - lo) / 2;  // entries of the first half
-        f0 = col[lo];
-        l0 = col[hi - 1];
-        const int32_t e0 = col[lo + (h > 0 ? h - 1 : 0)], b1 = col[lo + h];
-        if (!Few && h > 0 && b1 > e0 + 1 && (int64_t)e0 - f0 == h - 1 && (int64_t)l0 - b1 == hi - lo - h - 1) {
-          f1 = b1;
-          l1 = l0;
-          l0 = e0;
+      raw0[2 * t] = hi > lo ? col[lo] : 1;
+      raw1[2 * t] = hi > lo ? col[hi - 1] : 0;
+      raw0[2 * t + 1] = 1;
+      raw1[2 * t + 1] = 0;
+    }
+    // the spans of every step-th place, sorted by first column and merged
+    auto merge = [&](int step) {
+      __syncthreads();
+      const int ns = 2 / step * (int)nb;
+      if (t < ns) {  // each span to the place its rank gives
+        const int32_t x0 = raw0[t * step];
+        int rank = 0;
+        for (int u = 0; u < ns; ++u) {
+          const int32_t x = raw0[u * step];
+          rank += (x < x0 || (x == x0 && u < t)) ? 1 : 0;
         }
+        sp0[rank] = x0;
+        sp1[rank] = raw1[t * step];
       }
-      raw0[S * t] = f0;
-      raw1[S * t] = l0;
-      if constexpr (!Few) {
-        raw0[S * t + 1] = f1;
-        raw1[S * t + 1] = l1;
-      }
-    }
-    __syncthreads();
-    const int ns = S * (int)nb;
-    if (t < ns) {  // sorted by first column: each span to the place its rank gives
-      const int32_t x0 = raw0[t];
-      int rank = 0;
-      for (int u = 0; u < ns; ++u) rank += (raw0[u] < x0 || (raw0[u] == x0 && u < t)) ? 1 : 0;
-      sp0[rank] = x0;
-      sp1[rank] = raw1[t];
-    }
-    __syncthreads();
-    if (t == 0) {  // merge
-      int k = 0, total = 0;
-      for (int a = 0; a < ns; ++a) {
-        if (sp1[a] < sp0[a]) continue;  // empty
-        if (k > 0 && sp0[a] <= ien[k - 1] + 1) {
-          if (sp1[a] > ien[k - 1]) {
-            total += sp1[a] - ien[k - 1];
-            ien[k - 1] = sp1[a];
+      __syncthreads();
+      if (t == 0) {
+        int k = 0, total = 0;
+        for (int a = 0; a < ns; ++a) {
+          if (sp1[a] < sp0[a]) continue;  // empty
+          if (k > 0 && sp0[a] <= ien[k - 1] + 1) {
+            if (sp1[a] > ien[k - 1]) {
+              total += sp1[a] - ien[k - 1];
+              ien[k - 1] = sp1[a];
+            }
+          } else {
+            ist[k] = sp0[a];
+            ien[k] = sp1[a];
+            ioff[k] = total;
+            total += sp1[a] - sp0[a] + 1;
+            ++k;
           }
-        } else {
-          ist[k] = sp0[a];
-          ien[k] = sp1[a];
-          ioff[k] = total;
-          total += sp1[a] - sp0[a] + 1;
-          ++k;
+        }
+        nint_s = total <= kWin ? k : -1;
+      }
+      __syncthreads();
+    };
+    merge(2);
+    if (nint_s < 0) {
+      bool split = false;
+      if (t < nb && rlen[t] > 1) {
+        const int32_t h = rlen[t] / 2, f0 = raw0[2 * t], l0 = raw1[2 * t];  // entries of the first half
+        const int32_t e0 = col[(int64_t)rlo[t] + h - 1], b1 = col[(int64_t)rlo[t] + h];
+        split = b1 > e0 + 1 && e0 - f0 == h - 1 && l0 - b1 == rlen[t] - h - 1;
+        if (split) {
+          raw1[2 * t] = e0;
+          raw0[2 * t + 1] = b1;
+          raw1[2 * t + 1] = l0;
         }
       }
-      nint_s = total <= kWin ? k : -1;
+      two = __syncthreads_or(split);
+      if (two) merge(1);
     }
-    __syncthreads();
     nint = nint_s;
   }
   if (nint >= 0) {
@@ -263,23 +274,37 @@ __global__ void __launch_bounds__(sketch_threads(kWin), 8)
         if (c >= ist[k] && c <= ien[k]) return ioff[k] + (int)(c - ist[k]);
       return -1;
     };
-    if (t < S * (int)nb && raw1[t] >= raw0[t]) {
+    if (t < 2 * (int)nb && raw1[t] >= raw0[t]) {
       int k = 0;
       while (k + 1 < nint && ist[k + 1] <= raw0[t]) ++k;
       wof[t] = ioff[k] - ist[k];
     }
+    // the same near interval k, in a segment that k shares with one other at most (a
+    // segment has four columns, and intervals a gap between them)
+    auto wnear = [&](int64_t c, int k) -> int {
+      if (c >= ist[k] && c <= ien[k]) return ioff[k] + (int)(c - ist[k]);
+      const int o = c < ist[k] ? k - 1 : k + 1;
+      return o >= 0 && o < nint && c >= ist[o] && c <= ien[o] ? ioff[o] + (int)(c - ist[o]) : -1;
+    };
     const int64_t nseg = n / V;
+    // a wavefront an interval (or gap) where there is one for each, else the workgroup
+    const bool apart = nint >= NT / 64;
     // zeros for the whole segments between the intervals (no wait on anything below)
-    for (int k = 0; k <= nint; ++k) {
+    auto zeros = [&](int k, int64_t t0, int64_t step) {
       const int64_t g0 = k > 0 ? ien[k - 1] / V + 1 : 0;
       const int64_t g1 = k < nint && ist[k] / V < nseg ? ist[k] / V : nseg;
-      for (int64_t g = g0 + t; g < g1; g += NT) {
+      for (int64_t g = g0 + t0; g < g1; g += step) {
         if constexpr (Vec) {
           __builtin_nontemporal_store(vec_t{}, (vec_t*)(out + g * V));
         } else {
           __builtin_nontemporal_store((TOut)0, out + g);
         }
       }
+    };
+    if (apart) {
+      for (int k = t >> 6; k <= nint; k += NT / 64) zeros(k, t & 63, 64);
+    } else {
+      for (int k = 0; k <= nint; ++k) zeros(k, t, NT);
     }
     const int wlen = nint > 0 ? ioff[nint - 1] + ien[nint - 1] - ist[nint - 1] + 1 : 0;
     for (int w = t; w < wlen; w += NT) acc[w] = 0.0;
@@ -300,61 +325,69 @@ __global__ void __launch_bounds__(sketch_threads(kWin), 8)
         p.v[u] = in ? val[(int64_t)rlo[q] + e] : 0.0;
       }
     };
-    auto row = [&](const Ahead& p, int q) {
+    auto row = [&](const Ahead& p, int q, auto spans) {
+      constexpr bool kTwo = decltype(spans)::value == 2;
       const double sg = (double)rsg[q];
-      const int32_t a0 = raw0[S * q], a1 = raw1[S * q], b0 = Few ? 1 : raw0[S * q + S - 1],
-                    b1 = Few ? 0 : raw1[S * q + S - 1];
-      const int32_t aw = wof[S * q], bw = wof[S * q + S - 1];
+      const int32_t a0 = raw0[2 * q], a1 = raw1[2 * q], b0 = kTwo ? raw0[2 * q + 1] : 1, b1 = kTwo ? raw1[2 * q + 1] : 0;
+      const int32_t aw = wof[2 * q], bw = kTwo ? wof[2 * q + 1] : 0;
       // a column outside the row's spans (a row against the ascending-column
       // contract) is dropped rather than written outside the window
       auto add = [&](int32_t c, double x) {
         const bool ina = c >= a0 && c <= a1;
         if (ina || (c >= b0 && c <= b1)) acc[c + (ina ? aw : bw)] += x;
       };
-      if constexpr (!Few) {
+      if constexpr (kAhead) {
 #pragma unroll
         for (int u = 0; u <= kPre; ++u)
           if (t + u * NT < rlen[q]) add(p.c[u], sg * p.v[u]);
       }
-      for (int e = t + (Few ? 0 : kPre + 1) * NT; e < rlen[q]; e += NT)
+      for (int e = t + (kAhead ? kPre + 1 : 0) * NT; e < rlen[q]; e += NT)
         add(col[(int64_t)rlo[q] + e], sg * val[(int64_t)rlo[q] + e]);
       __syncthreads();
     };
     Ahead p0, p1, p2;
-    if constexpr (Few) {
-      for (int q = 0; q < (int)nb; ++q) row(p0, q);
+    if constexpr (!kAhead) {
+      if (two)
+        for (int q = 0; q < (int)nb; ++q) row(p0, q, std::integral_constant<int, 2>());
+      else
+        for (int q = 0; q < (int)nb; ++q) row(p0, q, std::integral_constant<int, 1>());
     } else {
       fetch(p0, 0);
       fetch(p1, 1);
       for (int q = 0; q < (int)nb; q += 3) {
         fetch(p2, q + 2);
-        row(p0, q);
+        row(p0, q, std::integral_constant<int, 2>());
         if (q + 1 >= (int)nb) break;
         fetch(p0, q + 3);
-        row(p1, q + 1);
+        row(p1, q + 1, std::integral_constant<int, 2>());
         if (q + 2 >= (int)nb) break;
         fetch(p1, q + 4);
-        row(p2, q + 2);
+        row(p2, q + 2, std::integral_constant<int, 2>());
       }
     }
     // the window's segments (a segment across two intervals is written twice, alike)
-    for (int k = 0; k < nint; ++k) {
+    auto window = [&](int k, int64_t t0, int64_t step) {
       const int64_t g0 = ist[k] / V, g1 = ien[k] / V < nseg ? ien[k] / V : nseg - 1;
-      for (int64_t g = g0 + t; g <= g1; g += NT) {
+      for (int64_t g = g0 + t0; g <= g1; g += step) {
         const int64_t c0 = g * V;
         if constexpr (Vec) {
           vec_t v;
 #pragma unroll
           for (int q = 0; q < V; ++q) {
-            const int p = wpos(c0 + q);
+            const int p = wnear(c0 + q, k);
             v[q] = p >= 0 ? (TOut)acc[p] : (TOut)0;
           }
           __builtin_nontemporal_store(v, (vec_t*)(out + c0));
         } else {
-          const int p = wpos(c0);
+          const int p = wnear(c0, k);
           __builtin_nontemporal_store(p >= 0 ? (TOut)acc[p] : (TOut)0, out + c0);
         }
       }
+    };
+    if (apart) {
+      for (int k = t >> 6; k < nint; k += NT / 64) window(k, t & 63, 64);
+    } else {
+      for (int k = 0; k < nint; ++k) window(k, t, NT);
     }
     // columns past the last whole segment
     for (int64_t c = nseg * V + t; c < n; c += NT) {
@@ -463,17 +496,15 @@ rfmls_status run_sketch(rfmls_handle* h, const rfmls_csr* A, int64_t s, const in
   // window of 2,048 columns (16 KB of LDS, eight workgroups per compute unit), or
   // 4,096 where the buckets hold more than 1,024 entries on average and so often
   // touch more than 2,048 columns: a bucket past the window reads its rows once per
-  // chunk.  With an interface row's two boxes as two spans and two rows' entries in
-  // flight, whole calls: 105,840 x 9,450, float32, 2,352 entries a bucket, 0.73 -> 0.57
-  // ms; Helmholtz system (2,900) 0.37 -> 0.27 ms.  Short rows over more columns than the
-  // wide window gain nothing from it and leave half of its 512 threads idle: 2,000,000 x
-  // 10,000 of 20 entries a row 8.60 ms narrow, 9.69 wide.
-  // Buckets of fewer than three rows on average take the one-span form: the 8x8-box
-  // sketch (2.2 rows, 475 entries, bound by writing 5.2 GB) 1.15 ms against 1.20 with two
-  // spans, the 4x4-box one 69 us against 75; with 3.5 rows of 270 entries 113 us
-  // against 100.
-  const bool wide = A->nnz > 1024 * s && (A->nnz >= 256 * A->m || A->n <= 4096);
-  const bool few = !wide && A->m < 3 * s;
+  // chunk.  Whole calls, narrow and wide: 105,840 x 9,450, float32, 2,352 entries a
+  // bucket, 0.67 and 0.45 ms; Helmholtz system (2,900) 0.32 and 0.25 ms; 25,688 x 1,840
+  // (1,859), which the narrow window holds, 95 and 109 us.  Short rows over more columns
+  // than the wide window gain nothing from it and leave half of its 512 threads idle:
+  // 2,000,000 x 10,000 of 20 entries a row 8.60 and 9.69 ms.
+  // Two rows' entries are read ahead beside the wide window only: the narrow one's
+  // buckets of a few short rows have little to wait for, and the registers cost them
+  // 3 to 10 % (32,805 x 1,890, 770 entries a bucket, 109 us against 102).
+  const bool wide = A->nnz > 1024 * s && A->n > 2048 && (A->nnz >= 256 * A->m || A->n <= 4096);
   auto rows = [&](auto tout, auto vtag) {
     using TOut = decltype(tout);
     constexpr bool V = decltype(vtag)::value;
@@ -481,9 +512,8 @@ rfmls_status run_sketch(rfmls_handle* h, const rfmls_csr* A, int64_t s, const in
       hipLaunchKernelGGL(fn, dim3((unsigned)s), dim3(sketch_threads(win)), 0, h->stream, A->row_ptr, A->col, A->val,
                          sign, bptr, perm, A->n, (TOut*)SA, ld);
     };
-    if (wide) launch(k_sketch_rows<TOut, V, 4096, false>, 4096);
-    else if (few) launch(k_sketch_rows<TOut, V, 2048, true>, 2048);
-    else launch(k_sketch_rows<TOut, V, 2048, false>, 2048);
+    if (wide) launch(k_sketch_rows<TOut, V, 4096>, 4096);
+    else launch(k_sketch_rows<TOut, V, 2048>, 2048);
   };
   if (dt == RFMLS_F64) {
     if (vec) rows(0.0, std::true_type());

@@ -47,3 +47,26 @@ def test_sketch_forms(m, n, w, s, pad, dtype):
     ho, so = countsketch.hash_sign(m, s, 11)
     ref, _ = countsketch.sketch_dense(ptr, col, val, ho, so, s, n)
     assert np.array_equal(SA.cpu().numpy(), ref if dtype == "f64" else ref.astype(np.float32))
+
+
+# Rows of one or two columns at every second place: more intervals than wavefronts, a
+# column between them, so that the 16-byte segments of the output hold parts of two, and
+# one span a row or, past the window, two.
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("pad", [0, 1])
+@pytest.mark.parametrize("n,far", [(37, 0), (64, 0), (2045, 0), (4999, 2498), (9000, 4500), (9001, 6000)])
+def test_sketch_of_many_intervals(n, far, pad, dtype):
+    m, s = 96, 9
+    rng = np.random.default_rng(n)
+    near = n - far if far else n
+    first = 2 * rng.integers(0, min(near, 60) // 2, size=m)
+    col = np.stack([first, first + far], 1).astype(np.int32) if far else first[:, None].astype(np.int32)
+    ptr = np.arange(m + 1) * col.shape[1]
+    val = rng.standard_normal(col.size)
+    td = torch.float64 if dtype == "f64" else torch.float32
+    SA = torch.full((s, n + 8 + pad), 7.0, dtype=td, device="cuda")[:, :n]
+    h = R.Handle(device="cuda:0")
+    R.rfmls_sketch(h, R.CSR.from_numpy(ptr, col.reshape(-1), val, m, n), s, 5, dtype=dtype, SA=SA)
+    ho, so = countsketch.hash_sign(m, s, 5)
+    ref, _ = countsketch.sketch_dense(ptr, col.reshape(-1), val, ho, so, s, n)
+    assert np.array_equal(SA.cpu().numpy(), ref if dtype == "f64" else ref.astype(np.float32))

@@ -140,7 +140,7 @@ __global__ void __launch_bounds__(256) k_sort_buckets(const int64_t* __restrict_
 // One block per sketch row j.  The bucket's rows (columns ascending within a
 // row) each cover one contiguous column span; the spans, merged in order of their
 // first column, map the row's touched columns onto a compact LDS window (at most
-// kWin doubles).  Where that is too narrow, a row whose halves are both gapless (an
+// kWin doubles).  Where that is too narrow (and halves is set), a row whose halves are both gapless (an
 // RFM interface row: two boxes, which may lie far apart) counts as two spans.  Zeros
 // go out first for every 16-byte segment clear of the window, the bucket's rows are
 // then added into the window in ascending row order (a barrier between rows), and
@@ -177,7 +177,7 @@ __global__ void __launch_bounds__(sketch_threads(kWin), 8)
     k_sketch_rows(const int64_t* __restrict__ row_ptr, const int32_t* __restrict__ col,
                   const double* __restrict__ val, const int8_t* __restrict__ sign,
                   const int64_t* __restrict__ bptr, const int32_t* __restrict__ perm, int64_t n,
-                  TOut* __restrict__ SA, int64_t ld) {
+                  TOut* __restrict__ SA, int64_t ld, bool halves) {
   constexpr int NT = sketch_threads(kWin);
   constexpr bool kAhead = kWin > 2048;
   constexpr int kMaxSpans = 2 * kMaxBucketRows;
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(sketch_threads(kWin), 8)
       __syncthreads();
     };
     merge(2);
-    if (nint_s < 0) {
+    if (halves && nint_s < 0) {
       bool split = false;
       if (t < nb && rlen[t] > 1) {
         const int32_t h = rlen[t] / 2, f0 = raw0[2 * t], l0 = raw1[2 * t];  // entries of the first half
@@ -505,12 +505,16 @@ rfmls_status run_sketch(rfmls_handle* h, const rfmls_csr* A, int64_t s, const in
   // buckets of a few short rows have little to wait for, and the registers cost them
   // 3 to 10 % (32,805 x 1,890, 770 entries a bucket, 109 us against 102).
   const bool wide = A->nnz > 1024 * s && A->n > 2048 && (A->nnz >= 256 * A->m || A->n <= 4096);
+  // Two spans where buckets hold three rows or more: the 8x8-box sketch (2.2 rows, bound
+  // by writing 5.2 GB) takes 1.17 ms with them and 1.16 in chunks, 86,697 x 6,804 (3.2)
+  // 0.34 ms and 0.38.
+  const bool halves = wide || A->m >= 3 * s;
   auto rows = [&](auto tout, auto vtag) {
     using TOut = decltype(tout);
     constexpr bool V = decltype(vtag)::value;
     auto launch = [&](auto fn, int win) {
       hipLaunchKernelGGL(fn, dim3((unsigned)s), dim3(sketch_threads(win)), 0, h->stream, A->row_ptr, A->col, A->val,
-                         sign, bptr, perm, A->n, (TOut*)SA, ld);
+                         sign, bptr, perm, A->n, (TOut*)SA, ld, halves);
     };
     if (wide) launch(k_sketch_rows<TOut, V, 4096>, 4096);
     else launch(k_sketch_rows<TOut, V, 2048>, 2048);
